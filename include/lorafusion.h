@@ -155,14 +155,14 @@ lora_status lora_debug_mask(int64_t M, int64_t K, float p, uint64_t seed, uint8_
  * reductions of operations (3) and (4) with row panels of 1024 down to 64 rows.  By default every launch
  * picks the height that fills the chip better (the small ones for short batches and narrow
  * projections).  rows = 256 fixes the large height of the first three and panels of at least 256 rows
- * for all later calls, rows = 128 the small height of the first three, rows = 0 restores the automatic
- * choice; any other value returns LORA_ERR_PARAM.  Y, S_saved and dX are bit-identical under all three
- * settings; dA and dB are fp32 sums over the row panels and agree up to the order of those sums. */
+ * for all later calls, rows = 128 GEMM tiles of 128 rows x 256 columns and the small height of the other two,
+ * rows = 0 restores the automatic choice; any other value returns LORA_ERR_PARAM.  Y, S_saved and dX are
+ * bit-identical under all three settings; dA and dB are fp32 sums over the row panels and agree up to the order of those sums. */
 lora_status lora_set_row_tile(int32_t rows);
 
 /* Tuning knob and test hook (process-wide, not thread safe).  The GEMM kernels of operations (2) and (5)
- * (Section 5.1) copy their operand slabs from global memory to LDS either one or two 64-deep slabs ahead of the
- * matrix work.  By default every launch chooses (two ahead when the frozen weight is too large to stay cached -
+ * (Section 5.1) with 256-row tiles copy their operand slabs from global memory to LDS either one or two 64-deep slabs
+ * ahead of the matrix work.  By default every launch chooses (two ahead when the frozen weight is too large to stay cached -
  * operation (5) - or the contraction is long enough - operation (2)).  slabs = 1 or 2 fixes the distance for all
  * later launches, slabs = 0 restores the automatic choice; any other value returns LORA_ERR_PARAM.  Every output
  * is bit-identical under all three settings. */

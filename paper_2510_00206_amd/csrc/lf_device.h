@@ -37,17 +37,19 @@ struct RowTile {
     int g, row_start, rows, local_row0;   // local_row0 = row_start - row0[g] (mask row index base)
 };
 
-// Tiles never straddle a segment: segment g contributes ceil(len/gran) tiles.
-__device__ __forceinline__ bool find_row_tile(const AdapterTable& tb, int gran, int tile, RowTile& rt) {
+// Tiles never straddle a segment: segment g contributes ceil(len/gran) tiles, len counting its rows in
+// [row_lo, row_hi).
+__device__ __forceinline__ bool find_row_tile(const AdapterTable& tb, int gran, int tile, RowTile& rt, int row_lo = 0,
+                                              int row_hi = 0x7FFFFFFF) {
     int t = tile;
     for (int g = 0; g < tb.G; ++g) {
-        const int lo = tb.row0[g], hi = tb.row0[g + 1];
-        const int nt = (hi - lo + gran - 1) / gran;
+        const int lo = max(tb.row0[g], row_lo), hi = min(tb.row0[g + 1], row_hi);
+        const int nt = max(hi - lo + gran - 1, 0) / gran;
         if (t < nt) {
             rt.g = g;
             rt.row_start = lo + t * gran;
             rt.rows = min(gran, hi - rt.row_start);
-            rt.local_row0 = t * gran;
+            rt.local_row0 = rt.row_start - tb.row0[g];
             return true;
         }
         t -= nt;

@@ -7,129 +7,69 @@
 // Both run a 256x256 output tile per workgroup: 4 waves, one per SIMD, each owning 128x128 of the
 // tile as 8x8 MFMA 16x16x32 bf16 blocks (256 fp32 accumulator registers).  The chip is power-limited
 // under these kernels, and a register-resident loop of the 16x16x32 instruction sustains about 14 % more
-// than one of 32x32x16 (half the accumulator traffic per flop), which decides the block shape.  A second
-// instantiation with 128 token rows per tile (4x8 blocks per wave) serves problems whose 256-row
-// tiling would leave compute units without a tile.  64-deep operand
+// than one of 32x32x16 (half the accumulator traffic per flop), which decides the block shape.  Launches whose
+// 256-row tiling would leave compute units without a tile go to the small tiles of lf_gemm_ring.hip, in whole or
+// for the rows of the last round (plan_gemm).  64-deep operand
 // slabs are copied global -> LDS without passing through registers, double-buffered, one or two slabs ahead
 // of the matrix work (see Sched), and the rank-r LoRA term rides as extra contraction steps on the same accumulators.  (2) contracts over
 // the contiguous dimension of both operands; (5) contracts over the row dimension of W (and of A),
 // which it reads from LDS with transposing loads so that no transposed copy of the frozen weight is
 // ever kept.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
 #include "lf_device.h"
+#include "lf_gemm_parts.h"
+#include "lf_gemm_ring.h"
 #include "lf_internal.h"
 
 namespace lf {
 
-constexpr int BN = 256, BK = 64;            // token rows per tile: 64 * MB (a wave owns 2 * MB blocks of 16 rows: MB = 4 or 2)
+constexpr int BM = 256, BN = 256;           // output tile: token rows x out columns
+constexpr int TB = 8;                       // 16-row blocks (and 16-column blocks) per wave
 constexpr int NTHREADS = 256;
 constexpr int NWAVES = NTHREADS / 64;
-constexpr int TILE_BYTES = BN * BK * 2;            // one 256x64 (or 64x256) bf16 slab: 32 KB (a 128-row token slab uses half)
+constexpr int TILE_BYTES = BN * BK * 2;            // one 256x64 (or 64x256) bf16 slab: 32 KB
 constexpr int STAGE_BYTES = 2 * TILE_BYTES;        // both operands
 constexpr int GEMM_LDS_BYTES = 2 * STAGE_BYTES;    // double buffered: 128 KB
 
-// Workgroup id -> output tile.  Consecutive workgroup ids go round-robin over the 8 XCDs, each
-// with a private L2, so ids are first regrouped per XCD and then walked in bands of 8 row tiles
-// so that the tiles resident on one XCD share operand slabs.
-__device__ __forceinline__ void tile_of_block(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int total = tiles_m * tiles_n;
-    int lid = bid;
-    if ((total & 7) == 0) lid = (bid & 7) * (total >> 3) + (bid >> 3);
-    constexpr int GROUP = 8;
-    const int per_group = GROUP * tiles_n;
-    const int group = lid / per_group;
-    const int first_m = group * GROUP;
-    const int gsz = min(tiles_m - first_m, GROUP);
-    const int in_group = lid - group * per_group;
-    tm = first_m + in_group % gsz;
-    tn = in_group / gsz;
-}
-
 // ---- slab movement ------------------------------------------------------------------------------
-// Slabs go from global memory straight into LDS (16 bytes per lane, no register staging): one wave
-// instruction fills 1024 contiguous LDS bytes, lane l writing bytes [16 l, 16 l + 16), so the
-// swizzle is applied by choosing which global chunk each lane fetches.  The load is issued from
-// inline assembly: the LDS destination (M0) and the completion wait are managed by hand, so that
-// the copy of the next slab stays in flight while the current one is consumed.
 constexpr int PASSES = 2048 / NTHREADS;              // 16-byte chunks per thread per 32 KB slab: 8
 
-__device__ __forceinline__ uint32_t lds_addr_of(const char* p) {
-    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
-}
-
-// The LDS destination of a copy is M0 + the instruction's immediate offset + 16 * lane, and the same
-// immediate also moves the memory address.  A wave's passes of one slab are therefore laid out 1024 bytes
-// apart (pass i of an NP-pass slab at immediate (i - NP/2) * 1024, M0 pointing at the middle), so that M0 is
-// written once per slab instead of once per copy - a copy is then a single instruction, which matters between
-// MFMAs of 16 cycles; the lane offsets are pre-biased by the opposite amount.  kCopyBias keeps those offsets
-// non-negative: every source address handed to a copy is the slab's first element MINUS kCopyBias bytes (an
-// address that is never dereferenced by itself).
-constexpr int kCopyBias = 4096;
-constexpr int pass_imm(int np, int i) { return (i - np / 2) * 1024; }
-
-// M0 is named as clobbered so that the compiler never keeps a value of its own in it across a copy (it
-// defines M0 itself before indirect register indexing, lane selects and its own LDS-DMA builtins; none of
-// these occur in the kernels below, whose later passes rely on the M0 of pass 0).  Clang warns about every
-// reserved register on a clobber list; the clobber is still recorded, hence the pragma.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-template <int IMM, bool SET_M0>
-__device__ __forceinline__ void copy16_to_lds(const char* biased_base, uint32_t lane_byte_off, uint32_t m0_value) {
-    if constexpr (SET_M0)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
-                     :: "s"(m0_value), "v"(lane_byte_off), "s"(biased_base), "n"(IMM) : "memory", "m0");
-    else
-        asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2"
-                     :: "v"(lane_byte_off), "s"(biased_base), "n"(IMM) : "memory");
-}
-#pragma clang diagnostic pop
-
-// M0 of a wave for an NP-pass slab whose first byte is at LDS address `lds_slab_addr`
-template <int NP>
+// M0 of a wave for a slab whose first byte is at LDS address `lds_slab_addr`
 __device__ __forceinline__ uint32_t slab_m0(uint32_t lds_slab_addr) {
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    return lds_slab_addr + w * (NP * 1024) + (NP / 2) * 1024;
+    return lds_slab_addr + w * (PASSES * 1024) + (PASSES / 2) * 1024;
 }
-
-__device__ __forceinline__ void wait_slab_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// all copies but the N issued last have landed (loads of a wave complete in order; only valid while no stores
-// of the wave are outstanding)
-template <int N> __device__ __forceinline__ void wait_slab_loads_but() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
 // Per-lane source offsets of one slab (bytes from the slab's first element), one per pass.
 struct SlabLanes { uint32_t off[PASSES]; };
 
-// Row-operand slab: 256 rows (NP = 8 passes; 128 rows and NP = 4 for the token slab of a 128-row tile) x 64
-// contraction elements, each row 8 chunks of 16 B (128 B).
-// Wave w, pass i fills rows 8*(NP*w + i) .. +7; lane l is (row l >> 3, physical chunk l & 7).
-template <int NP = PASSES>
+// Row-operand slab: 256 rows x 64 contraction elements, each row 8 chunks of 16 B (128 B).
+// Wave w, pass i fills rows 8*(PASSES*w + i) .. +7; lane l is (row l >> 3, physical chunk l & 7).
 __device__ __forceinline__ SlabLanes row_slab_lanes(int64_t ld, int rows_valid, int nchunk_valid) {
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
     SlabLanes s;
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
-        const int ii = i < NP ? i : 0;                 // (passes past NP are never issued)
-        const int row = 8 * (NP * w + ii) + (l >> 3);
+        const int row = 8 * (PASSES * w + i) + (l >> 3);
         const int chunk = min((l & 7) ^ row_slab_swz(row), nchunk_valid - 1);
-        s.off[i] = (uint32_t)((min(row, rows_valid - 1) * ld + chunk * 8) * 2 + kCopyBias - pass_imm(NP, ii));
+        s.off[i] = (uint32_t)((min(row, rows_valid - 1) * ld + chunk * 8) * 2 + kCopyBias - pass_imm(PASSES, i));
     }
     return s;
 }
 
-// Enqueue one slab of NP wave-passes (a 128-row token slab has 4): `src` is the (workgroup-uniform) address
-// of the slab's first element, `s` lanes formed for the same NP.
-template <int NP, int I = 0>
+// Enqueue one slab: `src` is the (workgroup-uniform) address of the slab's first element.
+template <int I = 0>
 __device__ __forceinline__ void load_slab_passes(const char* biased, const SlabLanes& s, uint32_t m0) {
-    if constexpr (I < NP) {
-        copy16_to_lds<pass_imm(NP, I), I == 0>(biased, s.off[I], m0);
-        load_slab_passes<NP, I + 1>(biased, s, m0);
+    if constexpr (I < PASSES) {
+        copy16_to_lds<pass_imm(PASSES, I), I == 0>(biased, s.off[I], m0);
+        load_slab_passes<I + 1>(biased, s, m0);
     }
 }
-template <int NP = PASSES>
 __device__ __forceinline__ void load_slab(uint32_t lds_slab_addr, const lora_bf16* src, const SlabLanes& s) {
-    load_slab_passes<NP>((const char*)src - kCopyBias, s, slab_m0<NP>(lds_slab_addr));
+    load_slab_passes((const char*)src - kCopyBias, s, slab_m0(lds_slab_addr));
 }
 
 // ---- MFMAs issued from assembly ------------------------------------------------------------------
@@ -142,7 +82,7 @@ __device__ __forceinline__ void mfma_in_place_done() { asm volatile("s_nop 15\n\
 
 struct NoShadow {};        // a slab step without hash pieces
 
-// What the next slab pair is copied from: a token slab of 2*MB wave-passes and an out slab of PASSES.
+// What the next slab pair is copied from: a token slab and an out slab of PASSES wave-passes each.
 struct NextSlabs {
     const char* src_tok; const char* src_out;     // workgroup-uniform addresses of the slabs' first elements - kCopyBias
     const SlabLanes& lanes_tok; const SlabLanes& lanes_out;
@@ -161,18 +101,16 @@ struct Pipe {
 
 // This wave's M0 values (slab_m0) for the token and the out slab of LDS stage 0.
 struct CopyOrg { uint32_t tok, out; };
-template <int MB>
 __device__ __forceinline__ CopyOrg copy_org(uint32_t lds0) {
-    return CopyOrg{slab_m0<2 * MB>(lds0), slab_m0<PASSES>(lds0 + TILE_BYTES)};
+    return CopyOrg{slab_m0(lds0), slab_m0(lds0 + TILE_BYTES)};
 }
 
-// Copy number J (0 .. 2*MB+PASSES-1) of the next slab pair.
-template <int MB, int J>
+// Copy number J (0 .. 2*PASSES-1) of the next slab pair.
+template <int J>
 __device__ __forceinline__ void issue_copy(const NextSlabs& nx) {
     if (!nx.valid) return;
-    constexpr int TOKP = 2 * MB;
-    if constexpr (J < TOKP) copy16_to_lds<pass_imm(TOKP, J), J == 0>(nx.src_tok, nx.lanes_tok.off[J], nx.m0_tok);
-    else copy16_to_lds<pass_imm(PASSES, J - TOKP), J == TOKP>(nx.src_out, nx.lanes_out.off[J - TOKP], nx.m0_out);
+    if constexpr (J < PASSES) copy16_to_lds<pass_imm(PASSES, J), J == 0>(nx.src_tok, nx.lanes_tok.off[J], nx.m0_tok);
+    else copy16_to_lds<pass_imm(PASSES, J - PASSES), J == PASSES>(nx.src_out, nx.lanes_out.off[J - PASSES], nx.m0_out);
 }
 
 // gm.g[q] for a run-time q, as a scalar (wave-uniform) value
@@ -192,16 +130,16 @@ struct TileCtx {
     bool ok;
 };
 
-__device__ __forceinline__ TileCtx decode_tile(const AdapterTable& tb, int M, int bm, int uniform_tiles, int tiles_m,
+__device__ __forceinline__ TileCtx decode_tile(const AdapterTable& tb, int M, int uniform_tiles, int tiles_m,
                                                int tiles_n, int id, int out_cols) {
     TileCtx c;
     int tm, tn;
     tile_of_block(id, tiles_m, tiles_n, tm, tn);
     c.ok = true;
     if (uniform_tiles) {
-        find_uniform_tile(tb, M, bm, tm, c.rt, c.gm);
+        find_uniform_tile(tb, M, BM, tm, c.rt, c.gm);
     } else {
-        c.ok = find_row_tile(tb, bm, tm, c.rt);
+        c.ok = find_row_tile(tb, BM, tm, c.rt);
         c.gm.g[0] = c.gm.g[1] = c.gm.g[2] = c.gm.g[3] = c.rt.g;
         c.gm.mixed = false;
     }
@@ -216,8 +154,6 @@ constexpr int WAVE_EXTRA_BYTES = 8192;
 constexpr int GEMM_LDS_TOTAL = GEMM_LDS_BYTES + NWAVES * WAVE_EXTRA_BYTES;     // 160 KB: all of a compute unit's
 
 // ---- fragments and the MFMA --------------------------------------------------------------------------
-#define LF_MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16((a), (b), (c), 0, 0, 0)
-
 // Per-lane LDS offsets of the operand fragments (16 rows or columns x 32 contraction elements per fragment;
 // lane l holds row or column l & 15, contraction elements 8 * (l >> 4) .. +7 of the sub-step).
 //  row slab: one 16-byte read at row_off[sub-step] + 2048 bytes per 16-row block;
@@ -237,7 +173,7 @@ __device__ __forceinline__ FragLanes frag_lanes(int wn) {
 
 // Fragments of a wave: the out operand double-buffered by sub-step, the token operand in place (block mi is
 // reloaded for the next sub-step as soon as the eight MFMAs of its row have been issued).
-template <int MB> struct Frags { bf16x8 fo[2][8]; bf16x8 ft[2 * MB]; };
+struct Frags { bf16x8 fo[2][8]; bf16x8 ft[TB]; };
 
 template <bool COL_SLAB>
 __device__ __forceinline__ bf16x8 read_out_frag(const char* lds_out, const FragLanes& fl, int blk, int sub) {
@@ -268,12 +204,12 @@ __device__ __forceinline__ bf16x8 read_tok_frag(const char* lds_tok, const FragL
 }
 
 // all fragments of sub-step 0 of a slab (start of a tile)
-template <bool COL_SLAB, int MB>
-__device__ __forceinline__ void read_frags(Frags<MB>& f, const char* lds_tok, const char* lds_out, const FragLanes& fl) {
+template <bool COL_SLAB>
+__device__ __forceinline__ void read_frags(Frags& f, const char* lds_tok, const char* lds_out, const FragLanes& fl) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) f.fo[0][k] = read_out_frag<COL_SLAB>(lds_out, fl, k, 0);
 #pragma unroll
-    for (int mi = 0; mi < 2 * MB; ++mi) f.ft[mi] = read_tok_frag(lds_tok, fl, mi, 0);
+    for (int mi = 0; mi < TB; ++mi) f.ft[mi] = read_tok_frag(lds_tok, fl, mi, 0);
 }
 
 // Where the copies of a slab step go.
@@ -288,31 +224,30 @@ __device__ __forceinline__ void read_frags(Frags<MB>& f, const char* lds_tok, co
 constexpr int kCopySpread1 = 0, kCopyEarly1 = 1, kCopyAhead2 = 2;
 
 // What rides on MFMA slot s of sub-step `sub` (slot s works on token block s >> 3; -1: nothing).
-template <int MB> struct Sched {
-    static constexpr int TB = 2 * MB, SS = 8 * TB;
+struct Sched {
+    static constexpr int SS = 8 * TB;
     // sub-step 1: hand-over after this slot
-    static constexpr int ho(int mode) { return mode == kCopyAhead2 ? (MB == 4 ? 7 : 3) : (MB == 4 ? 36 : 20); }
-    static constexpr int find(const int* at, int n, int s) {
-        for (int j = 0; j < n; ++j)
+    static constexpr int ho(int mode) { return mode == kCopyAhead2 ? 7 : 36; }
+    template <int N> static constexpr int find(const int (&at)[N], int s) {
+        for (int j = 0; j < N; ++j)
             if (at[j] == s) return j;
         return -1;
     }
     // read of out fragment k for the next sub-step (sub-step 0: of this slab; sub-step 1: of the next slab)
     static constexpr int fo_read(int sub, int s, int mode) {
-        if (sub == 0) return MB == 4 ? ((s & 7) == 4 ? s >> 3 : -1) : ((s & 3) == 0 ? s >> 2 : -1);
+        if (sub == 0) return (s & 7) == 4 ? s >> 3 : -1;
         if (mode == kCopyAhead2) {
-            constexpr int at4[8] = {12, 15, 19, 22, 28, 31, 35, 38}, at2[8] = {18, 19, 20, 21, 22, 23, 24, 26};
-            return find(MB == 4 ? at4 : at2, 8, s);
+            constexpr int at[8] = {12, 15, 19, 22, 28, 31, 35, 38};
+            return find(at, s);
         }
-        if (MB == 4) return s == 37 ? 0 : s >= 40 && s <= 52 && !(s & 1) ? (s - 38) >> 1 : -1;      // 37, 40, 42, .. 52 (in the order of their first use)
-        return s >= 22 && s <= 29 ? s - 22 : -1;
+        return s == 37 ? 0 : s >= 40 && s <= 52 && !(s & 1) ? (s - 38) >> 1 : -1;      // 37, 40, 42, .. 52 (in the order of their first use)
     }
-    // column slab, 256-row tile: the second transposing read of out fragment k (the first rides on fo_read's slot)
+    // column slab: the second transposing read of out fragment k (the first rides on fo_read's slot)
     static constexpr int fo_read_hi(int sub, int s, int mode) {
         if (sub == 0) return (s & 7) == 5 ? s >> 3 : -1;
         if (mode == kCopyAhead2) {
-            constexpr int at4[8] = {13, 16, 20, 23, 29, 32, 36, 39};
-            return find(at4, 8, s);
+            constexpr int at[8] = {13, 16, 20, 23, 29, 32, 36, 39};
+            return find(at, s);
         }
         return s == 38 ? 0 : s >= 41 && s <= 53 && (s & 1) ? (s - 39) >> 1 : -1;    // right after the first: 38, 41, 43, .. 53
     }
@@ -320,35 +255,26 @@ template <int MB> struct Sched {
     // over when the others are reloaded), the others that of the next sub-step
     static constexpr int ft_read(int sub, int s, int mode) {
         if (s == 1) return TB - 1;
-        if (sub == 1 && mode == kCopyAhead2) return (s & 7) == 1 && s >= 9 ? (s >> 3) - 1 : -1;   // as soon as the block row is over
-        if (sub == 0) {
-            if (MB == 4) return (s & 7) == 1 && s >= 9 ? (s >> 3) - 1 : -1;       // 9, 17, .. 57 -> 0 .. 6
-            return (s & 7) == 2 && s >= 10 ? (s >> 3) - 1 : -1;                   // 10, 18, 26 -> 0 .. 2
-        }
-        if (MB == 4) return s == 39 ? 0 : s >= 54 && s <= 59 ? s - 53 : -1;             // 39; 54 .. 59 -> 1 .. 6
-        return s == 21 ? 0 : s == 30 ? 1 : s == 31 ? 2 : -1;
+        if (sub == 0 || mode == kCopyAhead2) return (s & 7) == 1 && s >= 9 ? (s >> 3) - 1 : -1;   // as soon as the block row is over
+        return s == 39 ? 0 : s >= 54 && s <= 59 ? s - 53 : -1;             // 39; 54 .. 59 -> 1 .. 6
     }
-    // copy number (0 .. 2*MB + 7) of the slab pair the step brings.  Operation (5), whose slots also carry the
+    // copy number (0 .. 15) of the slab pair the step brings.  Operation (5), whose slots also carry the
     // transposing reads, wants its copies spread out whichever way they run; operation (2) wants them early when
     // they run one slab ahead (the last ones then have the longest to land) and spread when they run two ahead.
     static constexpr int copy_at(int sub, int s, int mode) {
         if (mode == kCopyAhead2) {
             if (sub != 1) return -1;
-            constexpr int at4[16] = {8, 11, 14, 18, 21, 24, 27, 30, 34, 37, 40, 43, 46, 50, 53, 56};
-            constexpr int at2[12] = {4, 5, 6, 7, 8, 10, 11, 12, 13, 14, 15, 16};
-            return MB == 4 ? find(at4, 16, s) : find(at2, 12, s);
+            constexpr int at[16] = {8, 11, 14, 18, 21, 24, 27, 30, 34, 37, 40, 43, 46, 50, 53, 56};
+            return find(at, s);
         }
         if (sub != 0) return -1;
-        if (MB == 4 && mode == kCopySpread1) return (s & 3) == 2 ? s >> 2 : -1;                  // 2, 6, .. 62 -> 0 .. 15
-        if (MB == 4) return s < 32 && (s & 2) ? (s >> 3) * 4 + (s & 1) + ((s & 4) >> 1) : -1;   // 2,3,6,7, 10,11,.. -> 0 .. 15
-        // 128-row tile: slots 2 .. 19 that carry no read
-        constexpr int at[12] = {2, 3, 5, 6, 7, 9, 11, 13, 14, 15, 17, 19};
-        return find(at, 12, s);
+        if (mode == kCopySpread1) return (s & 3) == 2 ? s >> 2 : -1;                  // 2, 6, .. 62 -> 0 .. 15
+        return s < 32 && (s & 2) ? (s >> 3) * 4 + (s & 1) + ((s & 4) >> 1) : -1;   // 2,3,6,7, 10,11,.. -> 0 .. 15
     }
 };
 
 // (operation (5) hangs its hash pieces on free slots; nothing for the others)
-template <int MB, int SUB, int S, int MODE> __device__ __forceinline__ void shadow_slot(NoShadow&) {}
+template <int SUB, int S, int MODE> __device__ __forceinline__ void shadow_slot(NoShadow&) {}
 
 // LDS side of one slab step: where the current slab pair lies and where the next one goes.
 struct StepLds {
@@ -356,15 +282,15 @@ struct StepLds {
     const char* nxt_tok; const char* nxt_out;     // ... and in the slabs being filled
 };
 
-template <bool COL_SLAB, int MB, int S, int MODE, class SH>
-__device__ __forceinline__ void slots(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, const StepLds& L, const FragLanes& fl,
+template <bool COL_SLAB, int S, int MODE, class SH>
+__device__ __forceinline__ void slots(f32x4 (&acc)[TB][8], Frags& f, const StepLds& L, const FragLanes& fl,
                                         const NextSlabs& nx, bool read_next, SH& sh, Pipe& pp) {
-    using SC = Sched<MB>;
+    using SC = Sched;
     // the out blocks of a token-block row are walked forth on even rows and back on odd ones: at a row's turn the
     // MFMA keeps its out operand (consecutive MFMAs always share one operand; measured 0.3 - 0.6 % of a GEMM)
     constexpr int sub = S / SC::SS, s = S % SC::SS, mi = s >> 3, ni = (mi & 1) ? 7 - (s & 7) : (s & 7);
     acc[mi][ni] = LF_MFMA(f.fo[sub][ni], f.ft[mi], acc[mi][ni]);
-    constexpr bool SPLIT = COL_SLAB && MB == 4;      // the two halves of an out fragment on two slots
+    constexpr bool SPLIT = COL_SLAB;      // the two halves of an out fragment on two slots
     constexpr int k = SC::fo_read(sub, s, MODE);
     if constexpr (k >= 0 && !SPLIT) {
         if constexpr (sub == 0) f.fo[1][k] = read_out_frag<COL_SLAB>(L.cur_out, fl, k, 1);
@@ -386,8 +312,8 @@ __device__ __forceinline__ void slots(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, con
         else if (read_next) f.ft[m] = read_tok_frag(L.nxt_tok, fl, m, 0);
     }
     constexpr int j = SC::copy_at(sub, s, MODE);
-    if constexpr (j >= 0) issue_copy<MB, j>(nx);
-    shadow_slot<MB, sub, s, MODE>(sh);
+    if constexpr (j >= 0) issue_copy<j>(nx);
+    shadow_slot<sub, s, MODE>(sh);
     if constexpr (sub == 1 && s == 0) {
         // every copy of this step has been issued: the sources move on to the slab pair after
         pp.src_tok += pp.adv_tok;
@@ -401,14 +327,14 @@ __device__ __forceinline__ void slots(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, con
         else wait_slab_loads();
         __syncthreads();
     }
-    if constexpr (S + 1 < 2 * SC::SS) slots<COL_SLAB, MB, S + 1, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
+    if constexpr (S + 1 < 2 * SC::SS) slots<COL_SLAB, S + 1, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
 }
 
-// One 64-deep slab pair: two sub-steps of 16*MB MFMAs; the copies of the next slab pair ride on sub-step 0,
+// One 64-deep slab pair: two sub-steps of 64 MFMAs; the copies of the next slab pair ride on sub-step 0,
 // the hand-over (copies landed, workgroup barrier) sits in sub-step 1 and is followed by the first fragment
 // reads of the next slab (if read_next).  On entry f holds the fragments of sub-step 0 of the current slab.
-template <bool COL_SLAB, int MB, int MODE, class SH>
-__device__ __forceinline__ void slab_step(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, const char* lds_tok_org,
+template <bool COL_SLAB, int MODE, class SH>
+__device__ __forceinline__ void slab_step(f32x4 (&acc)[TB][8], Frags& f, const char* lds_tok_org,
                                             const char* lds_out_org, CopyOrg lds_copy_org, const FragLanes& fl, Pipe& pp,
                                             const SlabLanes& lanes_tok, const SlabLanes& lanes_out, bool copy_next,
                                             bool read_next, SH& sh) {
@@ -418,19 +344,18 @@ __device__ __forceinline__ void slab_step(f32x4 (&acc)[2 * MB][8], Frags<MB>& f,
     const NextSlabs nx{pp.src_tok, pp.src_out, lanes_tok, lanes_out, lds_copy_org.tok + dst, lds_copy_org.out + dst,
                        copy_next};
     __builtin_amdgcn_sched_barrier(0);
-    slots<COL_SLAB, MB, 0, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
+    slots<COL_SLAB, 0, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
     pp.rd = nxt;
 }
 
-template <int MB>
-__device__ __forceinline__ void zero_acc(f32x4 (&acc)[2 * MB][8]) {
+__device__ __forceinline__ void zero_acc(f32x4 (&acc)[TB][8]) {
 #pragma unroll
-    for (int mi = 0; mi < 2 * MB; ++mi)
+    for (int mi = 0; mi < TB; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 8; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
     // pin the register writes here (between the issue of the first slab copies and the wait for them)
 #pragma unroll
-    for (int mi = 0; mi < 2 * MB; ++mi)
+    for (int mi = 0; mi < TB; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 8; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
 }
@@ -441,15 +366,6 @@ __device__ __forceinline__ void zero_acc(f32x4 (&acc)[2 * MB][8]) {
 // the two wait states are part of the statement.
 __device__ __forceinline__ void mfma_in_place(f32x4& c, bf16x8 a, bf16x8 b) {
     asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
-}
-
-// Lanes whose contraction elements lie at or past `valid_chunks` 16-byte chunks (8 elements each) of a rank-wide
-// slab get a zero fragment: the slab's LDS rows hold duplicates there (the copies clamp), and a 32-deep MFMA
-// sub-step reaches past a rank of 16 (or 48).
-__device__ __forceinline__ bf16x8 zero_past_rank(bf16x8 v, int chunk, int valid_chunks) {
-    u32x4 u = __builtin_bit_cast(u32x4, v);
-    if (chunk >= valid_chunks) u = u32x4{0u, 0u, 0u, 0u};
-    return __builtin_bit_cast(bf16x8, u);
 }
 
 // One 32-deep sub-step of t = dS A^T for the pair of block rows bp (operation (5), see block_store): MFMAs with a
@@ -483,7 +399,7 @@ __device__ __forceinline__ void lora_term_substep(f32x4 (&t)[2][8], int kk, int 
 }
 
 // ---- the way out of a tile, two 16-row blocks of a wave's sub-tile at a time ---------------------------
-// Accumulator element e of block (mi, ni) in lane l is tile row  wm*32*MB + mi*16 + (l & 15)  and tile column
+// Accumulator element e of block (mi, ni) in lane l is tile row  wm*128 + mi*16 + (l & 15)  and tile column
 // wn*128 + ni*16 + 4*(l >> 4) + e: a lane owns four consecutive columns of one row per block.  The 32 x 128 bf16
 // of a block-row pair go through 8 KB of LDS of the wave's own (`stage`: 32 rows x 32 eight-byte slots, slot
 // index XOR-ed with 2 * (row & 15) so that the 32 lanes served in one cycle - 16 rows x 2 slots - land in 32
@@ -491,8 +407,8 @@ __device__ __forceinline__ void lora_term_substep(f32x4 (&t)[2][8], int kk, int 
 // LORA (operation (5)): before rounding, the masked LoRA term is added to the finished base-gradient
 // accumulators: t = dS A^T per 16x16 block by MFMAs with a vector-register destination (dS arrives scaled by
 // s*q), t & flag, + acc.  F[h]: keep flags of block row 2*bp + h, bit ni*2 + pr for element 2*pr, +16 for 2*pr+1.
-template <int MB, bool LORA>
-__device__ __forceinline__ void block_store(f32x4 (&acc)[2 * MB][8], int bp, const char* lds_tok, const char* lds_out,
+template <bool LORA>
+__device__ __forceinline__ void block_store(f32x4 (&acc)[TB][8], int bp, const char* lds_tok, const char* lds_out,
                                               const FragLanes& fl, int rank_chunks, uint32_t F0, uint32_t F1, char* stage,
                                               lora_bf16* out, int64_t ld, int row0_glob, int rows_left, bool col_ok,
                                               int l) {
@@ -549,22 +465,21 @@ __device__ __forceinline__ void block_store(f32x4 (&acc)[2 * MB][8], int bp, con
 
 // ---- operation (2): Y = X W + S' B ---------------------------------------------------------------
 // LA: how many slabs ahead of the matrix work the copies run (1 or 2).
-template <int MB, int LA>
+template <int LA>
 __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
     constexpr int MODE = LA == 2 ? kCopyAhead2 : kCopyEarly1;
-    constexpr int BM = 64 * MB, TB = 2 * MB;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int total = p.tiles_m * p.tiles_n;
     int id = blockIdx.x;
-    TileCtx tc = decode_tile(p.tb, p.M, BM, p.uniform_tiles, p.tiles_m, p.tiles_n, id, p.N);
+    TileCtx tc = decode_tile(p.tb, p.M, p.uniform_tiles, p.tiles_m, p.tiles_n, id, p.N);
     if (!tc.ok) return;
     const int l = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w & 1, wn = w >> 1;
     const int nk = p.K / BK;
     const uint32_t lds0 = lds_addr_of(smem);
-    const CopyOrg corg = copy_org<MB>(lds0);
+    const CopyOrg corg = copy_org(lds0);
     const FragLanes fl = frag_lanes<false>(wn);
-    const int tok_org = wm * (32 * MB) * 128, out_org = TILE_BYTES + wn * 128 * 128;
+    const int tok_org = wm * 128 * 128, out_org = TILE_BYTES + wn * 128 * 128;
     // p.r == 0 (no LoRA slab) and p.K == 0 (LoRA slab only) serve the unfused baseline's plain GEMMs.
     const bool has_lora = p.r > 0;
     const int rr = has_lora ? p.r : 16;
@@ -572,15 +487,15 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
     Pipe pp{nullptr, nullptr, BK * 2, BK * 2, 0u};
 
     // first slab pair of the first tile
-    SlabLanes sx = row_slab_lanes<2 * MB>(p.K, tc.rt.rows, 8), sw = row_slab_lanes(p.K, tc.cols_valid, 8);
+    SlabLanes sx = row_slab_lanes(p.K, tc.rt.rows, 8), sw = row_slab_lanes(p.K, tc.cols_valid, 8);
     if (nk > 0) {
-        load_slab<2 * MB>(lds0, p.X + (int64_t)tc.rt.row_start * p.K, sx);
+        load_slab(lds0, p.X + (int64_t)tc.rt.row_start * p.K, sx);
         load_slab(lds0 + TILE_BYTES, p.W + (int64_t)tc.c0 * p.K, sw);
     }
     constexpr int D = LA;                            // how many slabs ahead the copies run
     bool second_on_its_way = false;                  // first tile only: the main loop starts on the first slab pair alone
     if (D == 2 && nk > 1) {
-        load_slab<2 * MB>(lds0 + STAGE_BYTES, p.X + (int64_t)tc.rt.row_start * p.K + BK, sx);
+        load_slab(lds0 + STAGE_BYTES, p.X + (int64_t)tc.rt.row_start * p.K + BK, sx);
         load_slab(lds0 + STAGE_BYTES + TILE_BYTES, p.W + (int64_t)tc.c0 * p.K + BK, sw);
         second_on_its_way = true;
     }
@@ -593,34 +508,34 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
         const lora_bf16* Ssrc = p.S + (int64_t)rt.row_start * p.r;
         const lora_bf16* Bsrc = p.B + ((int64_t)rt.g * p.N + n0) * p.r;
         if (nk == 0) {
-            const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
-            load_slab<2 * MB>(lds0 + pp.rd, Ssrc, ss);
+            const SlabLanes ss = row_slab_lanes(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
+            load_slab(lds0 + pp.rd, Ssrc, ss);
             load_slab(lds0 + pp.rd + TILE_BYTES, Bsrc, sb);
         }
         f32x4 acc[TB][8];
-        zero_acc<MB>(acc);                           // while the first slabs are on their way (first tile)
-        if (second_on_its_way) wait_slab_loads_but<2 * MB + PASSES>();
+        zero_acc(acc);                           // while the first slabs are on their way (first tile)
+        if (second_on_its_way) wait_slab_loads_but<2 * PASSES>();
         else wait_slab_loads();
         second_on_its_way = false;
         __syncthreads();
-        Frags<MB> f;
-        if (nk > 0) read_frags<false, MB>(f, smem + pp.rd + tok_org, smem + pp.rd + out_org, fl);
+        Frags f;
+        if (nk > 0) read_frags<false>(f, smem + pp.rd + tok_org, smem + pp.rd + out_org, fl);
         pp.src_tok = (const char*)(Xt + D * BK) - kCopyBias;
         pp.src_out = (const char*)(Wt + D * BK) - kCopyBias;
         for (int kt = 0; kt + D < nk; ++kt)          // step kt brings slab kt + D
-            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sx, sw, true, true, none);
+            slab_step<false, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sx, sw, true, true, none);
         // the lane offsets of the LoRA slab pair are formed only now: through the main loop they would cost
         // sixteen registers that it does not have
-        const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
+        const SlabLanes ss = row_slab_lanes(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
         // after the last base slab the LoRA step rides as one more slab (token operand S' [rows, r], out operand
         // B [N, r]): the last base step brings it or, two ahead, the last but one (the last then brings nothing)
         const bool lora_piped = has_lora && !gm.mixed && nk >= D;
         pp.src_tok = (const char*)Ssrc - kCopyBias;
         pp.src_out = (const char*)Bsrc - kCopyBias;
         if (D == 2 && nk > 1)
-            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, lora_piped, true, none);
+            slab_step<false, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, lora_piped, true, none);
         if (nk > 0)
-            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, D == 1 && lora_piped,
+            slab_step<false, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, D == 1 && lora_piped,
                                         false, none);
         const uint32_t lo = pp.rd;                     // the stage that holds (or receives) the LoRA slab pair
 
@@ -632,11 +547,11 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
         asm volatile("" : "+s"(next));
         const bool has_next = next < total;
         if (has_next) {
-            tc = decode_tile(p.tb, p.M, BM, p.uniform_tiles, p.tiles_m, p.tiles_n, next, p.N);
-            sx = row_slab_lanes<2 * MB>(p.K, tc.rt.rows, 8);
+            tc = decode_tile(p.tb, p.M, p.uniform_tiles, p.tiles_m, p.tiles_n, next, p.N);
+            sx = row_slab_lanes(p.K, tc.rt.rows, 8);
             sw = row_slab_lanes(p.K, tc.cols_valid, 8);
             if (nk > 0) {
-                load_slab<2 * MB>(lds0 + (STAGE_BYTES - lo), p.X + (int64_t)tc.rt.row_start * p.K, sx);
+                load_slab(lds0 + (STAGE_BYTES - lo), p.X + (int64_t)tc.rt.row_start * p.K, sx);
                 load_slab(lds0 + (STAGE_BYTES - lo) + TILE_BYTES, p.W + (int64_t)tc.c0 * p.K, sw);
             }
         }
@@ -654,7 +569,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
                 const int g = group_adapter(gm, q);
                 if (lora_sync) {
                     __syncthreads();                   // every wave is done with the stage's previous contents
-                    if (q == 0) load_slab<2 * MB>(lds0 + lo, Ssrc, ss);
+                    if (q == 0) load_slab(lds0 + lo, Ssrc, ss);
                     load_slab(lds0 + lo + TILE_BYTES, p.B + ((int64_t)g * p.N + n0) * p.r, sb);
                     wait_slab_loads();                 // (also the next tile's first slab pair: mixed tiles are rare)
                     __syncthreads();
@@ -672,7 +587,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
                                                 chunk, rank_chunks);
 #pragma unroll
                     for (int mi = 0; mi < TB; ++mi) {
-                        const int blk = wm * (32 * MB) + mi * 16;       // first tile row of the block
+                        const int blk = wm * 128 + mi * 16;       // first tile row of the block
                         if (blk < blk_lo || blk >= blk_hi) continue;
                         const bf16x8 ft = zero_past_rank(
                             __builtin_bit_cast(bf16x8, *(const u32x4*)(smem + lo + tok_org + off + mi * 2048)), chunk, rank_chunks);
@@ -686,7 +601,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
         if (D == 2 && has_next && nk > 1) {
             // the next tile's second slab pair, into the stage of the LoRA slab pair once every wave has left it
             __syncthreads();
-            load_slab<2 * MB>(lds0 + lo, p.X + (int64_t)tc.rt.row_start * p.K + BK, sx);
+            load_slab(lds0 + lo, p.X + (int64_t)tc.rt.row_start * p.K + BK, sx);
             load_slab(lds0 + lo + TILE_BYTES, p.W + (int64_t)tc.c0 * p.K + BK, sw);
         }
 
@@ -698,9 +613,9 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
             const bool col_ok = wn * 128 + (le & 15) * 8 < cols_valid;
             lora_bf16* out = p.Y + (int64_t)rt.row_start * p.N + n0 + wn * 128;
 #pragma unroll
-            for (int bp = 0; bp < MB; ++bp) {
-                const int blk = wm * (32 * MB) + bp * 32;
-                block_store<MB, false>(acc, bp, nullptr, nullptr, fl, 0, 0u, 0u, stage, out, p.N, blk, rt.rows - blk,
+            for (int bp = 0; bp < TB / 2; ++bp) {
+                const int blk = wm * 128 + bp * 32;
+                block_store<false>(acc, bp, nullptr, nullptr, fl, 0, 0u, 0u, stage, out, p.N, blk, rt.rows - blk,
                                          col_ok, le);
             }
         }
@@ -714,10 +629,11 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
 // Lane l of a wave owns, in 16x16 block (mi, ni), columns ni*16 + 4*(l >> 4) + {0..3} of tile row mi*16 + (l & 15):
 // column pairs cp0 + ni*8 + {0, 1} with cp0 the lane's first pair.  Word number of a block row wd = ni*2 + pr; one
 // flag register per block row, bit wd for the even column and bit wd + 16 for the odd one.  A slab step forms WPS
-// words (4 in a 256-row tile, 2 in a 128-row tile), so the flags of a tile are complete after 32 slab steps.
+// words, so the flags of a tile are complete after 32 slab steps.
 // The MFMA here takes 16 cycles, so a piece is at most three full-rate instructions or one 32-bit multiply
 // (16 cycles by itself); the words of a step go through the six stages two at a time, alternating, so that a
 // piece never waits for the multiply before it.
+constexpr int WPS = 4;
 struct KeepShadow {
     uint32_t xb, x[2], t[2], m4, fcur;     // vector registers: running hash state, flags of the current register
     uint32_t x0, rkb;                      // row keys of the current block row: rk.a + cp0 * kGold, rk.b
@@ -726,7 +642,7 @@ struct KeepShadow {
 
 // Piece PID of a slab step: round PID / 12 handles words J = 2*round + {0, 1}; stage (PID % 12) >> 1 of
 //   x = x0 + pair*kGold; x ^= x>>16 | x *= M1 | x += rk.b; x ^= x>>15 | x *= M2 | x ^= x>>16; saturating x - (T-1) | flags
-template <int WPS, int PID>
+template <int PID>
 __device__ __forceinline__ void keep_piece(KeepShadow& k) {
     constexpr int RND = PID / 12, Q = PID % 12, ST = Q >> 1, R = Q & 1, J = 2 * RND + R;
     constexpr uint32_t CJ = (uint32_t)((J >> 1) * 8 + (J & 1)) * kGold;      // pairs 0, 1, 8, 9 past the step's first
@@ -761,33 +677,24 @@ __device__ __forceinline__ void keep_piece(KeepShadow& k) {
 
 // pieces ride on slots 2 .. 6*WPS+1 of sub-step 1 (before the hand-over; slot 1 carries a fragment read)
 // (copies two slabs ahead: those slots carry the copies; the pieces ride on the slots of sub-step 0 that carry no read)
-template <int MB> constexpr int shadow_piece_pf2(int s) {
-    if (MB == 4) {
-        constexpr int at[24] = {2, 3, 6, 7, 8, 10, 11, 14, 15, 16, 18, 19, 22, 23, 24, 26, 27, 30, 31, 32, 34, 35, 38, 39};
-        for (int j = 0; j < 24; ++j)
-            if (at[j] == s) return j;
-        return -1;
-    }
-    constexpr int at[12] = {2, 3, 5, 6, 7, 9, 11, 13, 14, 15, 17, 19};
-    for (int j = 0; j < 12; ++j)
-        if (at[j] == s) return j;
-    return -1;
+constexpr int shadow_piece_pf2(int s) {
+    constexpr int at[24] = {2, 3, 6, 7, 8, 10, 11, 14, 15, 16, 18, 19, 22, 23, 24, 26, 27, 30, 31, 32, 34, 35, 38, 39};
+    return Sched::find(at, s);
 }
-template <int MB, int SUB, int S, int MODE> __device__ __forceinline__ void shadow_slot(KeepShadow& k) {
-    constexpr int WPS = MB == 4 ? 4 : 2;
+template <int SUB, int S, int MODE> __device__ __forceinline__ void shadow_slot(KeepShadow& k) {
     if constexpr (MODE != kCopyAhead2) {
-        if constexpr (SUB == 1 && S >= 2 && S < 2 + 6 * WPS) keep_piece<WPS, S - 2>(k);
+        if constexpr (SUB == 1 && S >= 2 && S < 2 + 6 * WPS) keep_piece<S - 2>(k);
     } else if constexpr (SUB == 0) {
-        constexpr int pid = shadow_piece_pf2<MB>(S);
-        if constexpr (pid >= 0) keep_piece<WPS, pid>(k);
+        constexpr int pid = shadow_piece_pf2(S);
+        if constexpr (pid >= 0) keep_piece<pid>(k);
     }
 }
 // the same pieces outside any slab step (tiles with fewer than 32 slab steps)
-template <int WPS, int PID = 0>
+template <int PID = 0>
 __device__ __forceinline__ void keep_pieces_plain(KeepShadow& k) {
     if constexpr (PID < 6 * WPS) {
-        keep_piece<WPS, PID>(k);
-        keep_pieces_plain<WPS, PID + 1>(k);
+        keep_piece<PID>(k);
+        keep_pieces_plain<PID + 1>(k);
     }
 }
 
@@ -810,12 +717,10 @@ __device__ __forceinline__ SlabLanes col_slab_lanes(int64_t ld, int rows_valid, 
 // product first, while the keep flags of the tile are formed in the shadow of its MFMAs; the LoRA slab
 // pair [dS | A] rides in as one more slab during the last base slab, and the masked LoRA term is added
 // pair of block rows by pair on the way out.  p.N == 0 (LoRA term only) serves the unfused baseline.
-template <int MB, bool LORA, int LA>
+template <bool LORA, int LA>
 __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     constexpr int CM = LA == 2 ? kCopyAhead2 : kCopySpread1;
     constexpr bool PF = LA == 2;                      // copies two slabs ahead (LA as in fwd_gemm_kernel)
-    constexpr int BM = 64 * MB, TB = 2 * MB;
-    constexpr int WPS = MB == 4 ? 4 : 2;             // hash words per slab step and lane
     constexpr int FLAG_STEPS = 16 * TB / WPS;        // slab steps until the tile's flags are complete: 32
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int tm, tn;
@@ -840,39 +745,39 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     const lora_bf16* Wt = p.W + j0;
     const uint32_t lds0 = lds_addr_of(smem);
     const FragLanes fl = frag_lanes<true>(wn);
-    const int tok_org = wm * (32 * MB) * 128, out_org = TILE_BYTES;      // (the wave's columns are in fl.col_off)
-    const SlabLanes sd = row_slab_lanes<2 * MB>(p.N, rt.rows, 8), sw = col_slab_lanes(p.K, BK, cols_valid);
+    const int tok_org = wm * 128 * 128, out_org = TILE_BYTES;      // (the wave's columns are in fl.col_off)
+    const SlabLanes sd = row_slab_lanes(p.N, rt.rows, 8), sw = col_slab_lanes(p.K, BK, cols_valid);
     const int nk = p.N / BK;
     const int rr = LORA ? p.r : 16;
     const lora_bf16* dSt = p.dS + (int64_t)rt.row_start * rr;
     const lora_bf16* At = p.A + (int64_t)gm.g[0] * rr * p.K + j0;         // A of the tile's first adapter
     const int lo = (nk & 1) * STAGE_BYTES;           // the stage that receives the LoRA slab pair
     if (nk > 0) {
-        load_slab<2 * MB>(lds0, dYt + 0, sd);
+        load_slab(lds0, dYt + 0, sd);
         load_slab(lds0 + TILE_BYTES, Wt, sw);
     }
     if (PF && nk > 1) {                              // copies run two slabs ahead
-        load_slab<2 * MB>(lds0 + STAGE_BYTES, dYt + BK, sd);
+        load_slab(lds0 + STAGE_BYTES, dYt + BK, sd);
         load_slab(lds0 + STAGE_BYTES + TILE_BYTES, Wt + (int64_t)BK * p.K, sw);
     }
     if (LORA && (nk == 0 || (PF && nk == 1))) {
-        const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sa = col_slab_lanes(p.K, rr, cols_valid);
-        load_slab<2 * MB>(lds0 + lo, dSt, ss);
+        const SlabLanes ss = row_slab_lanes(rr, rt.rows, rr >> 3), sa = col_slab_lanes(p.K, rr, cols_valid);
+        load_slab(lds0 + lo, dSt, ss);
         load_slab(lds0 + lo + TILE_BYTES, At, sa);
     }
-    zero_acc<MB>(acc);                               // while the first slabs are on their way
+    zero_acc(acc);                               // while the first slabs are on their way
 
     // keep flags: state of the hash pieces, and what changes with the 16-row block row they work on
     KeepShadow ks;
     NoShadow none;
     uint32_t keep_all = 0;
-    uint32_t* flags = (uint32_t*)(smem + GEMM_LDS_BYTES) + threadIdx.x;     // [2 * MB][NTHREADS]
+    uint32_t* flags = (uint32_t*)(smem + GEMM_LDS_BYTES) + threadIdx.x;     // [TB][NTHREADS]
     const uint32_t cp0 = (uint32_t)(j0 + wn * 128 + 4 * (l >> 4)) >> 1;     // this lane's first column pair
     auto keep_step_begin = [&](int kt) {
         const int wd0 = kt * WPS, idx = wd0 & 15;
         if (idx == 0) {
             // next block row of the wave: its adapter's threshold and the row keys of its rows
-            const int blk = wm * (32 * MB) + (wd0 >> 4) * 16;
+            const int blk = wm * 128 + (wd0 >> 4) * 16;
             const int g = group_adapter(gm, blk >> 6);
             const KeepThreshold kth = keep_threshold(p.tb.T[g]);
             ks.tm1 = kth.tm1_packed;
@@ -898,12 +803,12 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     }
 
     // (two slab pairs on their way: the main loop starts on the first alone)
-    if (PF && (nk > 1 || (nk == 1 && LORA))) wait_slab_loads_but<2 * MB + PASSES>();
+    if (PF && (nk > 1 || (nk == 1 && LORA))) wait_slab_loads_but<2 * PASSES>();
     else wait_slab_loads();
     __syncthreads();
-    Frags<MB> f;
-    if (nk > 0) read_frags<true, MB>(f, smem + tok_org, smem + out_org, fl);
-    const CopyOrg corg = copy_org<MB>(lds0);
+    Frags f;
+    if (nk > 0) read_frags<true>(f, smem + tok_org, smem + out_org, fl);
+    const CopyOrg corg = copy_org(lds0);
     // slab steps bring the next base slab pair (PF: the one after next); the first 32 of all steps also carry the
     // hash pieces.  D = how far ahead the copies run.
     constexpr int D = PF ? 2 : 1;
@@ -913,16 +818,16 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     if constexpr (LORA) {
         for (; kt < min(nk - D, FLAG_STEPS); ++kt) {
             keep_step_begin(kt);
-            slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, ks);
+            slab_step<true, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, ks);
             keep_step_end(kt);
         }
     }
     for (; kt < nk - D; ++kt)
-        slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, none);
+        slab_step<true, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, none);
     if (nk > 0) {
         // the last D base slabs: the LoRA slab pair [dS | A] rides in as one more slab (nothing if there is no
         // LoRA term); its lane offsets are formed only now, the main loop has no registers for them
-        const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sa = col_slab_lanes(p.K, rr, cols_valid);
+        const SlabLanes ss = row_slab_lanes(rr, rt.rows, rr >> 3), sa = col_slab_lanes(p.K, rr, cols_valid);
         pp.src_tok = (const char*)dSt - kCopyBias;
         pp.src_out = (const char*)At - kCopyBias;
         // step nk - D brings the LoRA slab pair; with D = 2 the last step brings nothing.  Each of the two steps is
@@ -933,10 +838,10 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
                 // past the 32nd step the hash pieces still run, on a step number that is never flushed
                 const bool forming = kt < FLAG_STEPS;
                 if (forming) keep_step_begin(kt);
-                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, LORA && bring(), read_next(), ks);
+                slab_step<true, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, LORA && bring(), read_next(), ks);
                 if (forming) keep_step_end(kt);
             } else {
-                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, false, read_next(), none);
+                slab_step<true, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, false, read_next(), none);
             }
             ++kt;
         };
@@ -954,7 +859,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
 #pragma unroll 1
         for (int kt = min(nk, FLAG_STEPS); kt < FLAG_STEPS; ++kt) {
             keep_step_begin(kt);
-            keep_pieces_plain<WPS>(ks);
+            keep_pieces_plain(ks);
             keep_step_end(kt);
         }
     }
@@ -972,9 +877,9 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     lora_bf16* out = p.dX + (int64_t)rt.row_start * p.K + j0 + wn * 128;
     if constexpr (!LORA) {
 #pragma unroll
-        for (int bp = 0; bp < MB; ++bp) {
-            const int blk = wm * (32 * MB) + bp * 32;
-            block_store<MB, false>(acc, bp, nullptr, nullptr, fl, 0, 0u, 0u, stage, out, p.K, blk, rt.rows - blk, col_ok, le);
+        for (int bp = 0; bp < TB / 2; ++bp) {
+            const int blk = wm * 128 + bp * 32;
+            block_store<false>(acc, bp, nullptr, nullptr, fl, 0, 0u, 0u, stage, out, p.K, blk, rt.rows - blk, col_ok, le);
         }
     } else {
         // One run of 64-row groups per adapter present in the tile (a single run unless the tile is mixed).
@@ -992,10 +897,10 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
             }
             const int rank_chunks = p.tb.rank[g] >> 3;
 #pragma unroll
-            for (int bp = 0; bp < MB; ++bp) {
-                const int blk = wm * (32 * MB) + bp * 32;          // first tile row of the pair
+            for (int bp = 0; bp < TB / 2; ++bp) {
+                const int blk = wm * 128 + bp * 32;          // first tile row of the pair
                 if (blk < 64 * q || blk >= 64 * qe) continue;
-                block_store<MB, true>(acc, bp, lds_tok, lds_out, fl, rank_chunks, flags_e[(2 * bp) * NTHREADS],
+                block_store<true>(acc, bp, lds_tok, lds_out, fl, rank_chunks, flags_e[(2 * bp) * NTHREADS],
                                         flags_e[(2 * bp + 1) * NTHREADS], stage, out, p.K, blk, rt.rows - blk, col_ok, le);
             }
             q = qe;
@@ -1004,7 +909,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
 }
 
 // ---- host launchers -------------------------------------------------------------------------------
-// Uniform tiles (256 or 128 rows) over the packed batch are possible when every segment boundary is a multiple
+// Uniform tiles of 256 rows over the packed batch are possible when every segment boundary is a multiple
 // of 64 rows (a tile then holds at most four adapters, one per 64-row group).
 static bool boundaries_on_64(const AdapterTable& tb) {
     for (int g = 0; g <= tb.G; ++g)
@@ -1012,33 +917,90 @@ static bool boundaries_on_64(const AdapterTable& tb) {
     return true;
 }
 
-static int count_row_tiles(const AdapterTable& tb, int gran) {
-    int n = 0;
-    for (int g = 0; g < tb.G; ++g) n += (tb.row0[g + 1] - tb.row0[g] + gran - 1) / gran;
+// Row tiles of height `gran` over rows [lo, M), cut at segment boundaries.
+static int64_t count_row_tiles(const AdapterTable& tb, int gran, int lo) {
+    int64_t n = 0;
+    for (int g = 0; g < tb.G; ++g) {
+        const int a = tb.row0[g] > lo ? tb.row0[g] : lo, b = tb.row0[g + 1];
+        if (b > a) n += (b - a + gran - 1) / gran;
+    }
     return n;
 }
 
-// Row tiling of one launch: uniform tiles over the packed batch or per-segment tiles, of 256 or 128 rows.
-struct RowTiling { int bm; int uniform; int tiles_m; };
+// First row of row tile number `tile` of a tiling of height `gran`.
+static int row_of_tile(const AdapterTable& tb, int gran, bool uniform, int64_t tile) {
+    if (uniform) return (int)(tile * gran);
+    for (int g = 0; g < tb.G; ++g) {
+        const int64_t n = (tb.row0[g + 1] - tb.row0[g] + gran - 1) / gran;
+        if (tile < n) return tb.row0[g] + (int)tile * gran;
+        tile -= n;
+    }
+    return tb.row0[tb.G];
+}
 
 static std::atomic<int> g_forced_row_tile{0};      // 0: chosen per launch; 128 or 256: fixed (tuning and tests)
 void force_row_tile(int rows) { g_forced_row_tile.store(rows, std::memory_order_relaxed); }
 int forced_row_tile() { return g_forced_row_tile.load(std::memory_order_relaxed); }
 
-static RowTiling plan_row_tiles(const AdapterTable& tb, int M, int tiles_n, int forced) {
-    RowTiling best{256, 0, 0};
-    double best_cost = 0.0;
-    const bool on64 = tb.G > 1 && boundaries_on_64(tb);
-    for (int bm = 256; bm >= 128; bm >>= 1) {
-        if (forced != 0 && bm != forced) continue;
-        RowTiling t{bm, 0, 0};
-        t.uniform = on64;
-        t.tiles_m = t.uniform ? (M + bm - 1) / bm : count_row_tiles(tb, bm);
-        // rounds of workgroups over the compute units, times the relative duration of one tile (a 128-row
-        // tile does half the work of a 256-row one at a lower rate: the out operand is re-read twice as often)
-        const int64_t wgs = (int64_t)t.tiles_m * tiles_n;
-        const double cost = (double)((wgs + kComputeUnits - 1) / kComputeUnits) * (bm == 256 ? 1.0 : 0.6);
-        if (bm == 256 || forced != 0 || cost < best_cost) { best = t; best_cost = cost; }
+// What one launch costs, in microseconds: start and way out, plus the slabs of the contraction times the time a slab
+// takes the compute unit with the most tiles.  us[0] is that time for one tile on every compute unit, us[1] for two
+// of the small tiles sharing one (measured at K = N = 4096, 64 to 4096 rows; two of the large ones run one after the
+// other).  With few tiles the operands reach them faster: down to three quarters of it.
+// At 4096 x 4096 the family meets at about 300 rows (64 x 64 / 64 x 128 tiles), 700 (64 x 128 / 128 x 128), 1100
+// (128 x 128 / 128 x 256) and 2300 (128 x 256 / 256 x 256).
+struct TileCost { float fixed, us[2]; };
+constexpr TileCost kLargeCost = {6.0f, {1.36f, 2.72f}};
+constexpr TileCost kRingCost[kRingKinds] = {{5.5f, {0.82f, 1.64f}}, {5.5f, {0.47f, 0.94f}}, {4.0f, {0.30f, 0.57f}},
+                                            {4.0f, {0.18f, 0.34f}}, {4.0f, {0.14f, 0.25f}}};
+
+static double launch_cost(const TileCost& c, int64_t tiles, int64_t slabs) {
+    const int64_t n = (tiles + kComputeUnits - 1) / kComputeUnits;
+    const double fill = tiles >= kComputeUnits ? 1.0 : 0.75 + 0.25 * (double)tiles / kComputeUnits;
+    return c.fixed + (double)slabs * fill * ((double)(n / 2) * c.us[1] + (double)(n & 1) * c.us[0]) + 1.0 * (double)(n - 1);
+}
+
+// How one GEMM is launched: one part, or two launches that share the rows.  kind -1: 256 x 256 tiles (first part only),
+// otherwise a small-tile kernel (kRingTiles).
+struct GemmPart { int kind, row_lo, row_hi; int64_t tiles_m; };
+struct GemmPlan { int uniform, parts; GemmPart part[2]; };
+
+static GemmPlan plan_gemm(const AdapterTable& tb, int M, int kc, int nc, int r, int forced) {
+    GemmPlan best{tb.G > 1 && boundaries_on_64(tb), 0, {}};
+    if (M == 0) return best;
+    const int64_t slabs = kc / BK + (r > 0);
+    auto tiles_of = [&](int kind, int lo) {
+        if (kind < 0) return best.uniform ? (int64_t)(M + 255) / 256 : count_row_tiles(tb, 256, 0);
+        return count_row_tiles(tb, kRingTiles[kind][0], lo);
+    };
+    auto columns = [&](int kind) { const int w = kind < 0 ? 256 : kRingTiles[kind][1]; return (int64_t)(nc + w - 1) / w; };
+    auto cost_of = [&](int kind, int64_t tiles) { return launch_cost(kind < 0 ? kLargeCost : kRingCost[kind], tiles, slabs); };
+    const int only = forced == 256 ? -1 : 0;         // (the knob fixes the 256-row tiles, or 128 x 256)
+    double cost = 1e30;
+    for (int k = forced ? only : -1; k < (forced ? only + 1 : kRingKinds); ++k) {
+        const int64_t tm = tiles_of(k, 0), tn = columns(k);
+        const double all = cost_of(k, tm * tn);
+        if (all < cost) {
+            cost = all;
+            best.parts = 1;
+            best.part[0] = GemmPart{k, 0, M, tm};
+        }
+        // A last round that leaves most compute units without a tile: the full rounds by themselves, and the rest of
+        // the rows as a launch of their own on smaller tiles (2.5 us for the gap between the two).  Measured: 5003
+        // rows, 14336 -> 4096: 531 us on 128 x 256 tiles, 401 us split; 4096 rows, 4096 -> 4096, need no second part.
+        const int64_t full = tm * tn / kComputeUnits * kComputeUnits / tn;
+        if (forced || k > 1 || full == 0 || full == tm) continue;
+        const int cut = row_of_tile(tb, k < 0 ? 256 : kRingTiles[k][0], k < 0 && best.uniform, full);
+        const double first = cost_of(k, full * tn) + 2.5;
+        for (int k2 = 0; k2 < kRingKinds; ++k2) {
+            const int64_t tm2 = tiles_of(k2, cut);
+            const double c = first + cost_of(k2, tm2 * columns(k2));
+            if (c < cost) {
+                cost = c;
+                best.parts = 2;
+                best.part[0] = GemmPart{k, 0, cut, full};
+                best.part[1] = GemmPart{k2, cut, M, tm2};
+            }
+        }
     }
     return best;
 }
@@ -1064,49 +1026,63 @@ void force_slab_lookahead(int slabs) { g_forced_lookahead.store(slabs, std::memo
 // streams from HBM in every launch.
 static bool weight_streams(int64_t K, int64_t N) { return K * N * 2 > (64ll << 20); }
 
-hipError_t launch_fwd_gemm(FwdGemmArgs a, int forced, hipStream_t st) {
+static hipError_t launch_ring_part(const GemmPart& t, bool col, RingArgs a, hipStream_t st) {
+    a.tiles_m = (int)t.tiles_m;
+    a.tiles_n = (a.NC + kRingTiles[t.kind][1] - 1) / kRingTiles[t.kind][1];
+    a.row_lo = t.row_lo;
+    a.row_hi = t.row_hi;
+    return launch_ring(t.kind, col, a, st);
+}
+
+static hipError_t launch_fwd_large(FwdGemmArgs a, const GemmPlan& t, hipStream_t st) {
     a.tiles_n = (a.N + BN - 1) / BN;
-    const RowTiling t = plan_row_tiles(a.tb, a.M, a.tiles_n, forced);
     a.uniform_tiles = t.uniform;
-    a.tiles_m = t.tiles_m;
-    if (a.tiles_m == 0) return hipSuccess;
-    static bool attr_set[4] = {false, false, false, false};
+    a.tiles_m = (int)t.part[0].tiles_m;
+    static bool attr_set[2] = {false, false};
     // copies two slabs ahead unless the contraction is short (measured: 2.5 % faster at K = N = 4096, 5 - 8 % with
     // weights of 117 and 470 MB; a contraction of 16 slabs, where every step waits for its copies anyway, 4 % slower)
     const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
     const bool ahead2 = knob ? knob == 2 : a.K >= 32 * BK;
-    if (t.bm == 256)
-        return ahead2 ? launch_gemm(fwd_gemm_kernel<4, 2>, attr_set[0], a, st, GEMM_LDS_TOTAL, true)
-                      : launch_gemm(fwd_gemm_kernel<4, 1>, attr_set[1], a, st, GEMM_LDS_TOTAL, true);
-    return ahead2 ? launch_gemm(fwd_gemm_kernel<2, 2>, attr_set[2], a, st, GEMM_LDS_TOTAL, true)
-                  : launch_gemm(fwd_gemm_kernel<2, 1>, attr_set[3], a, st, GEMM_LDS_TOTAL, true);
+    return ahead2 ? launch_gemm(fwd_gemm_kernel<2>, attr_set[0], a, st, GEMM_LDS_TOTAL, true)
+                  : launch_gemm(fwd_gemm_kernel<1>, attr_set[1], a, st, GEMM_LDS_TOTAL, true);
 }
 
-hipError_t launch_bwd_dx(DxGemmArgs a, int forced, hipStream_t st) {
+hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st) {
+    const GemmPlan t = plan_gemm(a.tb, a.M, a.K, a.N, a.r, forced);
+    const RingArgs ring{a.X, a.W, a.S, a.B, a.Y, a.M, a.K, a.N, a.r, 0, 0, 0, 0, a.tb};
+    for (int i = 0; i < t.parts; ++i) {
+        const hipError_t e = t.part[i].kind < 0 ? launch_fwd_large(a, t, st) : launch_ring_part(t.part[i], false, ring, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t st) {
     a.tiles_n = (a.K + BN - 1) / BN;
-    const RowTiling t = plan_row_tiles(a.tb, a.M, a.tiles_n, forced);
     a.uniform_tiles = t.uniform;
-    a.tiles_m = t.tiles_m;
-    if (a.tiles_m == 0) return hipSuccess;
-    static bool attr_set[8] = {false, false, false, false, false, false, false, false};
+    a.tiles_m = (int)t.part[0].tiles_m;
+    static bool attr_set[4] = {false, false, false, false};
     // copies two slabs ahead when the weight streams from HBM (measured: 3 - 7 % faster there, 0.5 - 1 % slower
     // with a cache-resident weight, whose copies land in time anyway)
     const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
     const bool ahead2 = knob ? knob == 2 : weight_streams(a.K, a.N);
-    // with a LoRA term: the slab stages plus the parked keep flags (2 * MB words per lane)
-    const int lds4 = GEMM_LDS_BYTES + 8 * NTHREADS * 4, lds2 = GEMM_LDS_BYTES + 4 * NTHREADS * 4;
-    if (a.r > 0) {
-        if (t.bm == 256)
-            return ahead2 ? launch_gemm(bwd_dx_kernel<4, true, 2>, attr_set[0], a, st, lds4)
-                          : launch_gemm(bwd_dx_kernel<4, true, 1>, attr_set[1], a, st, lds4);
-        return ahead2 ? launch_gemm(bwd_dx_kernel<2, true, 2>, attr_set[2], a, st, lds2)
-                      : launch_gemm(bwd_dx_kernel<2, true, 1>, attr_set[3], a, st, lds2);
+    // with a LoRA term: the slab stages plus the parked keep flags (8 words per lane)
+    const int lds = GEMM_LDS_BYTES + TB * NTHREADS * 4;
+    if (a.r > 0)
+        return ahead2 ? launch_gemm(bwd_dx_kernel<true, 2>, attr_set[0], a, st, lds)
+                      : launch_gemm(bwd_dx_kernel<true, 1>, attr_set[1], a, st, lds);
+    return ahead2 ? launch_gemm(bwd_dx_kernel<false, 2>, attr_set[2], a, st)
+                  : launch_gemm(bwd_dx_kernel<false, 1>, attr_set[3], a, st);
+}
+
+hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st) {
+    const GemmPlan t = plan_gemm(a.tb, a.M, a.N, a.K, a.r, forced);
+    const RingArgs ring{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, 0, 0, 0, 0, a.tb};
+    for (int i = 0; i < t.parts; ++i) {
+        const hipError_t e = t.part[i].kind < 0 ? launch_dx_large(a, t, st) : launch_ring_part(t.part[i], true, ring, st);
+        if (e != hipSuccess) return e;
     }
-    if (t.bm == 256)
-        return ahead2 ? launch_gemm(bwd_dx_kernel<4, false, 2>, attr_set[4], a, st)
-                      : launch_gemm(bwd_dx_kernel<4, false, 1>, attr_set[5], a, st);
-    return ahead2 ? launch_gemm(bwd_dx_kernel<2, false, 2>, attr_set[6], a, st)
-                  : launch_gemm(bwd_dx_kernel<2, false, 1>, attr_set[7], a, st);
+    return hipSuccess;
 }
 
 }  // namespace lf

@@ -1,0 +1,22 @@
+// Arguments of the small-tile GEMM kernels (lf_gemm_ring.hip).
+#pragma once
+#include "lf_internal.h"
+
+namespace lf {
+
+// Operation (2): tok X [M,KC], out W [NC,KC], ltok S' [M,r], lout B [G,NC,r], res Y [M,NC].
+// Operation (5): tok dY [M,KC], out W [KC,NC], ltok dS [M,r], lout A [G,r,NC], res dX [M,NC].
+// r == 0: no LoRA term.
+struct RingArgs {
+    const lora_bf16* tok; const lora_bf16* out; const lora_bf16* ltok; const lora_bf16* lout; lora_bf16* res;
+    int M, KC, NC, r, tiles_m, tiles_n;
+    int row_lo, row_hi;                              // the launch covers rows [row_lo, row_hi) of the packed batch
+    AdapterTable tb;
+};
+
+constexpr int kRingKinds = 5;
+constexpr int kRingTiles[kRingKinds][2] = {{128, 256}, {128, 128}, {64, 128}, {64, 64}, {32, 64}};   // rows x columns
+
+hipError_t launch_ring(int kind, bool col, const RingArgs& a, hipStream_t st);
+
+}  // namespace lf

@@ -93,12 +93,12 @@ inline int64_t max_stream_panels(int64_t M, int G) {
 // `forced`: the row-tile knob as read by the entry point (0, 128 or 256).  The streaming launchers need
 // StreamArgs::panel_rows, the finalize launchers FinalizeArgs::panel_rows_db / _da, filled in by the caller.
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st);
-hipError_t launch_fwd_gemm(FwdGemmArgs a, int forced, hipStream_t st);
+hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st);
 hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st);
 hipError_t launch_stream_da(StreamArgs a, hipStream_t st);
 hipError_t launch_finalize_ds_db(const FinalizeArgs& a, hipStream_t st);
 hipError_t launch_finalize_da(const FinalizeArgs& a, hipStream_t st);
-hipError_t launch_bwd_dx(DxGemmArgs a, int forced, hipStream_t st);
+hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st);
 hipError_t launch_debug_mask(int64_t M, int64_t K, uint32_t T, uint32_t k0, uint32_t k1, uint8_t* keep,
                              hipStream_t st);
 
