@@ -3,120 +3,203 @@
 //     S'[i,c] = s * q * sum_j keep(i,j) X[i,j] A[c,j],
 // with the keep mask regenerated in registers from (seed, local row, column) and never stored.
 // X is streamed once from HBM; A (r x K) stays cache resident.  Also the diagnostic mask writer.
+//
+// What bounds it: HBM once there are rows for every compute unit (8192 rows, K = 14336, r = 16: 37 us = 6.3 TB/s); below
+// that the sweep of one workgroup over K, whose price is the number of vector memory instructions and of cache lines
+// they touch (an instruction over 16 rows x 64 bytes costs the compute unit about 60 cycles, one over 8 rows x 128 bytes
+// about 25), then the mask (12 vector instructions per column pair).  Hence X and A go global -> LDS in whole 128-byte
+// lines, several stages of 256 columns ahead; A is fetched once per workgroup and stage, not once per wave; the masks
+// of a stage are formed while its copies land, and not at all without dropout.
+// Measured against fragments loaded straight into registers (same rows and K, us): K = 14336: 64 rows r = 16 29 -> 23,
+// r = 64 65 -> 32; 5003 rows r = 16 57 -> 36, r = 64 128 -> 43; 8192 rows r = 64 83 -> 50.  K = 4096: 8192 rows r = 16
+// 18 -> 15, 4096 rows r = 64 24 -> 15.
+#include <type_traits>
+
 #include "lf_device.h"
+#include "lf_gemm_parts.h"
 #include "lf_internal.h"
 
 namespace lf {
 
+constexpr int DOWN_SLABS = 4;                       // 64-column slabs per stage
+constexpr int DOWN_PARTS = 2 * DOWN_SLABS;          // a wave owns one half (32 columns) of one slab of every stage
 
-constexpr int DOWN_WAVES = 8;      // waves split the K dimension in 32-column chunks
+// CB = r / 16 column blocks of S'; RB 16-row blocks per workgroup, WR of them on waves of their own (the others in the
+// same wave); ring of NS stages in LDS.
+template <int CB_, int RB_, int WR_, int NS_>
+struct Down {
+    static constexpr int CB = CB_, RB = RB_, WR = WR_, RW = RB / WR, NS = NS_;
+    static constexpr int NW = DOWN_PARTS * WR, THREADS = 64 * NW;
+    static constexpr int X_COPIES = DOWN_SLABS * RB * 2, A_COPIES = DOWN_SLABS * CB * 2;   // 1 KB wave copies per stage
+    static constexpr int P = (X_COPIES + A_COPIES) / NW;                                   // ... per wave
+    static constexpr int STAGE = (X_COPIES + A_COPIES) * 1024;
+    static constexpr int LDS = NS * STAGE;
+    static_assert((X_COPIES + A_COPIES) % NW == 0 && P <= 8 && P * (NS - 1) < 64, "copies per wave; the wait counter has six bits");
+    static_assert(RB % WR == 0 && DOWN_PARTS * RB * CB * 1024 <= LDS, "the cross-wave sum goes through the ring");
+};
 
-#define LF_MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16((a), (b), (c), 0, 0, 0)
-
-// CB = r / 16 column blocks of S'; RB = 16-row MFMA blocks per workgroup.  The kernel is bound by the
-// vector ALU work of the mask (about 15 instructions per column pair), so a launch with fewer
-// 32-row workgroups than compute units is cut into 16-row workgroups instead.
-template <int CB, int RB>
-__global__ void __launch_bounds__(DOWN_WAVES * 64) down_kernel(DownArgs p) {
-    constexpr int DOWN_ROWS = 16 * RB;
-    __shared__ f32x4 red[DOWN_WAVES][RB][CB][64];
-    RowTile rt;
-    if (!find_row_tile(p.tb, DOWN_ROWS, blockIdx.x, rt)) return;
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int g = rt.g;
-    const KeepThreshold T = keep_threshold(p.tb.T[g]);
-    const lora_bf16* Ag = p.A + (int64_t)g * p.r * p.K;
-    const int cbn = p.tb.rank[g] >> 4;                  // 16-column blocks this adapter uses (<= CB)
-
-    const lora_bf16* xrow[RB];
-    RowKey rk[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        const int row = rb * 16 + (l & 15);
-        xrow[rb] = p.X + (int64_t)(rt.row_start + min(row, rt.rows - 1)) * p.K;
-        rk[rb] = row_key(p.tb.k0[g], p.tb.k1[g], (uint32_t)(rt.local_row0 + row));
+// This wave's copies I .. of one stage; src[i] is the stage's first column in the matrix of copy i.
+template <class C, int I = 0>
+__device__ __forceinline__ void down_copy(const char* const (&src)[C::P], const uint32_t (&off)[C::P], uint32_t m0) {
+    if constexpr (I < C::P) {
+        copy16_to_lds<pass_imm(C::P, I), I == 0>(src[I], off[I], m0);
+        down_copy<C, I + 1>(src, off, m0);
     }
-    f32x4 acc[RB][CB];
+}
+
+template <class C>
+__global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgs p) {
+    constexpr int CB = C::CB, RB = C::RB, RW = C::RW, NS = C::NS, P = C::P;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    RowTile rt;
+    if (!find_row_tile(p.tb, 16 * RB, blockIdx.x, rt)) return;
+    const int l = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = w % DOWN_PARTS, pos = part >> 1, sub = part & 1;
+    const int rb0 = w / DOWN_PARTS * RW;                // this wave's first row block
+    const int g = rt.g;
+    const uint32_t T = p.tb.T[g];
+    const KeepThreshold th = keep_threshold(T);
+    const int cbn = p.tb.rank[g] >> 4;                  // 16-column blocks this adapter uses (<= CB)
+    const int nslabs = p.K / BK, nst = (nslabs + DOWN_SLABS - 1) / DOWN_SLABS;
+
+    // This wave's copies: number q of a stage is X rows (8 per copy) of slab q / (2 RB), then A rows of a slab.
+    // Rows past the tile (or past the adapter's rank) repeat the last one.
+    uint32_t off[P];
+    const char* mat[P];
+    int slab[P];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+    for (int i = 0; i < P; ++i) {
+        const int q = w * P + i, qa = q - C::X_COPIES;
+        const bool is_x = q < C::X_COPIES;
+        slab[i] = is_x ? q / (2 * RB) : qa / (2 * CB);
+        const int row = (is_x ? q % (2 * RB) : qa % (2 * CB)) * 8 + (l >> 3);
+        const int last = is_x ? rt.rows - 1 : p.tb.rank[g] - 1;
+        mat[i] = (is_x ? (const char*)(p.X + (int64_t)rt.row_start * p.K) : (const char*)(p.A + (int64_t)g * p.r * p.K)) - kCopyBias;
+        off[i] = ((uint32_t)min(row, last) * (uint32_t)p.K + slab[i] * BK + (((l & 7) ^ row_slab_swz(row)) << 3)) * 2 +
+                 kCopyBias - pass_imm(P, i);
+    }
+    const uint32_t m0 = lds_addr_of(smem) + w * (P * 1024) + (P / 2) * 1024;
+    const int partial = nslabs % DOWN_SLABS;            // slabs of the last stage, if it is not full
+    auto issue = [&](int st, int ring) {
+        const char* src[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) src[i] = mat[i] + (int64_t)st * (DOWN_SLABS * BK * 2);
+        if (partial && st == nst - 1) {                 // slabs past K: copies of the last one (never used)
+#pragma unroll
+            for (int i = 0; i < P; ++i) src[i] -= max(slab[i] - (partial - 1), 0) * (BK * 2);
+        }
+        down_copy<C>(src, off, m0 + ring * C::STAGE);
+    };
+
+    // Every workgroup starts its sweep over K at a different stage (a function of its 32-row group within the segment,
+    // so that single- and multi-adapter calls, and both workgroup heights, sum in the same order): workgroups sweeping
+    // in lockstep would all hit the same few L2 channels, the row pitch being a multiple of the channel interleave.
+    int st = (int)(((unsigned)(rt.local_row0 / 32) * 5u) % (unsigned)nst), st_copy = st;
+    auto advance = [&](int& t) { t = t + 1 == nst ? 0 : t + 1; };
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < nst) {
+            issue(st_copy, s);
+            advance(st_copy);
+        }
+
+    RowKey rk[RW];
+    f32x4 acc[RW][CB];
+    u32x4 keep[RW];
+#pragma unroll
+    for (int rb = 0; rb < RW; ++rb) {
+        rk[rb] = row_key(p.tb.k0[g], p.tb.k1[g], (uint32_t)(rt.local_row0 + (rb0 + rb) * 16 + (l & 15)));
+        keep[rb] = u32x4{~0u, ~0u, ~0u, ~0u};
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    // keep masks of this lane's 8 columns in stage t
+    auto form_masks = [&](int t) {
+        const uint32_t x0 = (uint32_t)((t * DOWN_SLABS + pos) * (BK / 2) + 16 * sub + 4 * (l >> 4)) * kGold;
+#pragma unroll
+        for (int rb = 0; rb < RW; ++rb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                keep[rb][i] = keep_pair_mask(hash_word_at(rk[rb], rk[rb].a + x0 + (uint32_t)i * kGold), th);
+    };
+    const int o = row_slab_off(l & 15, 4 * sub + (l >> 4));
+    const char* xs = smem + (pos * RB + rb0) * 2048 + o;
+    const char* as = smem + C::X_COPIES * 1024 + pos * (CB * 2048) + o;
 
-    const int nchunks = p.K >> 5;
-    // each wave walks its 32-column chunks (w, w + 8, ...) with loads running DEPTH chunks ahead
-    constexpr int DEPTH = CB == 1 ? 4 : 2;
-    struct ChunkRegs { u32x4 x[RB], a[CB]; };
-    ChunkRegs ring[DEPTH];
-    // Every workgroup starts its sweep over K at a different column (a function of its 32-row group
-    // within the segment, so that single- and multi-adapter calls, and both workgroup heights, sum in
-    // the same order): workgroups
-    // sweeping in lockstep would all hit the same few L2 channels, the row pitch being a multiple of
-    // the channel interleave.
-    const int rot = (int)(((unsigned)(rt.local_row0 / 32) * 5u) % (unsigned)max(nchunks / DOWN_WAVES, 1)) * DOWN_WAVES;
-    auto load = [&](ChunkRegs& c, int kc0) {
-        const int kc = (kc0 + rot) % nchunks;
-        const int col = kc * 32 + 8 * (l >> 4);
+    int ring = 0;
+    auto step = [&](int s, auto steady) {
+        if (T) form_masks(st);                          // while the stage's copies land
+        // the stage has landed for every wave, and every wave has left the stage that the next copies overwrite
+        if (steady() || s + NS - 2 < nst) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(P*(NS - 2)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        asm volatile("s_barrier" ::: "memory");
+        u32x4 x[RW];
+        bf16x8 a[CB];
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) c.x[rb] = *(const u32x4*)(xrow[rb] + col);
+        for (int rb = 0; rb < RW; ++rb) x[rb] = *(const u32x4*)(xs + ring * C::STAGE + rb * 2048);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-            if (CB == 1 || cb < cbn) c.a[cb] = *(const u32x4*)(Ag + (int64_t)(cb * 16 + (l & 15)) * p.K + col);
-    };
-    auto consume = [&](const ChunkRegs& c, int kc0) {
-        const int kc = (kc0 + rot) % nchunks;
-        const uint32_t col = (uint32_t)(kc * 32 + 8 * (l >> 4));
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const bf16x8 xf = __builtin_bit_cast(bf16x8, mask8(c.x[rb], rk[rb], col, T));
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-                if (CB == 1 || cb < cbn) acc[rb][cb] = LF_MFMA16(__builtin_bit_cast(bf16x8, c.a[cb]), xf, acc[rb][cb]);
+        for (int cb = 0; cb < CB; ++cb) a[cb] = __builtin_bit_cast(bf16x8, *(const u32x4*)(as + ring * C::STAGE + cb * 2048));
+        __builtin_amdgcn_sched_barrier(0);
+        if (steady()) {
+            issue(st_copy, ring == 0 ? NS - 1 : ring - 1);
+            advance(st_copy);
         }
-    };
+        if (st * DOWN_SLABS + pos < nslabs) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d)
-        if (w + d * DOWN_WAVES < nchunks) load(ring[d], w + d * DOWN_WAVES);
-    for (int kc = w; kc < nchunks; kc += DEPTH * DOWN_WAVES) {
+            for (int rb = 0; rb < RW; ++rb) {
+                x[rb] &= keep[rb];
+                const bf16x8 xf = __builtin_bit_cast(bf16x8, x[rb]);
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int k = kc + d * DOWN_WAVES;
-            if (k < nchunks) {
-                consume(ring[d], k);
-                if (k + DEPTH * DOWN_WAVES < nchunks) load(ring[d], k + DEPTH * DOWN_WAVES);
+                for (int cb = 0; cb < CB; ++cb)
+                    if (CB == 1 || cb < cbn)               // (blocks past the adapter's rank hold nothing that may be used)
+                        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[rb][cb]) : "v"(a[cb]), "v"(xf));
             }
         }
-    }
+        advance(st);
+        ring = ring + 1 == NS ? 0 : ring + 1;
+    };
+    int s = 0;
+    for (; s + NS - 1 < nst; ++s) step(s, std::true_type{});
+    for (; s < nst; ++s) step(s, std::false_type{});
+
+    asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+    for (int rb = 0; rb < RW; ++rb)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) red[w][rb][cb][l] = acc[rb][cb];
+        for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+v"(acc[rb][cb]));
     __syncthreads();
-    // fixed-order sum over the waves, scale by s*q, round once to bf16
-    const float sq = p.tb.s[g] * p.tb.q[g];
-    for (int idx = threadIdx.x; idx < RB * CB * 64; idx += DOWN_WAVES * 64) {
-        const int lane = idx & 63, cb = (idx >> 6) % CB, rb = (idx >> 6) / CB;
-        f32x4 v = red[0][rb][cb][lane];
+    f32x4* red = (f32x4*)smem;                             // [DOWN_PARTS][RB][CB][64]
 #pragma unroll
-        for (int ww = 1; ww < DOWN_WAVES; ++ww) v += red[ww][rb][cb][lane];
+    for (int rb = 0; rb < RW; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) red[((part * RB + rb0 + rb) * CB + cb) * 64 + l] = acc[rb][cb];
+    __syncthreads();
+    // fixed-order sum over the column parts, scale by s*q, round once to bf16
+    const float sq = p.tb.s[g] * p.tb.q[g];
+    for (int idx = threadIdx.x; idx < RB * CB * 64; idx += C::THREADS) {
+        const int lane = idx & 63, cb = (idx >> 6) % CB, rb = (idx >> 6) / CB;
+        f32x4 v = red[idx];
+#pragma unroll
+        for (int ww = 1; ww < DOWN_PARTS; ++ww) v += red[ww * (RB * CB * 64) + idx];
         const int row = rb * 16 + (lane & 15);
         if (row < rt.rows) {
-            u32x2 o;
-            o.x = pack_bf16x2(v[0] * sq, v[1] * sq);
-            o.y = pack_bf16x2(v[2] * sq, v[3] * sq);
-            *(u32x2*)(p.S + (int64_t)(rt.row_start + row) * p.r + cb * 16 + 4 * (lane >> 4)) = o;
+            u32x2 out;
+            out.x = pack_bf16x2(v[0] * sq, v[1] * sq);
+            out.y = pack_bf16x2(v[2] * sq, v[3] * sq);
+            *(u32x2*)(p.S + (int64_t)(rt.row_start + row) * p.r + cb * 16 + 4 * (lane >> 4)) = out;
         }
     }
 }
 
-template <int RB>
-static hipError_t launch_down_rows(const DownArgs& a, int tiles, hipStream_t st) {
-    const dim3 grid(tiles), block(DOWN_WAVES * 64);
-    switch (a.r) {
-        case 16: hipLaunchKernelGGL((down_kernel<1, RB>), grid, block, 0, st, a); break;
-        case 32: hipLaunchKernelGGL((down_kernel<2, RB>), grid, block, 0, st, a); break;
-        case 64: hipLaunchKernelGGL((down_kernel<4, RB>), grid, block, 0, st, a); break;
-        default: return hipErrorInvalidValue;
+template <class C>
+static hipError_t launch_down_cfg(const DownArgs& a, int tiles, hipStream_t st) {
+    static bool attr_set = false;                      // one flag per instantiation
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)down_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
     }
+    hipLaunchKernelGGL((down_kernel<C>), dim3(tiles), dim3(C::THREADS), C::LDS, st, a);
     return hipGetLastError();
 }
 
@@ -128,8 +211,14 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
         tiles16 += (len + 15) / 16;
     }
     if (tiles32 == 0) return hipSuccess;
-    const bool small = forced ? forced == 128 : tiles32 < kComputeUnits;
-    return small ? launch_down_rows<1>(a, tiles16, st) : launch_down_rows<2>(a, tiles32, st);
+    // A 16-row workgroup takes 0.6 - 0.75 of a 32-row one's time (its copies of A serve half as many rows), so it is the
+    // faster one exactly while all of them run at once: K = 14336, r = 64: 4096 rows 38 against 43 us, 5003 rows 65
+    // against 43 us; r = 16: 26 against 37 and 36 against 36 us.
+    const bool small = forced ? forced == 128 : tiles16 <= kComputeUnits;
+    if (a.r == 16) return small ? launch_down_cfg<Down<1, 1, 1, 5>>(a, tiles16, st) : launch_down_cfg<Down<1, 2, 1, 3>>(a, tiles32, st);
+    if (a.r == 32) return small ? launch_down_cfg<Down<2, 1, 1, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 2, 2, 4>>(a, tiles32, st);
+    if (a.r == 64) return small ? launch_down_cfg<Down<4, 1, 1, 4>>(a, tiles16, st) : launch_down_cfg<Down<4, 2, 2, 3>>(a, tiles32, st);
+    return hipErrorInvalidValue;
 }
 
 // keep[i,j] for one adapter, one thread per column pair
