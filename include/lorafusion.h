@@ -150,14 +150,15 @@ lora_status lora_debug_mask(int64_t M, int64_t K, float p, uint64_t seed, uint8_
                             lora_stream stream);
 
 /* Tuning knob and test hook (process-wide, not thread safe).  Several kernels exist in more than
- * one height: the GEMMs of operations (2) and (5) (Section 5.1) with 256 or 128 token rows per output
- * tile, the down-projection of operation (1) with 32 or 16 token rows per workgroup, and the streaming
- * reductions of operations (3) and (4) with row panels of 1024 down to 64 rows.  By default every launch
- * picks the height that fills the chip better (the small ones for short batches and narrow
- * projections).  rows = 256 fixes the large height of the first three and panels of at least 256 rows
- * for all later calls, rows = 128 GEMM tiles of 128 rows x 256 columns and the small height of the other two,
- * rows = 0 restores the automatic choice; any other value returns LORA_ERR_PARAM.  Y, S_saved and dX are
- * bit-identical under all three settings; dA and dB are fp32 sums over the row panels and agree up to the order of those sums. */
+ * one height: the GEMMs of operations (2) and (5) (Section 5.1) with 256 down to 32 token rows per output
+ * tile, the down-projection of operation (1) with 32 or 16 token rows per workgroup, operation (3) with row
+ * panels of 1024 down to 64 rows, and operation (4) with whole segments or row panels of 256 rows and more.
+ * By default every launch picks the height that fills the chip better (the small ones for short batches and
+ * narrow projections; a GEMM may take two launches of different heights).  rows = 256 fixes the large height
+ * of the GEMMs and of (1), panels of at least 256 rows in (3) and of 256 in (4) for all later calls, rows = 128
+ * GEMM tiles of 128 rows x 256 columns and the small height of (1), rows = 0 restores the automatic choice;
+ * any other value returns LORA_ERR_PARAM.  Y, S_saved and dX are bit-identical under all three settings; dA
+ * and dB are fp32 sums over the row panels and agree up to the order of those sums. */
 lora_status lora_set_row_tile(int32_t rows);
 
 /* Tuning knob and test hook (process-wide, not thread safe).  The GEMM kernels of operations (2) and (5)
@@ -168,8 +169,8 @@ lora_status lora_set_row_tile(int32_t rows);
  * is bit-identical under all three settings. */
 lora_status lora_set_slab_lookahead(int32_t slabs);
 
-/* Diagnostic (host only, nothing is enqueued): the row-panel height the streaming reductions of operations
- * (3) / (4) (Section 5.1) would choose for an activation of C columns over these segments under the current
+/* Diagnostic (host only, nothing is enqueued): the row-panel height the streaming reduction of operation
+ * (3) (Section 5.1) would choose for an activation of C columns over these segments under the current
  * lora_set_row_tile setting, the number of panels that gives (each leaves one fp32 plane of partial dB or dA
  * in the workspace), and the number of planes lora_bwd_workspace_bytes provides for.  seg_offsets: host,
  * G+1 entries rising from 0 to M. */

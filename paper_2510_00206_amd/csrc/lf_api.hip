@@ -106,13 +106,13 @@ Workspace carve(void* base, int64_t M, int64_t K, int64_t N, int32_t r, int32_t 
 // What one backward call launches with: the knob is read once and the panel heights are chosen here, for
 // the streaming launches and for the finalize launches that add their partial planes, so that a change
 // of the knob by another thread in the middle of a call cannot make the two disagree.
-struct BwdPlan { int forced, rows_db, rows_da; };
+struct BwdPlan { int forced, rows_db; DaPlan da; };
 
 BwdPlan plan_bwd(const AdapterTable& tb, int64_t K, int64_t N) {
     BwdPlan pl;
     pl.forced = forced_row_tile();
     pl.rows_db = stream_panel_rows(tb, (int)N, pl.forced);
-    pl.rows_da = stream_panel_rows(tb, (int)K, pl.forced);
+    pl.da = plan_da(tb, (int)K, pl.forced);
     return pl;
 }
 
@@ -132,20 +132,20 @@ lora_status bwd_impl(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A,
                      const AdapterTable& tb, lora_bf16* dX, float* dA, float* dB, int accumulate,
                      const Workspace& ws, const BwdPlan& pl, hipStream_t st) {
     const int chunks = (int)((N + kStreamChunk - 1) / kStreamChunk);
-    const int forced = pl.forced, rows_db = pl.rows_db, rows_da = pl.rows_da;
+    const int forced = pl.forced, rows_db = pl.rows_db;
     StreamArgs s3{dY, S, B, ws.part_db, ws.part_ds, (int)M, (int)N, r, 0, 0, tb, rows_db};
     if (timed(LORA_PROF_DS_DB, st, [&] { return launch_stream_dsdb(s3, st); }) != hipSuccess) return LORA_ERR_HIP;
     FinalizeArgs fin{ws.part_ds, ws.dS, ws.part_db, dB, ws.part_da, dA,
-                     (int)M, (int)K, (int)N, r, chunks, accumulate, tb, rows_db, rows_da};
+                     (int)M, (int)K, (int)N, r, chunks, accumulate, tb, rows_db, pl.da.rows};
     if (timed(LORA_PROF_FIN_DS_DB, st, [&] { return launch_finalize_ds_db(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
     // (5) right after (3): it re-reads dY while that pass's copy still sits in the memory-side cache
     if (dX) {
         DxGemmArgs g5{dY, W, ws.dS, A, dX, (int)M, (int)K, (int)N, r, 0, 0, tb};
         if (timed(LORA_PROF_DX_GEMM, st, [&] { return launch_bwd_dx(g5, forced, st); }) != hipSuccess) return LORA_ERR_HIP;
     }
-    StreamArgs s4{X, ws.dS, nullptr, ws.part_da, nullptr, (int)M, (int)K, r, 0, 0, tb, rows_da};
-    if (timed(LORA_PROF_DA, st, [&] { return launch_stream_da(s4, st); }) != hipSuccess) return LORA_ERR_HIP;
-    if (timed(LORA_PROF_FIN_DA, st, [&] { return launch_finalize_da(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
+    DaArgs d4{X, ws.dS, ws.part_da, dA, (int)M, (int)K, r, tb, pl.da.rows, pl.da.direct, accumulate};
+    if (timed(LORA_PROF_DA, st, [&] { return launch_da(d4, st); }) != hipSuccess) return LORA_ERR_HIP;
+    if (!pl.da.direct && timed(LORA_PROF_FIN_DA, st, [&] { return launch_finalize_da(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
     return LORA_OK;
 }
 
@@ -273,7 +273,7 @@ lora_status lora_bwd_noalloc(const lora_bf16* X, const lora_bf16* W, const lora_
     if (st != LORA_OK) return st;
     // exactly the planes this call's launches will write (their panel heights are known here)
     const BwdPlan pl = plan_bwd(tb, K, N);
-    const int64_t planes_db = count_panels(tb, pl.rows_db), planes_da = count_panels(tb, pl.rows_da);
+    const int64_t planes_db = count_panels(tb, pl.rows_db), planes_da = pl.da.direct ? 0 : count_panels(tb, pl.da.rows);
     if (carve(nullptr, M, K, N, r, planes_db, planes_da).bytes > (size_t)LORA_NOALLOC_SCRATCH_BYTES)
         return LORA_ERR_WORKSPACE;
     void* base = nullptr;

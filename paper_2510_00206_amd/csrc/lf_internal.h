@@ -25,17 +25,29 @@ struct FwdGemmArgs {
     int uniform_tiles = 0;     // set by the launcher: uniform tiles over the packed batch (boundaries % 64 == 0)
 };
 
-// Operations (3) and (4) share one streaming kernel (see lf_stream.hip).
+// Operation (3) (lf_stream.hip).
 struct StreamArgs {
-    const lora_bf16* big;      // dY [M,N] for (3), X [M,K] for (4)
-    const lora_bf16* small_;   // S' [M,r] for (3), dS [M,r] for (4)
-    const lora_bf16* Bmat;     // B [G,N,r] for (3), unused for (4)
-    float* part_out;           // per-row-tile partials of dB ([tiles,N,r]) or dA ([tiles,r,K])
-    float* part_ds;            // (3): per-column-chunk partials of dS [chunks,M,r]
-    int M, C, r;               // C = N for (3), K for (4)
+    const lora_bf16* big;      // dY [M,N]
+    const lora_bf16* small_;   // S' [M,r]
+    const lora_bf16* Bmat;     // B [G,N,r]
+    float* part_out;           // per-row-panel partials of dB ([panels,N,r])
+    float* part_ds;            // per-column-chunk partials of dS [chunks,M,r]
+    int M, C, r;               // C = N
     int tiles_m, chunks;
     AdapterTable tb;
     int panel_rows = 0;        // rows per panel (stream_panel_rows), chosen once per entry-point call
+};
+
+// Operation (4) (lf_da.hip).
+struct DaArgs {
+    const lora_bf16* X; const lora_bf16* dS;
+    float* part;               // fp32 planes [panels, r, K] (not direct)
+    float* dA;                 // [G, r, K] (direct)
+    int M, K, r;
+    AdapterTable tb;
+    int panel_rows;            // rows per panel (not direct)
+    int direct;                // one panel per segment, dA written (or added to) by the kernel itself
+    int accumulate;
 };
 
 // Reductions of the partials.
@@ -58,26 +70,71 @@ struct DxGemmArgs {
 
 constexpr int kRowTile = 256;        // row-tile granularity of the dA/dB partials (and the GEMMs' larger tile)
 constexpr int kComputeUnits = 256;   // of the one chip this library is written for
-constexpr int kStreamChunk = 512;    // column-chunk width of the streaming kernel
+constexpr int kStreamChunk = 512;    // column-chunk width of operation (3)
 
 void force_row_tile(int rows);        // 0 (automatic), or the small (128) / large (256) height of every kernel that has two
 int forced_row_tile();                // an entry point reads this ONCE and hands the value to everything it launches
 void force_slab_lookahead(int slabs); // 0 (automatic), or how many slabs ahead the GEMMs' copies run (1 or 2); read per GEMM launch,
                                       // results do not depend on it
 
-// Rows per panel of a streaming reduction over a [M, C] activation.  Every panel leaves an fp32 partial
-// of C x r (dB) or r x C (dA) values, so taller panels mean less partial traffic, while a launch with
+// Longest row panel of a panel height.
+inline int longest_panel(const AdapterTable& tb, int rows) {
+    int n = 0;
+    for (int g = 0; g < tb.G; ++g) {
+        const SegmentPanels sp = segment_panels(tb, rows, g);
+        const int len = sp.has_long ? rows + sp.rem : sp.has_short ? sp.rem : sp.nreg ? rows : 0;
+        if (len > n) n = len;
+    }
+    return n;
+}
+
+// Rows per panel of operation (3) over a [M, C] activation.  Every panel leaves an fp32 partial
+// of C x r values, so taller panels mean less partial traffic, while a launch with
 // fewer workgroups than compute units is bound by the latency of one workgroup's sweep: the height is
 // the largest of 1024 .. 64 that still gives about one workgroup per compute unit (256 at least when
-// the large kernel heights are forced).  Evaluated once per entry-point call; the streaming launch and
+// the large kernel heights are forced) - or a taller one where that height's last round of workgroups would leave most
+// compute units idle (a workgroup takes about 5 us + 2.2 us per 64 rows; 2999 rows, C = 4096, r = 32, with the finalize
+// launch: 64-row panels in two rounds 31 us, 128-row panels in one 26 us).
+// Evaluated once per entry-point call; the streaming launch and
 // the finalize launch that adds its partial planes both receive the result.
 constexpr int kStreamFill = 224;     // workgroups that count as "about one per compute unit"
 inline int stream_panel_rows(const AdapterTable& tb, int C, int forced) {
     const int chunks = (C + kStreamChunk - 1) / kStreamChunk;
-    const int lowest = forced == 256 ? kRowTile : 64;
-    for (int rows = 4 * kRowTile; rows > lowest; rows >>= 1)
-        if (count_panels(tb, rows) * chunks >= kStreamFill) return rows;
-    return lowest;
+    const int lowest = forced == 256 ? kRowTile : 64, tallest = 4 * kRowTile;
+    int rows = tallest;
+    while (rows > lowest && count_panels(tb, rows) * chunks < kStreamFill) rows >>= 1;
+    auto cost = [&](int h) {
+        const int64_t wgs = (int64_t)count_panels(tb, h) * chunks, steps = (longest_panel(tb, h) + 63) / 64;
+        return (wgs + kComputeUnits - 1) / kComputeUnits * (50 + 22 * steps);
+    };
+    int best = rows;
+    for (int h = rows * 2; h <= tallest; h <<= 1)
+        if (cost(h) < cost(best)) best = h;
+    return best;
+}
+
+// How operation (4) cuts its rows.  A workgroup owns 64 columns of a panel and takes about 4 us + 1.3 us per 256 rows,
+// a few of them on every compute unit; panels shorter than a segment cost a finalize launch (5 us) and an fp32 plane of
+// r x K each.  `direct`: one panel per segment, no planes.  (8192 x 4096, r = 16: 2048-row panels 16.7 us, 512-row
+// panels 18.6 us, whole 43 us, as 64 workgroups; 5003 x 14336: whole 31 us, 512-row panels 34 us.)  The panels are never
+// more than operation (3)'s rule gives for the same sizes, which is what the workspace provides for.
+struct DaPlan { int rows, direct; };
+inline DaPlan plan_da(const AdapterTable& tb, int K, int forced) {
+    if (forced == 256) return DaPlan{kRowTile, 0};
+    const int64_t strips = K / 64;
+    auto cost = [&](int64_t panels, int longest, bool direct) {
+        const double rounds = (double)((panels * strips + kComputeUnits - 1) / kComputeUnits);
+        return 4.0 + rounds * 1.3 * (double)((longest + 255) / 256) + (direct ? 0.0 : 5.0 + 3.2e-5 * (double)(panels * K));
+    };
+    DaPlan best{0, 1};
+    double c = cost(tb.G, longest_panel(tb, 1 << 30), true);
+    int least = stream_panel_rows(tb, K, forced);
+    if (least < kRowTile) least = kRowTile;
+    for (int64_t h = least; h < longest_panel(tb, 1 << 30); h <<= 1) {
+        const double ch = cost(count_panels(tb, (int)h), longest_panel(tb, (int)h), false);
+        if (ch < c) { c = ch; best = DaPlan{(int)h, 0}; }
+    }
+    return best;
 }
 
 // Upper bound on the number of panels (planes of dA / dB partials) of any launch over M rows in G
@@ -91,11 +148,12 @@ inline int64_t max_stream_panels(int64_t M, int G) {
 }
 
 // `forced`: the row-tile knob as read by the entry point (0, 128 or 256).  The streaming launchers need
-// StreamArgs::panel_rows, the finalize launchers FinalizeArgs::panel_rows_db / _da, filled in by the caller.
+// StreamArgs::panel_rows, the finalize launchers FinalizeArgs::panel_rows_db / _da, filled in by the caller (operation
+// (4) with DaPlan::direct needs no finalize launch).
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st);
 hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st);
 hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st);
-hipError_t launch_stream_da(StreamArgs a, hipStream_t st);
+hipError_t launch_da(const DaArgs& a, hipStream_t st);
 hipError_t launch_finalize_ds_db(const FinalizeArgs& a, hipStream_t st);
 hipError_t launch_finalize_da(const FinalizeArgs& a, hipStream_t st);
 hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st);

@@ -1,12 +1,9 @@
-// The two bandwidth-bound backward operations of the fused LoRA linear layer (Section 5.1,
-// FusedLoRA Design), as one streaming kernel template over a big [M,C] activation:
-//   operation (3), big = dY [M,N]:  dS[i,c] = s sum_n dY[i,n] B[n,c]   and   dB[n,c] = sum_i dY[i,n] S'[i,c]
-//                                   (both from a single read of dY)
-//   operation (4), big = X  [M,K]:  dA[c,j] = q sum_i keep(i,j) X[i,j] dS[i,c]   (mask regenerated)
-// A workgroup owns a (row panel of 64 .. 1024 rows) x (512-column chunk) panel of `big`, walks it in 64-row steps
+// Operation (3) of the fused LoRA linear layer (Section 5.1, FusedLoRA Design), both results from a single read of dY:
+//     dS[i,c] = s sum_n dY[i,n] B[n,c]   and   dB[n,c] = sum_i dY[i,n] S'[i,c]
+// A workgroup owns a (row panel of 64 .. 1024 rows) x (512-column chunk) panel of dY, walks it in 64-row steps
 // through LDS and reduces over its rows with 16x16x32 bf16 MFMAs whose row-contracted operand is
-// fetched with transposing LDS reads.  Results are partial sums (dB/dA per row tile, dS per column
-// chunk) that the finalize kernels add in a fixed order, so repeated runs agree bit for bit.
+// fetched with transposing LDS reads.  Results are partial sums (dB per row panel, dS per column
+// chunk) that the finalize kernels add in a fixed order, so repeated runs agree bit for bit.  Also the finalize kernels.
 #include "lf_device.h"
 #include "lf_internal.h"
 
@@ -32,14 +29,14 @@ __device__ __forceinline__ bf16x8 read_panel_tr_frag(const char* lds, int r0, in
     return join_tr(lo, hi);
 }
 
-template <int CB, bool IS_DA>   // CB = r/16; IS_DA: operation (4), else operation (3)
+template <int CB>               // r / 16
 __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int R = CB * 16, RCH = CB * 2;                  // rank, 16-byte chunks per small row
     char* lds_big = smem;                                     // [64][64 chunks]
     char* lds_small = lds_big + ST_BIG_BYTES;                 // [64][RCH chunks]
-    char* lds_b = lds_small + ST_STEP * R * 2;                // (3): B chunk [512][RCH chunks]
-    char* lds_red = lds_b + (IS_DA ? 0 : kStreamChunk * R * 2);   // (3): [4][CB][64] f32x4
+    char* lds_b = lds_small + ST_STEP * R * 2;                // B chunk [512][RCH chunks]
+    char* lds_red = lds_b + kStreamChunk * R * 2;             // [4][CB][64] f32x4
 
     // Consecutive workgroup ids go to different XCDs (private L2s).  The column chunk is skewed by the
     // row tile so that one XCD does not end up reading a single column window of every row (which
@@ -53,14 +50,12 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
     const int t = threadIdx.x, l = t & 63, w = t >> 6;
     const int w_uniform = __builtin_amdgcn_readfirstlane(w);
     const int g = rt.g;
-    const KeepThreshold T = keep_threshold(p.tb.T[g]);
-    const uint32_t hk0 = p.tb.k0[g], hk1 = p.tb.k1[g];
     const int rank_g = p.tb.rank[g], cbn = rank_g >> 4;       // columns / 16-column blocks this adapter uses
     // Blocks past the adapter's rank hold zeros (S', dS and the staged B are zero there), so skipping
     // their MFMAs is only a saving; the rank-64 dS+dB variant has no register to spare for the test.
-    constexpr bool RANK_SKIP = CB > 1 && !(CB == 4 && !IS_DA);    // CB == 1: the rank can only be 16
+    constexpr bool RANK_SKIP = CB == 2;                           // CB == 1: the rank can only be 16
     // either output may be switched off (null pointer): the unfused baseline runs them as separate passes
-    const bool do_red = p.part_out != nullptr, do_ds = !IS_DA && p.part_ds != nullptr;
+    const bool do_red = p.part_out != nullptr, do_ds = p.part_ds != nullptr;
 
     f32x4 acc[4][CB];
 #pragma unroll
@@ -79,8 +74,7 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
     // count what is in flight and waits for all of it - also the loads of the step after - before a step's
     // data is used.  What the clamped lanes bring is multiplied by zero rows of the small operand (rows)
     // or never stored (columns).  For the same reason the loops below load two steps past the end of the
-    // panel (all lanes then read the panel's last row, which is cache resident) and, for an odd number
-    // of steps, run one empty step.
+    // panel (all lanes then read the panel's last row, which is cache resident).
     const int bchunk_ld = min(bchunk, (cols_valid >> 3) - 1);
     auto load_step = [&](StepRegs& rg, int step) {
 #pragma unroll
@@ -96,13 +90,7 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int row = w_uniform + 8 * i;
-            u32x4 v = rg.b[i];
-            if (IS_DA) {
-                // a wave stages one row per pass: the row's hash keys are formed on the scalar unit
-                const RowKey rk = row_key(hk0, hk1, (uint32_t)(rt.local_row0 + step * ST_STEP + row));
-                v = mask8(v, rk, (uint32_t)(c0 + bchunk * 8), T);
-            }
-            *(u32x4*)(lds_big + panel_off(row, bchunk)) = v;
+            *(u32x4*)(lds_big + panel_off(row, bchunk)) = rg.b[i];
         }
         if (t < ST_STEP * RCH) {
             const int row = t / RCH, ch = t - row * RCH;
@@ -113,7 +101,6 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
     };
 
     auto stage_b_chunk = [&]() {
-        if (IS_DA) return;
         // B chunk [cols_valid, r] of adapter g -> LDS once (rows past the end are zero)
         const lora_bf16* Bg = p.Bmat + ((int64_t)g * p.C + c0) * R;
         for (int idx = t; idx < kStreamChunk * RCH; idx += ST_THREADS) {
@@ -140,8 +127,7 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
                     if (!RANK_SKIP || cb < cbn)
-                        acc[jb][cb] = IS_DA ? LF_MFMA16(fb, fs[cb], acc[jb][cb])     // D[j][c]
-                                            : LF_MFMA16(fs[cb], fb, acc[jb][cb]);    // D[c][n]
+                        acc[jb][cb] = LF_MFMA16(fs[cb], fb, acc[jb][cb]);            // D[c][n]
             }
         }
 
@@ -186,7 +172,7 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
     // loads run two steps ahead of their use (two register sets), so that a step's HBM latency is
     // covered by two steps of work rather than one; the rank-64 dS+dB variant has no registers to
     // spare and stays one step ahead
-    constexpr bool TWO_AHEAD = !(CB == 4 && !IS_DA);
+    constexpr bool TWO_AHEAD = CB != 4;
     if constexpr (TWO_AHEAD) {
         StepRegs ra, rb2;
         load_step(ra, 0);
@@ -199,6 +185,7 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
             load_step(ra, step + 2);
             __builtin_amdgcn_sched_barrier(0);
             compute_step(step);
+            if (step + 1 >= nsteps) break;
             store_step(rb2, step + 1);
             __syncthreads();
             load_step(rb2, step + 3);
@@ -219,7 +206,7 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
         }
     }
 
-    // partial dB [tile][n][c] or dA [tile][c][j] of this panel
+    // partial dB [tile][n][c] of this panel
     if (do_red)
 #pragma unroll
     for (int jb = 0; jb < 4; ++jb) {
@@ -227,50 +214,35 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
         if (colb >= cols_valid) continue;
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-            if (IS_DA) {
-                const int c = cb * 16 + (l & 15), j = c0 + colb + 4 * (l >> 4);
-                *(f32x4*)(p.part_out + ((int64_t)tile * R + c) * p.C + j) = acc[jb][cb];
-            } else {
-                const int n = c0 + colb + (l & 15), c = cb * 16 + 4 * (l >> 4);
-                *(f32x4*)(p.part_out + ((int64_t)tile * p.C + n) * R + c) = acc[jb][cb];
-            }
+            const int n = c0 + colb + (l & 15), c = cb * 16 + 4 * (l >> 4);
+            *(f32x4*)(p.part_out + ((int64_t)tile * p.C + n) * R + c) = acc[jb][cb];
         }
     }
 }
 
-template <int CB, bool IS_DA>
+template <int CB>
 static hipError_t launch_stream_t(StreamArgs a, hipStream_t st) {
     constexpr int R = CB * 16;
-    const int lds = ST_BIG_BYTES + ST_STEP * R * 2 + (IS_DA ? 0 : kStreamChunk * R * 2 + 4 * CB * 64 * 16);
+    const int lds = ST_BIG_BYTES + ST_STEP * R * 2 + kStreamChunk * R * 2 + 4 * CB * 64 * 16;
     if (a.panel_rows < ST_STEP) return hipErrorInvalidValue;
     a.tiles_m = count_panels(a.tb, a.panel_rows);
     a.chunks = (a.C + kStreamChunk - 1) / kStreamChunk;
     if (a.tiles_m == 0) return hipSuccess;
     static bool attr_set = false;                      // one flag per instantiation
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)stream_kernel<CB, IS_DA>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void*)stream_kernel<CB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((stream_kernel<CB, IS_DA>), dim3(a.tiles_m * a.chunks), dim3(ST_THREADS), lds, st, a);
+    hipLaunchKernelGGL((stream_kernel<CB>), dim3(a.tiles_m * a.chunks), dim3(ST_THREADS), lds, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st) {
     switch (a.r) {
-        case 16: return launch_stream_t<1, false>(a, st);
-        case 32: return launch_stream_t<2, false>(a, st);
-        case 64: return launch_stream_t<4, false>(a, st);
-    }
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_stream_da(StreamArgs a, hipStream_t st) {
-    switch (a.r) {
-        case 16: return launch_stream_t<1, true>(a, st);
-        case 32: return launch_stream_t<2, true>(a, st);
-        case 64: return launch_stream_t<4, true>(a, st);
+        case 16: return launch_stream_t<1>(a, st);
+        case 32: return launch_stream_t<2>(a, st);
+        case 64: return launch_stream_t<4>(a, st);
     }
     return hipErrorInvalidValue;
 }

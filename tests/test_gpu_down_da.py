@@ -1,0 +1,59 @@
+"""Operations (1) and (4) at the edges of their tilings: rows around the 16- and 32-row blocks and the 256 rows that the
+waves of a workgroup walk together, contractions that end inside a 256-column stage, empty segments, ranks below the
+allocated one, no dropout, gradients written by the kernel itself and through partial planes, accumulation."""
+import pytest
+import torch
+
+from paper_2510_00206_amd import binding, workloads
+from gpu_util import compare, f64, rel_err, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+# K (64 columns: one strip, a quarter of a stage), N, r, p, segments
+CASES = [
+    (64, 64, 16, 0.5, (1, 15, 16, 17)),
+    (192, 128, 32, 0.1, (31, 33, 0, 32)),
+    (320, 192, 64, 0.0, (255, 257)),
+    (832, 64, 16, 0.25, (2305,)),
+    (1088, 128, 64, 0.1, (289, 0, 64)),
+    (4160, 64, 32, 0.1, (48, 5)),
+]
+
+
+@pytest.mark.parametrize("K,N,r,p,lens", CASES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_down_projection_and_da(K, N, r, p, lens):
+    print(f"(1) and (4) K={K} N={N} r={r} p={p} lens={lens}", flush=True)
+    L = workloads.custom_layer(sum(lens), K, N, r, 1.5, p, seg_lens=lens, cfg=71)
+    inp = workloads.make_inputs(L)
+    auto = run_gpu(L, *inp)
+    compare(auto, run_oracle(L, *inp), label=f"(1) (4) {K} {N} {r} {p} {lens}")
+    binding.lora_set_row_tile(256)                 # 32-row workgroups in (1), 256-row panels and partial planes in (4)
+    try:
+        planes = run_gpu(L, *inp)
+    finally:
+        binding.lora_set_row_tile(0)
+    assert torch.equal(auto["S"], planes["S"])     # same order of summation in (1)
+    # (4): fp32 sums of the same products in another order; 1e-5 of the largest element as in test_kernel_heights_agree
+    assert rel_err(auto["dA"], f64(planes["dA"])) <= 1e-5
+
+
+@pytest.mark.parametrize("rows", [0, 256], ids=["whole", "planes"])
+def test_da_accumulates(rows):
+    """accumulate adds to what dA holds; an empty segment's gradient stays untouched."""
+    L = workloads.custom_layer(700, 192, 128, 16, 1.0, 0.1, seg_lens=(300, 0, 400), cfg=72)
+    X, W, A, B, dY = (t.cuda() for t in workloads.make_inputs(L))
+    s, p = [L.s] * L.G, [L.p] * L.G
+    print(f"accumulate rows={rows}", flush=True)
+    binding.lora_set_row_tile(rows)
+    try:
+        _, S = binding.multi_lora_fwd(X, W, A, B, L.seg_offsets, s, p, L.seeds)
+        args = (X, W, A, B, S, dY, L.seg_offsets, s, p, L.seeds)
+        _, dA, _ = binding.multi_lora_bwd(*args)
+        base = torch.randn(L.G, L.r, L.K, device="cuda")
+        got = base.clone()
+        binding.multi_lora_bwd(*args, dA=got, dB=torch.zeros(L.G, L.N, L.r, device="cuda"), accumulate=True)
+        torch.cuda.synchronize()
+    finally:
+        binding.lora_set_row_tile(0)
+    assert torch.equal(got, base + dA)
+    assert torch.equal(got[1], base[1]) and not dA[1].any()
