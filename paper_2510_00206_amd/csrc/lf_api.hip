@@ -47,7 +47,7 @@ lora_status build_table(AdapterTable& tb, int64_t M, int32_t r, int32_t G, const
     for (int g = 0; g < G; ++g) {
         const int32_t rg = ranks ? ranks[g] : r;
         if (!(rg == 16 || rg == 32 || rg == 64) || rg > r) return LORA_ERR_UNSUPPORTED;
-        tb.rank[g] = (uint8_t)rg;
+        tb.rank[g] = rg;
     }
     if (off[0] != 0 || off[G] != M) return LORA_ERR_SEGMENTS;
     for (int g = 0; g < G; ++g)

@@ -29,7 +29,7 @@ struct AdapterTable {
     // rank of adapter g (16, 32 or 64), at most the call's r: the arrays are laid out with r columns
     // (rows of A) per adapter and adapter g uses the first rank[g]; the padding of A and B is never used
     // and the padding of S', dS, dA and dB is written as zeros
-    uint8_t rank[kMaxAdapters];
+    int rank[kMaxAdapters];       // (32 bits: a kernel reads it with a scalar load, a byte would take a vector load and its wait)
 };
 
 // A row tile: `rows` valid rows starting at global row `row_start`, owned by adapter g.
@@ -68,7 +68,7 @@ struct SegmentPanels { int nreg; bool has_long, has_short; int rem; };
 
 __host__ __device__ __forceinline__ SegmentPanels segment_panels(const AdapterTable& tb, int gran, int g) {
     const int len = tb.row0[g + 1] - tb.row0[g];
-    const int nf = len / gran;
+    const int nf = len >> __builtin_ctz((unsigned)gran);      // (every panel height is a power of two)
     SegmentPanels sp;
     sp.rem = len - nf * gran;
     sp.has_short = nf == 0 && sp.rem > 0;

@@ -1,17 +1,18 @@
 // Operation (3) of the fused LoRA linear layer (Section 5.1, FusedLoRA Design), both results from a single read of dY:
 //     dS[i,c] = s sum_n dY[i,n] B[n,c]   and   dB[n,c] = sum_i dY[i,n] S'[i,c]
-// A workgroup owns a (row panel of 64 .. 1024 rows) x (512-column chunk) panel of dY, walks it in 64-row steps
-// through LDS and reduces over its rows with 16x16x32 bf16 MFMAs whose row-contracted operand is
-// fetched with transposing LDS reads.  Results are partial sums (dB per row panel, dS per column
+// A workgroup owns a (row panel of 64 .. 1024 rows) x (512-column chunk) panel of dY and walks it in 32-row steps: the
+// rows go global -> LDS in whole lines, NS - 1 steps ahead, and are read twice from there, with transposing reads for the
+// row-contracted product dB and plainly for dS.  Results are partial sums (dB per row panel, dS per column
 // chunk) that the finalize kernels add in a fixed order, so repeated runs agree bit for bit.  Also the finalize kernels.
 #include "lf_device.h"
+#include "lf_gemm_parts.h"
 #include "lf_internal.h"
 
 namespace lf {
 
-constexpr int ST_THREADS = 512;
-constexpr int ST_STEP = 64;                        // rows per step
-constexpr int ST_BIG_BYTES = ST_STEP * kStreamChunk * 2;   // 64 KB
+constexpr int ST_THREADS = 512, ST_WAVES = 8;
+constexpr int ST_STEP = 32;                        // rows per step
+constexpr int ST_BIG_BYTES = ST_STEP * kStreamChunk * 2;   // 32 KB
 
 #define LF_MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16((a), (b), (c), 0, 0, 0)
 
@@ -29,14 +30,30 @@ __device__ __forceinline__ bf16x8 read_panel_tr_frag(const char* lds, int r0, in
     return join_tr(lo, hi);
 }
 
-template <int CB>               // r / 16
-__global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
+template <int CB_, int NS_>     // r / 16, ring depth in steps
+struct Stream {
+    static constexpr int CB = CB_, NS = NS_;
+    static constexpr int STAGE = ST_BIG_BYTES + CB * 1024;              // rows of dY, rows of S'
+    static constexpr int RED = 6 * CB * 1024;                           // dS of a step: quarters 1 .. 3 x two row blocks
+    static constexpr int LDS = NS * STAGE + 2 * RED;
+    static_assert((NS - 1) * STAGE >= kStreamChunk * CB * 32, "B passes through the ring's other stages at the start");
+    static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
+};
+
+// Elements of a row-contracted fragment (lane: contraction rows 8 * (l >> 4) .. +7) at or past `rows` become zero.
+__device__ __forceinline__ bf16x8 zero_past_rows(bf16x8 v, int rows) {
+    u32x4 u = __builtin_bit_cast(u32x4, v);
+    const int left = rows - 8 * ((threadIdx.x & 63) >> 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) u[i] &= left >= 2 * i + 2 ? 0xFFFFFFFFu : left == 2 * i + 1 ? 0x0000FFFFu : 0u;
+    return __builtin_bit_cast(bf16x8, u);
+}
+
+template <class C>
+__global__ void __launch_bounds__(ST_THREADS, 2) stream_kernel(StreamArgs p) {
+    constexpr int CB = C::CB, NS = C::NS, R = CB * 16, RCH = CB * 2;     // rank, 16-byte chunks per S' row
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int R = CB * 16, RCH = CB * 2;                  // rank, 16-byte chunks per small row
-    char* lds_big = smem;                                     // [64][64 chunks]
-    char* lds_small = lds_big + ST_BIG_BYTES;                 // [64][RCH chunks]
-    char* lds_b = lds_small + ST_STEP * R * 2;                // B chunk [512][RCH chunks]
-    char* lds_red = lds_b + kStreamChunk * R * 2;             // [4][CB][64] f32x4
+    f32x4* red = (f32x4*)(smem + NS * C::STAGE);
 
     // Consecutive workgroup ids go to different XCDs (private L2s).  The column chunk is skewed by the
     // row tile so that one XCD does not end up reading a single column window of every row (which
@@ -47,163 +64,142 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
     if (!find_panel(p.tb, p.panel_rows, tile, rt)) return;
     const int c0 = chunk_id * kStreamChunk;
     const int cols_valid = min(kStreamChunk, p.C - c0);       // multiple of 64
-    const int t = threadIdx.x, l = t & 63, w = t >> 6;
-    const int w_uniform = __builtin_amdgcn_readfirstlane(w);
+    const int t = threadIdx.x, l = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int quarter = w & 3, rb = w >> 2;                   // this wave's part of dS: 128 columns, 16 of the 32 rows
     const int g = rt.g;
     const int rank_g = p.tb.rank[g], cbn = rank_g >> 4;       // columns / 16-column blocks this adapter uses
-    // Blocks past the adapter's rank hold zeros (S', dS and the staged B are zero there), so skipping
-    // their MFMAs is only a saving; the rank-64 dS+dB variant has no register to spare for the test.
-    constexpr bool RANK_SKIP = CB == 2;                           // CB == 1: the rank can only be 16
     // either output may be switched off (null pointer): the unfused baseline runs them as separate passes
     const bool do_red = p.part_out != nullptr, do_ds = p.part_ds != nullptr;
+    const int nsteps = (rt.rows + ST_STEP - 1) / ST_STEP;
 
-    f32x4 acc[4][CB];
+    // Copies of a step: wave w brings rows 4w .. 4w+3 of dY, and waves 0 .. CB-1 one KB of S' each.  Rows past the end of
+    // the panel repeat its last row (the S' fragments are zero there), columns past the end the last valid chunk (never
+    // stored).
+    const char* big = (const char*)(p.big + (int64_t)rt.row_start * p.C + c0) - kCopyBias;
+    const char* small_ = (const char*)(p.small_ + (int64_t)rt.row_start * R) - kCopyBias;
+    uint32_t off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        off[i] = (uint32_t)(min(l ^ panel_swz(4 * w + i), (cols_valid >> 3) - 1) * 16 + kCopyBias - pass_imm(4, i));
+    const uint32_t lds0 = lds_addr_of(smem);
+    auto issue = [&](int step, int stage) {
+        const uint32_t m0 = lds0 + stage * C::STAGE + w * 4096 + 2048;
+        const int row = step * ST_STEP + 4 * w, last = rt.rows - 1;
+        copy16_to_lds<pass_imm(4, 0), true>(big + (int64_t)min(row, last) * p.C * 2, off[0], m0);
+        copy16_to_lds<pass_imm(4, 1), false>(big + (int64_t)min(row + 1, last) * p.C * 2, off[1], m0);
+        copy16_to_lds<pass_imm(4, 2), false>(big + (int64_t)min(row + 2, last) * p.C * 2, off[2], m0);
+        copy16_to_lds<pass_imm(4, 3), false>(big + (int64_t)min(row + 3, last) * p.C * 2, off[3], m0);
+        if (w < CB) {
+            const int pos = w * 64 + l, srow = pos / RCH, ch = (pos % RCH) ^ (swz(srow) & (RCH - 1));
+            const uint32_t so = (uint32_t)(min(step * ST_STEP + srow, last) * R + ch * 8) * 2 + kCopyBias;
+            copy16_to_lds<0, true>(small_, so, lds0 + stage * C::STAGE + ST_BIG_BYTES + w * 1024);
+        }
+    };
+    issue(0, 0);
+
+    // B fragments of this wave's quarter, kept in registers: [32-column block][16-column block of the rank].  The chunk
+    // passes through the other stages of the ring (rows past the end and columns past the adapter's rank are zero).
+    bf16x8 bf[4][CB];
+    if (do_ds) {
+        char* lds_b = smem + C::STAGE;
+        const lora_bf16* Bg = p.Bmat + ((int64_t)g * p.C + c0) * R;
+        u32x4 v[RCH];                              // all loads first (clamped, not predicated: one wait for all of them)
+#pragma unroll
+        for (int i = 0; i < RCH; ++i) {
+            const int idx = i * ST_THREADS + t, row = idx / RCH, ch = idx - row * RCH;
+            v[i] = *(const u32x4*)(Bg + (int64_t)min(row, cols_valid - 1) * R + min(ch * 8, rank_g - 8));
+        }
+#pragma unroll
+        for (int i = 0; i < RCH; ++i) {
+            const int idx = i * ST_THREADS + t, row = idx / RCH, ch = idx - row * RCH;
+            if (row >= cols_valid || ch * 8 >= rank_g) v[i] = u32x4{0u, 0u, 0u, 0u};
+            *(u32x4*)(lds_b + tile_off(row, ch, RCH)) = v[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int kq = 0; kq < 4; ++kq)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) bf[kq][cb] = read_tr_frag(lds_b, quarter * 128 + kq * 32 + 8 * (l >> 4), cb * 16, RCH);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+#pragma unroll
+    for (int s = 1; s < NS - 1; ++s)
+        if (s < nsteps) issue(s, s);
+
+    f32x4 acc[4][CB], hold[CB];
 #pragma unroll
     for (int jb = 0; jb < 4; ++jb)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[jb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const lora_bf16* big = p.big + (int64_t)rt.row_start * p.C + c0;
-    const lora_bf16* small_ = p.small_ + (int64_t)rt.row_start * R;
-    const int nsteps = (rt.rows + ST_STEP - 1) / ST_STEP;
-    const int bchunk = t & 63;                                // this thread's 16-byte chunk of a panel row
-
-    struct StepRegs { u32x4 b[8], s; };
-    // Every load is issued unconditionally from a clamped address (rows past the end of the tile read its
-    // last row, columns past the end read the last valid chunk): with predicated loads the compiler cannot
-    // count what is in flight and waits for all of it - also the loads of the step after - before a step's
-    // data is used.  What the clamped lanes bring is multiplied by zero rows of the small operand (rows)
-    // or never stored (columns).  For the same reason the loops below load two steps past the end of the
-    // panel (all lanes then read the panel's last row, which is cache resident).
-    const int bchunk_ld = min(bchunk, (cols_valid >> 3) - 1);
-    auto load_step = [&](StepRegs& rg, int step) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = min(step * ST_STEP + (t >> 6) + 8 * i, rt.rows - 1);     // row of the panel
-            rg.b[i] = *(const u32x4*)(big + (int64_t)row * p.C + bchunk_ld * 8);
-        }
-        const int ts = min(t, ST_STEP * RCH - 1);
-        const int row = ts / RCH, ch = ts - row * RCH;
-        rg.s = *(const u32x4*)(small_ + (int64_t)min(step * ST_STEP + row, rt.rows - 1) * R + ch * 8);
-    };
-    auto store_step = [&](const StepRegs& rg, int step) {
+    for (int cb = 0; cb < CB; ++cb) hold[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // dS of step s, one step late (its quarters meet at the next step's barrier): wave 0 for rows 0 .. 15, wave 4 for 16 .. 31
+    auto store_ds = [&](int s) {
+        const int row = s * ST_STEP + rb * 16 + (l & 15);
+        const f32x4* rd = red + (s & 1) * (C::RED / 16) + rb * (CB * 64) + l;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = w_uniform + 8 * i;
-            *(u32x4*)(lds_big + panel_off(row, bchunk)) = rg.b[i];
-        }
-        if (t < ST_STEP * RCH) {
-            const int row = t / RCH, ch = t - row * RCH;
-            // rows past the end of the tile are zero in the small operand: they cancel the clamped rows
-            const u32x4 v = row < rt.rows - step * ST_STEP ? rg.s : u32x4{0u, 0u, 0u, 0u};
-            *(u32x4*)(lds_small + tile_off(row, ch, RCH)) = v;
+        for (int cb = 0; cb < CB; ++cb) {
+            const f32x4 v = ((hold[cb] + rd[cb * 64]) + rd[(2 * CB + cb) * 64]) + rd[(4 * CB + cb) * 64];
+            if (row < rt.rows)
+                *(f32x4*)(p.part_ds + ((int64_t)chunk_id * p.M + rt.row_start + row) * R + cb * 16 + 4 * (l >> 4)) = v;
         }
     };
 
-    auto stage_b_chunk = [&]() {
-        // B chunk [cols_valid, r] of adapter g -> LDS once (rows past the end are zero)
-        const lora_bf16* Bg = p.Bmat + ((int64_t)g * p.C + c0) * R;
-        for (int idx = t; idx < kStreamChunk * RCH; idx += ST_THREADS) {
-            const int row = idx / RCH, ch = idx - row * RCH;
-            u32x4 v = u32x4{0u, 0u, 0u, 0u};
-            if (row < cols_valid && ch * 8 < rank_g) v = *(const u32x4*)(Bg + (int64_t)row * R + ch * 8);
-            *(u32x4*)(lds_b + tile_off(row, ch, RCH)) = v;
-        }
-    };
-
-    // everything that consumes the step's LDS tiles (ends with the barrier that frees them)
-    auto compute_step = [&](int step) {
-        // reduction over the step's 64 rows: this wave owns panel columns [64w, 64w+64)
-        if (do_red)
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            const int r0 = kk * 32 + 8 * (l >> 4);
+    int stage = 0;
+    for (int s = 0; s < nsteps; ++s) {
+        // this step's copies have landed for every wave, and every wave has left the stage that the next copies overwrite
+        if (s + NS - 2 >= nsteps) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        else if (w < CB) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(5 * (NS - 2)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(4 * (NS - 2)) : "memory");
+        asm volatile("s_barrier" ::: "memory");
+        if (s + NS - 1 < nsteps) issue(s + NS - 1, stage == 0 ? NS - 1 : stage - 1);
+        const char* lds_big = smem + stage * C::STAGE;
+        const char* lds_small = lds_big + ST_BIG_BYTES;
+        if (do_ds && quarter == 0 && s > 0) store_ds(s - 1);
+        if (do_red) {
+            // reduction over the step's 32 rows: this wave owns panel columns [64w, 64w+64)
+            const int rows_left = rt.rows - s * ST_STEP;
             bf16x8 fs[CB];
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) fs[cb] = read_tr_frag(lds_small, r0, cb * 16, RCH);
+            for (int cb = 0; cb < CB; ++cb) {
+                fs[cb] = read_tr_frag(lds_small, 8 * (l >> 4), cb * 16, RCH);
+                if (rows_left < ST_STEP) fs[cb] = zero_past_rows(fs[cb], rows_left);
+            }
 #pragma unroll
             for (int jb = 0; jb < 4; ++jb) {
-                const bf16x8 fb = read_panel_tr_frag(lds_big, r0, w * 64 + jb * 16);
+                const bf16x8 fb = read_panel_tr_frag(lds_big, 8 * (l >> 4), w * 64 + jb * 16);
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    if (!RANK_SKIP || cb < cbn)
-                        acc[jb][cb] = LF_MFMA16(fs[cb], fb, acc[jb][cb]);            // D[c][n]
+                for (int cb = 0; cb < CB; ++cb) acc[jb][cb] = LF_MFMA16(fs[cb], fb, acc[jb][cb]);    // D[c][n]
             }
         }
-
         if (do_ds) {
-            // dS for the step's rows over this panel's columns: wave = (16-row block, column half)
-            const int rb = w & 3, kh = w >> 2;
             f32x4 ads[CB];
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) ads[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kq = 0; kq < 8; ++kq) {
-                const int ncol = kh * 256 + kq * 32;              // panel column of this k-chunk
-                const u32x4 tv = *(const u32x4*)(lds_big + panel_off(rb * 16 + (l & 15), (ncol >> 3) + (l >> 4)));
-                const bf16x8 ft = __builtin_bit_cast(bf16x8, tv);
+            for (int kq = 0; kq < 4; ++kq) {
+                const u32x4 tv = *(const u32x4*)(lds_big + panel_off(rb * 16 + (l & 15), quarter * 16 + kq * 4 + (l >> 4)));
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    if (RANK_SKIP && cb >= cbn) continue;
-                    const bf16x8 fbm = read_tr_frag(lds_b, ncol + 8 * (l >> 4), cb * 16, RCH);
-                    ads[cb] = LF_MFMA16(fbm, ft, ads[cb]);         // D[c][i]
-                }
+                for (int cb = 0; cb < CB; ++cb)
+                    ads[cb] = LF_MFMA16(bf[kq][cb], __builtin_bit_cast(bf16x8, tv), ads[cb]);          // D[c][i]
             }
-            f32x4* red = (f32x4*)lds_red;
-            if (kh == 1) {
+            if (quarter == 0) {
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) red[(rb * CB + cb) * 64 + l] = ads[cb];
-            }
-            __syncthreads();
-            if (kh == 0) {
-                const int row = step * ST_STEP + rb * 16 + (l & 15);
-                if (row < rt.rows) {
+                for (int cb = 0; cb < CB; ++cb) hold[cb] = ads[cb];
+            } else {
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) {
-                        const f32x4 v = ads[cb] + red[(rb * CB + cb) * 64 + l];
-                        *(f32x4*)(p.part_ds + ((int64_t)chunk_id * p.M + rt.row_start + row) * R + cb * 16 + 4 * (l >> 4)) = v;
-                    }
-                }
+                for (int cb = 0; cb < CB; ++cb)
+                    red[(s & 1) * (C::RED / 16) + (((quarter - 1) * 2 + rb) * CB + cb) * 64 + l] = ads[cb];
             }
         }
+        stage = stage + 1 == NS ? 0 : stage + 1;
+    }
+    if (do_ds) {
         __syncthreads();
-    };
-
-    // loads run two steps ahead of their use (two register sets), so that a step's HBM latency is
-    // covered by two steps of work rather than one; the rank-64 dS+dB variant has no registers to
-    // spare and stays one step ahead
-    constexpr bool TWO_AHEAD = CB != 4;
-    if constexpr (TWO_AHEAD) {
-        StepRegs ra, rb2;
-        load_step(ra, 0);
-        load_step(rb2, 1);
-        __builtin_amdgcn_sched_barrier(0);             // (the scheduler otherwise sinks loads towards their use)
-        stage_b_chunk();                               // after the first panel loads are in flight
-        for (int step = 0; step < nsteps; step += 2) {
-            store_step(ra, step);
-            __syncthreads();
-            load_step(ra, step + 2);
-            __builtin_amdgcn_sched_barrier(0);
-            compute_step(step);
-            if (step + 1 >= nsteps) break;
-            store_step(rb2, step + 1);
-            __syncthreads();
-            load_step(rb2, step + 3);
-            __builtin_amdgcn_sched_barrier(0);
-            compute_step(step + 1);
-        }
-    } else {
-        StepRegs ra;
-        load_step(ra, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        stage_b_chunk();
-        for (int step = 0; step < nsteps; ++step) {
-            store_step(ra, step);
-            __syncthreads();
-            load_step(ra, step + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            compute_step(step);
-        }
+        if (quarter == 0) store_ds(nsteps - 1);
     }
 
     // partial dB [tile][n][c] of this panel
@@ -220,29 +216,27 @@ __global__ void __launch_bounds__(ST_THREADS, 1) stream_kernel(StreamArgs p) {
     }
 }
 
-template <int CB>
+template <class C>
 static hipError_t launch_stream_t(StreamArgs a, hipStream_t st) {
-    constexpr int R = CB * 16;
-    const int lds = ST_BIG_BYTES + ST_STEP * R * 2 + kStreamChunk * R * 2 + 4 * CB * 64 * 16;
     if (a.panel_rows < ST_STEP) return hipErrorInvalidValue;
     a.tiles_m = count_panels(a.tb, a.panel_rows);
     a.chunks = (a.C + kStreamChunk - 1) / kStreamChunk;
     if (a.tiles_m == 0) return hipSuccess;
     static bool attr_set = false;                      // one flag per instantiation
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)stream_kernel<CB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void*)stream_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((stream_kernel<CB>), dim3(a.tiles_m * a.chunks), dim3(ST_THREADS), lds, st, a);
+    hipLaunchKernelGGL((stream_kernel<C>), dim3(a.tiles_m * a.chunks), dim3(ST_THREADS), C::LDS, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st) {
     switch (a.r) {
-        case 16: return launch_stream_t<1>(a, st);
-        case 32: return launch_stream_t<2>(a, st);
-        case 64: return launch_stream_t<4>(a, st);
+        case 16: return launch_stream_t<Stream<1, 4>>(a, st);
+        case 32: return launch_stream_t<Stream<2, 4>>(a, st);
+        case 64: return launch_stream_t<Stream<4, 3>>(a, st);
     }
     return hipErrorInvalidValue;
 }
@@ -307,14 +301,14 @@ hipError_t launch_finalize_ds_db(const FinalizeArgs& a, hipStream_t st) {
     const int64_t n_db = a.part_db ? (int64_t)a.tb.G * a.N * (a.r >> 2) : 0;
     if (n_ds + n_db == 0) return hipSuccess;
     const int blocks_ds = (int)((n_ds + 255) / 256), blocks_db = (int)((n_db + 255) / 256);
-    if (n_db && a.panel_rows_db < ST_STEP) return hipErrorInvalidValue;
+    if (n_db && a.panel_rows_db < 64) return hipErrorInvalidValue;
     hipLaunchKernelGGL(finalize_ds_db_kernel, dim3(blocks_ds + blocks_db), dim3(256), 0, st, a, blocks_ds);
     return hipGetLastError();
 }
 
 hipError_t launch_finalize_da(const FinalizeArgs& a, hipStream_t st) {
     const int64_t n = (int64_t)a.tb.G * a.r * (a.K >> 2);
-    if (a.panel_rows_da < ST_STEP) return hipErrorInvalidValue;
+    if (a.panel_rows_da < 64) return hipErrorInvalidValue;
     hipLaunchKernelGGL(finalize_da_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
     return hipGetLastError();
 }

@@ -116,7 +116,7 @@ AdapterTable make_table(int64_t M, int32_t r, float s, float p, uint64_t seed, b
     memset(&tb, 0, sizeof(tb));
     tb.G = 1;
     tb.row0[1] = (int)M;
-    tb.rank[0] = (uint8_t)r;
+    tb.rank[0] = r;
     const double t = floor((double)p * 65536.0);
     const uint32_t T = plain ? 0u : (t > 65535.0 ? 65535u : (uint32_t)t);
     tb.T[0] = T;
