@@ -7,8 +7,11 @@
 // Both run a 256x256 output tile per workgroup: 4 waves, one per SIMD, each owning 128x128 of the
 // tile as 8x8 MFMA 16x16x32 bf16 blocks (256 fp32 accumulator registers).  The chip is power-limited
 // under these kernels, and a register-resident loop of the 16x16x32 instruction sustains about 14 % more
-// than one of 32x32x16 (half the accumulator traffic per flop), which decides the block shape.  Launches whose
-// 256-row tiling would leave compute units without a tile go to the small tiles of lf_gemm_ring.hip, in whole or
+// than one of 32x32x16 (half the accumulator traffic per flop), which decides the block shape.  A second
+// instantiation has 192-row tiles (6x8 blocks per wave): a tile takes about 0.78 of the time, so it is taken where it
+// needs no more rounds of workgroups than 256-row tiles (2999 x 4096 x 4096: 256 tiles instead of 192 on 256 compute units,
+// (2) 83 -> 75 us, (5) 90 -> 84 us; 5900 rows 163 -> 138 and 168 -> 143 us).  Launches whose
+// tiling would leave compute units without a tile go to the small tiles of lf_gemm_ring.hip, in whole or
 // for the rows of the last round (plan_gemm).  64-deep operand
 // slabs are copied global -> LDS without passing through registers, double-buffered, one or two slabs ahead
 // of the matrix work (see Sched), and the rank-r LoRA term rides as extra contraction steps on the same accumulators.  (2) contracts over
@@ -26,50 +29,55 @@
 
 namespace lf {
 
-constexpr int BM = 256, BN = 256;           // output tile: token rows x out columns
-constexpr int TB = 8;                       // 16-row blocks (and 16-column blocks) per wave
+constexpr int BN = 256;                     // token rows per tile: 64 * MB (a wave owns 2 * MB blocks of 16 rows: MB = 4 or 3)
 constexpr int NTHREADS = 256;
 constexpr int NWAVES = NTHREADS / 64;
-constexpr int TILE_BYTES = BN * BK * 2;            // one 256x64 (or 64x256) bf16 slab: 32 KB
+constexpr int TILE_BYTES = BN * BK * 2;            // one 256x64 (or 64x256) bf16 slab: 32 KB (a 192-row token slab uses three quarters)
 constexpr int STAGE_BYTES = 2 * TILE_BYTES;        // both operands
 constexpr int GEMM_LDS_BYTES = 2 * STAGE_BYTES;    // double buffered: 128 KB
 
 // ---- slab movement ------------------------------------------------------------------------------
 constexpr int PASSES = 2048 / NTHREADS;              // 16-byte chunks per thread per 32 KB slab: 8
 
-// M0 of a wave for a slab whose first byte is at LDS address `lds_slab_addr`
+// M0 of a wave for an NP-pass slab whose first byte is at LDS address `lds_slab_addr`
+template <int NP>
 __device__ __forceinline__ uint32_t slab_m0(uint32_t lds_slab_addr) {
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    return lds_slab_addr + w * (PASSES * 1024) + (PASSES / 2) * 1024;
+    return lds_slab_addr + w * (NP * 1024) + (NP / 2) * 1024;
 }
 
 // Per-lane source offsets of one slab (bytes from the slab's first element), one per pass.
 struct SlabLanes { uint32_t off[PASSES]; };
 
-// Row-operand slab: 256 rows x 64 contraction elements, each row 8 chunks of 16 B (128 B).
-// Wave w, pass i fills rows 8*(PASSES*w + i) .. +7; lane l is (row l >> 3, physical chunk l & 7).
+// Row-operand slab: 256 rows (NP = 8 passes; 192 rows and NP = 6 for the token slab of a 192-row tile) x 64
+// contraction elements, each row 8 chunks of 16 B (128 B).
+// Wave w, pass i fills rows 8*(NP*w + i) .. +7; lane l is (row l >> 3, physical chunk l & 7).
+template <int NP = PASSES>
 __device__ __forceinline__ SlabLanes row_slab_lanes(int64_t ld, int rows_valid, int nchunk_valid) {
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
     SlabLanes s;
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
-        const int row = 8 * (PASSES * w + i) + (l >> 3);
+        const int ii = i < NP ? i : 0;                 // (passes past NP are never issued)
+        const int row = 8 * (NP * w + ii) + (l >> 3);
         const int chunk = min((l & 7) ^ row_slab_swz(row), nchunk_valid - 1);
-        s.off[i] = (uint32_t)((min(row, rows_valid - 1) * ld + chunk * 8) * 2 + kCopyBias - pass_imm(PASSES, i));
+        s.off[i] = (uint32_t)((min(row, rows_valid - 1) * ld + chunk * 8) * 2 + kCopyBias - pass_imm(NP, ii));
     }
     return s;
 }
 
-// Enqueue one slab: `src` is the (workgroup-uniform) address of the slab's first element.
-template <int I = 0>
+// Enqueue one slab of NP wave-passes (a 192-row token slab has 6): `src` is the (workgroup-uniform) address
+// of the slab's first element, `s` lanes formed for the same NP.
+template <int NP, int I = 0>
 __device__ __forceinline__ void load_slab_passes(const char* biased, const SlabLanes& s, uint32_t m0) {
-    if constexpr (I < PASSES) {
-        copy16_to_lds<pass_imm(PASSES, I), I == 0>(biased, s.off[I], m0);
-        load_slab_passes<I + 1>(biased, s, m0);
+    if constexpr (I < NP) {
+        copy16_to_lds<pass_imm(NP, I), I == 0>(biased, s.off[I], m0);
+        load_slab_passes<NP, I + 1>(biased, s, m0);
     }
 }
+template <int NP = PASSES>
 __device__ __forceinline__ void load_slab(uint32_t lds_slab_addr, const lora_bf16* src, const SlabLanes& s) {
-    load_slab_passes((const char*)src - kCopyBias, s, slab_m0(lds_slab_addr));
+    load_slab_passes<NP>((const char*)src - kCopyBias, s, slab_m0<NP>(lds_slab_addr));
 }
 
 // ---- MFMAs issued from assembly ------------------------------------------------------------------
@@ -82,7 +90,7 @@ __device__ __forceinline__ void mfma_in_place_done() { asm volatile("s_nop 15\n\
 
 struct NoShadow {};        // a slab step without hash pieces
 
-// What the next slab pair is copied from: a token slab and an out slab of PASSES wave-passes each.
+// What the next slab pair is copied from: a token slab of 2*MB wave-passes and an out slab of PASSES.
 struct NextSlabs {
     const char* src_tok; const char* src_out;     // workgroup-uniform addresses of the slabs' first elements - kCopyBias
     const SlabLanes& lanes_tok; const SlabLanes& lanes_out;
@@ -101,16 +109,18 @@ struct Pipe {
 
 // This wave's M0 values (slab_m0) for the token and the out slab of LDS stage 0.
 struct CopyOrg { uint32_t tok, out; };
+template <int MB>
 __device__ __forceinline__ CopyOrg copy_org(uint32_t lds0) {
-    return CopyOrg{slab_m0(lds0), slab_m0(lds0 + TILE_BYTES)};
+    return CopyOrg{slab_m0<2 * MB>(lds0), slab_m0<PASSES>(lds0 + TILE_BYTES)};
 }
 
-// Copy number J (0 .. 2*PASSES-1) of the next slab pair.
-template <int J>
+// Copy number J (0 .. 2*MB+PASSES-1) of the next slab pair.
+template <int MB, int J>
 __device__ __forceinline__ void issue_copy(const NextSlabs& nx) {
     if (!nx.valid) return;
-    if constexpr (J < PASSES) copy16_to_lds<pass_imm(PASSES, J), J == 0>(nx.src_tok, nx.lanes_tok.off[J], nx.m0_tok);
-    else copy16_to_lds<pass_imm(PASSES, J - PASSES), J == PASSES>(nx.src_out, nx.lanes_out.off[J - PASSES], nx.m0_out);
+    constexpr int TOKP = 2 * MB;
+    if constexpr (J < TOKP) copy16_to_lds<pass_imm(TOKP, J), J == 0>(nx.src_tok, nx.lanes_tok.off[J], nx.m0_tok);
+    else copy16_to_lds<pass_imm(PASSES, J - TOKP), J == TOKP>(nx.src_out, nx.lanes_out.off[J - TOKP], nx.m0_out);
 }
 
 // gm.g[q] for a run-time q, as a scalar (wave-uniform) value
@@ -130,16 +140,16 @@ struct TileCtx {
     bool ok;
 };
 
-__device__ __forceinline__ TileCtx decode_tile(const AdapterTable& tb, int M, int uniform_tiles, int tiles_m,
+__device__ __forceinline__ TileCtx decode_tile(const AdapterTable& tb, int M, int bm, int uniform_tiles, int tiles_m,
                                                int tiles_n, int id, int out_cols) {
     TileCtx c;
     int tm, tn;
     tile_of_block(id, tiles_m, tiles_n, tm, tn);
     c.ok = true;
     if (uniform_tiles) {
-        find_uniform_tile(tb, M, BM, tm, c.rt, c.gm);
+        find_uniform_tile(tb, M, bm, tm, c.rt, c.gm);
     } else {
-        c.ok = find_row_tile(tb, BM, tm, c.rt);
+        c.ok = find_row_tile(tb, bm, tm, c.rt);
         c.gm.g[0] = c.gm.g[1] = c.gm.g[2] = c.gm.g[3] = c.rt.g;
         c.gm.mixed = false;
     }
@@ -173,7 +183,7 @@ __device__ __forceinline__ FragLanes frag_lanes(int wn) {
 
 // Fragments of a wave: the out operand double-buffered by sub-step, the token operand in place (block mi is
 // reloaded for the next sub-step as soon as the eight MFMAs of its row have been issued).
-struct Frags { bf16x8 fo[2][8]; bf16x8 ft[TB]; };
+template <int MB> struct Frags { bf16x8 fo[2][8]; bf16x8 ft[2 * MB]; };
 
 template <bool COL_SLAB>
 __device__ __forceinline__ bf16x8 read_out_frag(const char* lds_out, const FragLanes& fl, int blk, int sub) {
@@ -204,12 +214,12 @@ __device__ __forceinline__ bf16x8 read_tok_frag(const char* lds_tok, const FragL
 }
 
 // all fragments of sub-step 0 of a slab (start of a tile)
-template <bool COL_SLAB>
-__device__ __forceinline__ void read_frags(Frags& f, const char* lds_tok, const char* lds_out, const FragLanes& fl) {
+template <bool COL_SLAB, int MB>
+__device__ __forceinline__ void read_frags(Frags<MB>& f, const char* lds_tok, const char* lds_out, const FragLanes& fl) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) f.fo[0][k] = read_out_frag<COL_SLAB>(lds_out, fl, k, 0);
 #pragma unroll
-    for (int mi = 0; mi < TB; ++mi) f.ft[mi] = read_tok_frag(lds_tok, fl, mi, 0);
+    for (int mi = 0; mi < 2 * MB; ++mi) f.ft[mi] = read_tok_frag(lds_tok, fl, mi, 0);
 }
 
 // Where the copies of a slab step go.
@@ -223,9 +233,10 @@ __device__ __forceinline__ void read_frags(Frags& f, const char* lds_tok, const 
 //   does not.
 constexpr int kCopySpread1 = 0, kCopyEarly1 = 1, kCopyAhead2 = 2;
 
-// What rides on MFMA slot s of sub-step `sub` (slot s works on token block s >> 3; -1: nothing).
-struct Sched {
-    static constexpr int SS = 8 * TB;
+// What rides on MFMA slot s of sub-step `sub` (slot s works on token block s >> 3; -1: nothing).  The 192-row tile
+// runs its copies two slabs ahead only.
+template <int MB> struct Sched {
+    static constexpr int TB = 2 * MB, SS = 8 * TB;
     // sub-step 1: hand-over after this slot
     static constexpr int ho(int mode) { return mode == kCopyAhead2 ? 7 : 36; }
     template <int N> static constexpr int find(const int (&at)[N], int s) {
@@ -235,6 +246,10 @@ struct Sched {
     }
     // read of out fragment k for the next sub-step (sub-step 0: of this slab; sub-step 1: of the next slab)
     static constexpr int fo_read(int sub, int s, int mode) {
+        if (sub == 0 && MB == 3) {
+            constexpr int at[8] = {2, 6, 11, 15, 20, 27, 31, 36};
+            return find(at, s);
+        }
         if (sub == 0) return (s & 7) == 4 ? s >> 3 : -1;
         if (mode == kCopyAhead2) {
             constexpr int at[8] = {12, 15, 19, 22, 28, 31, 35, 38};
@@ -242,15 +257,8 @@ struct Sched {
         }
         return s == 37 ? 0 : s >= 40 && s <= 52 && !(s & 1) ? (s - 38) >> 1 : -1;      // 37, 40, 42, .. 52 (in the order of their first use)
     }
-    // column slab: the second transposing read of out fragment k (the first rides on fo_read's slot)
-    static constexpr int fo_read_hi(int sub, int s, int mode) {
-        if (sub == 0) return (s & 7) == 5 ? s >> 3 : -1;
-        if (mode == kCopyAhead2) {
-            constexpr int at[8] = {13, 16, 20, 23, 29, 32, 36, 39};
-            return find(at, s);
-        }
-        return s == 38 ? 0 : s >= 41 && s <= 53 && (s & 1) ? (s - 39) >> 1 : -1;    // right after the first: 38, 41, 43, .. 53
-    }
+    // column slab: the second transposing read of out fragment k, right after the first (which rides on fo_read's slot)
+    static constexpr int fo_read_hi(int sub, int s, int mode) { return s > 0 ? fo_read(sub, s - 1, mode) : -1; }
     // reload of token fragment mi; slot 1 brings the last block's fragment of THIS sub-step (its row is not
     // over when the others are reloaded), the others that of the next sub-step
     static constexpr int ft_read(int sub, int s, int mode) {
@@ -258,14 +266,15 @@ struct Sched {
         if (sub == 0 || mode == kCopyAhead2) return (s & 7) == 1 && s >= 9 ? (s >> 3) - 1 : -1;   // as soon as the block row is over
         return s == 39 ? 0 : s >= 54 && s <= 59 ? s - 53 : -1;             // 39; 54 .. 59 -> 1 .. 6
     }
-    // copy number (0 .. 15) of the slab pair the step brings.  Operation (5), whose slots also carry the
+    // copy number (0 .. 2*MB + 7) of the slab pair the step brings.  Operation (5), whose slots also carry the
     // transposing reads, wants its copies spread out whichever way they run; operation (2) wants them early when
     // they run one slab ahead (the last ones then have the longest to land) and spread when they run two ahead.
     static constexpr int copy_at(int sub, int s, int mode) {
         if (mode == kCopyAhead2) {
             if (sub != 1) return -1;
-            constexpr int at[16] = {8, 11, 14, 18, 21, 24, 27, 30, 34, 37, 40, 43, 46, 50, 53, 56};
-            return find(at, s);
+            constexpr int at4[16] = {8, 11, 14, 18, 21, 24, 27, 30, 34, 37, 40, 43, 46, 50, 53, 56};
+            constexpr int at3[14] = {8, 10, 11, 14, 18, 21, 24, 26, 27, 30, 34, 37, 40, 43};
+            return MB == 4 ? find(at4, s) : find(at3, s);
         }
         if (sub != 0) return -1;
         if (mode == kCopySpread1) return (s & 3) == 2 ? s >> 2 : -1;                  // 2, 6, .. 62 -> 0 .. 15
@@ -274,7 +283,7 @@ struct Sched {
 };
 
 // (operation (5) hangs its hash pieces on free slots; nothing for the others)
-template <int SUB, int S, int MODE> __device__ __forceinline__ void shadow_slot(NoShadow&) {}
+template <int MB, int SUB, int S, int MODE> __device__ __forceinline__ void shadow_slot(NoShadow&) {}
 
 // LDS side of one slab step: where the current slab pair lies and where the next one goes.
 struct StepLds {
@@ -282,10 +291,10 @@ struct StepLds {
     const char* nxt_tok; const char* nxt_out;     // ... and in the slabs being filled
 };
 
-template <bool COL_SLAB, int S, int MODE, class SH>
-__device__ __forceinline__ void slots(f32x4 (&acc)[TB][8], Frags& f, const StepLds& L, const FragLanes& fl,
+template <bool COL_SLAB, int MB, int S, int MODE, class SH>
+__device__ __forceinline__ void slots(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, const StepLds& L, const FragLanes& fl,
                                         const NextSlabs& nx, bool read_next, SH& sh, Pipe& pp) {
-    using SC = Sched;
+    using SC = Sched<MB>;
     // the out blocks of a token-block row are walked forth on even rows and back on odd ones: at a row's turn the
     // MFMA keeps its out operand (consecutive MFMAs always share one operand; measured 0.3 - 0.6 % of a GEMM)
     constexpr int sub = S / SC::SS, s = S % SC::SS, mi = s >> 3, ni = (mi & 1) ? 7 - (s & 7) : (s & 7);
@@ -312,8 +321,8 @@ __device__ __forceinline__ void slots(f32x4 (&acc)[TB][8], Frags& f, const StepL
         else if (read_next) f.ft[m] = read_tok_frag(L.nxt_tok, fl, m, 0);
     }
     constexpr int j = SC::copy_at(sub, s, MODE);
-    if constexpr (j >= 0) issue_copy<j>(nx);
-    shadow_slot<sub, s, MODE>(sh);
+    if constexpr (j >= 0) issue_copy<MB, j>(nx);
+    shadow_slot<MB, sub, s, MODE>(sh);
     if constexpr (sub == 1 && s == 0) {
         // every copy of this step has been issued: the sources move on to the slab pair after
         pp.src_tok += pp.adv_tok;
@@ -327,14 +336,15 @@ __device__ __forceinline__ void slots(f32x4 (&acc)[TB][8], Frags& f, const StepL
         else wait_slab_loads();
         __syncthreads();
     }
-    if constexpr (S + 1 < 2 * SC::SS) slots<COL_SLAB, S + 1, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
+    static_assert(MB == 4 || MODE == kCopyAhead2, "see Sched");
+    if constexpr (S + 1 < 2 * SC::SS) slots<COL_SLAB, MB, S + 1, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
 }
 
-// One 64-deep slab pair: two sub-steps of 64 MFMAs; the copies of the next slab pair ride on sub-step 0,
+// One 64-deep slab pair: two sub-steps of 16*MB MFMAs; the copies of the next slab pair ride on sub-step 0,
 // the hand-over (copies landed, workgroup barrier) sits in sub-step 1 and is followed by the first fragment
 // reads of the next slab (if read_next).  On entry f holds the fragments of sub-step 0 of the current slab.
-template <bool COL_SLAB, int MODE, class SH>
-__device__ __forceinline__ void slab_step(f32x4 (&acc)[TB][8], Frags& f, const char* lds_tok_org,
+template <bool COL_SLAB, int MB, int MODE, class SH>
+__device__ __forceinline__ void slab_step(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, const char* lds_tok_org,
                                             const char* lds_out_org, CopyOrg lds_copy_org, const FragLanes& fl, Pipe& pp,
                                             const SlabLanes& lanes_tok, const SlabLanes& lanes_out, bool copy_next,
                                             bool read_next, SH& sh) {
@@ -344,18 +354,19 @@ __device__ __forceinline__ void slab_step(f32x4 (&acc)[TB][8], Frags& f, const c
     const NextSlabs nx{pp.src_tok, pp.src_out, lanes_tok, lanes_out, lds_copy_org.tok + dst, lds_copy_org.out + dst,
                        copy_next};
     __builtin_amdgcn_sched_barrier(0);
-    slots<COL_SLAB, 0, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
+    slots<COL_SLAB, MB, 0, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
     pp.rd = nxt;
 }
 
-__device__ __forceinline__ void zero_acc(f32x4 (&acc)[TB][8]) {
+template <int MB>
+__device__ __forceinline__ void zero_acc(f32x4 (&acc)[2 * MB][8]) {
 #pragma unroll
-    for (int mi = 0; mi < TB; ++mi)
+    for (int mi = 0; mi < 2 * MB; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 8; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
     // pin the register writes here (between the issue of the first slab copies and the wait for them)
 #pragma unroll
-    for (int mi = 0; mi < TB; ++mi)
+    for (int mi = 0; mi < 2 * MB; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 8; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
 }
@@ -399,7 +410,7 @@ __device__ __forceinline__ void lora_term_substep(f32x4 (&t)[2][8], int kk, int 
 }
 
 // ---- the way out of a tile, two 16-row blocks of a wave's sub-tile at a time ---------------------------
-// Accumulator element e of block (mi, ni) in lane l is tile row  wm*128 + mi*16 + (l & 15)  and tile column
+// Accumulator element e of block (mi, ni) in lane l is tile row  wm*32*MB + mi*16 + (l & 15)  and tile column
 // wn*128 + ni*16 + 4*(l >> 4) + e: a lane owns four consecutive columns of one row per block.  The 32 x 128 bf16
 // of a block-row pair go through 8 KB of LDS of the wave's own (`stage`: 32 rows x 32 eight-byte slots, slot
 // index XOR-ed with 2 * (row & 15) so that the 32 lanes served in one cycle - 16 rows x 2 slots - land in 32
@@ -407,8 +418,8 @@ __device__ __forceinline__ void lora_term_substep(f32x4 (&t)[2][8], int kk, int 
 // LORA (operation (5)): before rounding, the masked LoRA term is added to the finished base-gradient
 // accumulators: t = dS A^T per 16x16 block by MFMAs with a vector-register destination (dS arrives scaled by
 // s*q), t & flag, + acc.  F[h]: keep flags of block row 2*bp + h, bit ni*2 + pr for element 2*pr, +16 for 2*pr+1.
-template <bool LORA>
-__device__ __forceinline__ void block_store(f32x4 (&acc)[TB][8], int bp, const char* lds_tok, const char* lds_out,
+template <int MB, bool LORA>
+__device__ __forceinline__ void block_store(f32x4 (&acc)[2 * MB][8], int bp, const char* lds_tok, const char* lds_out,
                                               const FragLanes& fl, int rank_chunks, uint32_t F0, uint32_t F1, char* stage,
                                               lora_bf16* out, int64_t ld, int row0_glob, int rows_left, bool col_ok,
                                               int l) {
@@ -465,21 +476,22 @@ __device__ __forceinline__ void block_store(f32x4 (&acc)[TB][8], int bp, const c
 
 // ---- operation (2): Y = X W + S' B ---------------------------------------------------------------
 // LA: how many slabs ahead of the matrix work the copies run (1 or 2).
-template <int LA>
+template <int MB, int LA>
 __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
     constexpr int MODE = LA == 2 ? kCopyAhead2 : kCopyEarly1;
+    constexpr int BM = 64 * MB, TB = 2 * MB;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int total = p.tiles_m * p.tiles_n;
     int id = blockIdx.x;
-    TileCtx tc = decode_tile(p.tb, p.M, p.uniform_tiles, p.tiles_m, p.tiles_n, id, p.N);
+    TileCtx tc = decode_tile(p.tb, p.M, BM, p.uniform_tiles, p.tiles_m, p.tiles_n, id, p.N);
     if (!tc.ok) return;
     const int l = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w & 1, wn = w >> 1;
     const int nk = p.K / BK;
     const uint32_t lds0 = lds_addr_of(smem);
-    const CopyOrg corg = copy_org(lds0);
+    const CopyOrg corg = copy_org<MB>(lds0);
     const FragLanes fl = frag_lanes<false>(wn);
-    const int tok_org = wm * 128 * 128, out_org = TILE_BYTES + wn * 128 * 128;
+    const int tok_org = wm * (32 * MB) * 128, out_org = TILE_BYTES + wn * 128 * 128;
     // p.r == 0 (no LoRA slab) and p.K == 0 (LoRA slab only) serve the unfused baseline's plain GEMMs.
     const bool has_lora = p.r > 0;
     const int rr = has_lora ? p.r : 16;
@@ -487,15 +499,15 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
     Pipe pp{nullptr, nullptr, BK * 2, BK * 2, 0u};
 
     // first slab pair of the first tile
-    SlabLanes sx = row_slab_lanes(p.K, tc.rt.rows, 8), sw = row_slab_lanes(p.K, tc.cols_valid, 8);
+    SlabLanes sx = row_slab_lanes<2 * MB>(p.K, tc.rt.rows, 8), sw = row_slab_lanes(p.K, tc.cols_valid, 8);
     if (nk > 0) {
-        load_slab(lds0, p.X + (int64_t)tc.rt.row_start * p.K, sx);
+        load_slab<2 * MB>(lds0, p.X + (int64_t)tc.rt.row_start * p.K, sx);
         load_slab(lds0 + TILE_BYTES, p.W + (int64_t)tc.c0 * p.K, sw);
     }
     constexpr int D = LA;                            // how many slabs ahead the copies run
     bool second_on_its_way = false;                  // first tile only: the main loop starts on the first slab pair alone
     if (D == 2 && nk > 1) {
-        load_slab(lds0 + STAGE_BYTES, p.X + (int64_t)tc.rt.row_start * p.K + BK, sx);
+        load_slab<2 * MB>(lds0 + STAGE_BYTES, p.X + (int64_t)tc.rt.row_start * p.K + BK, sx);
         load_slab(lds0 + STAGE_BYTES + TILE_BYTES, p.W + (int64_t)tc.c0 * p.K + BK, sw);
         second_on_its_way = true;
     }
@@ -508,34 +520,34 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
         const lora_bf16* Ssrc = p.S + (int64_t)rt.row_start * p.r;
         const lora_bf16* Bsrc = p.B + ((int64_t)rt.g * p.N + n0) * p.r;
         if (nk == 0) {
-            const SlabLanes ss = row_slab_lanes(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
-            load_slab(lds0 + pp.rd, Ssrc, ss);
+            const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
+            load_slab<2 * MB>(lds0 + pp.rd, Ssrc, ss);
             load_slab(lds0 + pp.rd + TILE_BYTES, Bsrc, sb);
         }
         f32x4 acc[TB][8];
-        zero_acc(acc);                           // while the first slabs are on their way (first tile)
-        if (second_on_its_way) wait_slab_loads_but<2 * PASSES>();
+        zero_acc<MB>(acc);                           // while the first slabs are on their way (first tile)
+        if (second_on_its_way) wait_slab_loads_but<2 * MB + PASSES>();
         else wait_slab_loads();
         second_on_its_way = false;
         __syncthreads();
-        Frags f;
-        if (nk > 0) read_frags<false>(f, smem + pp.rd + tok_org, smem + pp.rd + out_org, fl);
+        Frags<MB> f;
+        if (nk > 0) read_frags<false, MB>(f, smem + pp.rd + tok_org, smem + pp.rd + out_org, fl);
         pp.src_tok = (const char*)(Xt + D * BK) - kCopyBias;
         pp.src_out = (const char*)(Wt + D * BK) - kCopyBias;
         for (int kt = 0; kt + D < nk; ++kt)          // step kt brings slab kt + D
-            slab_step<false, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sx, sw, true, true, none);
+            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sx, sw, true, true, none);
         // the lane offsets of the LoRA slab pair are formed only now: through the main loop they would cost
         // sixteen registers that it does not have
-        const SlabLanes ss = row_slab_lanes(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
+        const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
         // after the last base slab the LoRA step rides as one more slab (token operand S' [rows, r], out operand
         // B [N, r]): the last base step brings it or, two ahead, the last but one (the last then brings nothing)
         const bool lora_piped = has_lora && !gm.mixed && nk >= D;
         pp.src_tok = (const char*)Ssrc - kCopyBias;
         pp.src_out = (const char*)Bsrc - kCopyBias;
         if (D == 2 && nk > 1)
-            slab_step<false, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, lora_piped, true, none);
+            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, lora_piped, true, none);
         if (nk > 0)
-            slab_step<false, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, D == 1 && lora_piped,
+            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, D == 1 && lora_piped,
                                         false, none);
         const uint32_t lo = pp.rd;                     // the stage that holds (or receives) the LoRA slab pair
 
@@ -547,11 +559,11 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
         asm volatile("" : "+s"(next));
         const bool has_next = next < total;
         if (has_next) {
-            tc = decode_tile(p.tb, p.M, p.uniform_tiles, p.tiles_m, p.tiles_n, next, p.N);
-            sx = row_slab_lanes(p.K, tc.rt.rows, 8);
+            tc = decode_tile(p.tb, p.M, BM, p.uniform_tiles, p.tiles_m, p.tiles_n, next, p.N);
+            sx = row_slab_lanes<2 * MB>(p.K, tc.rt.rows, 8);
             sw = row_slab_lanes(p.K, tc.cols_valid, 8);
             if (nk > 0) {
-                load_slab(lds0 + (STAGE_BYTES - lo), p.X + (int64_t)tc.rt.row_start * p.K, sx);
+                load_slab<2 * MB>(lds0 + (STAGE_BYTES - lo), p.X + (int64_t)tc.rt.row_start * p.K, sx);
                 load_slab(lds0 + (STAGE_BYTES - lo) + TILE_BYTES, p.W + (int64_t)tc.c0 * p.K, sw);
             }
         }
@@ -569,7 +581,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
                 const int g = group_adapter(gm, q);
                 if (lora_sync) {
                     __syncthreads();                   // every wave is done with the stage's previous contents
-                    if (q == 0) load_slab(lds0 + lo, Ssrc, ss);
+                    if (q == 0) load_slab<2 * MB>(lds0 + lo, Ssrc, ss);
                     load_slab(lds0 + lo + TILE_BYTES, p.B + ((int64_t)g * p.N + n0) * p.r, sb);
                     wait_slab_loads();                 // (also the next tile's first slab pair: mixed tiles are rare)
                     __syncthreads();
@@ -587,7 +599,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
                                                 chunk, rank_chunks);
 #pragma unroll
                     for (int mi = 0; mi < TB; ++mi) {
-                        const int blk = wm * 128 + mi * 16;       // first tile row of the block
+                        const int blk = wm * (32 * MB) + mi * 16;       // first tile row of the block
                         if (blk < blk_lo || blk >= blk_hi) continue;
                         const bf16x8 ft = zero_past_rank(
                             __builtin_bit_cast(bf16x8, *(const u32x4*)(smem + lo + tok_org + off + mi * 2048)), chunk, rank_chunks);
@@ -601,7 +613,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
         if (D == 2 && has_next && nk > 1) {
             // the next tile's second slab pair, into the stage of the LoRA slab pair once every wave has left it
             __syncthreads();
-            load_slab(lds0 + lo, p.X + (int64_t)tc.rt.row_start * p.K + BK, sx);
+            load_slab<2 * MB>(lds0 + lo, p.X + (int64_t)tc.rt.row_start * p.K + BK, sx);
             load_slab(lds0 + lo + TILE_BYTES, p.W + (int64_t)tc.c0 * p.K + BK, sw);
         }
 
@@ -613,9 +625,9 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
             const bool col_ok = wn * 128 + (le & 15) * 8 < cols_valid;
             lora_bf16* out = p.Y + (int64_t)rt.row_start * p.N + n0 + wn * 128;
 #pragma unroll
-            for (int bp = 0; bp < TB / 2; ++bp) {
-                const int blk = wm * 128 + bp * 32;
-                block_store<false>(acc, bp, nullptr, nullptr, fl, 0, 0u, 0u, stage, out, p.N, blk, rt.rows - blk,
+            for (int bp = 0; bp < MB; ++bp) {
+                const int blk = wm * (32 * MB) + bp * 32;
+                block_store<MB, false>(acc, bp, nullptr, nullptr, fl, 0, 0u, 0u, stage, out, p.N, blk, rt.rows - blk,
                                          col_ok, le);
             }
         }
@@ -629,7 +641,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
 // Lane l of a wave owns, in 16x16 block (mi, ni), columns ni*16 + 4*(l >> 4) + {0..3} of tile row mi*16 + (l & 15):
 // column pairs cp0 + ni*8 + {0, 1} with cp0 the lane's first pair.  Word number of a block row wd = ni*2 + pr; one
 // flag register per block row, bit wd for the even column and bit wd + 16 for the odd one.  A slab step forms WPS
-// words, so the flags of a tile are complete after 32 slab steps.
+// words, so the flags of a tile are complete after 32 slab steps (24 in a 192-row tile).
 // The MFMA here takes 16 cycles, so a piece is at most three full-rate instructions or one 32-bit multiply
 // (16 cycles by itself); the words of a step go through the six stages two at a time, alternating, so that a
 // piece never waits for the multiply before it.
@@ -677,15 +689,16 @@ __device__ __forceinline__ void keep_piece(KeepShadow& k) {
 
 // pieces ride on slots 2 .. 6*WPS+1 of sub-step 1 (before the hand-over; slot 1 carries a fragment read)
 // (copies two slabs ahead: those slots carry the copies; the pieces ride on the slots of sub-step 0 that carry no read)
-constexpr int shadow_piece_pf2(int s) {
-    constexpr int at[24] = {2, 3, 6, 7, 8, 10, 11, 14, 15, 16, 18, 19, 22, 23, 24, 26, 27, 30, 31, 32, 34, 35, 38, 39};
-    return Sched::find(at, s);
+template <int MB> constexpr int shadow_piece_pf2(int s) {
+    constexpr int at4[24] = {2, 3, 6, 7, 8, 10, 11, 14, 15, 16, 18, 19, 22, 23, 24, 26, 27, 30, 31, 32, 34, 35, 38, 39};
+    constexpr int at3[24] = {4, 5, 8, 10, 13, 14, 18, 19, 22, 23, 24, 26, 29, 30, 34, 35, 38, 39, 40, 42, 43, 44, 45, 46};
+    return MB == 4 ? Sched<MB>::find(at4, s) : Sched<MB>::find(at3, s);
 }
-template <int SUB, int S, int MODE> __device__ __forceinline__ void shadow_slot(KeepShadow& k) {
+template <int MB, int SUB, int S, int MODE> __device__ __forceinline__ void shadow_slot(KeepShadow& k) {
     if constexpr (MODE != kCopyAhead2) {
         if constexpr (SUB == 1 && S >= 2 && S < 2 + 6 * WPS) keep_piece<S - 2>(k);
     } else if constexpr (SUB == 0) {
-        constexpr int pid = shadow_piece_pf2(S);
+        constexpr int pid = shadow_piece_pf2<MB>(S);
         if constexpr (pid >= 0) keep_piece<pid>(k);
     }
 }
@@ -717,11 +730,12 @@ __device__ __forceinline__ SlabLanes col_slab_lanes(int64_t ld, int rows_valid, 
 // product first, while the keep flags of the tile are formed in the shadow of its MFMAs; the LoRA slab
 // pair [dS | A] rides in as one more slab during the last base slab, and the masked LoRA term is added
 // pair of block rows by pair on the way out.  p.N == 0 (LoRA term only) serves the unfused baseline.
-template <bool LORA, int LA>
+template <int MB, bool LORA, int LA>
 __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     constexpr int CM = LA == 2 ? kCopyAhead2 : kCopySpread1;
     constexpr bool PF = LA == 2;                      // copies two slabs ahead (LA as in fwd_gemm_kernel)
-    constexpr int FLAG_STEPS = 16 * TB / WPS;        // slab steps until the tile's flags are complete: 32
+    constexpr int BM = 64 * MB, TB = 2 * MB;
+    constexpr int FLAG_STEPS = 16 * TB / WPS;        // slab steps until the tile's flags are complete: 32 or 24
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int tm, tn;
     tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
@@ -745,39 +759,39 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     const lora_bf16* Wt = p.W + j0;
     const uint32_t lds0 = lds_addr_of(smem);
     const FragLanes fl = frag_lanes<true>(wn);
-    const int tok_org = wm * 128 * 128, out_org = TILE_BYTES;      // (the wave's columns are in fl.col_off)
-    const SlabLanes sd = row_slab_lanes(p.N, rt.rows, 8), sw = col_slab_lanes(p.K, BK, cols_valid);
+    const int tok_org = wm * (32 * MB) * 128, out_org = TILE_BYTES;      // (the wave's columns are in fl.col_off)
+    const SlabLanes sd = row_slab_lanes<2 * MB>(p.N, rt.rows, 8), sw = col_slab_lanes(p.K, BK, cols_valid);
     const int nk = p.N / BK;
     const int rr = LORA ? p.r : 16;
     const lora_bf16* dSt = p.dS + (int64_t)rt.row_start * rr;
     const lora_bf16* At = p.A + (int64_t)gm.g[0] * rr * p.K + j0;         // A of the tile's first adapter
     const int lo = (nk & 1) * STAGE_BYTES;           // the stage that receives the LoRA slab pair
     if (nk > 0) {
-        load_slab(lds0, dYt + 0, sd);
+        load_slab<2 * MB>(lds0, dYt + 0, sd);
         load_slab(lds0 + TILE_BYTES, Wt, sw);
     }
     if (PF && nk > 1) {                              // copies run two slabs ahead
-        load_slab(lds0 + STAGE_BYTES, dYt + BK, sd);
+        load_slab<2 * MB>(lds0 + STAGE_BYTES, dYt + BK, sd);
         load_slab(lds0 + STAGE_BYTES + TILE_BYTES, Wt + (int64_t)BK * p.K, sw);
     }
     if (LORA && (nk == 0 || (PF && nk == 1))) {
-        const SlabLanes ss = row_slab_lanes(rr, rt.rows, rr >> 3), sa = col_slab_lanes(p.K, rr, cols_valid);
-        load_slab(lds0 + lo, dSt, ss);
+        const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sa = col_slab_lanes(p.K, rr, cols_valid);
+        load_slab<2 * MB>(lds0 + lo, dSt, ss);
         load_slab(lds0 + lo + TILE_BYTES, At, sa);
     }
-    zero_acc(acc);                               // while the first slabs are on their way
+    zero_acc<MB>(acc);                               // while the first slabs are on their way
 
     // keep flags: state of the hash pieces, and what changes with the 16-row block row they work on
     KeepShadow ks;
     NoShadow none;
     uint32_t keep_all = 0;
-    uint32_t* flags = (uint32_t*)(smem + GEMM_LDS_BYTES) + threadIdx.x;     // [TB][NTHREADS]
+    uint32_t* flags = (uint32_t*)(smem + GEMM_LDS_BYTES) + threadIdx.x;     // [2 * MB][NTHREADS]
     const uint32_t cp0 = (uint32_t)(j0 + wn * 128 + 4 * (l >> 4)) >> 1;     // this lane's first column pair
     auto keep_step_begin = [&](int kt) {
         const int wd0 = kt * WPS, idx = wd0 & 15;
         if (idx == 0) {
             // next block row of the wave: its adapter's threshold and the row keys of its rows
-            const int blk = wm * 128 + (wd0 >> 4) * 16;
+            const int blk = wm * (32 * MB) + (wd0 >> 4) * 16;
             const int g = group_adapter(gm, blk >> 6);
             const KeepThreshold kth = keep_threshold(p.tb.T[g]);
             ks.tm1 = kth.tm1_packed;
@@ -803,13 +817,13 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     }
 
     // (two slab pairs on their way: the main loop starts on the first alone)
-    if (PF && (nk > 1 || (nk == 1 && LORA))) wait_slab_loads_but<2 * PASSES>();
+    if (PF && (nk > 1 || (nk == 1 && LORA))) wait_slab_loads_but<2 * MB + PASSES>();
     else wait_slab_loads();
     __syncthreads();
-    Frags f;
-    if (nk > 0) read_frags<true>(f, smem + tok_org, smem + out_org, fl);
-    const CopyOrg corg = copy_org(lds0);
-    // slab steps bring the next base slab pair (PF: the one after next); the first 32 of all steps also carry the
+    Frags<MB> f;
+    if (nk > 0) read_frags<true, MB>(f, smem + tok_org, smem + out_org, fl);
+    const CopyOrg corg = copy_org<MB>(lds0);
+    // slab steps bring the next base slab pair (PF: the one after next); the first FLAG_STEPS steps also carry the
     // hash pieces.  D = how far ahead the copies run.
     constexpr int D = PF ? 2 : 1;
     Pipe pp{(const char*)(dYt + D * BK) - kCopyBias, (const char*)(Wt + (int64_t)D * BK * p.K) - kCopyBias, BK * 2,
@@ -818,16 +832,16 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     if constexpr (LORA) {
         for (; kt < min(nk - D, FLAG_STEPS); ++kt) {
             keep_step_begin(kt);
-            slab_step<true, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, ks);
+            slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, ks);
             keep_step_end(kt);
         }
     }
     for (; kt < nk - D; ++kt)
-        slab_step<true, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, none);
+        slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, none);
     if (nk > 0) {
         // the last D base slabs: the LoRA slab pair [dS | A] rides in as one more slab (nothing if there is no
         // LoRA term); its lane offsets are formed only now, the main loop has no registers for them
-        const SlabLanes ss = row_slab_lanes(rr, rt.rows, rr >> 3), sa = col_slab_lanes(p.K, rr, cols_valid);
+        const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sa = col_slab_lanes(p.K, rr, cols_valid);
         pp.src_tok = (const char*)dSt - kCopyBias;
         pp.src_out = (const char*)At - kCopyBias;
         // step nk - D brings the LoRA slab pair; with D = 2 the last step brings nothing.  Each of the two steps is
@@ -835,13 +849,13 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
         auto tail_step = [&](auto bring, auto read_next) {
             if constexpr (LORA) {
                 // one code path for such a step whatever kt is (two would have to merge all the accumulators):
-                // past the 32nd step the hash pieces still run, on a step number that is never flushed
+                // past the last of those steps the hash pieces still run, on a step number that is never flushed
                 const bool forming = kt < FLAG_STEPS;
                 if (forming) keep_step_begin(kt);
-                slab_step<true, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, LORA && bring(), read_next(), ks);
+                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, LORA && bring(), read_next(), ks);
                 if (forming) keep_step_end(kt);
             } else {
-                slab_step<true, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, false, read_next(), none);
+                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, false, read_next(), none);
             }
             ++kt;
         };
@@ -855,7 +869,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
         }
     }
     if constexpr (LORA) {
-        // a contraction of fewer than 32 slabs has left flags to form: same pieces, on their own
+        // a shorter contraction has left flags to form: same pieces, on their own
 #pragma unroll 1
         for (int kt = min(nk, FLAG_STEPS); kt < FLAG_STEPS; ++kt) {
             keep_step_begin(kt);
@@ -877,9 +891,9 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     lora_bf16* out = p.dX + (int64_t)rt.row_start * p.K + j0 + wn * 128;
     if constexpr (!LORA) {
 #pragma unroll
-        for (int bp = 0; bp < TB / 2; ++bp) {
-            const int blk = wm * 128 + bp * 32;
-            block_store<false>(acc, bp, nullptr, nullptr, fl, 0, 0u, 0u, stage, out, p.K, blk, rt.rows - blk, col_ok, le);
+        for (int bp = 0; bp < MB; ++bp) {
+            const int blk = wm * (32 * MB) + bp * 32;
+            block_store<MB, false>(acc, bp, nullptr, nullptr, fl, 0, 0u, 0u, stage, out, p.K, blk, rt.rows - blk, col_ok, le);
         }
     } else {
         // One run of 64-row groups per adapter present in the tile (a single run unless the tile is mixed).
@@ -897,10 +911,10 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
             }
             const int rank_chunks = p.tb.rank[g] >> 3;
 #pragma unroll
-            for (int bp = 0; bp < TB / 2; ++bp) {
-                const int blk = wm * 128 + bp * 32;          // first tile row of the pair
+            for (int bp = 0; bp < MB; ++bp) {
+                const int blk = wm * (32 * MB) + bp * 32;          // first tile row of the pair
                 if (blk < 64 * q || blk >= 64 * qe) continue;
-                block_store<true>(acc, bp, lds_tok, lds_out, fl, rank_chunks, flags_e[(2 * bp) * NTHREADS],
+                block_store<MB, true>(acc, bp, lds_tok, lds_out, fl, rank_chunks, flags_e[(2 * bp) * NTHREADS],
                                         flags_e[(2 * bp + 1) * NTHREADS], stage, out, p.K, blk, rt.rows - blk, col_ok, le);
             }
             q = qe;
@@ -909,7 +923,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
 }
 
 // ---- host launchers -------------------------------------------------------------------------------
-// Uniform tiles of 256 rows over the packed batch are possible when every segment boundary is a multiple
+// Uniform tiles of 256 or 192 rows over the packed batch are possible when every segment boundary is a multiple
 // of 64 rows (a tile then holds at most four adapters, one per 64-row group).
 static bool boundaries_on_64(const AdapterTable& tb) {
     for (int g = 0; g <= tb.G; ++g)
@@ -949,7 +963,8 @@ int forced_row_tile() { return g_forced_row_tile.load(std::memory_order_relaxed)
 // At 4096 x 4096 the family meets at about 300 rows (64 x 64 / 64 x 128 tiles), 700 (64 x 128 / 128 x 128), 1100
 // (128 x 128 / 128 x 256) and 2300 (128 x 256 / 256 x 256).
 struct TileCost { float fixed, us[2]; };
-constexpr TileCost kLargeCost = {6.0f, {1.36f, 2.72f}};
+constexpr int kLargeKinds = 2, kLargeRows[kLargeKinds] = {256, 192};      // x 256 columns
+constexpr TileCost kLargeCost[kLargeKinds] = {{6.0f, {1.36f, 2.72f}}, {6.0f, {1.06f, 2.12f}}};
 constexpr TileCost kRingCost[kRingKinds] = {{5.5f, {0.82f, 1.64f}}, {5.5f, {0.47f, 0.94f}}, {4.0f, {0.30f, 0.57f}},
                                             {4.0f, {0.18f, 0.34f}}, {4.0f, {0.14f, 0.25f}}};
 
@@ -959,8 +974,8 @@ static double launch_cost(const TileCost& c, int64_t tiles, int64_t slabs) {
     return c.fixed + (double)slabs * fill * ((double)(n / 2) * c.us[1] + (double)(n & 1) * c.us[0]) + 1.0 * (double)(n - 1);
 }
 
-// How one GEMM is launched: one part, or two launches that share the rows.  kind -1: 256 x 256 tiles (first part only),
-// otherwise a small-tile kernel (kRingTiles).
+// How one GEMM is launched: one part, or two launches that share the rows.  kind -1 - i: large tiles of kLargeRows[i] rows
+// (first part only), otherwise a small-tile kernel (kRingTiles).
 struct GemmPart { int kind, row_lo, row_hi; int64_t tiles_m; };
 struct GemmPlan { int uniform, parts; GemmPart part[2]; };
 
@@ -968,15 +983,16 @@ static GemmPlan plan_gemm(const AdapterTable& tb, int M, int kc, int nc, int r, 
     GemmPlan best{tb.G > 1 && boundaries_on_64(tb), 0, {}};
     if (M == 0) return best;
     const int64_t slabs = kc / BK + (r > 0);
+    auto rows_of = [&](int kind) { return kind < 0 ? kLargeRows[-1 - kind] : kRingTiles[kind][0]; };
     auto tiles_of = [&](int kind, int lo) {
-        if (kind < 0) return best.uniform ? (int64_t)(M + 255) / 256 : count_row_tiles(tb, 256, 0);
-        return count_row_tiles(tb, kRingTiles[kind][0], lo);
+        if (kind < 0 && best.uniform) return (int64_t)(M + rows_of(kind) - 1) / rows_of(kind);
+        return count_row_tiles(tb, rows_of(kind), lo);
     };
     auto columns = [&](int kind) { const int w = kind < 0 ? 256 : kRingTiles[kind][1]; return (int64_t)(nc + w - 1) / w; };
-    auto cost_of = [&](int kind, int64_t tiles) { return launch_cost(kind < 0 ? kLargeCost : kRingCost[kind], tiles, slabs); };
+    auto cost_of = [&](int kind, int64_t tiles) { return launch_cost(kind < 0 ? kLargeCost[-1 - kind] : kRingCost[kind], tiles, slabs); };
     const int only = forced == 256 ? -1 : 0;         // (the knob fixes the 256-row tiles, or 128 x 256)
     double cost = 1e30;
-    for (int k = forced ? only : -1; k < (forced ? only + 1 : kRingKinds); ++k) {
+    for (int k = forced ? only : -kLargeKinds; k < (forced ? only + 1 : kRingKinds); ++k) {
         const int64_t tm = tiles_of(k, 0), tn = columns(k);
         const double all = cost_of(k, tm * tn);
         if (all < cost) {
@@ -989,7 +1005,7 @@ static GemmPlan plan_gemm(const AdapterTable& tb, int M, int kc, int nc, int r, 
         // rows, 14336 -> 4096: 531 us on 128 x 256 tiles, 401 us split; 4096 rows, 4096 -> 4096, need no second part.
         const int64_t full = tm * tn / kComputeUnits * kComputeUnits / tn;
         if (forced || k > 1 || full == 0 || full == tm) continue;
-        const int cut = row_of_tile(tb, k < 0 ? 256 : kRingTiles[k][0], k < 0 && best.uniform, full);
+        const int cut = row_of_tile(tb, rows_of(k), k < 0 && best.uniform, full);
         const double first = cost_of(k, full * tn) + 2.5;
         for (int k2 = 0; k2 < kRingKinds; ++k2) {
             const int64_t tm2 = tiles_of(k2, cut);
@@ -1038,13 +1054,14 @@ static hipError_t launch_fwd_large(FwdGemmArgs a, const GemmPlan& t, hipStream_t
     a.tiles_n = (a.N + BN - 1) / BN;
     a.uniform_tiles = t.uniform;
     a.tiles_m = (int)t.part[0].tiles_m;
-    static bool attr_set[2] = {false, false};
+    static bool attr_set[3] = {false, false, false};
+    if (t.part[0].kind < -1) return launch_gemm(fwd_gemm_kernel<3, 2>, attr_set[2], a, st, GEMM_LDS_TOTAL, true);
     // copies two slabs ahead unless the contraction is short (measured: 2.5 % faster at K = N = 4096, 5 - 8 % with
     // weights of 117 and 470 MB; a contraction of 16 slabs, where every step waits for its copies anyway, 4 % slower)
     const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
     const bool ahead2 = knob ? knob == 2 : a.K >= 32 * BK;
-    return ahead2 ? launch_gemm(fwd_gemm_kernel<2>, attr_set[0], a, st, GEMM_LDS_TOTAL, true)
-                  : launch_gemm(fwd_gemm_kernel<1>, attr_set[1], a, st, GEMM_LDS_TOTAL, true);
+    return ahead2 ? launch_gemm(fwd_gemm_kernel<4, 2>, attr_set[0], a, st, GEMM_LDS_TOTAL, true)
+                  : launch_gemm(fwd_gemm_kernel<4, 1>, attr_set[1], a, st, GEMM_LDS_TOTAL, true);
 }
 
 hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st) {
@@ -1061,18 +1078,21 @@ static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t s
     a.tiles_n = (a.K + BN - 1) / BN;
     a.uniform_tiles = t.uniform;
     a.tiles_m = (int)t.part[0].tiles_m;
-    static bool attr_set[4] = {false, false, false, false};
+    static bool attr_set[6] = {};
+    // with a LoRA term: the slab stages plus the parked keep flags (one word per lane and 16-row block of the wave)
+    const int lds = GEMM_LDS_BYTES + 8 * NTHREADS * 4;
+    if (t.part[0].kind < -1)
+        return a.r > 0 ? launch_gemm(bwd_dx_kernel<3, true, 2>, attr_set[4], a, st, lds)
+                       : launch_gemm(bwd_dx_kernel<3, false, 2>, attr_set[5], a, st);
     // copies two slabs ahead when the weight streams from HBM (measured: 3 - 7 % faster there, 0.5 - 1 % slower
     // with a cache-resident weight, whose copies land in time anyway)
     const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
     const bool ahead2 = knob ? knob == 2 : weight_streams(a.K, a.N);
-    // with a LoRA term: the slab stages plus the parked keep flags (8 words per lane)
-    const int lds = GEMM_LDS_BYTES + TB * NTHREADS * 4;
     if (a.r > 0)
-        return ahead2 ? launch_gemm(bwd_dx_kernel<true, 2>, attr_set[0], a, st, lds)
-                      : launch_gemm(bwd_dx_kernel<true, 1>, attr_set[1], a, st, lds);
-    return ahead2 ? launch_gemm(bwd_dx_kernel<false, 2>, attr_set[2], a, st)
-                  : launch_gemm(bwd_dx_kernel<false, 1>, attr_set[3], a, st);
+        return ahead2 ? launch_gemm(bwd_dx_kernel<4, true, 2>, attr_set[0], a, st, lds)
+                      : launch_gemm(bwd_dx_kernel<4, true, 1>, attr_set[1], a, st, lds);
+    return ahead2 ? launch_gemm(bwd_dx_kernel<4, false, 2>, attr_set[2], a, st)
+                  : launch_gemm(bwd_dx_kernel<4, false, 1>, attr_set[3], a, st);
 }
 
 hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st) {

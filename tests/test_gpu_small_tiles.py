@@ -1,5 +1,5 @@
-"""The small-tile GEMM kernels and the split of a launch between two of them, at sizes on the edges of their tiles:
-every output against the oracle, and Y, S' and dX bit for bit against the 256 x 256 tiles (the contraction is walked in
+"""The small-tile GEMM kernels, the 192-row large tiles and the split of a launch between two kernels, at sizes on the
+edges of their tiles: every output against the oracle, and Y, S' and dX bit for bit against the 256 x 256 tiles (the contraction is walked in
 the same order by every kernel, so the tolerance between them is zero)."""
 import pytest
 import torch
@@ -10,7 +10,7 @@ from gpu_util import compare, run_gpu, run_oracle
 pytestmark = pytest.mark.gpu
 
 # (K, N, r, segments).  Which tiles the two GEMMs take follows from the sizes: 32 x 64 and 64 x 64 (few rows), 64 x 128
-# and 128 x 128 (around a thousand rows and columns), 128 x 256 (more), and two launches for one GEMM where the last round
+# and 128 x 128 (around a thousand rows and columns), 128 x 256 and 192 x 256 (more), and two launches for one GEMM where the last round
 # of tiles would be nearly empty.
 CASES = [
     (64, 64, 16, (1,)),                      # one row, one slab, one column block
@@ -23,7 +23,8 @@ CASES = [
     (1024, 4096, 16, (4396,)),               # 256 x 256 for 4096 rows, small tiles for the rest
     (832, 4160, 32, (3000, 1500)),           # the cut falls inside the second segment
     (2112, 4096, 16, (1088, 3072, 256, 64)), # uniform 256-row tiles (boundaries on 64 rows), then small tiles
-    (4096, 4096, 16, (2113,)),               # 128 x 256 for 2048 rows, small tiles for the rest
+    (4096, 4096, 16, (2113,)),               # 192 x 256, last row tile of one row
+    (2048, 4096, 16, (64, 1152, 832, 640, 256)),   # 192 x 256 forward, several adapters in a tile
 ]
 
 
