@@ -966,7 +966,7 @@ struct TileCost { float fixed, us[2]; };
 constexpr int kLargeKinds = 2, kLargeRows[kLargeKinds] = {256, 192};      // x 256 columns
 constexpr TileCost kLargeCost[kLargeKinds] = {{6.0f, {1.36f, 2.72f}}, {6.0f, {1.06f, 2.12f}}};
 constexpr TileCost kRingCost[kRingKinds] = {{5.5f, {0.82f, 1.64f}}, {5.5f, {0.47f, 0.94f}}, {4.0f, {0.30f, 0.57f}},
-                                            {4.0f, {0.18f, 0.34f}}, {4.0f, {0.14f, 0.25f}}};
+                                            {4.0f, {0.18f, 0.34f}}, {4.0f, {0.14f, 0.25f}}, {4.0f, {0.275f, 0.62f}}};
 
 static double launch_cost(const TileCost& c, int64_t tiles, int64_t slabs) {
     const int64_t n = (tiles + kComputeUnits - 1) / kComputeUnits;

@@ -14,8 +14,8 @@ struct RingArgs {
     AdapterTable tb;
 };
 
-constexpr int kRingKinds = 5;
-constexpr int kRingTiles[kRingKinds][2] = {{128, 256}, {128, 128}, {64, 128}, {64, 64}, {32, 64}};   // rows x columns
+constexpr int kRingKinds = 6;
+constexpr int kRingTiles[kRingKinds][2] = {{128, 256}, {128, 128}, {64, 128}, {64, 64}, {32, 64}, {128, 64}};   // rows x columns
 
 hipError_t launch_ring(int kind, bool col, const RingArgs& a, hipStream_t st);
 

@@ -394,8 +394,10 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
 
 
 
-// Which kernel of the family: see kRingTiles.  Two workgroups of the three smallest fit on a compute unit (their rings
-// take 64 - 72 KB of LDS), one of the two largest.
+// Which kernel of the family: see kRingTiles.  Two workgroups of kinds 2, 3 and 4 fit on a compute unit (their rings
+// take 64 - 72 KB of LDS), one of the others.  Kind 5 is for launches of at most one workgroup per compute unit: the deeper
+// ring and the single pass over the weight pay when that comes from HBM (77 rows, 4096 -> 14336, weight not cached: 64 x 128
+// tiles 38 us, 128 x 64 tiles 32 us).
 template <bool COL>
 static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
     switch (kind) {
@@ -404,6 +406,7 @@ static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
         case 2: return launch_ring_cfg<Ring<64, 128, 2, 4, 3>, COL>(a, st);
         case 3: return launch_ring_cfg<Ring<64, 64, 2, 2, 4>, COL>(a, st);
         case 4: return launch_ring_cfg<Ring<32, 64, 2, 2, 6>, COL>(a, st);
+        case 5: return launch_ring_cfg<Ring<128, 64, 4, 2, 6>, COL>(a, st);
     }
     return hipErrorInvalidValue;
 }
