@@ -92,9 +92,10 @@ inline int longest_panel(const AdapterTable& tb, int rows) {
 // of C x r values, so taller panels mean less partial traffic, while a launch with
 // fewer workgroups than compute units is bound by the latency of one workgroup's sweep: the height is
 // the largest of 1024 .. 64 that still gives about one workgroup per compute unit (256 at least when
-// the large kernel heights are forced) - or a taller one where that height's last round of workgroups would leave most
-// compute units idle (a workgroup takes about 5 us + 2.2 us per 64 rows; 2999 rows, C = 4096, r = 32, with the finalize
-// launch: 64-row panels in two rounds 31 us, 128-row panels in one 26 us).
+// the large kernel heights are forced) - or a taller one where its rounds of workgroups and its fewer planes make up for
+// that: a workgroup takes about 6 us + 2 us per 64 rows, a plane 64 ns per 1000 columns (at rank 32; the rule knows no
+// rank, so that adapters of any rank are summed alike).  With the finalize launch, r = 32: 2999 rows, C = 4096: 64-row
+// panels in two rounds 31 us, 128-row panels in one 26 us; 2048 rows: 32 planes 20.5 us, 16 planes 17.8 us.
 // Evaluated once per entry-point call; the streaming launch and
 // the finalize launch that adds its partial planes both receive the result.
 constexpr int kStreamFill = 224;     // workgroups that count as "about one per compute unit"
@@ -104,8 +105,8 @@ inline int stream_panel_rows(const AdapterTable& tb, int C, int forced) {
     int rows = tallest;
     while (rows > lowest && count_panels(tb, rows) * chunks < kStreamFill) rows >>= 1;
     auto cost = [&](int h) {
-        const int64_t wgs = (int64_t)count_panels(tb, h) * chunks, steps = (longest_panel(tb, h) + 63) / 64;
-        return (wgs + kComputeUnits - 1) / kComputeUnits * (50 + 22 * steps);
+        const int64_t planes = count_panels(tb, h), steps = (longest_panel(tb, h) + 63) / 64;
+        return (double)((planes * chunks + kComputeUnits - 1) / kComputeUnits) * (6.0 + 2.0 * (double)steps) + 6.4e-5 * (double)(planes * C);
     };
     int best = rows;
     for (int h = rows * 2; h <= tallest; h <<= 1)

@@ -36,7 +36,9 @@ struct Stream {
     static constexpr int STAGE = ST_BIG_BYTES + CB * 1024;              // rows of dY, rows of S'
     static constexpr int RED = 6 * CB * 1024;                           // dS of a step: quarters 1 .. 3 x two row blocks
     static constexpr int LDS = NS * STAGE + 2 * RED;
-    static_assert((NS - 1) * STAGE >= kStreamChunk * CB * 32, "B passes through the ring's other stages at the start");
+    // B (16 CB KB) passes through the ring's last stages at the start
+    static constexpr int B_STAGES = (kStreamChunk * CB * 32 + STAGE - 1) / STAGE, FIRST = NS - B_STAGES;   // stages free for dY
+    static_assert(FIRST >= 1, "the first step's rows and B are in flight together");
     static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
 };
 
@@ -96,36 +98,40 @@ __global__ void __launch_bounds__(ST_THREADS, 2) stream_kernel(StreamArgs p) {
             copy16_to_lds<0, true>(small_, so, lds0 + stage * C::STAGE + ST_BIG_BYTES + w * 1024);
         }
     };
-    issue(0, 0);
-
-    // B fragments of this wave's quarter, kept in registers: [32-column block][16-column block of the rank].  The chunk
-    // passes through the other stages of the ring (rows past the end and columns past the adapter's rank are zero).
+    // B fragments of this wave's quarter, kept in registers: [32-column block][16-column block of the rank].  The chunk's
+    // rows come in first, then those of the first steps; blocks past the last column or the adapter's rank are zero.
     bf16x8 bf[4][CB];
+    char* lds_b = smem + C::FIRST * C::STAGE;
     if (do_ds) {
-        char* lds_b = smem + C::STAGE;
-        const lora_bf16* Bg = p.Bmat + ((int64_t)g * p.C + c0) * R;
-        u32x4 v[RCH];                              // all loads first (clamped, not predicated: one wait for all of them)
+        const char* Bg = (const char*)(p.Bmat + ((int64_t)g * p.C + c0) * R) - kCopyBias;
 #pragma unroll
-        for (int i = 0; i < RCH; ++i) {
-            const int idx = i * ST_THREADS + t, row = idx / RCH, ch = idx - row * RCH;
-            v[i] = *(const u32x4*)(Bg + (int64_t)min(row, cols_valid - 1) * R + min(ch * 8, rank_g - 8));
+        for (int i = 0; i < 2 * CB; ++i) {
+            const int q = w * 2 * CB + i, pos = q * 64 + l, row = pos / RCH, ch = (pos % RCH) ^ (swz(row) & (RCH - 1));
+            copy16_to_lds<0, true>(Bg, (uint32_t)(min(row, cols_valid - 1) * R + ch * 8) * 2 + kCopyBias, lds_addr_of(lds_b) + q * 1024);
         }
+    }
 #pragma unroll
-        for (int i = 0; i < RCH; ++i) {
-            const int idx = i * ST_THREADS + t, row = idx / RCH, ch = idx - row * RCH;
-            if (row >= cols_valid || ch * 8 >= rank_g) v[i] = u32x4{0u, 0u, 0u, 0u};
-            *(u32x4*)(lds_b + tile_off(row, ch, RCH)) = v[i];
-        }
-        __syncthreads();
+    for (int s = 0; s < C::FIRST && s < NS - 1; ++s)
+        if (s < nsteps) issue(s, s);
+    if (do_ds) {
+        constexpr int after = C::FIRST < NS - 1 ? C::FIRST : NS - 1;         // steps asked for after B
+        if (nsteps < after) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else if (w < CB) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(5 * after) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(4 * after) : "memory");
+        asm volatile("s_barrier" ::: "memory");
 #pragma unroll
         for (int kq = 0; kq < 4; ++kq)
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) bf[kq][cb] = read_tr_frag(lds_b, quarter * 128 + kq * 32 + 8 * (l >> 4), cb * 16, RCH);
+            for (int cb = 0; cb < CB; ++cb) {
+                const int col = quarter * 128 + kq * 32;
+                bf[kq][cb] = read_tr_frag(lds_b, col + 8 * (l >> 4), cb * 16, RCH);
+                if (col >= cols_valid || cb >= cbn) bf[kq][cb] = bf16x8{};
+            }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __syncthreads();
+        asm volatile("s_barrier" ::: "memory");
     }
 #pragma unroll
-    for (int s = 1; s < NS - 1; ++s)
+    for (int s = C::FIRST; s < NS - 1; ++s)
         if (s < nsteps) issue(s, s);
 
     f32x4 acc[4][CB], hold[CB];
