@@ -10,14 +10,12 @@
 // than one of 32x32x16 (half the accumulator traffic per flop), which decides the block shape.  A second
 // instantiation has 192-row tiles (6x8 blocks per wave): a tile takes about 0.78 of the time, so it is taken where it
 // needs no more rounds of workgroups than 256-row tiles (2999 x 4096 x 4096: 256 tiles instead of 192 on 256 compute units,
-// (2) 83 -> 75 us, (5) 90 -> 84 us; 5900 rows 163 -> 138 and 168 -> 143 us).  Launches whose
-// tiling would leave compute units without a tile go to the small tiles of lf_gemm_ring.hip, in whole or
-// for the rows of the last round (plan_gemm).  64-deep operand
-// slabs are copied global -> LDS without passing through registers, double-buffered, one or two slabs ahead
-// of the matrix work (see Sched), and the rank-r LoRA term rides as extra contraction steps on the same accumulators.  (2) contracts over
-// the contiguous dimension of both operands; (5) contracts over the row dimension of W (and of A),
-// which it reads from LDS with transposing loads so that no transposed copy of the frozen weight is
-// ever kept.
+// (2) 83 -> 75 us, (5) 90 -> 84 us; 5900 rows 163 -> 138 and 168 -> 143 us).  Launches whose tiling would leave compute
+// units without a tile go to the small tiles of lf_gemm_ring.hip, in whole or for the rows of the last round (plan_gemm).
+// 64-deep operand slabs are copied global -> LDS without passing through registers, double-buffered, one or two slabs
+// ahead of the matrix work (see Sched), and the rank-r LoRA term rides as extra contraction steps on the same
+// accumulators.  (2) contracts over the contiguous dimension of both operands; (5) contracts over the row dimension of W
+// (and of A), which it reads from LDS with transposing loads so that no transposed copy of the frozen weight is ever kept.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -642,9 +640,9 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
 // column pairs cp0 + ni*8 + {0, 1} with cp0 the lane's first pair.  Word number of a block row wd = ni*2 + pr; one
 // flag register per block row, bit wd for the even column and bit wd + 16 for the odd one.  A slab step forms WPS
 // words, so the flags of a tile are complete after 32 slab steps (24 in a 192-row tile).
-// The MFMA here takes 16 cycles, so a piece is at most three full-rate instructions or one 32-bit multiply
-// (16 cycles by itself); the words of a step go through the six stages two at a time, alternating, so that a
-// piece never waits for the multiply before it.
+// The MFMA here takes 16 cycles, so a piece is at most three vector instructions (a wave issues one in 4 - 5 cycles, the
+// 32-bit multiply too: 4.6 measured in a loop of independent ones); the words of a step go through the six stages two at
+// a time, alternating, so that a piece never waits for the one before it.
 constexpr int WPS = 4;
 struct KeepShadow {
     uint32_t xb, x[2], t[2], m4, fcur;     // vector registers: running hash state, flags of the current register

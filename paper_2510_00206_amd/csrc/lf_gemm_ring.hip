@@ -1,5 +1,5 @@
 // Operations (2) and (5) of the fused LoRA linear layer (Section 5.1, FusedLoRA Design) on small output tiles:
-// the launches whose 256-row (or 128 x 256) tiles of lf_gemm.hip would leave most compute units without work.
+// the launches whose 256- or 192-row tiles of lf_gemm.hip would leave most compute units without work.
 //   (2)  Y  = X W + S' B                     out operand W [N,K], B [N,r]: contiguous along the contraction
 //   (5)  dX = dY W^T + mask*q*(dS A^T)       out operand W [N,K], A [r,K]: contraction over the rows
 // Every output element is formed by the same MFMAs in the same order as on the large tiles (contraction in steps of
