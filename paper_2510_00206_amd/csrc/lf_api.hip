@@ -271,11 +271,13 @@ lora_status lora_bwd_noalloc(const lora_bf16* X, const lora_bf16* W, const lora_
     AdapterTable tb;
     st = build_table(tb, M, r, 1, off, &s, &p, &seed, nullptr);
     if (st != LORA_OK) return st;
-    // exactly the planes this call's launches will write (their panel heights are known here)
+    // The limit goes by the most panels of these sizes (fill_panel_rows), so that it does not move with the launches'
+    // choice of taller ones; the planes laid out are exactly those that this call's launches will write.
     const BwdPlan pl = plan_bwd(tb, K, N);
-    const int64_t planes_db = count_panels(tb, pl.rows_db), planes_da = pl.da.direct ? 0 : count_panels(tb, pl.da.rows);
-    if (carve(nullptr, M, K, N, r, planes_db, planes_da).bytes > (size_t)LORA_NOALLOC_SCRATCH_BYTES)
+    if (carve(nullptr, M, K, N, r, count_panels(tb, fill_panel_rows(tb, (int)N, pl.forced)),
+              count_panels(tb, fill_panel_rows(tb, (int)K, pl.forced))).bytes > (size_t)LORA_NOALLOC_SCRATCH_BYTES)
         return LORA_ERR_WORKSPACE;
+    const int64_t planes_db = count_panels(tb, pl.rows_db), planes_da = pl.da.direct ? 0 : count_panels(tb, pl.da.rows);
     void* base = nullptr;
     st = scratch_of_current_device(&base);
     if (st != LORA_OK) return st;

@@ -88,28 +88,32 @@ inline int longest_panel(const AdapterTable& tb, int rows) {
     return n;
 }
 
-// Rows per panel of operation (3) over a [M, C] activation.  Every panel leaves an fp32 partial
-// of C x r values, so taller panels mean less partial traffic, while a launch with
-// fewer workgroups than compute units is bound by the latency of one workgroup's sweep: the height is
-// the largest of 1024 .. 64 that still gives about one workgroup per compute unit (256 at least when
-// the large kernel heights are forced) - or a taller one where its rounds of workgroups and its fewer planes make up for
-// that: a workgroup takes about 6 us + 2 us per 64 rows, a plane 64 ns per 1000 columns (at rank 32; the rule knows no
-// rank, so that adapters of any rank are summed alike).  With the finalize launch, r = 32: 2999 rows, C = 4096: 64-row
+// Row panels of a reduction over a [M, C] activation.  Every panel leaves an fp32 partial of C x r values, so taller
+// panels mean less partial traffic, while a launch with fewer workgroups than compute units is bound by the latency of
+// one workgroup's sweep: the largest of 1024 .. 64 rows that still gives about one workgroup of 512 columns per compute
+// unit (256 rows at least when the large kernel heights are forced).  No launch takes more panels than this gives.
+constexpr int kStreamFill = 224;     // workgroups that count as "about one per compute unit"
+inline int fill_panel_rows(const AdapterTable& tb, int C, int forced) {
+    const int chunks = (C + kStreamChunk - 1) / kStreamChunk, lowest = forced == 256 ? kRowTile : 64;
+    int rows = 4 * kRowTile;
+    while (rows > lowest && count_panels(tb, rows) * chunks < kStreamFill) rows >>= 1;
+    return rows;
+}
+
+// Rows per panel of operation (3): that height, or a taller one where its rounds of workgroups and its fewer planes make
+// up for it: a workgroup takes about 6 us + 2 us per 64 rows, a plane 64 ns per 1000 columns (at rank 32; the rule knows
+// no rank, so that adapters of any rank are summed alike).  With the finalize launch, r = 32: 2999 rows, C = 4096: 64-row
 // panels in two rounds 31 us, 128-row panels in one 26 us; 2048 rows: 32 planes 20.5 us, 16 planes 17.8 us.
 // Evaluated once per entry-point call; the streaming launch and
 // the finalize launch that adds its partial planes both receive the result.
-constexpr int kStreamFill = 224;     // workgroups that count as "about one per compute unit"
 inline int stream_panel_rows(const AdapterTable& tb, int C, int forced) {
     const int chunks = (C + kStreamChunk - 1) / kStreamChunk;
-    const int lowest = forced == 256 ? kRowTile : 64, tallest = 4 * kRowTile;
-    int rows = tallest;
-    while (rows > lowest && count_panels(tb, rows) * chunks < kStreamFill) rows >>= 1;
     auto cost = [&](int h) {
         const int64_t planes = count_panels(tb, h), steps = (longest_panel(tb, h) + 63) / 64;
         return (double)((planes * chunks + kComputeUnits - 1) / kComputeUnits) * (6.0 + 2.0 * (double)steps) + 6.4e-5 * (double)(planes * C);
     };
-    int best = rows;
-    for (int h = rows * 2; h <= tallest; h <<= 1)
+    int best = fill_panel_rows(tb, C, forced);
+    for (int h = best * 2; h <= 4 * kRowTile; h <<= 1)
         if (cost(h) < cost(best)) best = h;
     return best;
 }
@@ -118,10 +122,10 @@ inline int stream_panel_rows(const AdapterTable& tb, int C, int forced) {
 // a few of them on every compute unit; panels shorter than a segment cost a finalize launch (5 us) and an fp32 plane of
 // r x K each.  `direct`: one panel per segment, no planes.  (8192 x 4096, r = 16: 2048-row panels 16.7 us, 512-row
 // panels 18.6 us, whole 43 us, as 64 workgroups; 5003 x 14336: whole 31 us, 512-row panels 34 us.)  The panels are never
-// more than operation (3)'s rule gives for the same sizes, which is what the workspace provides for.
+// more than fill_panel_rows gives for the same sizes, which is what the workspace provides for.
 struct DaPlan { int rows, direct; };
 inline DaPlan plan_da(const AdapterTable& tb, int K, int forced) {
-    if (forced == 256) return DaPlan{kRowTile, 0};
+    if (forced == 256) return DaPlan{fill_panel_rows(tb, K, forced), 0};
     const int64_t strips = K / 64;
     auto cost = [&](int64_t panels, int longest, bool direct) {
         const double rounds = (double)((panels * strips + kComputeUnits - 1) / kComputeUnits);

@@ -103,6 +103,17 @@ def test_noalloc_backward_validates_on_the_host(lib):
     assert b"scratch" in lib.lora_status_string(6)
 
 
+@pytest.mark.parametrize("M,K,N,r", [(8192, 4096, 4096, 32), (2048, 14336, 14336, 32), (40000, 4096, 4096, 16)])
+def test_noalloc_limit_follows_the_sizes(lib, M, K, N, r):
+    """The scratch limit counts a plane per panel of the fill rule, also where the launches write fewer planes or none
+    (8192 x 4096 x 4096, r = 32: 2 x 16 MiB of planes, of which dA's launch writes 2 MiB)."""
+    ok = C.c_void_p(0x1000)
+    f = lib.lora_bwd_noalloc
+    f.argtypes = [C.c_void_p] * 6 + [C.c_int64] * 3 + [C.c_int32, C.c_float, C.c_float, C.c_uint64] + [C.c_void_p] * 3 + [C.c_int, C.c_void_p]
+    f.restype = C.c_int
+    assert f(ok, ok, ok, ok, ok, ok, M, K, N, r, 1.0, 0.1, 1, ok, ok, ok, 0, None) == 6
+
+
 def test_workspace_holds_every_panel_choice(lib):
     """Host logic: whatever row-panel height the streaming reductions pick (all three row-tile settings), the
     number of partial planes stays within what the workspace query provides for."""
