@@ -31,11 +31,11 @@ lora_status fill_adapter(AdapterTable& tb, int g, float s, float p, uint64_t see
     if (!(p >= 0.0f && p < 1.0f) || !isfinite(s)) return LORA_ERR_PARAM;
     double t = floor((double)p * 65536.0);
     uint32_t T = t > 65535.0 ? 65535u : (uint32_t)t;
-    tb.T[g] = T;
-    tb.q[g] = (float)(65536.0 / (65536.0 - (double)T));
-    tb.s[g] = s;
-    tb.k0[g] = mix32((uint32_t)(seed & 0xFFFFFFFFull) ^ kC5);
-    tb.k1[g] = mix32((uint32_t)(seed >> 32) + tb.k0[g]);
+    tb.a[g].T = T;
+    tb.a[g].q = (float)(65536.0 / (65536.0 - (double)T));
+    tb.a[g].s = s;
+    tb.a[g].k0 = mix32((uint32_t)(seed & 0xFFFFFFFFull) ^ kC5);
+    tb.a[g].k1 = mix32((uint32_t)(seed >> 32) + tb.a[g].k0);
     return LORA_OK;
 }
 
@@ -47,12 +47,12 @@ lora_status build_table(AdapterTable& tb, int64_t M, int32_t r, int32_t G, const
     for (int g = 0; g < G; ++g) {
         const int32_t rg = ranks ? ranks[g] : r;
         if (!(rg == 16 || rg == 32 || rg == 64) || rg > r) return LORA_ERR_UNSUPPORTED;
-        tb.rank[g] = rg;
+        tb.a[g].rank = rg;
     }
     if (off[0] != 0 || off[G] != M) return LORA_ERR_SEGMENTS;
     for (int g = 0; g < G; ++g)
         if (off[g + 1] < off[g]) return LORA_ERR_SEGMENTS;
-    for (int g = 0; g <= G; ++g) tb.row0[g] = (int)off[g];
+    for (int g = 0; g <= G; ++g) tb.a[g].row0 = (int)off[g];
     for (int g = 0; g < G; ++g) {
         lora_status st = fill_adapter(tb, g, s[g], p[g], seeds[g]);
         if (st != LORA_OK) return st;
@@ -122,7 +122,7 @@ lora_status fwd_impl(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A,
     const int forced = forced_row_tile();              // the knob is read once per call
     DownArgs d{X, A, S, (int)M, (int)K, r, tb};
     if (timed(LORA_PROF_DOWN, st, [&] { return launch_down(d, forced, st); }) != hipSuccess) return LORA_ERR_HIP;
-    FwdGemmArgs f{X, W, S, B, Y, (int)M, (int)K, (int)N, r, 0, 0, tb};
+    FwdGemmArgs f{X, W, S, B, Y, (int)M, (int)K, (int)N, r, 0, 0, 0, tb};
     if (timed(LORA_PROF_FWD_GEMM, st, [&] { return launch_fwd_gemm(f, forced, st); }) != hipSuccess) return LORA_ERR_HIP;
     return LORA_OK;
 }
@@ -133,17 +133,17 @@ lora_status bwd_impl(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A,
                      const Workspace& ws, const BwdPlan& pl, hipStream_t st) {
     const int chunks = (int)((N + kStreamChunk - 1) / kStreamChunk);
     const int forced = pl.forced, rows_db = pl.rows_db;
-    StreamArgs s3{dY, S, B, ws.part_db, ws.part_ds, (int)M, (int)N, r, 0, 0, tb, rows_db};
+    StreamArgs s3{dY, S, B, ws.part_db, ws.part_ds, (int)M, (int)N, r, 0, 0, rows_db, tb};
     if (timed(LORA_PROF_DS_DB, st, [&] { return launch_stream_dsdb(s3, st); }) != hipSuccess) return LORA_ERR_HIP;
     FinalizeArgs fin{ws.part_ds, ws.dS, ws.part_db, dB, ws.part_da, dA,
-                     (int)M, (int)K, (int)N, r, chunks, accumulate, tb, rows_db, pl.da.rows};
+                     (int)M, (int)K, (int)N, r, chunks, accumulate, rows_db, pl.da.rows, tb};
     if (timed(LORA_PROF_FIN_DS_DB, st, [&] { return launch_finalize_ds_db(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
     // (5) right after (3): it re-reads dY while that pass's copy still sits in the memory-side cache
     if (dX) {
-        DxGemmArgs g5{dY, W, ws.dS, A, dX, (int)M, (int)K, (int)N, r, 0, 0, tb};
+        DxGemmArgs g5{dY, W, ws.dS, A, dX, (int)M, (int)K, (int)N, r, 0, 0, 0, tb};
         if (timed(LORA_PROF_DX_GEMM, st, [&] { return launch_bwd_dx(g5, forced, st); }) != hipSuccess) return LORA_ERR_HIP;
     }
-    DaArgs d4{X, ws.dS, ws.part_da, dA, (int)M, (int)K, r, tb, pl.da.rows, pl.da.direct, accumulate};
+    DaArgs d4{X, ws.dS, ws.part_da, dA, (int)M, (int)K, r, pl.da.rows, pl.da.direct, accumulate, tb};
     if (timed(LORA_PROF_DA, st, [&] { return launch_da(d4, st); }) != hipSuccess) return LORA_ERR_HIP;
     if (!pl.da.direct && timed(LORA_PROF_FIN_DA, st, [&] { return launch_finalize_da(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
     return LORA_OK;
@@ -294,7 +294,7 @@ lora_status lora_debug_mask(int64_t M, int64_t K, float p, uint64_t seed, uint8_
     if (st != LORA_OK) return st;
     if (M == 0 || K == 0) return LORA_OK;
     if (!keep) return LORA_ERR_NULL;
-    if (launch_debug_mask(M, K, tb.T[0], tb.k0[0], tb.k1[0], keep, (hipStream_t)stream) != hipSuccess)
+    if (launch_debug_mask(M, K, tb.a[0].T, tb.a[0].k0, tb.a[0].k1, keep, (hipStream_t)stream) != hipSuccess)
         return LORA_ERR_HIP;
     return LORA_OK;
 }
@@ -310,7 +310,7 @@ lora_status lora_debug_stream_panels(int64_t M, int64_t C, int32_t G, const int6
     if (seg_offsets[0] != 0 || seg_offsets[G] != M) return LORA_ERR_SEGMENTS;
     for (int g = 0; g < G; ++g)
         if (seg_offsets[g + 1] < seg_offsets[g]) return LORA_ERR_SEGMENTS;
-    for (int g = 0; g <= G; ++g) tb.row0[g] = (int)seg_offsets[g];
+    for (int g = 0; g <= G; ++g) tb.a[g].row0 = (int)seg_offsets[g];
     *panel_rows = stream_panel_rows(tb, (int)C, forced_row_tile());
     *panels = count_panels(tb, *panel_rows);
     *panels_bound = max_stream_panels(M, G);

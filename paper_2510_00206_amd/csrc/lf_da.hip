@@ -33,14 +33,14 @@ __global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgs 
     RowTile rt;
     if (p.direct) {                                // panel = segment, empty ones too (their gradient is zero)
         rt.g = tile;
-        rt.row_start = p.tb.row0[tile];
-        rt.rows = p.tb.row0[tile + 1] - rt.row_start;
+        rt.row_start = p.tb.a[tile].row0;
+        rt.rows = p.tb.a[tile + 1].row0 - rt.row_start;
         rt.local_row0 = 0;
         if (rt.rows == 0 && p.accumulate) return;
     } else if (!find_panel(p.tb, p.panel_rows, tile, rt)) return;
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = rt.g, cbn = p.tb.rank[g] >> 4;
-    const uint32_t T = p.tb.T[g], hk0 = p.tb.k0[g], hk1 = p.tb.k1[g];
+    const int g = rt.g, cbn = p.tb.a[g].rank >> 4;
+    const uint32_t T = p.tb.a[g].T, hk0 = p.tb.a[g].k0, hk1 = p.tb.a[g].k1;
     const KeepThreshold th = keep_threshold(T);
     char* lds_x = smem + w * WAVE_LDS;
     char* lds_s = lds_x + DA_BLOCK * DA_STRIP * 2;

@@ -17,19 +17,24 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 constexpr int kMaxAdapters = 64;
 
-// Lookup table passed by value in the kernel arguments.
+// Lookup table passed by value in the kernel arguments.  One entry per adapter, so that what a kernel reads of its adapter lies in one or two cache lines of the arguments (the
+// reads are a latency at the start of every launch; against one array per field: two backward passes of four launches each
+// over 2048 x 4096 x 4096 46.0 -> 44.8 us, a step of six launches over 1024 x 4096 x 4096 94.6 -> 93.3 us).
+struct Adapter {
+    int row0;                         // segment g owns rows [a[g].row0, a[g + 1].row0)
+    // rank of the adapter (16, 32 or 64), at most the call's r: the arrays are laid out with r columns
+    // (rows of A) per adapter and the adapter uses the first `rank`; the padding of A and B is never used
+    // and the padding of S', dS, dA and dB is written as zeros
+    int rank;                         // (32 bits: a kernel reads it with a scalar load, a byte would take a vector load and its wait)
+    uint32_t T;                       // dropout threshold: keep iff bits16 >= T
+    uint32_t k0, k1;                  // seed-derived hash keys
+    float s;                          // the paper's alpha
+    float q;                          // survivor scale 65536/(65536-T)
+};
+
 struct AdapterTable {
     int G;
-    int row0[kMaxAdapters + 1];   // segment g owns rows [row0[g], row0[g+1])
-    uint32_t T[kMaxAdapters];     // dropout threshold: keep iff bits16 >= T
-    uint32_t k0[kMaxAdapters];    // seed-derived hash keys
-    uint32_t k1[kMaxAdapters];
-    float s[kMaxAdapters];        // the paper's alpha
-    float q[kMaxAdapters];        // survivor scale 65536/(65536-T)
-    // rank of adapter g (16, 32 or 64), at most the call's r: the arrays are laid out with r columns
-    // (rows of A) per adapter and adapter g uses the first rank[g]; the padding of A and B is never used
-    // and the padding of S', dS, dA and dB is written as zeros
-    int rank[kMaxAdapters];       // (32 bits: a kernel reads it with a scalar load, a byte would take a vector load and its wait)
+    Adapter a[kMaxAdapters + 1];      // (the last one: row0 only)
 };
 
 // A row tile: `rows` valid rows starting at global row `row_start`, owned by adapter g.
@@ -43,13 +48,13 @@ __device__ __forceinline__ bool find_row_tile(const AdapterTable& tb, int gran, 
                                               int row_hi = 0x7FFFFFFF) {
     int t = tile;
     for (int g = 0; g < tb.G; ++g) {
-        const int lo = max(tb.row0[g], row_lo), hi = min(tb.row0[g + 1], row_hi);
+        const int lo = max(tb.a[g].row0, row_lo), hi = min(tb.a[g + 1].row0, row_hi);
         const int nt = max(hi - lo + gran - 1, 0) / gran;
         if (t < nt) {
             rt.g = g;
             rt.row_start = lo + t * gran;
             rt.rows = min(gran, hi - rt.row_start);
-            rt.local_row0 = rt.row_start - tb.row0[g];
+            rt.local_row0 = rt.row_start - tb.a[g].row0;
             return true;
         }
         t -= nt;
@@ -67,7 +72,7 @@ __device__ __forceinline__ bool find_row_tile(const AdapterTable& tb, int gran, 
 struct SegmentPanels { int nreg; bool has_long, has_short; int rem; };
 
 __host__ __device__ __forceinline__ SegmentPanels segment_panels(const AdapterTable& tb, int gran, int g) {
-    const int len = tb.row0[g + 1] - tb.row0[g];
+    const int len = tb.a[g + 1].row0 - tb.a[g].row0;
     const int nf = len >> __builtin_ctz((unsigned)gran);      // (every panel height is a power of two)
     SegmentPanels sp;
     sp.rem = len - nf * gran;
@@ -94,7 +99,7 @@ __device__ __forceinline__ bool find_panel(const AdapterTable& tb, int gran, int
         if (idx == 0) {
             rt.g = g;
             rt.local_row0 = sp.nreg * gran;
-            rt.row_start = tb.row0[g] + rt.local_row0;
+            rt.row_start = tb.a[g].row0 + rt.local_row0;
             rt.rows = gran + sp.rem;
             return true;
         }
@@ -105,7 +110,7 @@ __device__ __forceinline__ bool find_panel(const AdapterTable& tb, int gran, int
         if (idx < sp.nreg) {
             rt.g = g;
             rt.local_row0 = idx * gran;
-            rt.row_start = tb.row0[g] + rt.local_row0;
+            rt.row_start = tb.a[g].row0 + rt.local_row0;
             rt.rows = gran;
             return true;
         }
@@ -117,7 +122,7 @@ __device__ __forceinline__ bool find_panel(const AdapterTable& tb, int gran, int
         if (idx == 0) {
             rt.g = g;
             rt.local_row0 = 0;
-            rt.row_start = tb.row0[g];
+            rt.row_start = tb.a[g].row0;
             rt.rows = sp.rem;
             return true;
         }
@@ -141,30 +146,34 @@ __device__ __forceinline__ void segment_planes(const AdapterTable& tb, int gran,
     extra = me.has_long ? long_before : me.has_short ? n_long + n_reg + short_before : -1;
 }
 
-__device__ __forceinline__ int segment_of_row(const AdapterTable& tb, int row) {
-    int g = 0;
-    while (g + 1 < tb.G && row >= tb.row0[g + 1]) ++g;
-    return g;
-}
-
 // Packed tiling for the GEMMs: when every segment boundary is a multiple of 64 rows, the packed
-// batch is cut into uniform tiles of 256 (or 128) rows and a tile may hold up to four (two) adapters, one per 64-row
-// group; only such mixed tiles take the slower per-group LoRA path.
-struct GroupMap { int g[4]; bool mixed; };
+// batch is cut into uniform tiles of 256 (or 192) rows and a tile may hold up to four (three) adapters, one per 64-row
+// group; only such mixed tiles take the slower per-group LoRA path.  `g`: one byte per group.
+struct GroupMap {
+    uint32_t g;
+    bool mixed;
+    __device__ __forceinline__ int adapter(int q) const { return (int)(g >> (8 * q) & 0xFFu); }
+};
+static_assert(kMaxAdapters <= 256, "a group's adapter is one byte");
+
+__device__ __forceinline__ GroupMap one_group(int g) { return GroupMap{(uint32_t)g * 0x01010101u, false}; }
 
 __device__ __forceinline__ void find_uniform_tile(const AdapterTable& tb, int M, int gran, int tile, RowTile& rt,
                                                   GroupMap& gm) {
     rt.row_start = tile * gran;
     rt.rows = min(gran, M - rt.row_start);
-    gm.mixed = false;
+    gm.g = 0;
+    int g = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int row = rt.row_start + 64 * q;
-        gm.g[q] = (q == 0 || (64 * q < gran && row < M)) ? segment_of_row(tb, row) : gm.g[q - 1];
-        if (q > 0 && gm.g[q] != gm.g[0]) gm.mixed = true;
+        if (q == 0 || (64 * q < gran && row < M))
+            while (g + 1 < tb.G && row >= tb.a[g + 1].row0) ++g;
+        if (q == 0) rt.g = g;
+        gm.g |= (uint32_t)g << (8 * q);
     }
-    rt.g = gm.g[0];
-    rt.local_row0 = rt.row_start - tb.row0[rt.g];
+    gm.mixed = gm.g != (uint32_t)rt.g * 0x01010101u;
+    rt.local_row0 = rt.row_start - tb.a[rt.g].row0;
 }
 
 // ---- dropout hash (unsigned 32-bit arithmetic) ------------------------------------------------

@@ -57,9 +57,9 @@ __global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgs p) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = w % DOWN_PARTS, pos = part >> 1, sub = part & 1;
     const int rb0 = w / DOWN_PARTS * RW;                // this wave's first row block
     const int g = rt.g;
-    const uint32_t T = p.tb.T[g];
+    const uint32_t T = p.tb.a[g].T;
     const KeepThreshold th = keep_threshold(T);
-    const int cbn = p.tb.rank[g] >> 4;                  // 16-column blocks this adapter uses (<= CB)
+    const int cbn = p.tb.a[g].rank >> 4;                  // 16-column blocks this adapter uses (<= CB)
     const int nslabs = p.K / BK, nst = (nslabs + DOWN_SLABS - 1) / DOWN_SLABS;
 
     // This wave's copies: number q of a stage is X rows (8 per copy) of slab q / (2 RB), then A rows of a slab.
@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgs p) {
         const bool is_x = q < C::X_COPIES;
         slab[i] = is_x ? q / (2 * RB) : qa / (2 * CB);
         const int row = (is_x ? q % (2 * RB) : qa % (2 * CB)) * 8 + (l >> 3);
-        const int last = is_x ? rt.rows - 1 : p.tb.rank[g] - 1;
+        const int last = is_x ? rt.rows - 1 : p.tb.a[g].rank - 1;
         mat[i] = (is_x ? (const char*)(p.X + (int64_t)rt.row_start * p.K) : (const char*)(p.A + (int64_t)g * p.r * p.K)) - kCopyBias;
         off[i] = ((uint32_t)min(row, last) * (uint32_t)p.K + slab[i] * BK + (((l & 7) ^ row_slab_swz(row)) << 3)) * 2 +
                  kCopyBias - pass_imm(P, i);
@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgs p) {
     u32x4 keep[RW];
 #pragma unroll
     for (int rb = 0; rb < RW; ++rb) {
-        rk[rb] = row_key(p.tb.k0[g], p.tb.k1[g], (uint32_t)(rt.local_row0 + (rb0 + rb) * 16 + (l & 15)));
+        rk[rb] = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.local_row0 + (rb0 + rb) * 16 + (l & 15)));
         keep[rb] = u32x4{~0u, ~0u, ~0u, ~0u};
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -175,7 +175,7 @@ __global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgs p) {
         for (int cb = 0; cb < CB; ++cb) red[((part * RB + rb0 + rb) * CB + cb) * 64 + l] = acc[rb][cb];
     __syncthreads();
     // fixed-order sum over the column parts, scale by s*q, round once to bf16
-    const float sq = p.tb.s[g] * p.tb.q[g];
+    const float sq = p.tb.a[g].s * p.tb.a[g].q;
     for (int idx = threadIdx.x; idx < RB * CB * 64; idx += C::THREADS) {
         const int lane = idx & 63, cb = (idx >> 6) % CB, rb = (idx >> 6) / CB;
         f32x4 v = red[idx];
@@ -206,7 +206,7 @@ static hipError_t launch_down_cfg(const DownArgs& a, int tiles, hipStream_t st) 
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
     int tiles32 = 0, tiles16 = 0;
     for (int g = 0; g < a.tb.G; ++g) {
-        const int len = a.tb.row0[g + 1] - a.tb.row0[g];
+        const int len = a.tb.a[g + 1].row0 - a.tb.a[g].row0;
         tiles32 += (len + 31) / 32;
         tiles16 += (len + 15) / 16;
     }

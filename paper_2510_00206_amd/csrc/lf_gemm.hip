@@ -121,10 +121,9 @@ __device__ __forceinline__ void issue_copy(const NextSlabs& nx) {
     else copy16_to_lds<pass_imm(PASSES, J - TOKP), J == TOKP>(nx.src_out, nx.lanes_out.off[J - TOKP], nx.m0_out);
 }
 
-// gm.g[q] for a run-time q, as a scalar (wave-uniform) value
+// adapter of 64-row group q as a scalar (wave-uniform) value
 __device__ __forceinline__ int group_adapter(const GroupMap& gm, int q) {
-    const int g = q == 0 ? gm.g[0] : q == 1 ? gm.g[1] : q == 2 ? gm.g[2] : gm.g[3];
-    return __builtin_amdgcn_readfirstlane(g);
+    return __builtin_amdgcn_readfirstlane(gm.adapter(q));
 }
 
 // ---- tiles of a persistent workgroup ---------------------------------------------------------------
@@ -148,8 +147,7 @@ __device__ __forceinline__ TileCtx decode_tile(const AdapterTable& tb, int M, in
         find_uniform_tile(tb, M, bm, tm, c.rt, c.gm);
     } else {
         c.ok = find_row_tile(tb, bm, tm, c.rt);
-        c.gm.g[0] = c.gm.g[1] = c.gm.g[2] = c.gm.g[3] = c.rt.g;
-        c.gm.mixed = false;
+        c.gm = one_group(c.rt.g);
     }
     c.c0 = tn * BN;
     c.cols_valid = min(BN, out_cols - c.c0);
@@ -585,7 +583,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
                     __syncthreads();
                 }
                 const int blk_lo = gm.mixed ? 64 * q : 0, blk_hi = gm.mixed ? 64 * q + 64 : BM;
-                const int rank_chunks = p.tb.rank[g] >> 3, nkk = (rank_chunks + 3) >> 2;
+                const int rank_chunks = p.tb.a[g].rank >> 3, nkk = (rank_chunks + 3) >> 2;
 #pragma unroll 1
                 for (int kk = 0; kk < nkk; ++kk) {
                     const int chunk = 4 * kk + (l >> 4);
@@ -743,8 +741,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
         find_uniform_tile(p.tb, p.M, BM, tm, rt, gm);
     } else {
         if (!find_row_tile(p.tb, BM, tm, rt)) return;
-        gm.g[0] = gm.g[1] = gm.g[2] = gm.g[3] = rt.g;
-        gm.mixed = false;
+        gm = one_group(rt.g);
     }
     const int j0 = tn * BN;                          // output columns are input features
     const int cols_valid = min(BN, p.K - j0);
@@ -762,7 +759,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     const int nk = p.N / BK;
     const int rr = LORA ? p.r : 16;
     const lora_bf16* dSt = p.dS + (int64_t)rt.row_start * rr;
-    const lora_bf16* At = p.A + (int64_t)gm.g[0] * rr * p.K + j0;         // A of the tile's first adapter
+    const lora_bf16* At = p.A + (int64_t)rt.g * rr * p.K + j0;         // A of the tile's first adapter
     const int lo = (nk & 1) * STAGE_BYTES;           // the stage that receives the LoRA slab pair
     if (nk > 0) {
         load_slab<2 * MB>(lds0, dYt + 0, sd);
@@ -791,10 +788,10 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
             // next block row of the wave: its adapter's threshold and the row keys of its rows
             const int blk = wm * (32 * MB) + (wd0 >> 4) * 16;
             const int g = group_adapter(gm, blk >> 6);
-            const KeepThreshold kth = keep_threshold(p.tb.T[g]);
+            const KeepThreshold kth = keep_threshold(p.tb.a[g].T);
             ks.tm1 = kth.tm1_packed;
             keep_all = kth.keep_all;
-            const RowKey rk = row_key(p.tb.k0[g], p.tb.k1[g], (uint32_t)(rt.row_start - p.tb.row0[g] + blk + (l & 15)));
+            const RowKey rk = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.row_start - p.tb.a[g].row0 + blk + (l & 15)));
             ks.x0 = rk.a + cp0 * kGold;
             ks.rkb = rk.b;
         }
@@ -907,7 +904,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
                 wait_slab_loads();
                 __syncthreads();
             }
-            const int rank_chunks = p.tb.rank[g] >> 3;
+            const int rank_chunks = p.tb.a[g].rank >> 3;
 #pragma unroll
             for (int bp = 0; bp < MB; ++bp) {
                 const int blk = wm * (32 * MB) + bp * 32;          // first tile row of the pair
@@ -925,7 +922,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
 // of 64 rows (a tile then holds at most four adapters, one per 64-row group).
 static bool boundaries_on_64(const AdapterTable& tb) {
     for (int g = 0; g <= tb.G; ++g)
-        if (tb.row0[g] & 63) return false;
+        if (tb.a[g].row0 & 63) return false;
     return true;
 }
 
@@ -933,7 +930,7 @@ static bool boundaries_on_64(const AdapterTable& tb) {
 static int64_t count_row_tiles(const AdapterTable& tb, int gran, int lo) {
     int64_t n = 0;
     for (int g = 0; g < tb.G; ++g) {
-        const int a = tb.row0[g] > lo ? tb.row0[g] : lo, b = tb.row0[g + 1];
+        const int a = tb.a[g].row0 > lo ? tb.a[g].row0 : lo, b = tb.a[g + 1].row0;
         if (b > a) n += (b - a + gran - 1) / gran;
     }
     return n;
@@ -943,11 +940,11 @@ static int64_t count_row_tiles(const AdapterTable& tb, int gran, int lo) {
 static int row_of_tile(const AdapterTable& tb, int gran, bool uniform, int64_t tile) {
     if (uniform) return (int)(tile * gran);
     for (int g = 0; g < tb.G; ++g) {
-        const int64_t n = (tb.row0[g + 1] - tb.row0[g] + gran - 1) / gran;
-        if (tile < n) return tb.row0[g] + (int)tile * gran;
+        const int64_t n = (tb.a[g + 1].row0 - tb.a[g].row0 + gran - 1) / gran;
+        if (tile < n) return tb.a[g].row0 + (int)tile * gran;
         tile -= n;
     }
-    return tb.row0[tb.G];
+    return tb.a[tb.G].row0;
 }
 
 static std::atomic<int> g_forced_row_tile{0};      // 0: chosen per launch; 128 or 256: fixed (tuning and tests)

@@ -252,14 +252,14 @@ __global__ void __launch_bounds__(C::THREADS) ring_gemm_kernel(RingArgs p) {
     if constexpr (COL) {
 #pragma unroll
         for (int i = 0; i < FW; ++i) keep[i] = 0xFFFFFFFFu;
-        if (has_lora && p.tb.T[rt.g]) {
-            const KeepThreshold th = keep_threshold(p.tb.T[rt.g]);
+        if (has_lora && p.tb.a[rt.g].T) {
+            const KeepThreshold th = keep_threshold(p.tb.a[rt.g].T);
             const uint32_t cp0 = (uint32_t)(c0 + wn * NI * 16 + 4 * (l >> 4)) >> 1;
 #pragma unroll
             for (int i = 0; i < FW; ++i) keep[i] = 0;
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) {
-                const RowKey rk = row_key(p.tb.k0[rt.g], p.tb.k1[rt.g],
+                const RowKey rk = row_key(p.tb.a[rt.g].k0, p.tb.a[rt.g].k1,
                                           (uint32_t)(rt.local_row0 + (wm * MI + mi) * 16 + (l & 15)));
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)
@@ -313,7 +313,7 @@ __global__ void __launch_bounds__(C::THREADS) ring_gemm_kernel(RingArgs p) {
     for (; kt < nk; ++kt) step(kt, std::false_type{});
 
     // LoRA term: (2) on the same accumulators; (5) by itself, masked and added
-    const int rank_chunks = has_lora ? p.tb.rank[rt.g] >> 3 : 0;
+    const int rank_chunks = has_lora ? p.tb.a[rt.g].rank >> 3 : 0;
     if (has_lora) {
         f32x4 t[MI][NI];
 #pragma unroll

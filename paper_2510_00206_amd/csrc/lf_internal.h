@@ -21,8 +21,8 @@ struct DownArgs {
 struct FwdGemmArgs {
     const lora_bf16* X; const lora_bf16* W; const lora_bf16* S; const lora_bf16* B; lora_bf16* Y;
     int M, K, N, r, tiles_m, tiles_n;
+    int uniform_tiles;         // set by the launcher: uniform tiles over the packed batch (boundaries % 64 == 0)
     AdapterTable tb;
-    int uniform_tiles = 0;     // set by the launcher: uniform tiles over the packed batch (boundaries % 64 == 0)
 };
 
 // Operation (3) (lf_stream.hip).
@@ -34,8 +34,8 @@ struct StreamArgs {
     float* part_ds;            // per-column-chunk partials of dS [chunks,M,r]
     int M, C, r;               // C = N
     int tiles_m, chunks;
+    int panel_rows;            // rows per panel (stream_panel_rows), chosen once per entry-point call
     AdapterTable tb;
-    int panel_rows = 0;        // rows per panel (stream_panel_rows), chosen once per entry-point call
 };
 
 // Operation (4) (lf_da.hip).
@@ -44,10 +44,10 @@ struct DaArgs {
     float* part;               // fp32 planes [panels, r, K] (not direct)
     float* dA;                 // [G, r, K] (direct)
     int M, K, r;
-    AdapterTable tb;
     int panel_rows;            // rows per panel (not direct)
     int direct;                // one panel per segment, dA written (or added to) by the kernel itself
     int accumulate;
+    AdapterTable tb;
 };
 
 // Reductions of the partials.
@@ -56,16 +56,16 @@ struct FinalizeArgs {
     const float* part_db; float* dB;            // dB[g,n,c] (+)= sum over the row tiles of segment g
     const float* part_da; float* dA;            // dA[g,c,j] (+)= q_g * sum over the row tiles of segment g
     int M, K, N, r, chunks, accumulate;
+    int panel_rows_db, panel_rows_da;           // the panel heights operations (3) / (4) ran with (same call, same values)
     AdapterTable tb;
-    int panel_rows_db = 0, panel_rows_da = 0;   // the panel heights operations (3) / (4) ran with (same call, same values)
 };
 
 // Operation (5).
 struct DxGemmArgs {
     const lora_bf16* dY; const lora_bf16* W; const lora_bf16* dS; const lora_bf16* A; lora_bf16* dX;
     int M, K, N, r, tiles_m, tiles_n;
+    int uniform_tiles;
     AdapterTable tb;
-    int uniform_tiles = 0;
 };
 
 constexpr int kRowTile = 256;        // row-tile granularity of the dA/dB partials (and the GEMMs' larger tile)

@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(ST_THREADS, 2) stream_kernel(StreamArgs p) {
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int quarter = w & 3, rb = w >> 2;                   // this wave's part of dS: 128 columns, 16 of the 32 rows
     const int g = rt.g;
-    const int rank_g = p.tb.rank[g], cbn = rank_g >> 4;       // columns / 16-column blocks this adapter uses
+    const int rank_g = p.tb.a[g].rank, cbn = rank_g >> 4;       // columns / 16-column blocks this adapter uses
     // either output may be switched off (null pointer): the unfused baseline runs them as separate passes
     const bool do_red = p.part_out != nullptr, do_ds = p.part_ds != nullptr;
     const int nsteps = (rt.rows + ST_STEP - 1) / ST_STEP;
@@ -258,7 +258,7 @@ __global__ void __launch_bounds__(256) finalize_ds_db_kernel(FinalizeArgs p, int
         // dS leaves here scaled by s*q: the survivor scale q of the dropout that operations (4) and (5)
         // owe their LoRA terms is applied once, to the small matrix, instead of per element of dA and dX
         const int seg = segment_of_row(p.tb, row);
-        const float s = p.tb.s[seg] * p.tb.q[seg];
+        const float s = p.tb.a[seg].s * p.tb.a[seg].q;
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
         for (int ch = 0; ch < p.chunks; ++ch) v += *(const f32x4*)(p.part_ds + ((int64_t)ch * p.M * r4 + idx) * 4);

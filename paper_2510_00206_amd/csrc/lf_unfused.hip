@@ -115,15 +115,15 @@ AdapterTable make_table(int64_t M, int32_t r, float s, float p, uint64_t seed, b
     AdapterTable tb;
     memset(&tb, 0, sizeof(tb));
     tb.G = 1;
-    tb.row0[1] = (int)M;
-    tb.rank[0] = r;
+    tb.a[1].row0 = (int)M;
+    tb.a[0].rank = r;
     const double t = floor((double)p * 65536.0);
     const uint32_t T = plain ? 0u : (t > 65535.0 ? 65535u : (uint32_t)t);
-    tb.T[0] = T;
-    tb.q[0] = plain ? 1.0f : (float)(65536.0 / (65536.0 - (double)T));
-    tb.s[0] = plain ? 1.0f : s;
-    tb.k0[0] = mix32((uint32_t)(seed & 0xFFFFFFFFull) ^ kC5);
-    tb.k1[0] = mix32((uint32_t)(seed >> 32) + tb.k0[0]);
+    tb.a[0].T = T;
+    tb.a[0].q = plain ? 1.0f : (float)(65536.0 / (65536.0 - (double)T));
+    tb.a[0].s = plain ? 1.0f : s;
+    tb.a[0].k0 = mix32((uint32_t)(seed & 0xFFFFFFFFull) ^ kC5);
+    tb.a[0].k1 = mix32((uint32_t)(seed >> 32) + tb.a[0].k0);
     return tb;
 }
 
@@ -152,17 +152,17 @@ lora_status lora_unfused_fwd(const lora_bf16* X, const lora_bf16* W, const lora_
     const int forced = forced_row_tile();
     // 1. Xhat = dropout(X)
     hipLaunchKernelGGL(dropout_kernel, dim3(blocks_for(M * (K >> 3))), dim3(EW_THREADS), 0, st, X, ws.Xhat, M, (int)K,
-                       real.T[0], real.q[0], real.k0[0], real.k1[0]);
+                       real.a[0].T, real.a[0].q, real.a[0].k0, real.a[0].k1);
     LF_LAUNCHED();
     // 2. S = Xhat A^T
     LF_TRY(launch_down(DownArgs{ws.Xhat, A, ws.S, (int)M, (int)K, r, plain}, forced, st));
     // 3. Y2 = S B^T
-    LF_TRY(launch_fwd_gemm(FwdGemmArgs{nullptr, nullptr, ws.S, B, ws.Y2, (int)M, 0, (int)N, r, 0, 0, plain}, forced, st));
+    LF_TRY(launch_fwd_gemm(FwdGemmArgs{nullptr, nullptr, ws.S, B, ws.Y2, (int)M, 0, (int)N, r, 0, 0, 0, plain}, forced, st));
     // 4. Y2 *= s
     hipLaunchKernelGGL(scale_kernel, dim3(blocks_for(M * N / 8)), dim3(EW_THREADS), 0, st, ws.Y2, ws.Y2, M * N / 8, s);
     LF_LAUNCHED();
     // 5. Y1 = X W^T
-    LF_TRY(launch_fwd_gemm(FwdGemmArgs{X, W, nullptr, nullptr, ws.Y1, (int)M, (int)K, (int)N, 0, 0, 0, plain}, forced, st));
+    LF_TRY(launch_fwd_gemm(FwdGemmArgs{X, W, nullptr, nullptr, ws.Y1, (int)M, (int)K, (int)N, 0, 0, 0, 0, plain}, forced, st));
     // 6. Y = Y1 + Y2
     hipLaunchKernelGGL(add_kernel, dim3(blocks_for(M * N / 8)), dim3(EW_THREADS), 0, st, ws.Y1, ws.Y2, Y, M * N / 8);
     LF_LAUNCHED();
@@ -188,24 +188,24 @@ lora_status lora_unfused_bwd(const lora_bf16* W, const lora_bf16* A, const lora_
     hipLaunchKernelGGL(scale_kernel, dim3(blocks_for(M * N / 8)), dim3(EW_THREADS), 0, st, dY, ws.dY2, M * N / 8, s);
     LF_LAUNCHED();
     // 2. dB = dY2^T S     3. dS = dY2 B      (one pass over dY2 each)
-    LF_TRY(launch_stream_dsdb(StreamArgs{ws.dY2, ws.S, B, ws.part_db, nullptr, (int)M, (int)N, r, 0, 0, plain, rows_db}, st));
+    LF_TRY(launch_stream_dsdb(StreamArgs{ws.dY2, ws.S, B, ws.part_db, nullptr, (int)M, (int)N, r, 0, 0, rows_db, plain}, st));
     LF_TRY(launch_finalize_ds_db(FinalizeArgs{nullptr, nullptr, ws.part_db, dB, nullptr, nullptr,
-                                              (int)M, (int)K, (int)N, r, chunks, 0, plain, rows_db, da.rows}, st));
-    LF_TRY(launch_stream_dsdb(StreamArgs{ws.dY2, ws.S, B, nullptr, ws.part_ds, (int)M, (int)N, r, 0, 0, plain, rows_db}, st));
+                                              (int)M, (int)K, (int)N, r, chunks, 0, rows_db, da.rows, plain}, st));
+    LF_TRY(launch_stream_dsdb(StreamArgs{ws.dY2, ws.S, B, nullptr, ws.part_ds, (int)M, (int)N, r, 0, 0, rows_db, plain}, st));
     LF_TRY(launch_finalize_ds_db(FinalizeArgs{ws.part_ds, ws.dS, nullptr, nullptr, nullptr, nullptr,
-                                              (int)M, (int)K, (int)N, r, chunks, 0, plain, rows_db, da.rows}, st));
+                                              (int)M, (int)K, (int)N, r, chunks, 0, rows_db, da.rows, plain}, st));
     // 4. dA = Xhat^T dS
-    LF_TRY(launch_da(DaArgs{ws.Xhat, ws.dS, ws.part_da, dA, (int)M, (int)K, r, plain, da.rows, da.direct, 0}, st));
+    LF_TRY(launch_da(DaArgs{ws.Xhat, ws.dS, ws.part_da, dA, (int)M, (int)K, r, da.rows, da.direct, 0, plain}, st));
     if (!da.direct) LF_TRY(launch_finalize_da(FinalizeArgs{nullptr, nullptr, nullptr, nullptr, ws.part_da, dA,
-                                           (int)M, (int)K, (int)N, r, chunks, 0, plain, rows_db, da.rows}, st));
+                                           (int)M, (int)K, (int)N, r, chunks, 0, rows_db, da.rows, plain}, st));
     // 5. dXhat = dS A
-    LF_TRY(launch_bwd_dx(DxGemmArgs{nullptr, nullptr, ws.dS, A, ws.dXhat, (int)M, (int)K, 0, r, 0, 0, plain}, forced, st));
+    LF_TRY(launch_bwd_dx(DxGemmArgs{nullptr, nullptr, ws.dS, A, ws.dXhat, (int)M, (int)K, 0, r, 0, 0, 0, plain}, forced, st));
     // 6. dXhat = mask * q * dXhat
     hipLaunchKernelGGL(mask_scale_kernel, dim3(blocks_for(M * (K >> 3))), dim3(EW_THREADS), 0, st, ws.dXhat, M, (int)K,
-                       real.T[0], real.q[0], real.k0[0], real.k1[0]);
+                       real.a[0].T, real.a[0].q, real.a[0].k0, real.a[0].k1);
     LF_LAUNCHED();
     // 7. dX1 = dY W
-    LF_TRY(launch_bwd_dx(DxGemmArgs{dY, W, nullptr, nullptr, ws.dX1, (int)M, (int)K, (int)N, 0, 0, 0, plain}, forced, st));
+    LF_TRY(launch_bwd_dx(DxGemmArgs{dY, W, nullptr, nullptr, ws.dX1, (int)M, (int)K, (int)N, 0, 0, 0, 0, plain}, forced, st));
     // 8. dX = dX1 + dXhat
     hipLaunchKernelGGL(add_kernel, dim3(blocks_for(M * K / 8)), dim3(EW_THREADS), 0, st, ws.dX1, ws.dXhat, dX, M * K / 8);
     LF_LAUNCHED();
@@ -217,7 +217,7 @@ lora_status lora_frozen_fwd(const lora_bf16* X, const lora_bf16* W, int64_t M, i
     if (!X || !W || !Y) return LORA_ERR_NULL;
     if (!supported(M, K, N, 16)) return LORA_ERR_UNSUPPORTED;
     const AdapterTable plain = make_table(M, 0, 1.f, 0.f, 0, true);
-    LF_TRY(launch_fwd_gemm(FwdGemmArgs{X, W, nullptr, nullptr, Y, (int)M, (int)K, (int)N, 0, 0, 0, plain}, forced_row_tile(), (hipStream_t)stream));
+    LF_TRY(launch_fwd_gemm(FwdGemmArgs{X, W, nullptr, nullptr, Y, (int)M, (int)K, (int)N, 0, 0, 0, 0, plain}, forced_row_tile(), (hipStream_t)stream));
     return LORA_OK;
 }
 
@@ -226,7 +226,7 @@ lora_status lora_frozen_bwd(const lora_bf16* dY, const lora_bf16* W, int64_t M, 
     if (!dY || !W || !dX) return LORA_ERR_NULL;
     if (!supported(M, K, N, 16)) return LORA_ERR_UNSUPPORTED;
     const AdapterTable plain = make_table(M, 0, 1.f, 0.f, 0, true);
-    LF_TRY(launch_bwd_dx(DxGemmArgs{dY, W, nullptr, nullptr, dX, (int)M, (int)K, (int)N, 0, 0, 0, plain}, forced_row_tile(), (hipStream_t)stream));
+    LF_TRY(launch_bwd_dx(DxGemmArgs{dY, W, nullptr, nullptr, dX, (int)M, (int)K, (int)N, 0, 0, 0, 0, plain}, forced_row_tile(), (hipStream_t)stream));
     return LORA_OK;
 }
 
