@@ -146,6 +146,11 @@ __device__ __forceinline__ void segment_planes(const AdapterTable& tb, int gran,
     extra = me.has_long ? long_before : me.has_short ? n_long + n_reg + short_before : -1;
 }
 
+__device__ __forceinline__ int segment_of_row(const AdapterTable& tb, int row, int g = 0) {
+    while (g + 1 < tb.G && row >= tb.a[g + 1].row0) ++g;
+    return g;
+}
+
 // Packed tiling for the GEMMs: when every segment boundary is a multiple of 64 rows, the packed
 // batch is cut into uniform tiles of 256 (or 192) rows and a tile may hold up to four (three) adapters, one per 64-row
 // group; only such mixed tiles take the slower per-group LoRA path.  `g`: one byte per group.
@@ -168,7 +173,7 @@ __device__ __forceinline__ void find_uniform_tile(const AdapterTable& tb, int M,
     for (int q = 0; q < 4; ++q) {
         const int row = rt.row_start + 64 * q;
         if (q == 0 || (64 * q < gran && row < M))
-            while (g + 1 < tb.G && row >= tb.a[g + 1].row0) ++g;
+            g = segment_of_row(tb, row, g);
         if (q == 0) rt.g = g;
         gm.g |= (uint32_t)g << (8 * q);
     }
