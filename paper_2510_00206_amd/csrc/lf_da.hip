@@ -23,8 +23,8 @@ __device__ __forceinline__ int da_x_off(int row, int chunk) {
     return row * 128 + ((chunk ^ ((row & 2) | ((row & 8) >> 1))) << 4);
 }
 
-template <int CB>                                  // r / 16
-__global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgs p) {
+template <int CB, class TB>                        // r / 16
+__global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgsOf<TB> p) {
     constexpr int R = CB * 16, RCH = CB * 2;       // rank, 16-byte chunks per dS row
     constexpr int WAVE_LDS = DA_BLOCK * (DA_STRIP + R) * 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -144,14 +144,17 @@ static hipError_t launch_da_t(const DaArgs& a, hipStream_t st) {
     const int lds = DA_WAVES * DA_BLOCK * (DA_STRIP + CB * 16) * 2;
     const int panels = a.direct ? a.tb.G : count_panels(a.tb, a.panel_rows);
     if (panels == 0) return hipSuccess;
-    static bool attr_set = false;                  // one flag per instantiation
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)da_kernel<CB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL((da_kernel<CB>), dim3((unsigned)((int64_t)panels * (a.K / DA_STRIP))), dim3(DA_THREADS), lds, st, a);
-    return hipGetLastError();
+    return with_few(a, [&](const auto& b) {
+        constexpr auto kernel = da_kernel<CB, std::decay_t<decltype(b.tb)>>;
+        static bool attr_set = false;              // one flag per instantiation
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((int64_t)panels * (a.K / DA_STRIP))), dim3(DA_THREADS), lds, st, b);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_da(const DaArgs& a, hipStream_t st) {

@@ -32,10 +32,18 @@ struct Adapter {
     float q;                          // survivor scale 65536/(65536-T)
 };
 
-struct AdapterTable {
+template <int MAX>
+struct AdapterTableOf {
     int G;
-    Adapter a[kMaxAdapters + 1];      // (the last one: row0 only)
+    Adapter a[MAX + 1];               // (the last one: row0 only)
 };
+using AdapterTable = AdapterTableOf<kMaxAdapters>;
+
+// What a launch of few adapters takes of it.  The table is nearly all of a kernel's arguments (1.8 KB of 1.9), which are
+// copied several times on the way to the device and written there over the bus; the kernels that small launches use are
+// instantiated for both sizes (a step of six launches over 256 x 1024 x 1024 33.9 -> 30.7 us, 1000 rows and more level).
+constexpr int kFewAdapters = 4;
+using FewAdapters = AdapterTableOf<kFewAdapters>;
 
 // A row tile: `rows` valid rows starting at global row `row_start`, owned by adapter g.
 struct RowTile {
@@ -44,7 +52,8 @@ struct RowTile {
 
 // Tiles never straddle a segment: segment g contributes ceil(len/gran) tiles, len counting its rows in
 // [row_lo, row_hi).
-__device__ __forceinline__ bool find_row_tile(const AdapterTable& tb, int gran, int tile, RowTile& rt, int row_lo = 0,
+template <class TB>
+__device__ __forceinline__ bool find_row_tile(const TB& tb, int gran, int tile, RowTile& rt, int row_lo = 0,
                                               int row_hi = 0x7FFFFFFF) {
     int t = tile;
     for (int g = 0; g < tb.G; ++g) {
@@ -71,7 +80,8 @@ __device__ __forceinline__ bool find_row_tile(const AdapterTable& tb, int gran, 
 // ones, then the short ones; the number is also the plane index of the panel's partial sums.
 struct SegmentPanels { int nreg; bool has_long, has_short; int rem; };
 
-__host__ __device__ __forceinline__ SegmentPanels segment_panels(const AdapterTable& tb, int gran, int g) {
+template <class TB>
+__host__ __device__ __forceinline__ SegmentPanels segment_panels(const TB& tb, int gran, int g) {
     const int len = tb.a[g + 1].row0 - tb.a[g].row0;
     const int nf = len >> __builtin_ctz((unsigned)gran);      // (every panel height is a power of two)
     SegmentPanels sp;
@@ -82,7 +92,8 @@ __host__ __device__ __forceinline__ SegmentPanels segment_panels(const AdapterTa
     return sp;
 }
 
-__host__ __device__ __forceinline__ int count_panels(const AdapterTable& tb, int gran) {
+template <class TB>
+__host__ __device__ __forceinline__ int count_panels(const TB& tb, int gran) {
     int n = 0;
     for (int g = 0; g < tb.G; ++g) {
         const SegmentPanels sp = segment_panels(tb, gran, g);
@@ -91,7 +102,8 @@ __host__ __device__ __forceinline__ int count_panels(const AdapterTable& tb, int
     return n;
 }
 
-__device__ __forceinline__ bool find_panel(const AdapterTable& tb, int gran, int panel, RowTile& rt) {
+template <class TB>
+__device__ __forceinline__ bool find_panel(const TB& tb, int gran, int panel, RowTile& rt) {
     int idx = panel;
     for (int g = 0; g < tb.G; ++g) {                     // long panels
         const SegmentPanels sp = segment_panels(tb, gran, g);
@@ -133,7 +145,8 @@ __device__ __forceinline__ bool find_panel(const AdapterTable& tb, int gran, int
 
 // Plane indices of segment g's panels: regular planes [reg0, reg0 + nreg), then `extra` (its long or
 // short panel, -1 if none).  The finalize kernels add them in exactly this order.
-__device__ __forceinline__ void segment_planes(const AdapterTable& tb, int gran, int g, int& reg0, int& nreg, int& extra) {
+template <class TB>
+__device__ __forceinline__ void segment_planes(const TB& tb, int gran, int g, int& reg0, int& nreg, int& extra) {
     int n_long = 0, n_reg = 0, long_before = 0, reg_before = 0, short_before = 0;
     for (int gg = 0; gg < tb.G; ++gg) {
         const SegmentPanels sp = segment_panels(tb, gran, gg);
@@ -146,7 +159,8 @@ __device__ __forceinline__ void segment_planes(const AdapterTable& tb, int gran,
     extra = me.has_long ? long_before : me.has_short ? n_long + n_reg + short_before : -1;
 }
 
-__device__ __forceinline__ int segment_of_row(const AdapterTable& tb, int row, int g = 0) {
+template <class TB>
+__device__ __forceinline__ int segment_of_row(const TB& tb, int row, int g = 0) {
     while (g + 1 < tb.G && row >= tb.a[g + 1].row0) ++g;
     return g;
 }

@@ -47,8 +47,8 @@ __device__ __forceinline__ void down_copy(const char* const (&src)[C::P], const 
     }
 }
 
-template <class C>
-__global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgs p) {
+template <class C, class TB>
+__global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgsOf<TB> p) {
     constexpr int CB = C::CB, RB = C::RB, RW = C::RW, NS = C::NS, P = C::P;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     RowTile rt;
@@ -193,14 +193,17 @@ __global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgs p) {
 
 template <class C>
 static hipError_t launch_down_cfg(const DownArgs& a, int tiles, hipStream_t st) {
-    static bool attr_set = false;                      // one flag per instantiation
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)down_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL((down_kernel<C>), dim3(tiles), dim3(C::THREADS), C::LDS, st, a);
-    return hipGetLastError();
+    return with_few(a, [&](const auto& b) {
+        constexpr auto kernel = down_kernel<C, std::decay_t<decltype(b.tb)>>;
+        static bool attr_set = false;                  // one flag per instantiation
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(C::THREADS), C::LDS, st, b);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {

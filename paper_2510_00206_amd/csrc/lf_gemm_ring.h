@@ -7,12 +7,14 @@ namespace lf {
 // Operation (2): tok X [M,KC], out W [NC,KC], ltok S' [M,r], lout B [G,NC,r], res Y [M,NC].
 // Operation (5): tok dY [M,KC], out W [KC,NC], ltok dS [M,r], lout A [G,r,NC], res dX [M,NC].
 // r == 0: no LoRA term.
-struct RingArgs {
+template <class TB>
+struct RingArgsOf {
     const lora_bf16* tok; const lora_bf16* out; const lora_bf16* ltok; const lora_bf16* lout; lora_bf16* res;
     int M, KC, NC, r, tiles_m, tiles_n;
     int row_lo, row_hi;                              // the launch covers rows [row_lo, row_hi) of the packed batch
-    AdapterTable tb;
+    TB tb;
 };
+using RingArgs = RingArgsOf<AdapterTable>;
 
 constexpr int kRingKinds = 6;
 constexpr int kRingTiles[kRingKinds][2] = {{128, 256}, {128, 128}, {64, 128}, {64, 64}, {32, 64}, {128, 64}};   // rows x columns

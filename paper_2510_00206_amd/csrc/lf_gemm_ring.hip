@@ -204,8 +204,8 @@ __device__ __forceinline__ void ring_half(f32x4 (&acc)[C::MI][C::NI], const Ring
     }
 }
 
-template <class C, bool COL>
-__global__ void __launch_bounds__(C::THREADS) ring_gemm_kernel(RingArgs p) {
+template <class C, bool COL, class TB>
+__global__ void __launch_bounds__(C::THREADS) ring_gemm_kernel(RingArgsOf<TB> p) {
     constexpr int NS = C::NS, MI = C::MI, NI = C::NI;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int tm, tn;
@@ -380,18 +380,20 @@ __global__ void __launch_bounds__(C::THREADS) ring_gemm_kernel(RingArgs p) {
 
 template <class C, bool COL>
 static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
-    static bool attr_set = false;                      // one flag per instantiation
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)ring_gemm_kernel<C, COL>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL((ring_gemm_kernel<C, COL>), dim3((unsigned)tiles), dim3(C::THREADS), C::LDS, st, a);
-    return hipGetLastError();
+    return with_few(a, [&](const auto& b) {
+        constexpr auto kernel = ring_gemm_kernel<C, COL, std::decay_t<decltype(b.tb)>>;
+        static bool attr_set = false;                  // one flag per instantiation
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(C::THREADS), C::LDS, st, b);
+        return hipGetLastError();
+    });
 }
-
 
 
 // Which kernel of the family: see kRingTiles.  Two workgroups of kinds 2, 3 and 4 fit on a compute unit (their rings

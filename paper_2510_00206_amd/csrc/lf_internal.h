@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <type_traits>
+#include <string.h>
 
 #include "lf_device.h"
 
@@ -11,11 +13,13 @@ typedef uint16_t lora_bf16;
 namespace lf {
 
 // Operation (1): S' = s*q*(mask.X) A^T.
-struct DownArgs {
+template <class TB>
+struct DownArgsOf {
     const lora_bf16* X; const lora_bf16* A; lora_bf16* S;
     int M, K, r;
-    AdapterTable tb;
+    TB tb;
 };
+using DownArgs = DownArgsOf<AdapterTable>;
 
 // Operation (2).
 struct FwdGemmArgs {
@@ -26,7 +30,8 @@ struct FwdGemmArgs {
 };
 
 // Operation (3) (lf_stream.hip).
-struct StreamArgs {
+template <class TB>
+struct StreamArgsOf {
     const lora_bf16* big;      // dY [M,N]
     const lora_bf16* small_;   // S' [M,r]
     const lora_bf16* Bmat;     // B [G,N,r]
@@ -35,11 +40,13 @@ struct StreamArgs {
     int M, C, r;               // C = N
     int tiles_m, chunks;
     int panel_rows;            // rows per panel (stream_panel_rows), chosen once per entry-point call
-    AdapterTable tb;
+    TB tb;
 };
+using StreamArgs = StreamArgsOf<AdapterTable>;
 
 // Operation (4) (lf_da.hip).
-struct DaArgs {
+template <class TB>
+struct DaArgsOf {
     const lora_bf16* X; const lora_bf16* dS;
     float* part;               // fp32 planes [panels, r, K] (not direct)
     float* dA;                 // [G, r, K] (direct)
@@ -47,18 +54,21 @@ struct DaArgs {
     int panel_rows;            // rows per panel (not direct)
     int direct;                // one panel per segment, dA written (or added to) by the kernel itself
     int accumulate;
-    AdapterTable tb;
+    TB tb;
 };
+using DaArgs = DaArgsOf<AdapterTable>;
 
 // Reductions of the partials.
-struct FinalizeArgs {
+template <class TB>
+struct FinalizeArgsOf {
     const float* part_ds; lora_bf16* dS;        // dS[i,c] = s_g * sum over chunks
     const float* part_db; float* dB;            // dB[g,n,c] (+)= sum over the row tiles of segment g
     const float* part_da; float* dA;            // dA[g,c,j] (+)= q_g * sum over the row tiles of segment g
     int M, K, N, r, chunks, accumulate;
     int panel_rows_db, panel_rows_da;           // the panel heights operations (3) / (4) ran with (same call, same values)
-    AdapterTable tb;
+    TB tb;
 };
+using FinalizeArgs = FinalizeArgsOf<AdapterTable>;
 
 // Operation (5).
 struct DxGemmArgs {
@@ -71,6 +81,16 @@ struct DxGemmArgs {
 constexpr int kRowTile = 256;        // row-tile granularity of the dA/dB partials (and the GEMMs' larger tile)
 constexpr int kComputeUnits = 256;   // of the one chip this library is written for
 constexpr int kStreamChunk = 512;    // column-chunk width of operation (3)
+
+// Calls launch(arguments) with a table no larger than the batch needs.
+template <template <class> class Args, class F>
+hipError_t with_few(const Args<AdapterTable>& a, F&& launch) {
+    if (a.tb.G > kFewAdapters) return launch(a);
+    Args<FewAdapters> few;
+    static_assert(offsetof(Args<FewAdapters>, tb) == offsetof(Args<AdapterTable>, tb), "the table is the last member");
+    memcpy((void*)&few, (const void*)&a, offsetof(Args<FewAdapters>, tb) + sizeof(FewAdapters));
+    return launch(few);
+}
 
 void force_row_tile(int rows);        // 0 (automatic), or the small (128) / large (256) height of every kernel that has two
 int forced_row_tile();                // an entry point reads this ONCE and hands the value to everything it launches

@@ -51,8 +51,8 @@ __device__ __forceinline__ bf16x8 zero_past_rows(bf16x8 v, int rows) {
     return __builtin_bit_cast(bf16x8, u);
 }
 
-template <class C>
-__global__ void __launch_bounds__(ST_THREADS, 2) stream_kernel(StreamArgs p) {
+template <class C, class TB>
+__global__ void __launch_bounds__(ST_THREADS, 2) stream_kernel(StreamArgsOf<TB> p) {
     constexpr int CB = C::CB, NS = C::NS, R = CB * 16, RCH = CB * 2;     // rank, 16-byte chunks per S' row
     extern __shared__ __attribute__((aligned(16))) char smem[];
     f32x4* red = (f32x4*)(smem + NS * C::STAGE);
@@ -228,14 +228,17 @@ static hipError_t launch_stream_t(StreamArgs a, hipStream_t st) {
     a.tiles_m = count_panels(a.tb, a.panel_rows);
     a.chunks = (a.C + kStreamChunk - 1) / kStreamChunk;
     if (a.tiles_m == 0) return hipSuccess;
-    static bool attr_set = false;                      // one flag per instantiation
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)stream_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL((stream_kernel<C>), dim3(a.tiles_m * a.chunks), dim3(ST_THREADS), C::LDS, st, a);
-    return hipGetLastError();
+    return with_few(a, [&](const auto& b) {
+        constexpr auto kernel = stream_kernel<C, std::decay_t<decltype(b.tb)>>;
+        static bool attr_set = false;                  // one flag per instantiation
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+        hipLaunchKernelGGL(kernel, dim3(a.tiles_m * a.chunks), dim3(ST_THREADS), C::LDS, st, b);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st) {
@@ -249,7 +252,8 @@ hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st) {
 
 // ---- finalize: fixed-order sums of the partials ---------------------------------------------------
 // job 1: dS[i, c..c+3] = bf16(s_g * q_g * sum_chunks part_ds);  job 2: dB[g, n, c..c+3] (+)= sum over tiles of g
-__global__ void __launch_bounds__(256) finalize_ds_db_kernel(FinalizeArgs p, int blocks_ds) {
+template <class TB>
+__global__ void __launch_bounds__(256) finalize_ds_db_kernel(FinalizeArgsOf<TB> p, int blocks_ds) {
     const int r4 = p.r >> 2;
     if ((int)blockIdx.x < blocks_ds) {
         const int64_t idx = blockIdx.x * 256ll + threadIdx.x;
@@ -285,7 +289,8 @@ __global__ void __launch_bounds__(256) finalize_ds_db_kernel(FinalizeArgs p, int
 }
 
 // dA[g, c, j..j+3] (+)= sum over the row tiles of segment g (q_g is already in dS)
-__global__ void __launch_bounds__(256) finalize_da_kernel(FinalizeArgs p) {
+template <class TB>
+__global__ void __launch_bounds__(256) finalize_da_kernel(FinalizeArgsOf<TB> p) {
     const int64_t per_g = (int64_t)p.r * (p.K >> 2);
     const int64_t idx = blockIdx.x * 256ll + threadIdx.x;
     if (idx >= per_g * p.tb.G) return;
@@ -308,15 +313,21 @@ hipError_t launch_finalize_ds_db(const FinalizeArgs& a, hipStream_t st) {
     if (n_ds + n_db == 0) return hipSuccess;
     const int blocks_ds = (int)((n_ds + 255) / 256), blocks_db = (int)((n_db + 255) / 256);
     if (n_db && a.panel_rows_db < 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(finalize_ds_db_kernel, dim3(blocks_ds + blocks_db), dim3(256), 0, st, a, blocks_ds);
-    return hipGetLastError();
+    return with_few(a, [&](const auto& b) {
+        constexpr auto kernel = finalize_ds_db_kernel<std::decay_t<decltype(b.tb)>>;
+        hipLaunchKernelGGL(kernel, dim3(blocks_ds + blocks_db), dim3(256), 0, st, b, blocks_ds);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_finalize_da(const FinalizeArgs& a, hipStream_t st) {
     const int64_t n = (int64_t)a.tb.G * a.r * (a.K >> 2);
     if (a.panel_rows_da < 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(finalize_da_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
+    return with_few(a, [&](const auto& b) {
+        constexpr auto kernel = finalize_da_kernel<std::decay_t<decltype(b.tb)>>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, b);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace lf
