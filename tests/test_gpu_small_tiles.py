@@ -27,6 +27,8 @@ CASES = [
     (1024, 4096, 16, (4396,)),               # 256 x 256 for 4096 rows, small tiles for the rest
     (832, 4160, 32, (3000, 1500)),           # the cut falls inside the second segment
     (2112, 4096, 16, (1088, 3072, 256, 64)), # uniform 256-row tiles (boundaries on 64 rows), then small tiles
+    (320, 448, 32, (33, 0, 70, 1)),          # four adapters: the last count with the small adapter table
+    (320, 448, 32, (33, 0, 70, 1, 64)),      # five: the full one
     (4096, 4096, 16, (2113,)),               # 192 x 256, last row tile of one row
     (2048, 4096, 16, (64, 1152, 832, 640, 256)),   # 192 x 256 forward, several adapters in a tile
 ]
