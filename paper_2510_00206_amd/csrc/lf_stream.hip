@@ -217,7 +217,8 @@ __global__ void __launch_bounds__(ST_THREADS, 2) stream_kernel(StreamArgsOf<TB> 
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             const int n = c0 + colb + (l & 15), c = cb * 16 + 4 * (l >> 4);
-            *(f32x4*)(p.part_out + ((int64_t)tile * p.C + n) * R + c) = acc[jb][cb];
+            // past the adapter's rank S' is zero, but zero times a non-finite dY is not: the padding of dB is set to zero here
+            *(f32x4*)(p.part_out + ((int64_t)tile * p.C + n) * R + c) = cb < cbn ? acc[jb][cb] : f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
 }
