@@ -52,7 +52,7 @@ lora_status build_table(AdapterTable& tb, int64_t M, int32_t r, int32_t G, const
     if (off[0] != 0 || off[G] != M) return LORA_ERR_SEGMENTS;
     for (int g = 0; g < G; ++g)
         if (off[g + 1] < off[g]) return LORA_ERR_SEGMENTS;
-    for (int g = 0; g <= G; ++g) tb.a[g].row0 = (int)off[g];
+    for (int g = 0; g <= G; ++g) tb.row0[g] = (int)off[g];
     for (int g = 0; g < G; ++g) {
         lora_status st = fill_adapter(tb, g, s[g], p[g], seeds[g]);
         if (st != LORA_OK) return st;
@@ -310,7 +310,7 @@ lora_status lora_debug_stream_panels(int64_t M, int64_t C, int32_t G, const int6
     if (seg_offsets[0] != 0 || seg_offsets[G] != M) return LORA_ERR_SEGMENTS;
     for (int g = 0; g < G; ++g)
         if (seg_offsets[g + 1] < seg_offsets[g]) return LORA_ERR_SEGMENTS;
-    for (int g = 0; g <= G; ++g) tb.a[g].row0 = (int)seg_offsets[g];
+    for (int g = 0; g <= G; ++g) tb.row0[g] = (int)seg_offsets[g];
     *panel_rows = stream_panel_rows(tb, (int)C, forced_row_tile());
     *panels = count_panels(tb, *panel_rows);
     *panels_bound = max_stream_panels(M, G);

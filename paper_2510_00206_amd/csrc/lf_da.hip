@@ -33,8 +33,8 @@ __global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgsO
     RowTile rt;
     if (p.direct) {                                // panel = segment, empty ones too (their gradient is zero)
         rt.g = tile;
-        rt.row_start = p.tb.a[tile].row0;
-        rt.rows = p.tb.a[tile + 1].row0 - rt.row_start;
+        rt.row_start = p.tb.row0[tile];
+        rt.rows = p.tb.row0[tile + 1] - rt.row_start;
         rt.local_row0 = 0;
         if (rt.rows == 0 && p.accumulate) return;
     } else if (!find_panel(p.tb, p.panel_rows, tile, rt)) return;

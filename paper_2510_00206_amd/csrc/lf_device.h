@@ -17,11 +17,13 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 constexpr int kMaxAdapters = 64;
 
-// Lookup table passed by value in the kernel arguments.  One entry per adapter, so that what a kernel reads of its adapter lies in one or two cache lines of the arguments (the
-// reads are a latency at the start of every launch; against one array per field: two backward passes of four launches each
-// over 2048 x 4096 x 4096 46.0 -> 44.8 us, a step of six launches over 1024 x 4096 x 4096 94.6 -> 93.3 us).
+// Lookup table passed by value in the kernel arguments.  Every workgroup walks the segments to find its tile and then reads
+// the fields of one adapter: the row offsets lie side by side (16 of them to a cache line of the arguments), the fields of an
+// adapter in one or two lines.  These reads are a latency at the start of every launch.  Against one array per field, two
+// backward passes of four launches each over 2048 x 4096 x 4096: 46.0 -> 44.8 us; against offsets that lie in the adapters'
+// entries, 28 bytes apart, (1) over 64 adapters x 4 rows, K = 1024: 16.5 -> 11.9 us, (2) 4096 -> 1024 over 64 x 100 rows:
+// 66 -> 60 us.
 struct Adapter {
-    int row0;                         // segment g owns rows [a[g].row0, a[g + 1].row0)
     // rank of the adapter (16, 32 or 64), at most the call's r: the arrays are laid out with r columns
     // (rows of A) per adapter and the adapter uses the first `rank`; the padding of A and B is never used
     // and the padding of S', dS, dA and dB is written as zeros
@@ -35,7 +37,8 @@ struct Adapter {
 template <int MAX>
 struct AdapterTableOf {
     int G;
-    Adapter a[MAX + 1];               // (the last one: row0 only)
+    int row0[MAX + 1];                // segment g owns rows [row0[g], row0[g + 1])
+    Adapter a[MAX];
 };
 using AdapterTable = AdapterTableOf<kMaxAdapters>;
 
@@ -57,13 +60,13 @@ __device__ __forceinline__ bool find_row_tile(const TB& tb, int gran, int tile, 
                                               int row_hi = 0x7FFFFFFF) {
     int t = tile;
     for (int g = 0; g < tb.G; ++g) {
-        const int lo = max(tb.a[g].row0, row_lo), hi = min(tb.a[g + 1].row0, row_hi);
+        const int lo = max(tb.row0[g], row_lo), hi = min(tb.row0[g + 1], row_hi);
         const int nt = max(hi - lo + gran - 1, 0) / gran;
         if (t < nt) {
             rt.g = g;
             rt.row_start = lo + t * gran;
             rt.rows = min(gran, hi - rt.row_start);
-            rt.local_row0 = rt.row_start - tb.a[g].row0;
+            rt.local_row0 = rt.row_start - tb.row0[g];
             return true;
         }
         t -= nt;
@@ -82,7 +85,7 @@ struct SegmentPanels { int nreg; bool has_long, has_short; int rem; };
 
 template <class TB>
 __host__ __device__ __forceinline__ SegmentPanels segment_panels(const TB& tb, int gran, int g) {
-    const int len = tb.a[g + 1].row0 - tb.a[g].row0;
+    const int len = tb.row0[g + 1] - tb.row0[g];
     const int nf = len >> __builtin_ctz((unsigned)gran);      // (every panel height is a power of two)
     SegmentPanels sp;
     sp.rem = len - nf * gran;
@@ -111,7 +114,7 @@ __device__ __forceinline__ bool find_panel(const TB& tb, int gran, int panel, Ro
         if (idx == 0) {
             rt.g = g;
             rt.local_row0 = sp.nreg * gran;
-            rt.row_start = tb.a[g].row0 + rt.local_row0;
+            rt.row_start = tb.row0[g] + rt.local_row0;
             rt.rows = gran + sp.rem;
             return true;
         }
@@ -122,7 +125,7 @@ __device__ __forceinline__ bool find_panel(const TB& tb, int gran, int panel, Ro
         if (idx < sp.nreg) {
             rt.g = g;
             rt.local_row0 = idx * gran;
-            rt.row_start = tb.a[g].row0 + rt.local_row0;
+            rt.row_start = tb.row0[g] + rt.local_row0;
             rt.rows = gran;
             return true;
         }
@@ -134,7 +137,7 @@ __device__ __forceinline__ bool find_panel(const TB& tb, int gran, int panel, Ro
         if (idx == 0) {
             rt.g = g;
             rt.local_row0 = 0;
-            rt.row_start = tb.a[g].row0;
+            rt.row_start = tb.row0[g];
             rt.rows = sp.rem;
             return true;
         }
@@ -161,7 +164,7 @@ __device__ __forceinline__ void segment_planes(const TB& tb, int gran, int g, in
 
 template <class TB>
 __device__ __forceinline__ int segment_of_row(const TB& tb, int row, int g = 0) {
-    while (g + 1 < tb.G && row >= tb.a[g + 1].row0) ++g;
+    while (g + 1 < tb.G && row >= tb.row0[g + 1]) ++g;
     return g;
 }
 
@@ -192,7 +195,7 @@ __device__ __forceinline__ void find_uniform_tile(const AdapterTable& tb, int M,
         gm.g |= (uint32_t)g << (8 * q);
     }
     gm.mixed = gm.g != (uint32_t)rt.g * 0x01010101u;
-    rt.local_row0 = rt.row_start - tb.a[rt.g].row0;
+    rt.local_row0 = rt.row_start - tb.row0[rt.g];
 }
 
 // ---- dropout hash (unsigned 32-bit arithmetic) ------------------------------------------------

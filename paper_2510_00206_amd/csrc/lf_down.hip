@@ -209,7 +209,7 @@ static hipError_t launch_down_cfg(const DownArgs& a, int tiles, hipStream_t st) 
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
     int tiles32 = 0, tiles16 = 0;
     for (int g = 0; g < a.tb.G; ++g) {
-        const int len = a.tb.a[g + 1].row0 - a.tb.a[g].row0;
+        const int len = a.tb.row0[g + 1] - a.tb.row0[g];
         tiles32 += (len + 31) / 32;
         tiles16 += (len + 15) / 16;
     }

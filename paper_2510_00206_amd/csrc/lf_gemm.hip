@@ -791,7 +791,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
             const KeepThreshold kth = keep_threshold(p.tb.a[g].T);
             ks.tm1 = kth.tm1_packed;
             keep_all = kth.keep_all;
-            const RowKey rk = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.row_start - p.tb.a[g].row0 + blk + (l & 15)));
+            const RowKey rk = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.row_start - p.tb.row0[g] + blk + (l & 15)));
             ks.x0 = rk.a + cp0 * kGold;
             ks.rkb = rk.b;
         }
@@ -922,7 +922,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
 // of 64 rows (a tile then holds at most four adapters, one per 64-row group).
 static bool boundaries_on_64(const AdapterTable& tb) {
     for (int g = 0; g <= tb.G; ++g)
-        if (tb.a[g].row0 & 63) return false;
+        if (tb.row0[g] & 63) return false;
     return true;
 }
 
@@ -930,7 +930,7 @@ static bool boundaries_on_64(const AdapterTable& tb) {
 static int64_t count_row_tiles(const AdapterTable& tb, int gran, int lo) {
     int64_t n = 0;
     for (int g = 0; g < tb.G; ++g) {
-        const int a = tb.a[g].row0 > lo ? tb.a[g].row0 : lo, b = tb.a[g + 1].row0;
+        const int a = tb.row0[g] > lo ? tb.row0[g] : lo, b = tb.row0[g + 1];
         if (b > a) n += (b - a + gran - 1) / gran;
     }
     return n;
@@ -940,11 +940,11 @@ static int64_t count_row_tiles(const AdapterTable& tb, int gran, int lo) {
 static int row_of_tile(const AdapterTable& tb, int gran, bool uniform, int64_t tile) {
     if (uniform) return (int)(tile * gran);
     for (int g = 0; g < tb.G; ++g) {
-        const int64_t n = (tb.a[g + 1].row0 - tb.a[g].row0 + gran - 1) / gran;
-        if (tile < n) return tb.a[g].row0 + (int)tile * gran;
+        const int64_t n = (tb.row0[g + 1] - tb.row0[g] + gran - 1) / gran;
+        if (tile < n) return tb.row0[g] + (int)tile * gran;
         tile -= n;
     }
-    return tb.a[tb.G].row0;
+    return tb.row0[tb.G];
 }
 
 static std::atomic<int> g_forced_row_tile{0};      // 0: chosen per launch; 128 or 256: fixed (tuning and tests)

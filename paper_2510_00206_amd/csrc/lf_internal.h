@@ -88,7 +88,10 @@ hipError_t with_few(const Args<AdapterTable>& a, F&& launch) {
     if (a.tb.G > kFewAdapters) return launch(a);
     Args<FewAdapters> few;
     static_assert(offsetof(Args<FewAdapters>, tb) == offsetof(Args<AdapterTable>, tb), "the table is the last member");
-    memcpy((void*)&few, (const void*)&a, offsetof(Args<FewAdapters>, tb) + sizeof(FewAdapters));
+    memcpy((void*)&few, (const void*)&a, offsetof(Args<FewAdapters>, tb));
+    few.tb.G = a.tb.G;
+    memcpy(few.tb.row0, a.tb.row0, sizeof(few.tb.row0));
+    memcpy(few.tb.a, a.tb.a, sizeof(few.tb.a));
     return launch(few);
 }
 

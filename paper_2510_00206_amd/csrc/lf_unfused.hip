@@ -115,7 +115,7 @@ AdapterTable make_table(int64_t M, int32_t r, float s, float p, uint64_t seed, b
     AdapterTable tb;
     memset(&tb, 0, sizeof(tb));
     tb.G = 1;
-    tb.a[1].row0 = (int)M;
+    tb.row0[1] = (int)M;
     tb.a[0].rank = r;
     const double t = floor((double)p * 65536.0);
     const uint32_t T = plain ? 0u : (t > 65535.0 ? 65535u : (uint32_t)t);
