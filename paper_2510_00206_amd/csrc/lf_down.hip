@@ -12,7 +12,8 @@
 // of a stage are formed while its copies land, and not at all without dropout.
 // Measured against fragments loaded straight into registers (same rows and K, us): K = 14336: 64 rows r = 16 29 -> 23,
 // r = 64 65 -> 32; 5003 rows r = 16 57 -> 36, r = 64 128 -> 43; 8192 rows r = 64 83 -> 50.  K = 4096: 8192 rows r = 16
-// 18 -> 15, 4096 rows r = 64 24 -> 15.
+// 18 -> 15, 4096 rows r = 64 24 -> 15.  Short contractions keep the registers (down_direct_kernel, rule in launch_down).  The
+// order of the sums is the same in both kernels and in every height, so S' has the same bits whichever is picked.
 #include <type_traits>
 
 #include "lf_device.h"
@@ -44,6 +45,25 @@ __device__ __forceinline__ void down_copy(const char* const (&src)[C::P], const 
     if constexpr (I < C::P) {
         copy16_to_lds<pass_imm(C::P, I), I == 0>(src[I], off[I], m0);
         down_copy<C, I + 1>(src, off, m0);
+    }
+}
+
+// Fixed-order sum over the column parts ([DOWN_PARTS][RB][CB][64] in LDS), scaled by s*q and rounded once to bf16.
+template <int CB, int RB, int THREADS, class TB>
+__device__ __forceinline__ void down_store(const DownArgsOf<TB>& p, const RowTile& rt, const f32x4* red) {
+    const float sq = p.tb.a[rt.g].s * p.tb.a[rt.g].q;
+    for (int idx = threadIdx.x; idx < RB * CB * 64; idx += THREADS) {
+        const int lane = idx & 63, cb = (idx >> 6) % CB, rb = (idx >> 6) / CB;
+        f32x4 v = red[idx];
+#pragma unroll
+        for (int ww = 1; ww < DOWN_PARTS; ++ww) v += red[ww * (RB * CB * 64) + idx];
+        const int row = rb * 16 + (lane & 15);
+        if (row < rt.rows) {
+            u32x2 out;
+            out.x = pack_bf16x2(v[0] * sq, v[1] * sq);
+            out.y = pack_bf16x2(v[2] * sq, v[3] * sq);
+            *(u32x2*)(p.S + (int64_t)(rt.row_start + row) * p.r + cb * 16 + 4 * (lane >> 4)) = out;
+        }
     }
 }
 
@@ -174,21 +194,82 @@ __global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgsOf<TB> p) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) red[((part * RB + rb0 + rb) * CB + cb) * 64 + l] = acc[rb][cb];
     __syncthreads();
-    // fixed-order sum over the column parts, scale by s*q, round once to bf16
-    const float sq = p.tb.a[g].s * p.tb.a[g].q;
-    for (int idx = threadIdx.x; idx < RB * CB * 64; idx += C::THREADS) {
-        const int lane = idx & 63, cb = (idx >> 6) % CB, rb = (idx >> 6) / CB;
-        f32x4 v = red[idx];
+    down_store<CB, RB, C::THREADS>(p, rt, red);
+}
+
+// The same sums without LDS: wave w loads the fragments of column part w of every stage straight into registers, D stages
+// ahead.  No stage to fill and 64 KB of LDS at most, so several workgroups share a compute unit and cover for each other:
+// the faster way where a workgroup's sweep is short against its start and its end (see launch_down).
+template <int CB, int RB, class TB>
+__global__ void __launch_bounds__(64 * DOWN_PARTS) down_direct_kernel(DownArgsOf<TB> p) {
+    __shared__ f32x4 red[DOWN_PARTS * RB * CB * 64];
+    RowTile rt;
+    if (!find_row_tile(p.tb, 16 * RB, blockIdx.x, rt)) return;
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = rt.g;
+    const uint32_t T = p.tb.a[g].T;
+    const KeepThreshold th = keep_threshold(T);
+    const int cbn = p.tb.a[g].rank >> 4;                  // 16-column blocks this adapter uses (<= CB)
+    const lora_bf16* Ag = p.A + (int64_t)g * p.r * p.K + (int64_t)(l & 15) * p.K;
+    const lora_bf16* xrow[RB];
+    RowKey rk[RB];
 #pragma unroll
-        for (int ww = 1; ww < DOWN_PARTS; ++ww) v += red[ww * (RB * CB * 64) + idx];
-        const int row = rb * 16 + (lane & 15);
-        if (row < rt.rows) {
-            u32x2 out;
-            out.x = pack_bf16x2(v[0] * sq, v[1] * sq);
-            out.y = pack_bf16x2(v[2] * sq, v[3] * sq);
-            *(u32x2*)(p.S + (int64_t)(rt.row_start + row) * p.r + cb * 16 + 4 * (lane >> 4)) = out;
-        }
+    for (int rb = 0; rb < RB; ++rb) {
+        const int row = rb * 16 + (l & 15);
+        xrow[rb] = p.X + (int64_t)(rt.row_start + min(row, rt.rows - 1)) * p.K;
+        rk[rb] = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.local_row0 + row));
     }
+    f32x4 acc[RB][CB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    constexpr int D = CB == 1 ? 4 : 2;
+    const int nchunks = p.K / 32, nst = (nchunks + DOWN_PARTS - 1) / DOWN_PARTS;
+    struct Regs { u32x4 x[RB], a[CB]; } ring[D];
+    int st = (int)(((unsigned)(rt.local_row0 / 32) * 5u) % (unsigned)nst), st_load = st;      // as in down_kernel
+    auto advance = [&](int& t) { t = t + 1 == nst ? 0 : t + 1; };
+    auto load = [&](Regs& c) {                            // (a part past K is never used)
+        const int chunk = st_load * DOWN_PARTS + w, col = chunk * 32 + 8 * (l >> 4);
+        advance(st_load);
+        if (chunk >= nchunks) return;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) c.x[rb] = *(const u32x4*)(xrow[rb] + col);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+            if (CB == 1 || cb < cbn) c.a[cb] = *(const u32x4*)(Ag + (int64_t)(cb * 16) * p.K + col);
+    };
+    auto consume = [&](const Regs& c) {
+        const int chunk = st * DOWN_PARTS + w;
+        advance(st);
+        if (chunk >= nchunks) return;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const u32x4 x = T ? mask8(c.x[rb], rk[rb], (uint32_t)(chunk * 32 + 8 * (l >> 4)), th) : c.x[rb];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                if (CB == 1 || cb < cbn)
+                    acc[rb][cb] = LF_MFMA(__builtin_bit_cast(bf16x8, c.a[cb]), __builtin_bit_cast(bf16x8, x), acc[rb][cb]);
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (d < nst) load(ring[d]);
+    for (int s = 0; s < nst; s += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (s + d < nst) {
+                consume(ring[d]);
+                if (s + d + D < nst) load(ring[d]);
+            }
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) red[((w * RB + rb) * CB + cb) * 64 + l] = acc[rb][cb];
+    __syncthreads();
+    down_store<CB, RB, 64 * DOWN_PARTS>(p, rt, red);
 }
 
 template <class C>
@@ -206,6 +287,15 @@ static hipError_t launch_down_cfg(const DownArgs& a, int tiles, hipStream_t st) 
     });
 }
 
+template <int CB, int RB>
+static hipError_t launch_down_direct(const DownArgs& a, int tiles, hipStream_t st) {
+    return with_few(a, [&](const auto& b) {
+        constexpr auto kernel = down_direct_kernel<CB, RB, std::decay_t<decltype(b.tb)>>;
+        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(64 * DOWN_PARTS), 0, st, b);
+        return hipGetLastError();
+    });
+}
+
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
     int tiles32 = 0, tiles16 = 0;
     for (int g = 0; g < a.tb.G; ++g) {
@@ -217,9 +307,24 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
     // A 16-row workgroup takes 0.6 - 0.75 of a 32-row one's time (its copies of A serve half as many rows), so it is the
     // faster one exactly while all of them run at once: K = 14336, r = 64: 4096 rows 38 against 43 us, 5003 rows 65
     // against 43 us; r = 16: 26 against 37 and 36 against 36 us.
-    const bool small = forced ? forced == 128 : tiles16 <= kComputeUnits;
+    const bool one_round = tiles16 <= kComputeUnits, many = tiles32 > kComputeUnits;
+    const bool small = forced ? forced == 128 : one_round;
+    // Short contractions: a ring of one or two stages has nothing to run ahead of, and its LDS leaves room for one or two
+    // workgroups on a compute unit, which tells when they come in several rounds (us, direct / ring): K = 64, r = 64: 5000
+    // rows 3.8 / 5.2, 100000 rows 21 / 49; K = 256: r = 16 1000 rows 3.4 / 3.8, r = 64 16384 rows 7.0 / 9.9; K = 512, r = 64:
+    // 5000 rows 6.6 / 6.3, 40000 rows 19 / 23; K = 768: r = 32 40000 rows 18 / 20, r = 16 16384 rows 8.2 / 7.7.
+    const int direct_up_to = !many ? 320 : a.r == 32 && tiles32 > 2 * kComputeUnits ? 768 : 512;
+    if (a.K <= direct_up_to) {
+        if (a.r == 16) return small ? launch_down_direct<1, 1>(a, tiles16, st) : launch_down_direct<1, 2>(a, tiles32, st);
+        if (a.r == 32) return small ? launch_down_direct<2, 1>(a, tiles16, st) : launch_down_direct<2, 2>(a, tiles32, st);
+        if (a.r == 64) return small ? launch_down_direct<4, 1>(a, tiles16, st) : launch_down_direct<4, 2>(a, tiles32, st);
+        return hipErrorInvalidValue;
+    }
+    // r = 32: two of the 16-row workgroups fit on a compute unit, one of the 32-row ones (16 waves); in several rounds
+    // that is worth more than the second reading of A up to K = 2048 (40000 rows: K = 1024 23 / 27 us, K = 4096 69 / 68 us).
+    const bool small32 = forced ? forced == 128 : one_round || (many && a.K <= 2048);
     if (a.r == 16) return small ? launch_down_cfg<Down<1, 1, 1, 5>>(a, tiles16, st) : launch_down_cfg<Down<1, 2, 1, 3>>(a, tiles32, st);
-    if (a.r == 32) return small ? launch_down_cfg<Down<2, 1, 1, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 2, 2, 4>>(a, tiles32, st);
+    if (a.r == 32) return small32 ? launch_down_cfg<Down<2, 1, 1, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 2, 2, 4>>(a, tiles32, st);
     if (a.r == 64) return small ? launch_down_cfg<Down<4, 1, 1, 4>>(a, tiles16, st) : launch_down_cfg<Down<4, 2, 2, 3>>(a, tiles32, st);
     return hipErrorInvalidValue;
 }

@@ -4,8 +4,9 @@ allocated one, no dropout, gradients written by the kernel itself and through pa
 import pytest
 import torch
 
+import oracle
 from paper_2510_00206_amd import binding, workloads
-from gpu_util import compare, f64, rel_err, run_gpu, run_oracle
+from gpu_util import TOL, compare, f64, rel_err, run_gpu, run_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -35,6 +36,35 @@ def test_down_projection_and_da(K, N, r, p, lens):
     assert torch.equal(auto["S"], planes["S"])     # same order of summation in (1)
     # (4): fp32 sums of the same products in another order; 1e-5 of the largest element as in test_kernel_heights_agree
     assert rel_err(auto["dA"], f64(planes["dA"])) <= 1e-5
+
+
+# K, r, rows of the long segment: (1) loads fragments straight into registers for short contractions, the shorter the fewer
+# rows there are, and goes through LDS otherwise; the batch and its short segments by themselves lie on both sides of that rule
+MIXED_ROUTES = [(320, 16, 700), (384, 64, 700), (512, 16, 8200), (512, 64, 8200), (448, 32, 8200), (576, 32, 8200), (768, 32, 16400),
+                (704, 16, 16400), (1024, 32, 8200)]
+
+
+@pytest.mark.parametrize("K,r,rows", MIXED_ROUTES, ids=lambda v: str(v))
+def test_down_projection_same_bits_by_every_route(K, r, rows):
+    L = workloads.custom_layer(rows + 373, K, 64, r, 1.5, 0.1, seg_lens=(rows, 40, 333), cfg=73)
+    print(f"(1) by every route {L}", flush=True)
+    inp = workloads.make_inputs(L)
+    X, W, A, B, _ = (t.cuda() for t in inp)
+    s, p, o = [L.s] * L.G, [0.1, 0.0, 0.5], L.seg_offsets
+    _, S = binding.multi_lora_fwd(X, W, A, B, o, s, p, L.seeds)
+    one = [binding.lora_fwd(X[o[g]:o[g + 1]], W, A[g], B[g], s[g], p[g], L.seeds[g])[1] for g in range(L.G)]
+    by_height = []
+    try:
+        for height in (128, 256):
+            binding.lora_set_row_tile(height)
+            by_height.append(binding.multi_lora_fwd(X, W, A, B, o, s, p, L.seeds)[1])
+    finally:
+        binding.lora_set_row_tile(0)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat(one), S) and all(torch.equal(h, S) for h in by_height)
+    for g in range(L.G):
+        Sg = oracle.lora_fwd(f64(inp[0][o[g]:o[g + 1]]), f64(inp[1]), f64(inp[2][g]), f64(inp[3][g]), s[g], p[g], L.seeds[g])[1]
+        assert rel_err(S[o[g]:o[g + 1]], s[g] * Sg) <= TOL
 
 
 @pytest.mark.parametrize("rows", [0, 256], ids=["whole", "planes"])
