@@ -963,10 +963,14 @@ constexpr TileCost kLargeCost[kLargeKinds] = {{6.0f, {1.36f, 2.72f}}, {6.0f, {1.
 constexpr TileCost kRingCost[kRingKinds] = {{5.5f, {0.82f, 1.64f}}, {5.5f, {0.47f, 0.94f}}, {4.0f, {0.30f, 0.57f}},
                                             {4.0f, {0.18f, 0.34f}}, {4.0f, {0.14f, 0.25f}}, {4.0f, {0.275f, 0.62f}}};
 
-static double launch_cost(const TileCost& c, int64_t tiles, int64_t slabs) {
+// A workgroup starts with a walk over the adapters, which a further round on a compute unit waits for in part (64 adapters x
+// 192 rows, 256 -> 256: 384 tiles of 64 x 128 18.0 us, 256 of 128 x 128 13.6; 64 x 8 rows, 4096 -> 1024: 1024 tiles of 32 x 64
+// 49.8, 512 of 64 x 128 45.0).
+static double launch_cost(const TileCost& c, int64_t tiles, int64_t slabs, int adapters) {
     const int64_t n = (tiles + kComputeUnits - 1) / kComputeUnits;
     const double fill = tiles >= kComputeUnits ? 1.0 : 0.75 + 0.25 * (double)tiles / kComputeUnits;
-    return c.fixed + (double)slabs * fill * ((double)(n / 2) * c.us[1] + (double)(n & 1) * c.us[0]) + 1.0 * (double)(n - 1);
+    return c.fixed + (double)slabs * fill * ((double)(n / 2) * c.us[1] + (double)(n & 1) * c.us[0]) +
+           (1.0 + 0.03 * (adapters - 1)) * (double)(n - 1);
 }
 
 // How one GEMM is launched: one part, or two launches that share the rows.  kind -1 - i: large tiles of kLargeRows[i] rows
@@ -984,7 +988,7 @@ static GemmPlan plan_gemm(const AdapterTable& tb, int M, int kc, int nc, int r, 
         return count_row_tiles(tb, rows_of(kind), lo);
     };
     auto columns = [&](int kind) { const int w = kind < 0 ? 256 : kRingTiles[kind][1]; return (int64_t)(nc + w - 1) / w; };
-    auto cost_of = [&](int kind, int64_t tiles) { return launch_cost(kind < 0 ? kLargeCost[-1 - kind] : kRingCost[kind], tiles, slabs); };
+    auto cost_of = [&](int kind, int64_t tiles) { return launch_cost(kind < 0 ? kLargeCost[-1 - kind] : kRingCost[kind], tiles, slabs, tb.G); };
     const int only = forced == 256 ? -1 : 0;         // (the knob fixes the 256-row tiles, or 128 x 256)
     double cost = 1e30;
     for (int k = forced ? only : -kLargeKinds; k < (forced ? only + 1 : kRingKinds); ++k) {
