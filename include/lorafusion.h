@@ -171,11 +171,24 @@ lora_status lora_set_slab_lookahead(int32_t slabs);
 
 /* Diagnostic (host only, nothing is enqueued): the row-panel height the streaming reduction of operation
  * (3) (Section 5.1) would choose for an activation of C columns over these segments under the current
- * lora_set_row_tile setting, the number of panels that gives (each leaves one fp32 plane of partial dB or dA
- * in the workspace), and the number of planes lora_bwd_workspace_bytes provides for.  seg_offsets: host,
+ * lora_set_row_tile setting, the number of panels that gives (each leaves one fp32 plane of partial dB in the workspace), and the number of planes lora_bwd_workspace_bytes provides for.  seg_offsets: host,
  * G+1 entries rising from 0 to M. */
 lora_status lora_debug_stream_panels(int64_t M, int64_t C, int32_t G, const int64_t* seg_offsets,
                                      int32_t* panel_rows, int64_t* panels, int64_t* panels_bound);
+
+/* Diagnostic (host only): how operation (4) would cut its rows for an input of K columns over these segments.  *panel_rows = 0:
+ * one panel per segment, dA written by the kernel itself, no planes; otherwise panels of that height, *panels planes in the
+ * workspace.  panels_bound as in lora_debug_stream_panels. */
+lora_status lora_debug_da_panels(int64_t M, int64_t K, int32_t G, const int64_t* seg_offsets,
+                                 int32_t* panel_rows, int64_t* panels, int64_t* panels_bound);
+
+/* Diagnostic (host only): the output tiles that a GEMM over `contraction` elements to `columns` columns (operation (2):
+ * K, N; operation (5): N, K) would run with under the current lora_set_row_tile setting; r = 0: no LoRA term.  *parts launches
+ * (0 for M = 0, at most 2), launch i with tiles of tile_rows[i] x tile_columns[i] from row first_row[i] on; each array has
+ * two entries.  256 and 192 x 256 are the large tiles, everything else the small ones. */
+lora_status lora_debug_gemm_tiles(int64_t M, int64_t contraction, int64_t columns, int32_t r, int32_t G,
+                                  const int64_t* seg_offsets, int32_t* parts, int32_t* tile_rows, int32_t* tile_columns,
+                                  int64_t* first_row);
 
 /* Diagnostic per-kernel timing for benchmarks.  Between lora_profile_begin() and
  * lora_profile_end() every kernel the entry points above enqueue is bracketed by a pair of HIP

@@ -19,6 +19,7 @@ LIB_PATH = os.path.join(_HERE, "liblorafusion_hip.so")
 EXPORTS = ("lora_fwd", "lora_bwd", "lora_bwd_noalloc", "multi_lora_fwd", "multi_lora_bwd", "multi_lora_fwd_ranked",
            "multi_lora_bwd_ranked", "lora_bwd_workspace_bytes",
            "lora_debug_mask", "lora_status_string", "lora_version", "lora_set_row_tile", "lora_set_slab_lookahead", "lora_debug_stream_panels",
+           "lora_debug_da_panels", "lora_debug_gemm_tiles",
            "lora_unfused_fwd", "lora_unfused_bwd", "lora_unfused_workspace_bytes")
 
 _lib = None
@@ -63,6 +64,12 @@ def load_library() -> C.CDLL:
     lib.lora_frozen_bwd.restype = C.c_int
     lib.lora_unfused_fwd.restype = C.c_int
     lib.lora_unfused_bwd.restype = C.c_int
+    lib.lora_debug_gemm_tiles.argtypes = [I64, I64, I64, I32, I32, C.POINTER(I64), C.POINTER(I32), C.POINTER(I32),
+                                          C.POINTER(I32), C.POINTER(I64)]
+    lib.lora_debug_gemm_tiles.restype = C.c_int
+    for f in ("lora_debug_stream_panels", "lora_debug_da_panels"):
+        getattr(lib, f).argtypes = [I64, I64, I32, C.POINTER(I64), C.POINTER(I32), C.POINTER(I64), C.POINTER(I64)]
+        getattr(lib, f).restype = C.c_int
     lib.lora_profile_end.argtypes = [C.POINTER(F), C.POINTER(I32)]
     lib.lora_ceiling_mfma.argtypes = [P, P, I32, I32, I32, C.POINTER(C.c_double), P]
     lib.lora_ceiling_mfma.restype = C.c_int
@@ -200,6 +207,15 @@ def lora_debug_mask(M, K, p, seed, device="cuda"):
     keep = torch.empty((M, K), dtype=torch.uint8, device=device)
     _check(load_library().lora_debug_mask(M, K, p, seed, _ptr(keep), _stream()))
     return keep
+
+
+def lora_debug_gemm_tiles(contraction, columns, r, seg_offsets):
+    """[(tile rows, tile columns, first row)] of the one or two launches of a GEMM over these segments (host only)."""
+    G = len(seg_offsets) - 1
+    parts, rows, cols, first = C.c_int32(), (C.c_int32 * 2)(), (C.c_int32 * 2)(), (C.c_int64 * 2)()
+    _check(load_library().lora_debug_gemm_tiles(seg_offsets[-1], contraction, columns, r, G, _arr(C.c_int64, seg_offsets),
+                                                C.byref(parts), rows, cols, first))
+    return [(rows[i], cols[i], first[i]) for i in range(parts.value)]
 
 
 def lora_set_row_tile(rows: int):

@@ -60,6 +60,19 @@ lora_status build_table(AdapterTable& tb, int64_t M, int32_t r, int32_t G, const
     return LORA_OK;
 }
 
+// A table that knows the segments only, for the diagnostics of what a launch would choose over C columns.
+lora_status segments_only(AdapterTable& tb, int64_t M, int64_t C, int32_t G, const int64_t* off) {
+    if (M < 0 || C <= 0 || M >= (1ll << 31) || C >= (1ll << 31) || G < 1) return LORA_ERR_SHAPE;
+    if (G > kMaxAdapters) return LORA_ERR_UNSUPPORTED;
+    memset(&tb, 0, sizeof(tb));
+    tb.G = G;
+    if (off[0] != 0 || off[G] != M) return LORA_ERR_SEGMENTS;
+    for (int g = 0; g < G; ++g)
+        if (off[g + 1] < off[g]) return LORA_ERR_SEGMENTS;
+    for (int g = 0; g <= G; ++g) tb.row0[g] = (int)off[g];
+    return LORA_OK;
+}
+
 // Optional per-kernel timing (diagnostic): HIP events bracket every launch on the caller's stream.
 struct ProfRec { hipEvent_t beg, end; int id; };
 bool g_prof_on = false;
@@ -302,18 +315,44 @@ lora_status lora_debug_mask(int64_t M, int64_t K, float p, uint64_t seed, uint8_
 lora_status lora_debug_stream_panels(int64_t M, int64_t C, int32_t G, const int64_t* seg_offsets,
                                      int32_t* panel_rows, int64_t* panels, int64_t* panels_bound) {
     if (!seg_offsets || !panel_rows || !panels || !panels_bound) return LORA_ERR_NULL;
-    if (M < 0 || C <= 0 || M >= (1ll << 31) || C >= (1ll << 31) || G < 1) return LORA_ERR_SHAPE;
-    if (G > kMaxAdapters) return LORA_ERR_UNSUPPORTED;
     AdapterTable tb;
-    memset(&tb, 0, sizeof(tb));
-    tb.G = G;
-    if (seg_offsets[0] != 0 || seg_offsets[G] != M) return LORA_ERR_SEGMENTS;
-    for (int g = 0; g < G; ++g)
-        if (seg_offsets[g + 1] < seg_offsets[g]) return LORA_ERR_SEGMENTS;
-    for (int g = 0; g <= G; ++g) tb.row0[g] = (int)seg_offsets[g];
+    const lora_status st = segments_only(tb, M, C, G, seg_offsets);
+    if (st != LORA_OK) return st;
     *panel_rows = stream_panel_rows(tb, (int)C, forced_row_tile());
     *panels = count_panels(tb, *panel_rows);
     *panels_bound = max_stream_panels(M, G);
+    return LORA_OK;
+}
+
+lora_status lora_debug_da_panels(int64_t M, int64_t K, int32_t G, const int64_t* seg_offsets,
+                                 int32_t* panel_rows, int64_t* panels, int64_t* panels_bound) {
+    if (!seg_offsets || !panel_rows || !panels || !panels_bound) return LORA_ERR_NULL;
+    AdapterTable tb;
+    const lora_status st = segments_only(tb, M, K, G, seg_offsets);
+    if (st != LORA_OK) return st;
+    const DaPlan pl = plan_da(tb, (int)K, forced_row_tile());
+    *panel_rows = pl.direct ? 0 : pl.rows;
+    *panels = pl.direct ? 0 : count_panels(tb, pl.rows);
+    *panels_bound = max_stream_panels(M, G);
+    return LORA_OK;
+}
+
+lora_status lora_debug_gemm_tiles(int64_t M, int64_t contraction, int64_t columns, int32_t r, int32_t G,
+                                  const int64_t* seg_offsets, int32_t* parts, int32_t* tile_rows, int32_t* tile_columns,
+                                  int64_t* first_row) {
+    if (!seg_offsets || !parts || !tile_rows || !tile_columns || !first_row) return LORA_ERR_NULL;
+    lora_status st = check_shape(M, contraction, columns, r ? r : 16, G);
+    if (st != LORA_OK) return st;
+    AdapterTable tb;
+    st = segments_only(tb, M, contraction, G, seg_offsets);
+    if (st != LORA_OK) return st;
+    GemmTile t[2];
+    *parts = gemm_tiles(tb, (int)M, (int)contraction, (int)columns, r, forced_row_tile(), t);
+    for (int i = 0; i < *parts; ++i) {
+        tile_rows[i] = t[i].rows;
+        tile_columns[i] = t[i].columns;
+        first_row[i] = t[i].first_row;
+    }
     return LORA_OK;
 }
 

@@ -1020,6 +1020,16 @@ static GemmPlan plan_gemm(const AdapterTable& tb, int M, int kc, int nc, int r, 
     return best;
 }
 
+int gemm_tiles(const AdapterTable& tb, int M, int contraction, int columns, int r, int forced, GemmTile (&out)[2]) {
+    const GemmPlan t = plan_gemm(tb, M, contraction, columns, r, forced);
+    for (int i = 0; i < t.parts; ++i) {
+        const int k = t.part[i].kind;
+        out[i] = k < 0 ? GemmTile{kLargeRows[-1 - k], BN, t.part[i].row_lo}
+                       : GemmTile{kRingTiles[k][0], kRingTiles[k][1], t.part[i].row_lo};
+    }
+    return t.parts;
+}
+
 // `persistent`: one workgroup per compute unit walks the tiles (fewer workgroups if there are fewer tiles)
 template <typename K, typename A>
 static hipError_t launch_gemm(K kernel, bool& attr_set, const A& a, hipStream_t st, int lds_bytes = GEMM_LDS_BYTES,

@@ -185,6 +185,11 @@ hipError_t launch_da(const DaArgs& a, hipStream_t st);
 hipError_t launch_finalize_ds_db(const FinalizeArgs& a, hipStream_t st);
 hipError_t launch_finalize_da(const FinalizeArgs& a, hipStream_t st);
 hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st);
+
+// The output tiles of a GEMM's one or two launches (returns how many), as launch_fwd_gemm and launch_bwd_dx choose them.
+struct GemmTile { int rows, columns, first_row; };
+int gemm_tiles(const AdapterTable& tb, int M, int contraction, int columns, int r, int forced, GemmTile (&out)[2]);
+
 hipError_t launch_debug_mask(int64_t M, int64_t K, uint32_t T, uint32_t k0, uint32_t k1, uint8_t* keep,
                              hipStream_t st);
 

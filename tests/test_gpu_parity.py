@@ -17,8 +17,9 @@ def _lib(request):
     """Every test of this module runs with the large and with the small height of the kernels that
     have two (GEMM tiles of 256 / 128 rows, down-projection workgroups of 32 / 16 rows) fixed: small
     shapes would otherwise all take the small one; and with the GEMMs' slab copies one and two slabs ahead
-    (small weights would otherwise never take the second in operation (5)).  The automatic choices are what
-    the full-size tests run."""
+    (small weights would otherwise never take the second in operation (5); the 128-row tiles have one distance, so
+    tile128-ahead2 runs the GEMMs of tile128-ahead1).  The automatic choices are what the full-size tests and
+    test_gpu_small_tiles.py run."""
     assert torch.cuda.is_available(), "GPU tests need a GPU"
     binding.load_library()          # raises if the HIP library is not built: no fallback
     binding.lora_set_row_tile(request.param[0])

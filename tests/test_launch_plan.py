@@ -1,0 +1,100 @@
+"""Host logic: what the launches would choose, asked of the library without a GPU.  The GEMM tests name the tiles that each of
+their sizes stands for; operation (4) never cuts more panels than the workspace provides planes for."""
+import ctypes as C
+import os
+import random
+
+import pytest
+
+from paper_2510_00206_amd import binding
+from test_gpu_small_tiles import PLANS, POISON_PLANS
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    if not os.path.exists(binding.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
+    binding.load_library()
+    yield
+    binding.lora_set_row_tile(0)
+
+
+def _offsets(lens):
+    off = [0]
+    for n in lens:
+        off.append(off[-1] + n)
+    return off
+
+
+def _name(tiles):
+    return "+".join(f"{r}x{c}" + (f"@{first}" if first else "") for r, c, first in tiles)
+
+
+@pytest.mark.parametrize("case", list(PLANS) + list(POISON_PLANS), ids=lambda c: "x".join(map(str, c[:3] + c[3])))
+def test_gemm_cases_take_the_tiles_they_stand_for(case):
+    K, N, r, lens = case[:4]
+    off = _offsets(lens)
+    assert (_name(binding.lora_debug_gemm_tiles(K, N, r, off)), _name(binding.lora_debug_gemm_tiles(N, K, r, off))) == \
+        (PLANS.get(case) or POISON_PLANS.get(case))
+
+
+@pytest.mark.parametrize("plans", [PLANS, POISON_PLANS], ids=["values", "poison"])
+def test_gemm_cases_cover_every_tile_both_ways(plans):
+    small = {"32x64", "64x64", "128x64", "64x128", "128x128"}
+    for way in (0, 1):
+        names = [v[way] for v in plans.values()]
+        first = {n.split("+")[0] for n in names}
+        assert small | {"192x256", "256x256"} <= first and any("+" in n for n in names), (way, first)
+        assert plans is POISON_PLANS or "128x256" in first
+
+
+def test_row_tile_setting_fixes_the_tiles():
+    for rows in (128, 256):
+        binding.lora_set_row_tile(rows)
+        assert all(_name(binding.lora_debug_gemm_tiles(K, N, r, _offsets(lens))) == f"{rows}x256" for K, N, r, lens in PLANS)
+    binding.lora_set_row_tile(0)
+
+
+def _panels(lens, height):
+    return sum(n // height or (n > 0) for n in lens)
+
+
+def test_da_planes_stay_within_the_workspace():
+    """Planes of operation (4): at most what the workspace provides, and at most what the limit of the allocation-free
+    backward counts (a plane per panel of the largest height of 1024 .. 64, 256 with the large heights fixed, that gives about
+    one workgroup of 512 columns per compute unit)."""
+    rnd = random.Random(7)
+    lib = binding.load_library()
+    rows, panels, bound = C.c_int32(), C.c_int64(), C.c_int64()
+    seen = set()
+    for it in range(2000):
+        G = rnd.randint(1, 64) if it % 3 else rnd.randint(1, 3)
+        top = rnd.choice((130, 1000, 6000, 40000))
+        lens = [rnd.randrange(top) if it % 2 else 64 * rnd.randrange(top // 64 + 1) for _ in range(G)]
+        if sum(lens) == 0:
+            lens[0] = 1
+        off = (C.c_int64 * (G + 1))(*_offsets(lens))
+        for setting in (0, 128, 256):
+            binding.lora_set_row_tile(setting)
+            for K in (64, 512, 4096, 14336, 28672):
+                assert lib.lora_debug_da_panels(sum(lens), K, G, off, C.byref(rows), C.byref(panels), C.byref(bound)) == 0
+                h, chunks = 1024, (K + 511) // 512
+                while h > (256 if setting == 256 else 64) and _panels(lens, h) * chunks < 224:
+                    h //= 2
+                assert panels.value == (_panels(lens, rows.value) if rows.value else 0)
+                assert panels.value <= min(bound.value, _panels(lens, h)), (lens, K, setting, rows.value)
+                assert rows.value == 0 or rows.value >= 256
+                seen.add((setting, rows.value == 0))
+    assert seen == {(0, True), (0, False), (128, True), (128, False), (256, False)}
+
+
+def test_diagnostics_refuse_what_the_entry_points_refuse():
+    off = (C.c_int64 * 2)(0, 64)
+    f = lambda M, k, c, r, G, o: binding.load_library().lora_debug_gemm_tiles(
+        M, k, c, r, G, o, C.byref(C.c_int32()), (C.c_int32 * 2)(), (C.c_int32 * 2)(), (C.c_int64 * 2)())
+    assert [f(64, 64, 64, 0, 1, off), f(64, 64, 64, 16, 1, None), f(64, 0, 64, 16, 1, off), f(64, 96, 64, 16, 1, off),
+            f(64, 64, 64, 8, 1, off), f(128, 64, 64, 16, 1, off), f(64, 64, 64, 16, 65, off)] == [0, 1, 2, 7, 7, 5, 7]
+    g = lambda M, K, G, o: binding.load_library().lora_debug_da_panels(
+        M, K, G, o, C.byref(C.c_int32()), C.byref(C.c_int64()), C.byref(C.c_int64()))
+    assert [g(64, 64, 1, off), g(64, 64, 1, None), g(-1, 64, 1, off), g(128, 64, 1, off), g(64, 64, 65, off)] == [0, 1, 2, 5, 7]
