@@ -155,7 +155,7 @@ lora_status lora_debug_mask(int64_t M, int64_t K, float p, uint64_t seed, uint8_
  * panels of 1024 down to 64 rows, and operation (4) with whole segments or row panels of 256 rows and more.
  * By default every launch picks the height that fills the chip better (the small ones for short batches and
  * narrow projections; a GEMM may take two launches of different heights).  rows = 256 fixes the large height
- * of the GEMMs and of (1), panels of at least 256 rows in (3) and of 256 in (4) for all later calls, rows = 128
+ * of the GEMMs and of (1) and panels of at least 256 rows in (3) and (4) for all later calls, rows = 128
  * GEMM tiles of 128 rows x 256 columns and the small height of (1), rows = 0 restores the automatic choice;
  * any other value returns LORA_ERR_PARAM.  Y, S_saved and dX are bit-identical under all three settings; dA
  * and dB are fp32 sums over the row panels and agree up to the order of those sums. */
@@ -195,14 +195,15 @@ lora_status lora_debug_gemm_tiles(int64_t M, int64_t contraction, int64_t column
  * events on the caller's stream (the events are created by the library: do not use inside graph
  * capture).  lora_profile_end() waits for the recorded events, adds the elapsed milliseconds and
  * the launch count of each kernel into ms_total / launches (host arrays of LORA_PROF_KERNELS
- * entries, indexed by lora_prof_kernel) and switches timing off.  Not thread safe. */
+ * entries, indexed by lora_prof_kernel) and switches timing off.  A GEMM that takes two launches counts as
+ * one, from the start of the first to the end of the second.  Not thread safe. */
 typedef enum {
     LORA_PROF_DOWN = 0,       /* operation (1): dropout + down-projection            */
     LORA_PROF_FWD_GEMM = 1,   /* operation (2): Y = X W + S' B                        */
     LORA_PROF_DS_DB = 2,      /* operation (3): dS and dB partials from one dY pass   */
     LORA_PROF_FIN_DS_DB = 3,  /* fixed-order reduction of the dS / dB partials        */
-    LORA_PROF_DA = 4,         /* operation (4): dA partials from one X pass           */
-    LORA_PROF_FIN_DA = 5,     /* fixed-order reduction of the dA partials             */
+    LORA_PROF_DA = 4,         /* operation (4): dA, or its partials, from one X pass  */
+    LORA_PROF_FIN_DA = 5,     /* fixed-order reduction of the dA partials, if any     */
     LORA_PROF_DX_GEMM = 6,    /* operation (5): dX = dY W^T + mask*q*(dS A^T)         */
     LORA_PROF_KERNELS = 7
 } lora_prof_kernel;

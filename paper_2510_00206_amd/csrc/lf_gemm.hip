@@ -955,8 +955,9 @@ int forced_row_tile() { return g_forced_row_tile.load(std::memory_order_relaxed)
 // takes the compute unit with the most tiles.  us[0] is that time for one tile on every compute unit, us[1] for two
 // of the small tiles sharing one (measured at K = N = 4096, 64 to 4096 rows; two of the large ones run one after the
 // other).  With few tiles the operands reach them faster: down to three quarters of it.
-// At 4096 x 4096 the family meets at about 300 rows (64 x 64 / 64 x 128 tiles), 700 (64 x 128 / 128 x 128), 1100
-// (128 x 128 / 128 x 256) and 2300 (128 x 256 / 256 x 256).
+// At 4096 x 4096, one adapter, r = 16, the table gives 32 x 64 tiles up to 128 rows, 64 x 64 up to 256, 128 x 64 up to 512,
+// 128 x 128 up to 1024 (then with a second launch for the rest of the rows), 128 x 256 from 1217, 192 x 256 from 2049 and
+// 256 x 256 from 3169 (192 x 256 again from 5121); 64 x 128 comes in with other widths.
 struct TileCost { float fixed, us[2]; };
 constexpr int kLargeKinds = 2, kLargeRows[kLargeKinds] = {256, 192};      // x 256 columns
 constexpr TileCost kLargeCost[kLargeKinds] = {{6.0f, {1.36f, 2.72f}}, {6.0f, {1.06f, 2.12f}}};

@@ -13,9 +13,9 @@
 // read one sub-step ahead, eight waves where the tile has work for them, and two workgroups on a compute unit for the
 // tiles whose ring leaves room.  Accumulators are vector registers, the MFMAs assembly (see ring_mfma): the compiler's
 // own moved every accumulator block in every step (M = 1024, 4096 x 4096: 40 -> 35 us).
-// Measured, one launch, against the 128-row tiles that served these sizes before: 256 x 1024 x 1024 15.4 -> 7.4 us
-// forward, 15.9 -> 7.5 us backward; 1024 x 4096 x 4096 53 -> 34 and 61 -> 36 us; 77 rows, 4096 -> 14336 51 -> 23 and
-// (backward) 172 -> 41 us; 64 rows, 15616 -> 320 176 -> 34 us.
+// Measured, one launch, against the 128-row tiles that served these sizes before: 256 x 1024 x 1024 16 -> 6.1 us
+// forward, 22 -> 6.7 us backward; 1024 x 4096 x 4096 56 -> 35 and 66 -> 39 us; 77 rows, 4096 -> 14336 51 -> 24 and
+// (backward) 174 -> 41 us; 64 rows, 15616 -> 320 176 -> 33 us.
 #include <type_traits>
 
 #include "lf_device.h"

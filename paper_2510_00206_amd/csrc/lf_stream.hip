@@ -10,7 +10,7 @@
 
 namespace lf {
 
-constexpr int ST_THREADS = 512, ST_WAVES = 8;
+constexpr int ST_THREADS = 512;
 constexpr int ST_STEP = 32;                        // rows per step
 constexpr int ST_BIG_BYTES = ST_STEP * kStreamChunk * 2;   // 32 KB
 

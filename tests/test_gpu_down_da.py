@@ -28,7 +28,7 @@ def test_down_projection_and_da(K, N, r, p, lens):
     inp = workloads.make_inputs(L)
     auto = run_gpu(L, *inp)
     compare(auto, run_oracle(L, *inp), label=f"(1) (4) {K} {N} {r} {p} {lens}")
-    binding.lora_set_row_tile(256)                 # 32-row workgroups in (1), 256-row panels and partial planes in (4)
+    binding.lora_set_row_tile(256)                 # 32-row workgroups in (1), panels of 256 rows and more and partial planes in (4)
     try:
         planes = run_gpu(L, *inp)
     finally:
