@@ -177,7 +177,7 @@ lora_status lora_debug_stream_panels(int64_t M, int64_t C, int32_t G, const int6
                                      int32_t* panel_rows, int64_t* panels, int64_t* panels_bound);
 
 /* Diagnostic (host only): how operation (4) would cut its rows for an input of K columns over these segments.  *panel_rows = 0:
- * one panel per segment, dA written by the kernel itself, no planes; otherwise panels of that height, *panels planes in the
+ * one panel per segment, no partial sums; otherwise panels of that height, *panels fp32 partial sums in the
  * workspace.  panels_bound as in lora_debug_stream_panels. */
 lora_status lora_debug_da_panels(int64_t M, int64_t K, int32_t G, const int64_t* seg_offsets,
                                  int32_t* panel_rows, int64_t* panels, int64_t* panels_bound);
@@ -200,9 +200,9 @@ lora_status lora_debug_gemm_tiles(int64_t M, int64_t contraction, int64_t column
 typedef enum {
     LORA_PROF_DOWN = 0,       /* operation (1): dropout + down-projection            */
     LORA_PROF_FWD_GEMM = 1,   /* operation (2): Y = X W + S' B                        */
-    LORA_PROF_DS_DB = 2,      /* operation (3): dS and dB partials from one dY pass   */
+    LORA_PROF_DS_DB = 2,      /* operation (3): dS and dB partials, or dS by itself   */
     LORA_PROF_FIN_DS_DB = 3,  /* fixed-order reduction of the dS / dB partials        */
-    LORA_PROF_DA = 4,         /* operation (4): dA, or its partials, from one X pass  */
+    LORA_PROF_DA = 4,         /* operation (4); dB too where (3) formed dS by itself   */
     LORA_PROF_FIN_DA = 5,     /* fixed-order reduction of the dA partials, if any     */
     LORA_PROF_DX_GEMM = 6,    /* operation (5): dX = dY W^T + mask*q*(dS A^T)         */
     LORA_PROF_KERNELS = 7

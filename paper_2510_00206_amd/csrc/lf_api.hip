@@ -91,15 +91,34 @@ hipError_t timed(int id, hipStream_t st, F&& launch) {
     return e != hipSuccess ? e : e2;
 }
 
+// What one backward call launches with: the knob is read once and the panel heights are chosen here, for the launches that
+// leave partial sums and for those that add them, so that a change of the knob by another thread in the middle of a call
+// cannot make the two disagree.
+struct BwdPlan {
+    int forced;
+    bool split;                // dS by itself, dB beside (4)
+    int rows_db, rows_da;      // panel heights (0: whole segments, no partial sums)
+};
+
+BwdPlan plan_bwd(const AdapterTable& tb, int64_t M, int64_t K, int64_t N) {
+    BwdPlan pl;
+    pl.forced = forced_row_tile();
+    pl.split = split_ds_db((int)M, (int)N, (int)K, pl.forced);
+    pl.rows_da = plan_da(tb, (int)K, pl.forced);
+    pl.rows_db = pl.split ? plan_db(tb, (int)N, (int)K, pl.rows_da) : stream_panel_rows(tb, (int)N, pl.forced);
+    return pl;
+}
+
 struct Workspace {
     lora_bf16* dS; float* part_ds; float* part_db; float* part_da; size_t bytes;
+    uint32_t* counters;        // NULL: no room (finalize_da adds the planes)
+    int n_counters;
 };
 
 // planes_db / planes_da: fp32 planes of dB / dA partials to provide for (one per row panel)
-Workspace carve(void* base, int64_t M, int64_t K, int64_t N, int32_t r, int64_t planes_db, int64_t planes_da) {
-    const int64_t chunks = (N + kStreamChunk - 1) / kStreamChunk;
+Workspace carve(void* base, int64_t M, int64_t K, int64_t N, int32_t r, int64_t planes_db, int64_t planes_da, int64_t chunks) {
     size_t off = 0;
-    Workspace w;
+    Workspace w{};
     char* b = (char*)base;
     w.dS = (lora_bf16*)(b + off);      off += align_up((size_t)M * r * 2);
     w.part_ds = (float*)(b + off);     off += align_up((size_t)chunks * M * r * 4);
@@ -109,24 +128,27 @@ Workspace carve(void* base, int64_t M, int64_t K, int64_t N, int32_t r, int64_t 
     return w;
 }
 
+int64_t stream_chunks(int64_t N) { return (N + kStreamChunk - 1) / kStreamChunk; }
+
 // The caller-provided workspace is sized before the call's panel heights are known: for the most panels
 // any launch over M rows in G segments can choose.
-Workspace carve(void* base, int64_t M, int64_t K, int64_t N, int32_t r, int32_t G) {
+size_t workspace_bytes_of(int64_t M, int64_t K, int64_t N, int32_t r, int32_t G) {
     const int64_t tiles = max_stream_panels(M, G);
-    return carve(base, M, K, N, r, tiles, tiles);
+    return carve(nullptr, M, K, N, r, tiles, tiles, stream_chunks(N)).bytes;
 }
 
-// What one backward call launches with: the knob is read once and the panel heights are chosen here, for
-// the streaming launches and for the finalize launches that add their partial planes, so that a change
-// of the knob by another thread in the middle of a call cannot make the two disagree.
-struct BwdPlan { int forced, rows_db; DaPlan da; };
-
-BwdPlan plan_bwd(const AdapterTable& tb, int64_t K, int64_t N) {
-    BwdPlan pl;
-    pl.forced = forced_row_tile();
-    pl.rows_db = stream_panel_rows(tb, (int)N, pl.forced);
-    pl.da = plan_da(tb, (int)K, pl.forced);
-    return pl;
+// What a call lays out in `bytes` of it: the planes that its launches write, and behind them the counters of the strips.
+Workspace lay_out(void* base, size_t bytes, int64_t M, int64_t K, int64_t N, int32_t r, const AdapterTable& tb, BwdPlan& pl) {
+    Workspace w = carve(base, M, K, N, r, pl.rows_db ? count_panels(tb, pl.rows_db) : 0,
+                        pl.rows_da ? count_panels(tb, pl.rows_da) : 0, pl.split ? 0 : stream_chunks(N));
+    const int64_t n = tb.G * ((pl.rows_da ? K / 64 : 0) + (pl.split && pl.rows_db ? N / 64 : 0));
+    if (n && w.bytes + (size_t)n * 4 <= bytes) {
+        w.counters = (uint32_t*)((char*)base + w.bytes);
+        w.n_counters = (int)n;
+    } else if (pl.split) {
+        pl.rows_db = 0;        // (nothing else would add the pieces of dB)
+    }
+    return w;
 }
 
 lora_status fwd_impl(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A, const lora_bf16* B,
@@ -144,21 +166,28 @@ lora_status bwd_impl(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A,
                      const lora_bf16* S, const lora_bf16* dY, int64_t M, int64_t K, int64_t N, int32_t r,
                      const AdapterTable& tb, lora_bf16* dX, float* dA, float* dB, int accumulate,
                      const Workspace& ws, const BwdPlan& pl, hipStream_t st) {
-    const int chunks = (int)((N + kStreamChunk - 1) / kStreamChunk);
-    const int forced = pl.forced, rows_db = pl.rows_db;
-    StreamArgs s3{dY, S, B, ws.part_db, ws.part_ds, (int)M, (int)N, r, 0, 0, rows_db, tb};
-    if (timed(LORA_PROF_DS_DB, st, [&] { return launch_stream_dsdb(s3, st); }) != hipSuccess) return LORA_ERR_HIP;
+    const int chunks = (int)stream_chunks(N);
     FinalizeArgs fin{ws.part_ds, ws.dS, ws.part_db, dB, ws.part_da, dA,
-                     (int)M, (int)K, (int)N, r, chunks, accumulate, rows_db, pl.da.rows, tb};
-    if (timed(LORA_PROF_FIN_DS_DB, st, [&] { return launch_finalize_ds_db(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
+                     (int)M, (int)K, (int)N, r, chunks, accumulate, pl.rows_db, pl.rows_da, ws.counters, ws.n_counters, tb};
+    if (pl.split) {
+        DsArgs s3{dY, B, ws.dS, ws.counters, ws.n_counters, (int)M, (int)N, r, tb};
+        if (timed(LORA_PROF_DS_DB, st, [&] { return launch_ds(s3, st); }) != hipSuccess) return LORA_ERR_HIP;
+    } else {
+        StreamArgs s3{dY, S, B, ws.part_db, ws.part_ds, (int)M, (int)N, r, 0, 0, pl.rows_db, tb};
+        if (timed(LORA_PROF_DS_DB, st, [&] { return launch_stream_dsdb(s3, st); }) != hipSuccess) return LORA_ERR_HIP;
+        if (timed(LORA_PROF_FIN_DS_DB, st, [&] { return launch_finalize_ds_db(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
+    }
     // (5) right after (3): it re-reads dY while that pass's copy still sits in the memory-side cache
     if (dX) {
         DxGemmArgs g5{dY, W, ws.dS, A, dX, (int)M, (int)K, (int)N, r, 0, 0, 0, tb};
-        if (timed(LORA_PROF_DX_GEMM, st, [&] { return launch_bwd_dx(g5, forced, st); }) != hipSuccess) return LORA_ERR_HIP;
+        if (timed(LORA_PROF_DX_GEMM, st, [&] { return launch_bwd_dx(g5, pl.forced, st); }) != hipSuccess) return LORA_ERR_HIP;
     }
-    DaArgs d4{X, ws.dS, ws.part_da, dA, (int)M, (int)K, r, pl.da.rows, pl.da.direct, accumulate, tb};
-    if (timed(LORA_PROF_DA, st, [&] { return launch_da(d4, st); }) != hipSuccess) return LORA_ERR_HIP;
-    if (!pl.da.direct && timed(LORA_PROF_FIN_DA, st, [&] { return launch_finalize_da(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
+    StripArgs s4{{X, ws.dS, dA, ws.part_da, ws.counters, (int)K, pl.rows_da, 0, 0}, {}, 0, r, accumulate, tb};
+    if (pl.split)
+        s4.b = StripJob{dY, S, dB, ws.part_db, ws.counters + (pl.rows_da ? tb.G * (K / 64) : 0), (int)N, pl.rows_db, 0, 0};
+    if (timed(LORA_PROF_DA, st, [&] { return launch_strips(s4, st); }) != hipSuccess) return LORA_ERR_HIP;
+    if (pl.rows_da && !ws.counters &&
+        timed(LORA_PROF_FIN_DA, st, [&] { return launch_finalize_da(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
     return LORA_OK;
 }
 
@@ -192,7 +221,7 @@ extern "C" {
 
 size_t lora_bwd_workspace_bytes(int64_t M, int64_t K, int64_t N, int32_t r, int32_t G) {
     if (check_shape(M, K, N, r, G) != LORA_OK) return 0;
-    return carve(nullptr, M, K, N, r, G).bytes;
+    return workspace_bytes_of(M, K, N, r, G);
 }
 
 lora_status multi_lora_fwd_ranked(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A, const lora_bf16* B,
@@ -243,10 +272,12 @@ lora_status multi_lora_bwd_ranked(const lora_bf16* X, const lora_bf16* W, const 
     AdapterTable tb;
     st = build_table(tb, M, r, G, seg_offsets, s, p, seeds, ranks);
     if (st != LORA_OK) return st;
-    const Workspace ws = carve(workspace, M, K, N, r, G);
-    if (workspace_bytes < ws.bytes) return LORA_ERR_WORKSPACE;
-    return bwd_impl(X, W, A, B, S_saved, dY, M, K, N, r, tb, dX, dA, dB, accumulate, ws, plan_bwd(tb, K, N),
-                    (hipStream_t)stream);
+    const size_t need = workspace_bytes_of(M, K, N, r, G);
+    if (workspace_bytes < need) return LORA_ERR_WORKSPACE;
+    BwdPlan pl = plan_bwd(tb, M, K, N);
+    const Workspace ws = lay_out(workspace, need, M, K, N, r, tb, pl);
+    return bwd_impl(X, W, A, B, S_saved, dY, M, K, N, r, tb, dX, dA, dB, accumulate,
+                    ws, pl, (hipStream_t)stream);
 }
 
 lora_status multi_lora_bwd(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A, const lora_bf16* B,
@@ -286,18 +317,17 @@ lora_status lora_bwd_noalloc(const lora_bf16* X, const lora_bf16* W, const lora_
     if (st != LORA_OK) return st;
     // The limit goes by the most panels of these sizes (fill_panel_rows), so that it does not move with the launches'
     // choice of taller ones; the planes laid out are exactly those that this call's launches will write.
-    const BwdPlan pl = plan_bwd(tb, K, N);
+    BwdPlan pl = plan_bwd(tb, M, K, N);
     if (carve(nullptr, M, K, N, r, count_panels(tb, fill_panel_rows(tb, (int)N, pl.forced)),
-              count_panels(tb, fill_panel_rows(tb, (int)K, pl.forced))).bytes > (size_t)LORA_NOALLOC_SCRATCH_BYTES)
+              count_panels(tb, fill_panel_rows(tb, (int)K, pl.forced)), stream_chunks(N)).bytes > (size_t)LORA_NOALLOC_SCRATCH_BYTES)
         return LORA_ERR_WORKSPACE;
-    const int64_t planes_db = count_panels(tb, pl.rows_db), planes_da = pl.da.direct ? 0 : count_panels(tb, pl.da.rows);
     void* base = nullptr;
     st = scratch_of_current_device(&base);
     if (st != LORA_OK) return st;
     // Nothing in the scratch has to start at zero: every partial plane and every dS element that a
     // later kernel of this call reads is written by an earlier kernel of this call.
-    return bwd_impl(X, W, A, B, S_saved, dY, M, K, N, r, tb, dX, dA, dB, accumulate,
-                    carve(base, M, K, N, r, planes_db, planes_da), pl, (hipStream_t)stream);
+    const Workspace ws = lay_out(base, (size_t)LORA_NOALLOC_SCRATCH_BYTES, M, K, N, r, tb, pl);
+    return bwd_impl(X, W, A, B, S_saved, dY, M, K, N, r, tb, dX, dA, dB, accumulate, ws, pl, (hipStream_t)stream);
 }
 
 lora_status lora_debug_mask(int64_t M, int64_t K, float p, uint64_t seed, uint8_t* keep, lora_stream stream) {
@@ -330,9 +360,8 @@ lora_status lora_debug_da_panels(int64_t M, int64_t K, int32_t G, const int64_t*
     AdapterTable tb;
     const lora_status st = segments_only(tb, M, K, G, seg_offsets);
     if (st != LORA_OK) return st;
-    const DaPlan pl = plan_da(tb, (int)K, forced_row_tile());
-    *panel_rows = pl.direct ? 0 : pl.rows;
-    *panels = pl.direct ? 0 : count_panels(tb, pl.rows);
+    *panel_rows = plan_da(tb, (int)K, forced_row_tile());
+    *panels = *panel_rows ? count_panels(tb, *panel_rows) : 0;
     *panels_bound = max_stream_panels(M, G);
     return LORA_OK;
 }

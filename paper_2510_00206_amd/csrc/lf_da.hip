@@ -1,11 +1,17 @@
-// Operation (4) of the fused LoRA linear layer (Section 5.1, FusedLoRA Design), one pass over X with the mask
-// regenerated:
+// Sums over the rows of an activation, in strips of 64 columns.  Operation (4) of the fused LoRA linear layer (Section 5.1,
+// FusedLoRA Design), one pass over X with the mask regenerated:
 //     dA[c,j] = q sum_i keep(i,j) X[i,j] dS[i,c]          (dS arrives scaled by s*q)
+// and, beside it in the same launch, the dB half of operation (3) where dS has been formed by itself (lf_ds.hip):
+//     dB[n,c] = sum_i dY[i,n] S'[i,c]
 // A workgroup owns a strip of 64 columns (one 128-byte line of every row) over a panel of rows; each of its eight waves
 // walks the 32-row blocks w, w + 8, ... of the panel by itself: global -> registers two blocks ahead, mask, LDS of the
-// wave's own, transposing reads, 16x16x32 bf16 MFMAs.  No barrier until the waves' sums are added, in a fixed order.
-// A panel is a whole segment where that leaves the chip enough workgroups (the sum is then dA itself); otherwise the
-// panels leave fp32 partial planes that finalize_da_kernel adds in a fixed order.  Repeated runs agree bit for bit.
+// wave's own, transposing reads, 16x16x32 bf16 MFMAs.  No barrier until the waves' sums are added, pairwise.
+// A panel is a whole segment where that leaves the chip enough workgroups (the sum is then the gradient itself); otherwise the
+// panels leave fp32 pieces that the last workgroup of the strip adds in a fixed order (plan_strips).  Repeated runs
+// agree bit for bit.
+// What bounds it: the mask of dA (about 0.85 us of a compute unit per 256 rows x 64 columns; 13 vector instructions a
+// column pair), then memory.  (3) and (4) in two launches instead of four, us: 256 x 1024 x 1024, r = 16 12.2 -> 7.6; 1531 x 4096 ->
+// 1024 in three segments, r = 64 29 -> 16.4; 2999 x 4096 x 4096, r = 32 37 -> 29; 2048 x 4096 x 4096, r = 16 22 -> 18.6.
 #include "lf_device.h"
 #include "lf_internal.h"
 
@@ -23,24 +29,58 @@ __device__ __forceinline__ int da_x_off(int row, int chunk) {
     return row * 128 + ((chunk ^ ((row & 2) | ((row & 8) >> 1))) << 4);
 }
 
-template <int CB, class TB>                        // r / 16
-__global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgsOf<TB> p) {
-    constexpr int R = CB * 16, RCH = CB * 2;       // rank, 16-byte chunks per dS row
+// Partial sums of a strip meet in the last of its workgroups: every workgroup leaves an fp32 piece of R x 64, counts itself in,
+// and the one that finds all others there adds the pieces in the order of the panels (segment_planes).  The pieces are
+// written and read with agent-scope atomic stores and loads, which go past the XCDs' own L2s; a store has arrived there when
+// the wave's vmcnt counts it, so that no cache has to be written back or invalidated around the counter (a release and an
+// acquire fence instead, which do that, cost 2048 x 4096, r = 16, 256 workgroups 40 us).
+__device__ __forceinline__ void store_piece(f32x4* p, f32x4 v) {
+    const float a = v[0], b = v[1], c = v[2], d = v[3];
+    uint64_t* q = (uint64_t*)p;
+    __hip_atomic_store(q, (uint64_t)__builtin_bit_cast(uint32_t, a) | (uint64_t)__builtin_bit_cast(uint32_t, b) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q + 1, (uint64_t)__builtin_bit_cast(uint32_t, c) | (uint64_t)__builtin_bit_cast(uint32_t, d) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x4 load_piece(const f32x4* p) {
+    const uint64_t* q = (const uint64_t*)p;
+    const uint64_t lo = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return f32x4{__builtin_bit_cast(float, (uint32_t)lo), __builtin_bit_cast(float, (uint32_t)(lo >> 32)),
+                 __builtin_bit_cast(float, (uint32_t)hi), __builtin_bit_cast(float, (uint32_t)(hi >> 32))};
+}
+__device__ __forceinline__ bool last_of_strip(uint32_t* counter, uint32_t panels, uint32_t* flag) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's piece has arrived ...
+    __syncthreads();                                      // ... and every wave's
+    if (threadIdx.x == 0) *flag = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == panels;
+    __syncthreads();
+    return *flag != 0;
+}
+
+// One workgroup of a strip job.  MASKED: dA [r, C] of operation (4); otherwise dB [C, r] of operation (3).
+template <int CB, bool MASKED, class TB>
+__device__ __forceinline__ void strip_body(const StripArgsOf<TB>& p, const StripJob& job, int block, char* smem) {
+    constexpr int R = CB * 16, RCH = CB * 2;       // rank, 16-byte chunks per dS (S') row
     constexpr int WAVE_LDS = DA_BLOCK * (DA_STRIP + R) * 2;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int strips = p.K / DA_STRIP;
-    const int tile = blockIdx.x / strips, c0 = (blockIdx.x - tile * strips) * DA_STRIP;
+    const int strips = job.C / DA_STRIP;
+    const int tile = block / strips, strip = block - tile * strips, c0 = strip * DA_STRIP;
     RowTile rt;
-    if (p.direct) {                                // panel = segment, empty ones too (their gradient is zero)
+    if (job.panel_rows == 0) {                     // panel = segment, empty ones too (their gradient is zero)
         rt.g = tile;
         rt.row_start = p.tb.row0[tile];
         rt.rows = p.tb.row0[tile + 1] - rt.row_start;
         rt.local_row0 = 0;
-        if (rt.rows == 0 && p.accumulate) return;
-    } else if (!find_panel(p.tb, p.panel_rows, tile, rt)) return;
+    } else if (tile < job.panels) {
+        find_panel(p.tb, job.panel_rows, tile, rt);
+    } else {                                       // no panel cuts an empty segment: one workgroup each writes its zeros
+        int n = tile - job.panels;
+        rt.g = 0;
+        while (p.tb.row0[rt.g] != p.tb.row0[rt.g + 1] || n-- > 0) ++rt.g;
+        rt.row_start = p.tb.row0[rt.g];
+        rt.rows = rt.local_row0 = 0;
+    }
+    if (rt.rows == 0 && p.accumulate) return;
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = rt.g, cbn = p.tb.a[g].rank >> 4;
-    const uint32_t T = p.tb.a[g].T, hk0 = p.tb.a[g].k0, hk1 = p.tb.a[g].k1;
+    const uint32_t T = MASKED ? p.tb.a[g].T : 0u, hk0 = p.tb.a[g].k0, hk1 = p.tb.a[g].k1;
     const KeepThreshold th = keep_threshold(T);
     char* lds_x = smem + w * WAVE_LDS;
     char* lds_s = lds_x + DA_BLOCK * DA_STRIP * 2;
@@ -51,15 +91,15 @@ __global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgsO
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[jb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const lora_bf16* X = p.X + (int64_t)rt.row_start * p.K + c0 + (l & 7) * 8;
-    const lora_bf16* dS = p.dS + (int64_t)rt.row_start * R;
+    const lora_bf16* X = job.big + (int64_t)rt.row_start * job.C + c0 + (l & 7) * 8;
+    const lora_bf16* dS = job.small_ + (int64_t)rt.row_start * R;
     const int nblocks = (rt.rows + DA_BLOCK - 1) / DA_BLOCK;
     // lane l holds rows 8*i + (l >> 3), chunk l & 7 of a block; dS rows as they lie in memory, 1 KB per register
     struct Regs { u32x4 x[4], s[CB]; };
     auto load = [&](Regs& r, int blk) {            // (rows past the end read the last one: never used)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            r.x[i] = *(const u32x4*)(X + (int64_t)min(blk * DA_BLOCK + 8 * i + (l >> 3), rt.rows - 1) * p.K);
+            r.x[i] = *(const u32x4*)(X + (int64_t)min(blk * DA_BLOCK + 8 * i + (l >> 3), rt.rows - 1) * job.C);
 #pragma unroll
         for (int i = 0; i < CB; ++i) {
             const int e = i * 64 + l;
@@ -71,7 +111,7 @@ __global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgsO
         for (int i = 0; i < 4; ++i) {
             const int row = 8 * i + (l >> 3), prow = blk * DA_BLOCK + row;
             u32x4 v = r.x[i];
-            if (T) v = mask8(v, row_key(hk0, hk1, (uint32_t)(rt.local_row0 + prow)), (uint32_t)(c0 + (l & 7) * 8), th);
+            if (MASKED && T) v = mask8(v, row_key(hk0, hk1, (uint32_t)(rt.local_row0 + prow)), (uint32_t)(c0 + (l & 7) * 8), th);
             if (prow >= rt.rows) v = u32x4{0u, 0u, 0u, 0u};
             *(u32x4*)(lds_x + da_x_off(row, l & 7)) = v;
         }
@@ -94,7 +134,8 @@ __global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgsO
             const bf16x8 fb = join_tr(lds_read_tr(lds_x, o), lds_read_tr(lds_x, o + 4 * 128));   // (row + 4: same swizzle)
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
-                if (CB == 1 || cb < cbn) acc[jb][cb] = LF_MFMA16(fb, fs[cb], acc[jb][cb]);       // D[j][c]
+                if (CB == 1 || cb < cbn)           // D[j][c], resp. D[c][n]: four consecutive elements of the output to a lane
+                    acc[jb][cb] = MASKED ? LF_MFMA16(fb, fs[cb], acc[jb][cb]) : LF_MFMA16(fs[cb], fb, acc[jb][cb]);
         }
     };
     if (w < nblocks) {
@@ -114,9 +155,21 @@ __global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgsO
         }
     }
 
-    // fixed-order sum over the waves, one 16-row block of dA at a time; plane layout [c][j]
+    // Where the sum goes: the gradient itself if this workgroup has the whole segment, else a piece for the last workgroup of
+    // the strip (counters), or a plane for finalize_da_kernel.
+    int reg0 = 0, nreg = 1, extra = -1;
+    if (job.panel_rows && rt.rows) segment_planes(p.tb, job.panel_rows, g, reg0, nreg, extra);
+    const int panels = nreg + (extra >= 0);
+    const bool whole = job.panel_rows == 0 || (job.counters && panels == 1) || rt.rows == 0;
+    f32x4* piece = (f32x4*)(job.part + ((int64_t)tile * strips + strip) * (R * DA_STRIP));
+    float* grad = job.out + (int64_t)g * R * job.C;
+    auto grad_at = [&](int cb, int jb) {
+        return (f32x4*)(MASKED ? grad + (int64_t)(cb * 16 + (l & 15)) * job.C + c0 + jb * 16 + 4 * (l >> 4)
+                               : grad + (int64_t)(c0 + jb * 16 + (l & 15)) * R + cb * 16 + 4 * (l >> 4));
+    };
+
+    // fixed-order sum over the waves, one 16-column block of the rank at a time
     f32x4* red = (f32x4*)smem;                     // [DA_WAVES][4][64]
-    float* out = p.direct ? p.dA + (int64_t)g * R * p.K : p.part + (int64_t)tile * R * p.K;
     for (int cb = 0; cb < CB; ++cb) {
         __syncthreads();
 #pragma unroll
@@ -129,40 +182,86 @@ __global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) da_kernel(DaArgsO
         }
         __syncthreads();
         if (threadIdx.x < 256) {
-            const int jb = threadIdx.x >> 6;
-            f32x4 v = red[threadIdx.x];
+            f32x4 v[DA_WAVES];
 #pragma unroll
-            for (int ww = 1; ww < DA_WAVES; ++ww) v += red[ww * 256 + threadIdx.x];
-            f32x4* o = (f32x4*)(out + (int64_t)(cb * 16 + (l & 15)) * p.K + c0 + jb * 16 + 4 * (l >> 4));
-            *o = p.direct && p.accumulate ? *o + v : v;
+            for (int ww = 0; ww < DA_WAVES; ++ww) v[ww] = red[ww * 256 + threadIdx.x];
+#pragma unroll
+            for (int d = 1; d < DA_WAVES; d *= 2)  // pairwise: the smaller rounding error
+#pragma unroll
+                for (int ww = 0; ww < DA_WAVES; ww += 2 * d) v[ww] += v[ww + d];
+            if (whole) {
+                f32x4* o = grad_at(cb, threadIdx.x >> 6);
+                *o = p.accumulate ? *o + v[0] : v[0];
+            } else if (job.counters) {
+                store_piece(piece + cb * 256 + threadIdx.x, v[0]);
+            } else {
+                *(f32x4*)(job.part + (int64_t)tile * R * job.C + (grad_at(cb, threadIdx.x >> 6) - (f32x4*)grad) * 4) = v[0];
+            }
         }
+    }
+    if (whole || !job.counters) return;
+    __syncthreads();                               // (the flag lies where the waves' sums were)
+    if (!last_of_strip(job.counters + g * strips + strip, panels, (uint32_t*)smem)) return;
+    const int64_t pitch = (int64_t)strips * (R * DA_STRIP / 4);
+    const f32x4* first = (const f32x4*)job.part + (int64_t)strip * (R * DA_STRIP / 4);
+    for (int i = threadIdx.x; i < CB * 256; i += DA_THREADS) {
+        f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+        for (int t = reg0; t < reg0 + nreg; ++t) v += load_piece(first + t * pitch + i);
+        if (extra >= 0) v += load_piece(first + extra * pitch + i);
+        f32x4* o = grad_at(i >> 8, (i >> 6) & 3);
+        *o = p.accumulate ? *o + v : v;
     }
 }
 
+template <int CB, class TB>                        // r / 16
+__global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) strip_kernel(StripArgsOf<TB> p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int first = p.b_first ? p.b.blocks : p.a.blocks, block = blockIdx.x;
+    if ((block < first) != (p.b_first != 0)) strip_body<CB, true>(p, p.a, p.b_first ? block - first : block, smem);
+    else strip_body<CB, false>(p, p.b, p.b_first ? block : block - first, smem);
+}
+
+// Workgroups of a job: strips x (panels, and with counters the empty segments).
+static void plan_job(const AdapterTable& tb, StripJob& job) {
+    job.blocks = 0;
+    if (!job.big && !job.out) return;
+    int tiles = tb.G;
+    if (job.panel_rows) {
+        tiles = job.panels = count_panels(tb, job.panel_rows);
+        if (job.counters)
+            for (int g = 0; g < tb.G; ++g) tiles += tb.row0[g] == tb.row0[g + 1];
+    }
+    job.blocks = tiles * (job.C / DA_STRIP);
+}
+
 template <int CB>
-static hipError_t launch_da_t(const DaArgs& a, hipStream_t st) {
-    const int lds = DA_WAVES * DA_BLOCK * (DA_STRIP + CB * 16) * 2;
-    const int panels = a.direct ? a.tb.G : count_panels(a.tb, a.panel_rows);
-    if (panels == 0) return hipSuccess;
+static hipError_t launch_strips_t(const StripArgs& a, hipStream_t st) {
+    constexpr int lds = DA_WAVES * DA_BLOCK * (DA_STRIP + CB * 16) * 2;
+    if (a.a.blocks + a.b.blocks == 0) return hipSuccess;
     return with_few(a, [&](const auto& b) {
-        constexpr auto kernel = da_kernel<CB, std::decay_t<decltype(b.tb)>>;
+        constexpr auto kernel = strip_kernel<CB, std::decay_t<decltype(b.tb)>>;
         static bool attr_set = false;              // one flag per instantiation
         if (!attr_set) {
             hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
             attr_set = true;
         }
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((int64_t)panels * (a.K / DA_STRIP))), dim3(DA_THREADS), lds, st, b);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(b.a.blocks + b.b.blocks)), dim3(DA_THREADS), lds, st, b);
         return hipGetLastError();
     });
 }
 
-hipError_t launch_da(const DaArgs& a, hipStream_t st) {
-    if (!a.direct && a.panel_rows < DA_BLOCK) return hipErrorInvalidValue;
+hipError_t launch_strips(StripArgs a, hipStream_t st) {
+    if ((a.a.panel_rows && a.a.panel_rows < DA_BLOCK) || (a.b.panel_rows && a.b.panel_rows < DA_BLOCK)) return hipErrorInvalidValue;
+    plan_job(a.tb, a.a);
+    plan_job(a.tb, a.b);
+    a.b_first = a.b.blocks && kDbBlock * longest_panel(a.tb, a.b.panel_rows ? a.b.panel_rows : 1 << 30) >
+                                  kDaBlock * longest_panel(a.tb, a.a.panel_rows ? a.a.panel_rows : 1 << 30);
     switch (a.r) {
-        case 16: return launch_da_t<1>(a, st);
-        case 32: return launch_da_t<2>(a, st);
-        case 64: return launch_da_t<4>(a, st);
+        case 16: return launch_strips_t<1>(a, st);
+        case 32: return launch_strips_t<2>(a, st);
+        case 64: return launch_strips_t<4>(a, st);
     }
     return hipErrorInvalidValue;
 }

@@ -44,19 +44,36 @@ struct StreamArgsOf {
 };
 using StreamArgs = StreamArgsOf<AdapterTable>;
 
-// Operation (4) (lf_da.hip).
+// dS by itself (lf_ds.hip); the launch also clears `n_zero` words for the counters of the strips that follow.
 template <class TB>
-struct DaArgsOf {
-    const lora_bf16* X; const lora_bf16* dS;
-    float* part;               // fp32 planes [panels, r, K] (not direct)
-    float* dA;                 // [G, r, K] (direct)
-    int M, K, r;
-    int panel_rows;            // rows per panel (not direct)
-    int direct;                // one panel per segment, dA written (or added to) by the kernel itself
-    int accumulate;
+struct DsArgsOf {
+    const lora_bf16* dY; const lora_bf16* Bmat; lora_bf16* dS;
+    uint32_t* zero;
+    int n_zero;
+    int M, C, r;               // C = N
     TB tb;
 };
-using DaArgs = DaArgsOf<AdapterTable>;
+using DsArgs = DsArgsOf<AdapterTable>;
+
+// Operation (4), and dB by itself (lf_da.hip): sums over the rows of a [M, C] activation in strips of 64 columns.
+struct StripJob {
+    const lora_bf16* big;      // X for dA, dY for dB
+    const lora_bf16* small_;   // dS, resp. S'
+    float* out;                // dA [G, r, C], resp. dB [G, C, r]; NULL: no such job
+    float* part;               // fp32 partial sums of the panels (not whole segments)
+    uint32_t* counters;        // [G, C / 64], zero, for the sum over the panels; NULL: `part` holds planes [panels] for finalize_da
+    int C;
+    int panel_rows;            // 0: one panel per segment
+    int panels, blocks;        // set by the launcher
+};
+template <class TB>
+struct StripArgsOf {
+    StripJob a, b;             // dA, dB
+    int b_first;               // set by the launcher: the job whose workgroups run longest starts first
+    int r, accumulate;
+    TB tb;
+};
+using StripArgs = StripArgsOf<AdapterTable>;
 
 // Reductions of the partials.
 template <class TB>
@@ -66,6 +83,7 @@ struct FinalizeArgsOf {
     const float* part_da; float* dA;            // dA[g,c,j] (+)= q_g * sum over the row tiles of segment g
     int M, K, N, r, chunks, accumulate;
     int panel_rows_db, panel_rows_da;           // the panel heights operations (3) / (4) ran with (same call, same values)
+    uint32_t* zero; int n_zero;                 // words that finalize_ds_db clears for the strips that follow
     TB tb;
 };
 using FinalizeArgs = FinalizeArgsOf<AdapterTable>;
@@ -141,28 +159,51 @@ inline int stream_panel_rows(const AdapterTable& tb, int C, int forced) {
     return best;
 }
 
-// How operation (4) cuts its rows.  A workgroup owns 64 columns of a panel and takes about 4 us + 1.3 us per 256 rows,
-// a few of them on every compute unit; panels shorter than a segment cost a finalize launch (5 us) and an fp32 plane of
-// r x K each.  `direct`: one panel per segment, no planes.  (8192 x 4096, r = 16: 2048-row panels 16.7 us, 512-row
-// panels 18.6 us, whole 43 us, as 64 workgroups; 5003 x 14336: whole 31 us, 512-row panels 34 us.)  The panels are never
-// more than fill_panel_rows gives for the same sizes, which is what the workspace provides for.
-struct DaPlan { int rows, direct; };
-inline DaPlan plan_da(const AdapterTable& tb, int K, int forced) {
-    if (forced == 256) return DaPlan{fill_panel_rows(tb, K, forced), 0};
-    const int64_t strips = K / 64;
-    auto cost = [&](int64_t panels, int longest, bool direct) {
-        const double rounds = (double)((panels * strips + kComputeUnits - 1) / kComputeUnits);
-        return 4.0 + rounds * 1.3 * (double)((longest + 255) / 256) + (direct ? 0.0 : 5.0 + 3.2e-5 * (double)(panels * K));
+// How the strips of operation (4), and of dB beside it, cut their rows.  A workgroup owns 64 columns of a panel and takes
+// about 1.3 us (dA: the mask) or 0.6 us (dB) per 256 rows, two of them on a compute unit as long as one after the other;
+// panels shorter than a segment leave an fp32 piece of r x 64 each, which the last workgroup of the strip adds: 2 us, and
+// 40 ns per panel and 1000 columns.  Height 0: whole segments, no pieces.  (dA, 8192 x 4096, r = 16: 2048-row panels 16 us, 512-row
+// panels 19 us, whole 43 us, as 64 workgroups; 5003 x 14336: whole 31 us, 512-row panels 34 us.)  The rule knows no rank, so
+// that adapters of any rank are summed alike.  The panels are never more than fill_panel_rows gives for the same
+// sizes, which is what the workspace provides for.
+constexpr int kLowestStripPanel = 512;               // (two rounds of a workgroup's eight 32-row blocks)
+struct StripLoad { double path, work; };           // us: the longest workgroup; all of them, per compute unit
+inline StripLoad strip_load(const AdapterTable& tb, int C, int rows, double us_per_block) {
+    const int64_t panels = rows ? count_panels(tb, rows) : tb.G;
+    const double t = us_per_block * (double)((longest_panel(tb, rows ? rows : 1 << 30) + 255) / 256);
+    return StripLoad{t, t * (double)(panels * (C / 64)) / kComputeUnits};
+}
+inline int plan_strips(const AdapterTable& tb, int C, double us_per_block, StripLoad beside, int highest = 1 << 30) {
+    const int longest = longest_panel(tb, 1 << 30);
+    auto cost = [&](int rows) {
+        const StripLoad l = strip_load(tb, C, rows, us_per_block);
+        const double path = l.path > beside.path ? l.path : beside.path, work = l.work + beside.work;
+        return (path > work ? path : work) + (rows ? 2.0 + 4e-5 * (double)count_panels(tb, rows) * C : 0.0);
     };
-    DaPlan best{0, 1};
-    double c = cost(tb.G, longest_panel(tb, 1 << 30), true);
-    int least = stream_panel_rows(tb, K, forced);
-    if (least < kRowTile) least = kRowTile;
-    for (int64_t h = least; h < longest_panel(tb, 1 << 30); h <<= 1) {
-        const double ch = cost(count_panels(tb, (int)h), longest_panel(tb, (int)h), false);
-        if (ch < c) { c = ch; best = DaPlan{(int)h, 0}; }
-    }
+    int best = 0, least = fill_panel_rows(tb, C, 0);
+    if (least < kLowestStripPanel) least = kLowestStripPanel;
+    for (int64_t h = least; h < longest && (h <= highest || best == 0); h <<= 1)
+        if (cost((int)h) < cost(best) || (best == 0 && longest > highest)) best = (int)h;
     return best;
+}
+constexpr double kDaBlock = 1.3, kDbBlock = 0.6;   // us per 256 rows
+inline int plan_da(const AdapterTable& tb, int K, int forced) {
+    if (forced == 256) return fill_panel_rows(tb, K, forced);
+    return plan_strips(tb, K, kDaBlock, StripLoad{0, 0});
+}
+// dB: at most 1024 rows to a panel, that no wave chains more than a few MFMAs on one sum (fp32 error against 64 bits, 2999 x 4096,
+// r = 32: whole segments 1.21e-7, the one-pass form 1.09e-7).
+inline int plan_db(const AdapterTable& tb, int N, int K, int rows_da) {
+    return plan_strips(tb, N, kDbBlock, strip_load(tb, K, rows_da, kDaBlock), 1024);
+}
+// Operation (3) as one pass over dY whose partial sums a second launch adds (lf_stream.hip), or as dS in one launch without
+// partial sums (lf_ds.hip) and dB as further strips beside (4), reading dY twice: the latter while the pass is bound by the
+// latency of its launches rather than by memory.  One workgroup sweeps all of N for dS, and the strips of (4) and dB
+// share the chip.  (3) and (4) together, us, one pass / split, K = 2048: r = 16: 64 x 256 10.4 / 7.1, 1024 x 1024 16.1 / 11.6,
+// 3000 x 4096 27.8 / 21.9, 6000 x 4096 35.8 / 34.5, 8192 x 4096 34.2 / 39.9, 64 x 8192 11.2 / 13.6; r = 64: 1024 x 4096
+// 33 / 26, 3000 x 4096 1.32 times, 64 x 6144 0.81 times; K = 8192, r = 64, 4096 x 2048: 0.93 times.
+inline bool split_ds_db(int M, int N, int K, int forced) {
+    return forced != 256 && N <= 4096 && M <= 6144 && (int64_t)M * K <= (24ll << 20);
 }
 
 // Upper bound on the number of panels (planes of dA / dB partials) of any launch over M rows in G
@@ -181,7 +222,8 @@ inline int64_t max_stream_panels(int64_t M, int G) {
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st);
 hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st);
 hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st);
-hipError_t launch_da(const DaArgs& a, hipStream_t st);
+hipError_t launch_ds(const DsArgs& a, hipStream_t st);
+hipError_t launch_strips(StripArgs a, hipStream_t st);
 hipError_t launch_finalize_ds_db(const FinalizeArgs& a, hipStream_t st);
 hipError_t launch_finalize_da(const FinalizeArgs& a, hipStream_t st);
 hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st);

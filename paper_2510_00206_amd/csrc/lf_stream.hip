@@ -256,6 +256,7 @@ hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st) {
 template <class TB>
 __global__ void __launch_bounds__(256) finalize_ds_db_kernel(FinalizeArgsOf<TB> p, int blocks_ds) {
     const int r4 = p.r >> 2;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < p.n_zero; i += gridDim.x * 256) p.zero[i] = 0;
     if ((int)blockIdx.x < blocks_ds) {
         const int64_t idx = blockIdx.x * 256ll + threadIdx.x;
         if (idx >= (int64_t)p.M * r4) return;

@@ -183,21 +183,21 @@ lora_status lora_unfused_bwd(const lora_bf16* W, const lora_bf16* A, const lora_
     const int chunks = (int)((N + kStreamChunk - 1) / kStreamChunk);
     const int forced = forced_row_tile();
     const int rows_db = stream_panel_rows(plain, (int)N, forced);
-    const DaPlan da = plan_da(plain, (int)K, forced);
+    const int rows_da = plan_da(plain, (int)K, forced);
     // 1. dY2 = s dY
     hipLaunchKernelGGL(scale_kernel, dim3(blocks_for(M * N / 8)), dim3(EW_THREADS), 0, st, dY, ws.dY2, M * N / 8, s);
     LF_LAUNCHED();
     // 2. dB = dY2^T S     3. dS = dY2 B      (one pass over dY2 each)
     LF_TRY(launch_stream_dsdb(StreamArgs{ws.dY2, ws.S, B, ws.part_db, nullptr, (int)M, (int)N, r, 0, 0, rows_db, plain}, st));
     LF_TRY(launch_finalize_ds_db(FinalizeArgs{nullptr, nullptr, ws.part_db, dB, nullptr, nullptr,
-                                              (int)M, (int)K, (int)N, r, chunks, 0, rows_db, da.rows, plain}, st));
+                                              (int)M, (int)K, (int)N, r, chunks, 0, rows_db, rows_da, nullptr, 0, plain}, st));
     LF_TRY(launch_stream_dsdb(StreamArgs{ws.dY2, ws.S, B, nullptr, ws.part_ds, (int)M, (int)N, r, 0, 0, rows_db, plain}, st));
     LF_TRY(launch_finalize_ds_db(FinalizeArgs{ws.part_ds, ws.dS, nullptr, nullptr, nullptr, nullptr,
-                                              (int)M, (int)K, (int)N, r, chunks, 0, rows_db, da.rows, plain}, st));
+                                              (int)M, (int)K, (int)N, r, chunks, 0, rows_db, rows_da, nullptr, 0, plain}, st));
     // 4. dA = Xhat^T dS
-    LF_TRY(launch_da(DaArgs{ws.Xhat, ws.dS, ws.part_da, dA, (int)M, (int)K, r, da.rows, da.direct, 0, plain}, st));
-    if (!da.direct) LF_TRY(launch_finalize_da(FinalizeArgs{nullptr, nullptr, nullptr, nullptr, ws.part_da, dA,
-                                           (int)M, (int)K, (int)N, r, chunks, 0, rows_db, da.rows, plain}, st));
+    LF_TRY(launch_strips(StripArgs{{ws.Xhat, ws.dS, dA, ws.part_da, nullptr, (int)K, rows_da, 0, 0}, {}, 0, r, 0, plain}, st));
+    if (rows_da) LF_TRY(launch_finalize_da(FinalizeArgs{nullptr, nullptr, nullptr, nullptr, ws.part_da, dA,
+                                           (int)M, (int)K, (int)N, r, chunks, 0, rows_db, rows_da, nullptr, 0, plain}, st));
     // 5. dXhat = dS A
     LF_TRY(launch_bwd_dx(DxGemmArgs{nullptr, nullptr, ws.dS, A, ws.dXhat, (int)M, (int)K, 0, r, 0, 0, 0, plain}, forced, st));
     // 6. dXhat = mask * q * dXhat

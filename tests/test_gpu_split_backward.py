@@ -1,0 +1,68 @@
+"""Operation (3) in its two forms: dS by itself with dB as further strips beside (4) (batches of up to 6144 rows, N <= 4096), and one
+pass over dY with partial sums (the large heights fixed).  Sizes at the edges of the 16-row workgroups, the 256- and 512-column
+stages, the 64-column strips and the panels whose sums meet in the last workgroup of a strip."""
+import pytest
+import torch
+
+from paper_2510_00206_amd import binding, workloads
+from gpu_util import compare, f64, rel_err, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+# K, N, r, segments
+CASES = [
+    (64, 64, 16, (1,)),
+    (128, 320, 64, (15, 16, 17)),
+    (192, 512, 32, (33, 0, 31)),
+    (64, 576, 16, (100, 64)),
+    (128, 832, 64, (48, 5)),
+    (64, 4096, 64, (40,)),
+    (64, 4160, 16, (40,)),                         # past the rule: the same route both times
+    (192, 1088, 16, (2600, 0, 700)),               # panels of 512 rows with a remainder, an empty segment, a segment of one panel
+    (320, 576, 64, (1536, 1024)),                  # whole panels
+    (64, 64, 32, (6143,)),
+    (64, 64, 32, (6145,)),
+]
+
+
+@pytest.mark.parametrize("K,N,r,lens", CASES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_both_forms(K, N, r, lens):
+    L = workloads.custom_layer(sum(lens), K, N, r, 1.5, 0.1, seg_lens=lens, cfg=91)
+    print(f"both forms of (3) {L}", flush=True)
+    inp = workloads.make_inputs(L)
+    auto = run_gpu(L, *inp)
+    compare(auto, run_oracle(L, *inp), label=f"(3) {K} {N} {r} {lens}")
+    binding.lora_set_row_tile(256)
+    try:
+        one_pass = run_gpu(L, *inp)
+    finally:
+        binding.lora_set_row_tile(0)
+    assert torch.equal(auto["dX"], one_pass["dX"])         # dS is the same bits, and with it dX
+    for name in ("dA", "dB"):                              # fp32 sums of the same products in another order: as in test_kernel_heights_agree
+        assert rel_err(auto[name], f64(one_pass[name])) <= 1e-5
+
+
+@pytest.mark.parametrize("lens,ranks", [((2600, 0, 700), (64, 16, 32)), ((300, 20), (16, 64))], ids=["panels", "whole"])
+def test_counters_ranks_and_accumulation(lens, ranks):
+    """Whatever the workspace holds, two calls give the same bits; accumulate adds those; padding and empty segments are zeros."""
+    L = workloads.custom_layer(sum(lens), 192, 320, 64, 1.0, 0.1, seg_lens=lens, cfg=92)
+    print(f"counters {L}", flush=True)
+    X, W, A, B, dY = (t.cuda() for t in workloads.make_inputs(L))
+    s, p, o = [L.s] * L.G, [L.p] * L.G, L.seg_offsets
+    _, S = binding.multi_lora_fwd(X, W, A, B, o, s, p, L.seeds, ranks=ranks)
+    ws = binding.alloc_workspace(L.M, L.K, L.N, L.r, L.G)
+    outs = []
+    for fill in (0, 255):
+        ws.fill_(fill)
+        outs.append(binding.multi_lora_bwd(X, W, A, B, S, dY, o, s, p, L.seeds, workspace=ws, ranks=ranks))
+    base = [torch.randn_like(t) for t in outs[0][1:]]
+    got = [t.clone() for t in base]
+    ws.fill_(170)
+    binding.multi_lora_bwd(X, W, A, B, S, dY, o, s, p, L.seeds, need_dx=False, dA=got[0], dB=got[1], accumulate=True, workspace=ws, ranks=ranks)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    assert all(torch.equal(g, b + t) for g, b, t in zip(got, base, outs[0][1:]))
+    for g in range(L.G):
+        assert not outs[0][1][g, ranks[g]:].any() and not outs[0][2][g, :, ranks[g]:].any()
+        if o[g] == o[g + 1]:
+            assert not outs[0][1][g].any() and not outs[0][2][g].any()
