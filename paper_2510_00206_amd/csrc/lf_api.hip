@@ -111,7 +111,7 @@ BwdPlan plan_bwd(const AdapterTable& tb, int64_t M, int64_t K, int64_t N) {
 
 struct Workspace {
     lora_bf16* dS; float* part_ds; float* part_db; float* part_da; size_t bytes;
-    uint32_t* counters;        // NULL: no room (finalize_da adds the planes)
+    uint32_t* counters;        // NULL: finalize_da adds the planes
     int n_counters;
 };
 

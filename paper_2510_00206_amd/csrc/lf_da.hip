@@ -31,21 +31,19 @@ __device__ __forceinline__ int da_x_off(int row, int chunk) {
 
 // Partial sums of a strip meet in the last of its workgroups: every workgroup leaves an fp32 piece of R x 64, counts itself in,
 // and the one that finds all others there adds the pieces in the order of the panels (segment_planes).  The pieces are
-// written and read with agent-scope atomic stores and loads, which go past the XCDs' own L2s; a store has arrived there when
-// the wave's vmcnt counts it, so that no cache has to be written back or invalidated around the counter (a release and an
-// acquire fence instead, which do that, cost 2048 x 4096, r = 16, 256 workgroups 40 us).
-__device__ __forceinline__ void store_piece(f32x4* p, f32x4 v) {
-    const float a = v[0], b = v[1], c = v[2], d = v[3];
-    uint64_t* q = (uint64_t*)p;
-    __hip_atomic_store(q, (uint64_t)__builtin_bit_cast(uint32_t, a) | (uint64_t)__builtin_bit_cast(uint32_t, b) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(q + 1, (uint64_t)__builtin_bit_cast(uint32_t, c) | (uint64_t)__builtin_bit_cast(uint32_t, d) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// written and read past the XCDs' own L2s (sc1, as agent-scope atomic stores and loads are, sixteen bytes at a time); a store has
+// arrived when the wave's vmcnt counts it, so that no cache has to be written back or invalidated around the counter (a
+// release and an acquire fence instead, which do that, cost 2048 x 4096, r = 16, 256 workgroups 40 us).
+constexpr int kPastL2 = 16;                        // cache policy bits of a buffer access: sc1
+typedef __attribute__((__vector_size__(16))) uint32_t buffer_u32x4;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t piece_of(float* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x27000);
 }
-__device__ __forceinline__ f32x4 load_piece(const f32x4* p) {
-    const uint64_t* q = (const uint64_t*)p;
-    const uint64_t lo = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return f32x4{__builtin_bit_cast(float, (uint32_t)lo), __builtin_bit_cast(float, (uint32_t)(lo >> 32)),
-                 __builtin_bit_cast(float, (uint32_t)hi), __builtin_bit_cast(float, (uint32_t)(hi >> 32))};
+__device__ __forceinline__ void store_piece(__amdgpu_buffer_rsrc_t piece, int i, f32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(buffer_u32x4, v), piece, i * 16, 0, kPastL2);
+}
+__device__ __forceinline__ f32x4 load_piece(__amdgpu_buffer_rsrc_t piece, int i) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(piece, i * 16, 0, kPastL2));
 }
 __device__ __forceinline__ bool last_of_strip(uint32_t* counter, uint32_t panels, uint32_t* flag) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's piece has arrived ...
@@ -122,6 +120,8 @@ __device__ __forceinline__ void strip_body(const StripArgsOf<TB>& p, const Strip
             *(u32x4*)(lds_s + tile_off(row, e % RCH, RCH)) = v;
         }
         // (LDS operations of one wave complete in order: no barrier between its writes and its reads)
+        // (all of the call's rank: the padding past the adapter's is zeroed on the way out; a test per MFMA would wait for every
+        // fragment by itself)
         const int r0 = 8 * (l >> 4);
         bf16x8 fs[CB];
 #pragma unroll
@@ -133,9 +133,8 @@ __device__ __forceinline__ void strip_body(const StripArgsOf<TB>& p, const Strip
             const int o = da_x_off(row, col >> 3) + ((col & 7) << 1);
             const bf16x8 fb = join_tr(lds_read_tr(lds_x, o), lds_read_tr(lds_x, o + 4 * 128));   // (row + 4: same swizzle)
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-                if (CB == 1 || cb < cbn)           // D[j][c], resp. D[c][n]: four consecutive elements of the output to a lane
-                    acc[jb][cb] = MASKED ? LF_MFMA16(fb, fs[cb], acc[jb][cb]) : LF_MFMA16(fs[cb], fb, acc[jb][cb]);
+            for (int cb = 0; cb < CB; ++cb)        // D[j][c], resp. D[c][n]: four consecutive elements of the output to a lane
+                acc[jb][cb] = MASKED ? LF_MFMA16(fb, fs[cb], acc[jb][cb]) : LF_MFMA16(fs[cb], fb, acc[jb][cb]);
         }
     };
     if (w < nblocks) {
@@ -157,11 +156,14 @@ __device__ __forceinline__ void strip_body(const StripArgsOf<TB>& p, const Strip
 
     // Where the sum goes: the gradient itself if this workgroup has the whole segment, else a piece for the last workgroup of
     // the strip (counters), or a plane for finalize_da_kernel.
-    int reg0 = 0, nreg = 1, extra = -1;
-    if (job.panel_rows && rt.rows) segment_planes(p.tb, job.panel_rows, g, reg0, nreg, extra);
-    const int panels = nreg + (extra >= 0);
-    const bool whole = job.panel_rows == 0 || (job.counters && panels == 1) || rt.rows == 0;
-    f32x4* piece = (f32x4*)(job.part + ((int64_t)tile * strips + strip) * (R * DA_STRIP));
+    int panels = 1;
+    if (job.panel_rows) {
+        const SegmentPanels sp = segment_panels(p.tb, job.panel_rows, g);
+        panels = sp.nreg + sp.has_long + sp.has_short;
+    }
+    const bool whole = job.panel_rows == 0 || (job.counters && panels <= 1);
+    constexpr int PIECE = R * DA_STRIP;
+    auto piece = [&](int t) { return piece_of(job.part + ((int64_t)t * strips + strip) * PIECE, PIECE * 4); };
     float* grad = job.out + (int64_t)g * R * job.C;
     auto grad_at = [&](int cb, int jb) {
         return (f32x4*)(MASKED ? grad + (int64_t)(cb * 16 + (l & 15)) * job.C + c0 + jb * 16 + 4 * (l >> 4)
@@ -178,6 +180,7 @@ __device__ __forceinline__ void strip_body(const StripArgsOf<TB>& p, const Strip
 #pragma unroll
             for (int k = 1; k < CB; ++k)
                 if (cb == k) v = acc[jb][k];
+            if (cb >= cbn) v = f32x4{0.f, 0.f, 0.f, 0.f};     // zero times a non-finite element is not zero
             red[(w * 4 + jb) * 64 + l] = v;
         }
         __syncthreads();
@@ -193,7 +196,7 @@ __device__ __forceinline__ void strip_body(const StripArgsOf<TB>& p, const Strip
                 f32x4* o = grad_at(cb, threadIdx.x >> 6);
                 *o = p.accumulate ? *o + v[0] : v[0];
             } else if (job.counters) {
-                store_piece(piece + cb * 256 + threadIdx.x, v[0]);
+                store_piece(piece(tile), cb * 256 + threadIdx.x, v[0]);
             } else {
                 *(f32x4*)(job.part + (int64_t)tile * R * job.C + (grad_at(cb, threadIdx.x >> 6) - (f32x4*)grad) * 4) = v[0];
             }
@@ -202,13 +205,13 @@ __device__ __forceinline__ void strip_body(const StripArgsOf<TB>& p, const Strip
     if (whole || !job.counters) return;
     __syncthreads();                               // (the flag lies where the waves' sums were)
     if (!last_of_strip(job.counters + g * strips + strip, panels, (uint32_t*)smem)) return;
-    const int64_t pitch = (int64_t)strips * (R * DA_STRIP / 4);
-    const f32x4* first = (const f32x4*)job.part + (int64_t)strip * (R * DA_STRIP / 4);
+    int reg0, nreg, extra;
+    segment_planes(p.tb, job.panel_rows, g, reg0, nreg, extra);
     for (int i = threadIdx.x; i < CB * 256; i += DA_THREADS) {
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
-        for (int t = reg0; t < reg0 + nreg; ++t) v += load_piece(first + t * pitch + i);
-        if (extra >= 0) v += load_piece(first + extra * pitch + i);
+        for (int t = reg0; t < reg0 + nreg; ++t) v += load_piece(piece(t), i);
+        if (extra >= 0) v += load_piece(piece(extra), i);
         f32x4* o = grad_at(i >> 8, (i >> 6) & 3);
         *o = p.accumulate ? *o + v : v;
     }
