@@ -5,14 +5,17 @@
 // Every output element is formed by the same MFMAs in the same order as on the large tiles (contraction in steps of
 // 32 from zero, then the LoRA term), so Y and dX are bit-identical whichever kernel a launch picks.
 //
-// What bounds them: with one small tile on a compute unit neither the matrix pipe nor memory is busy; a 64-deep slab
-// costs its MFMAs plus about 0.1 us in which the waves meet, read their first fragments and issue copies (128 x 128:
-// 0.33 us a slab against 0.21 us of MFMAs; without the copies 0.23 us, without the barrier 0.28 us), and with every
-// compute unit loaded the copies out of L2 (0.47 us a slab).  Hence: a ring of three to six slabs in LDS, copied
-// global -> LDS several slabs ahead (a slab then has about a microsecond to arrive), one barrier per slab, fragments
-// read one sub-step ahead, eight waves where the tile has work for them, and two workgroups on a compute unit for the
-// tiles whose ring leaves room.  Accumulators are vector registers, the MFMAs assembly (see ring_mfma): the compiler's
-// own moved every accumulator block in every step (M = 1024, 4096 x 4096: 40 -> 35 us).
+// What bounds them: the copies out of L2 (a compute unit takes in 120 GB/s when all of them copy, 147 by itself; 128 x 128 tiles,
+// one on every compute unit, use 80), and the meeting of the waves once a slab.  Hence: a ring of three to six slabs in LDS,
+// filled several slabs ahead by waves that do nothing else (a copy holds the wave that issues it up until the memory pipeline
+// takes it, and a wave that waits for copies to land is late for its MFMAs), one barrier per slab; the computing waves read
+// their fragments one sub-step ahead or, in the tiles whose waves have the registers and eight MFMAs or more a sub-step to
+// cover the reads with, a whole slab ahead, which leaves nothing but the barrier between two slabs' MFMAs; two workgroups on a
+// compute unit for the tiles whose ring leaves room.  Accumulators are vector registers, the MFMAs assembly (see ring_mfma): the
+// compiler's own moved every accumulator block in every step (M = 1024, 4096 x 4096: 40 -> 35 us).
+// Against copies issued by the computing waves between their MFMAs, us, (2) / (5): 1024 x 4096 x 4096 36.0 -> 33.4 / 36.1 -> 33.3; 1000 rows,
+// 14336 -> 4096 110 -> 104 / 109 -> 99; 512 x 4096 x 4096 23.6 -> 22.2 / 24.0 -> 22.9; 256 rows, 17024 -> 17856 247 -> 239 /
+// 236 -> 212; 128 rows, 26496 -> 960 54 -> 55 / 64 -> 54.5; 256 x 1024 x 1024 5.4 -> 4.8 / 5.8 -> 4.9.
 // Measured, one launch, against the 128-row tiles that served these sizes before: 256 x 1024 x 1024 16 -> 6.1 us
 // forward, 22 -> 6.7 us backward; 1024 x 4096 x 4096 56 -> 35 and 66 -> 39 us; 77 rows, 4096 -> 14336 51 -> 24 and
 // (backward) 174 -> 41 us; 64 rows, 15616 -> 320 176 -> 33 us.
@@ -25,20 +28,22 @@
 
 namespace lf {
 
-// One kernel of the family.  TM x TN output tile, WM x WN waves of (TM / WM) x (TN / WN) each, ring of NS LDS stages,
-// one 64-deep slab pair per stage.
-template <int TM_, int TN_, int WM_, int WN_, int NS_>
+// One kernel of the family.  TM x TN output tile, WM x WN computing waves of (TM / WM) x (TN / WN) each, ring of NS LDS stages,
+// one 64-deep slab pair per stage.  TW waves copy the token slabs and OW the out slabs; TW = 0: OW waves copy both (the better
+// way for the one tile whose out slab is the larger one: 256 rows, 17024 -> 17856, (5) 222 -> 212 us).
+template <int TM_, int TN_, int WM_, int WN_, int NS_, int TW_, int OW_>
 struct Ring {
-    static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, NS = NS_;
-    static constexpr int NW = WM * WN, THREADS = 64 * NW;
+    static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, NS = NS_, TW = TW_, OW = OW_, CW = TW + OW;
+    static constexpr int NW = WM * WN, THREADS = 64 * NW;             // waves and threads that compute
     static constexpr int MI = TM / WM / 16, NI = TN / WN / 16;        // 16x16 blocks per wave
-    static constexpr int PASS_TOK = TM / 8;                           // wave copies (1 KB) of a token slab
-    static constexpr int PASSES = (TM + TN) / 8 / NW;                 // ... of a slab pair, per wave
     static constexpr int STAGE = (TM + TN) * BK * 2;
     static constexpr int LDS = NS * STAGE;
-    static_assert((TM + TN) / 8 % NW == 0 && PASSES <= 8, "the copies of a slab pair divide evenly over the waves");
+    static constexpr int REGS = 512 / ((NW + CW + 3) / 4);            // of a wave, with a SIMD's share of the workgroup on it
+    // fragments of two slabs in registers: where they fit beside the accumulators and some forty others (128 x 64 tiles with the
+    // shorter sub-steps of a 2 x 4 split, 512 x 4096 x 4096: 22.4 -> 23.8 us, so not below eight MFMAs)
+    static constexpr bool AHEAD = MI * NI >= 8 && MI * NI * 4 + (MI + NI) * 16 + 40 <= REGS;
+    static_assert(TM / 8 % (TW ? TW : OW) == 0 && TN / 8 % OW == 0, "the copies of a slab divide evenly over the waves");
     static_assert(NS >= 2, "ring depth");
-    static_assert(PASSES * (NS - 1) < 64, "the wait counter has six bits");
     static_assert(TM * TN * 2 <= LDS, "the way out goes through the ring");
 };
 
@@ -50,45 +55,82 @@ __device__ __forceinline__ int ring_col_swz(int row) {
     return TN >= 128 ? col_slab_swz(row) : TN == 64 ? (row & 2) | ((row & 8) >> 1) : (row & 8) >> 2;
 }
 
-// Source offsets of a lane for the copies of one slab pair (bytes from the token or the out slab's first element).
-// Copies are numbered token slab first; wave w issues numbers PASSES*w .. +PASSES-1.
-template <class C> struct RingLanes { uint32_t off[C::PASSES]; };
+// ---- the copying waves -----------------------------------------------------------------------------
+// Where a slab comes from: rows (token: of the tile; out: output columns or, COL, contraction rows) `ld` elements apart, `rows`
+// of them valid; chunks: valid 16-byte chunks along the contraction (8, or r / 8 for the LoRA slab), COL: along the columns.
+struct RingSource { const char* biased; uint32_t ld; int rows, chunks; };
 
-// tok_chunks / out_chunks: valid 16-byte chunks along the contraction (8, or r / 8 for the LoRA slab);
-// out_rows (COL): valid contraction rows (64, or r).
-template <class C, bool COL>
-__device__ __forceinline__ RingLanes<C> ring_lanes(int w, uint32_t tok_ld, uint32_t out_ld, int tok_rows, int out_cols,
-                                                   int chunks, int out_rows) {
-    const int l = threadIdx.x & 63;
-    RingLanes<C> s;
-#pragma unroll
-    for (int i = 0; i < C::PASSES; ++i) {
-        const int q = w * C::PASSES + i;
+// Copies of a slab pair by one wave: NT of the token slab, then NO of the out slab (1 KB each); either may be none.  Those of
+// a slab share an M0.
+template <class C, bool COL, int NT_, int NO_>
+struct RingCopies {
+    static constexpr int NT = NT_, NO = NO_, N = NT + NO;
+    static_assert(NT <= 8 && NO <= 8 && N * (C::NS - 1) < 64, "immediates of the copies; the wait counter has six bits");
+
+    // Source offset of this lane for copy I of wave w, bytes from the slab's first element.
+    template <int I>
+    static __device__ __forceinline__ uint32_t lane(int w, const RingSource& tok, const RingSource& out) {
+        const int l = threadIdx.x & 63;
         uint32_t e;                                                   // < 2^30: at most 256 rows of 2^22 elements
-        if (q < C::PASS_TOK) {
-            const int row = 8 * q + (l >> 3);
-            e = (uint32_t)min(row, tok_rows - 1) * tok_ld + min((l & 7) ^ row_slab_swz(row), chunks - 1) * 8;
-        } else if (!COL) {
-            const int row = 8 * (q - C::PASS_TOK) + (l >> 3);
-            e = (uint32_t)min(row, out_cols - 1) * out_ld + min((l & 7) ^ row_slab_swz(row), chunks - 1) * 8;
+        if constexpr (I < NT) {
+            const int row = 8 * (w * NT + I) + (l >> 3);
+            e = (uint32_t)min(row, tok.rows - 1) * tok.ld + min((l & 7) ^ row_slab_swz(row), tok.chunks - 1) * 8;
+        } else if constexpr (!COL) {
+            const int row = 8 * (w * NO + I - NT) + (l >> 3);
+            e = (uint32_t)min(row, out.rows - 1) * out.ld + min((l & 7) ^ row_slab_swz(row), out.chunks - 1) * 8;
         } else {
             constexpr int CPR = C::TN / 8;                            // chunks per slab row
-            const int pos = (q - C::PASS_TOK) * 64 + l, row = pos / CPR;
-            e = (uint32_t)min(row, out_rows - 1) * out_ld + min((pos % CPR) ^ ring_col_swz<C::TN>(row), (out_cols >> 3) - 1) * 8;
+            const int pos = (w * NO + I - NT) * 64 + l, row = pos / CPR;
+            e = (uint32_t)min(row, out.rows - 1) * out.ld + min((pos % CPR) ^ ring_col_swz<C::TN>(row), out.chunks - 1) * 8;
         }
-        s.off[i] = e * 2 + kCopyBias - pass_imm(C::PASSES, i);
+        return e * 2 + kCopyBias - (I < NT ? pass_imm(NT, I) : pass_imm(NO, I - NT));
     }
-    return s;
-}
 
-// Copies I .. END-1 of this wave.  tok / out: slab addresses - kCopyBias; m0: its destination (middle of its PASSES KB)
-template <class C, int I = 0, int END = C::PASSES>
-__device__ __forceinline__ void ring_issue(int w, const char* tok, const char* out, const RingLanes<C>& s, uint32_t m0) {
-    if constexpr (I < END) {
-        copy16_to_lds<pass_imm(C::PASSES, I), I == 0>(w * C::PASSES + I < C::PASS_TOK ? tok : out, s.off[I], m0);
-        ring_issue<C, I + 1, END>(w, tok, out, s, m0);
+    // One slab pair's copies into the stage at LDS address `stage`.  FORM: the lane offsets are formed on the way, each right before
+    // its copy (the first slab of a launch waits for nothing else).
+    template <bool FORM, int I = 0>
+    static __device__ __forceinline__ void issue(int w, const RingSource& tok, const RingSource& out, uint32_t (&off)[N], uint32_t stage) {
+        if constexpr (I < N) {
+            if constexpr (FORM) off[I] = lane<I>(w, tok, out);
+            if constexpr (I < NT) copy16_to_lds<pass_imm(NT, I), I == 0>(tok.biased, off[I], stage + (w * NT + NT / 2) * 1024);
+            else copy16_to_lds<pass_imm(NO, I - NT), I == NT>(out.biased, off[I], stage + C::TM * BK * 2 + (w * NO + NO / 2) * 1024);
+            if constexpr (FORM) __builtin_amdgcn_sched_barrier(0);
+            issue<FORM, I + 1>(w, tok, out, off, stage);
+        }
     }
-}
+
+    // Slab `kt` goes into stage kt % NS: a base slab (out_adv bytes further each time), the LoRA slab (kt == nk, if there is one),
+    // or nothing.  The barriers are those of the computing waves: one before the first slab, then one per slab, at which the
+    // copies of slab kt + 1 have landed and the stage of slab kt is free.
+    static __device__ __forceinline__ void run(int w, RingSource tok, RingSource out, int64_t out_adv, const RingSource& ltok,
+                                               const RingSource& lout, int nk, int nkt, uint32_t lds) {
+        constexpr int NS = C::NS;
+        uint32_t off[N];
+        auto slab = [&](int kt, int stage, auto form) {
+            if (kt < nk) {
+                issue<form()>(w, tok, out, off, lds + stage * C::STAGE);
+                tok.biased += BK * 2;
+                out.biased += out_adv;
+            } else if (kt < nkt) {
+                issue<true>(w, ltok, lout, off, lds + stage * C::STAGE);
+            }
+        };
+        slab(0, 0, std::true_type{});
+#pragma unroll
+        for (int s = 1; s < NS; ++s) slab(s, s, std::false_type{});
+        if (nkt >= NS) wait_slab_loads_but<N*(NS - 1)>();
+        else wait_slab_loads();
+        asm volatile("s_barrier" ::: "memory");
+        int stage = 0;
+        for (int kt = 0; kt < nk; ++kt) {
+            if (kt + NS <= nkt) wait_slab_loads_but<N*(NS - 2)>();
+            else wait_slab_loads();
+            asm volatile("s_barrier" ::: "memory");
+            slab(kt + NS, stage, std::false_type{});
+            stage = stage + 1 == NS ? 0 : stage + 1;
+        }
+    }
+};
 
 template <class C> struct RingFrags { bf16x8 ft[C::MI], fo[C::NI]; };
 
@@ -124,29 +166,29 @@ __device__ __forceinline__ void ring_read(RingFrags<C>& f, const char* st, int s
     }
 }
 
-// All MFMAs of a sub-step, from assembly with the accumulators tied in place: with the builtin the compiler moves
+// MFMAs of a sub-step (block rows FIRST .. of the fragments), from assembly with the accumulators tied in place: with the builtin the compiler moves
 // accumulator blocks between registers in every step of the loop.  OPS_FROM_VALU: the operands may come straight from
 // the vector ALU (zero_past_rank); the compiler keeps the wait states that needs only for its own MFMAs.
-template <class C, bool OPS_FROM_VALU>
-__device__ __forceinline__ void ring_mfma(f32x4 (&acc)[C::MI][C::NI], const RingFrags<C>& f) {
+template <class C, bool OPS_FROM_VALU, int FIRST, int ROWS>
+__device__ __forceinline__ void ring_mfma(f32x4 (&acc)[ROWS][C::NI], const RingFrags<C>& f) {
 #pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi)
+    for (int mi = 0; mi < ROWS; ++mi)
 #pragma unroll
         for (int ni = 0; ni < C::NI; ++ni) {
             if constexpr (OPS_FROM_VALU)
-                asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(f.fo[ni]), "v"(f.ft[mi]));
+                asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(f.fo[ni]), "v"(f.ft[FIRST + mi]));
             else
-                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(f.fo[ni]), "v"(f.ft[mi]));
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(f.fo[ni]), "v"(f.ft[FIRST + mi]));
         }
 }
 // ... and the distance to the vector ALU's first read of their results.
-template <class C>
-__device__ __forceinline__ void ring_mfma_done(f32x4 (&acc)[C::MI][C::NI]) {
+template <int MI, int NI>
+__device__ __forceinline__ void ring_mfma_done(f32x4 (&acc)[MI][NI]) {
     asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
 #pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi)
+    for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < C::NI; ++ni) asm volatile("" : "+v"(acc[mi][ni]));
+        for (int ni = 0; ni < NI; ++ni) asm volatile("" : "+v"(acc[mi][ni]));
 }
 
 template <class C>
@@ -158,22 +200,13 @@ __device__ __forceinline__ void ring_zero_past_rank(RingFrags<C>& f, int sub, in
     for (int ni = 0; ni < C::NI; ++ni) f.fo[ni] = zero_past_rank(f.fo[ni], chunk, rank_chunks);
 }
 
-// Waits until all but the VM newest copies of the wave have landed and, with LGKM, all its LDS reads have returned.
-// The builtin, not assembly: the compiler counts it, and does not wait again for reads it orders before.
-template <int VM, bool LGKM>
-__device__ __forceinline__ void ring_wait() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | ((LGKM ? 0 : 15) << 8) | ((VM >> 4) << 14));
-    asm volatile("" ::: "memory");
-}
-
 // One sub-step of a slab: its MFMAs, and between them the reads of the fragments `nxt` (sub-step nxt_sub of the slab at
-// `st`) and, in the second sub-step (HAND), the hand-over to the next slab and the copies of a slab.  A wave issues in
-// order, so the three have to be mixed by hand.  With four or fewer MFMAs a sub-step the reads go out in its first half, so
+// `st`) and, in the second sub-step (HAND), the hand-over to the next slab.  A wave issues in order, so they have to be
+// mixed by hand.  With four or fewer MFMAs a sub-step the reads go out in its first half, so
 // that the last one has returned when the hand-over (or the next sub-step) needs it, and the hand-over sits a quarter
 // into the second sub-step; with more the reads spread evenly.
 template <class C> struct RingSlots {
-    static constexpr int SLOTS = C::MI * C::NI, READS = C::MI + C::NI, P = C::PASSES;
+    static constexpr int SLOTS = C::MI * C::NI, READS = C::MI + C::NI;
     static constexpr bool SHORT = SLOTS < 8;
     static constexpr int HAND_AT = SHORT ? SLOTS / 4 : 0;                       // hand-over before this slot's MFMA
     static constexpr int first(bool hand) { return hand ? HAND_AT : 0; }        // first slot that carries reads
@@ -182,30 +215,44 @@ template <class C> struct RingSlots {
         const int k = s - first(hand);
         return k <= 0 ? 0 : k >= span(hand) ? READS : k * READS / span(hand);
     }
-    static constexpr int copies_before(int s) {
-        const int k = s - HAND_AT, n = SLOTS - HAND_AT;
-        return k <= 0 ? 0 : k * P / n;
-    }
 };
 
-template <class C, bool COL, bool HAND, bool COPY, int I, class F>
+template <class C, bool COL, bool HAND, int I>
 __device__ __forceinline__ void ring_half(f32x4 (&acc)[C::MI][C::NI], const RingFrags<C>& cur, RingFrags<C>& nxt, const char* st,
-                                          int nxt_sub, int w, int wm, int wn, const char* tok, const char* out,
-                                          const RingLanes<C>& lanes, uint32_t m0, F& hand_over) {
+                                          int nxt_sub, int wm, int wn) {
     using S = RingSlots<C>;
     if constexpr (I < S::SLOTS) {
         constexpr int mi = I / C::NI, ni = I % C::NI;
-        if constexpr (HAND && I == S::HAND_AT) hand_over();
+        // hand-over: every read of the stage is behind this wave; behind the barrier the next slab has landed, too
+        if constexpr (HAND && I == S::HAND_AT) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         ring_read<C, COL, S::reads_before(HAND, I), S::reads_before(HAND, I + 1)>(nxt, st, nxt_sub, wm, wn);
-        if constexpr (COPY) ring_issue<C, S::copies_before(I), S::copies_before(I + 1)>(w, tok, out, lanes, m0);
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(cur.fo[ni]), "v"(cur.ft[mi]));
         __builtin_amdgcn_sched_barrier(0);
-        ring_half<C, COL, HAND, COPY, I + 1>(acc, cur, nxt, st, nxt_sub, w, wm, wn, tok, out, lanes, m0, hand_over);
+        ring_half<C, COL, HAND, I + 1>(acc, cur, nxt, st, nxt_sub, wm, wn);
+    }
+}
+
+// A slab with the fragments of two slabs in registers (AHEAD): the MFMAs of `cur`, and in their first half the reads of the next
+// slab's fragments, from `st`.
+template <class C, bool COL, int I>
+__device__ __forceinline__ void ring_slab(f32x4 (&acc)[C::MI][C::NI], const RingFrags<C> (&cur)[2], RingFrags<C> (&nxt)[2],
+                                          const char* st, int wm, int wn) {
+    constexpr int SLOTS = C::MI * C::NI, READS = C::MI + C::NI;
+    if constexpr (I < 2 * SLOTS) {
+        constexpr int h = I / SLOTS, mi = I % SLOTS / C::NI, ni = I % C::NI;
+        constexpr int lo = I * 2 * READS / SLOTS, hi = (I + 1) * 2 * READS / SLOTS;
+        if constexpr (lo < 2 * READS) {
+            ring_read<C, COL, lo < READS ? lo : READS, hi < READS ? hi : READS>(nxt[0], st, 0, wm, wn);
+            ring_read<C, COL, lo < READS ? 0 : lo - READS, hi < READS ? 0 : hi - READS>(nxt[1], st, 1, wm, wn);
+        }
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(cur[h].fo[ni]), "v"(cur[h].ft[mi]));
+        __builtin_amdgcn_sched_barrier(0);
+        ring_slab<C, COL, I + 1>(acc, cur, nxt, st, wm, wn);
     }
 }
 
 template <class C, bool COL, class TB>
-__global__ void __launch_bounds__(C::THREADS) ring_gemm_kernel(RingArgsOf<TB> p) {
+__global__ void __launch_bounds__(C::THREADS + 64 * C::CW) ring_gemm_kernel(RingArgsOf<TB> p) {
     constexpr int NS = C::NS, MI = C::MI, NI = C::NI;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int tm, tn;
@@ -218,32 +265,24 @@ __global__ void __launch_bounds__(C::THREADS) ring_gemm_kernel(RingArgsOf<TB> p)
     const bool has_lora = p.r > 0;
     const int nk = p.KC / BK, nkt = nk + (has_lora ? 1 : 0);
 
-    const int out_ld = COL ? p.NC : p.KC;
-    const char* tok_src = (const char*)(p.tok + (int64_t)rt.row_start * p.KC) - kCopyBias;
-    const char* out_src = (const char*)(COL ? p.out + c0 : p.out + (int64_t)c0 * p.KC) - kCopyBias;
-    const int64_t out_adv = COL ? (int64_t)BK * p.NC * 2 : BK * 2;
-    const uint32_t m0 = lds_addr_of(smem) + w * (C::PASSES * 1024) + (C::PASSES / 2) * 1024;
-    const RingLanes<C> base_lanes = ring_lanes<C, COL>(w, p.KC, out_ld, rt.rows, cols_valid, 8, BK);
-
-    // Slab `kt` into stage `stage`: a base slab pair, the LoRA pair [S' | B] resp. [dS | A] (kt == nk), or nothing.
-    auto issue_base = [&](int stage) {
-        ring_issue<C>(w, tok_src, out_src, base_lanes, m0 + stage * C::STAGE);
-        tok_src += BK * 2;
-        out_src += out_adv;
-    };
-    auto issue = [&](int kt, int stage) {
-        if (kt < nk) {
-            issue_base(stage);
-        } else if (kt < nkt) {
-            const lora_bf16* lt = p.ltok + (int64_t)rt.row_start * p.r;
-            const lora_bf16* lo = COL ? p.lout + (int64_t)rt.g * p.r * p.NC + c0 : p.lout + ((int64_t)rt.g * p.NC + c0) * p.r;
-            const RingLanes<C> s = ring_lanes<C, COL>(w, p.r, COL ? p.NC : p.r, rt.rows, cols_valid, p.r >> 3, p.r);
-            ring_issue<C>(w, (const char*)lt - kCopyBias, (const char*)lo - kCopyBias, s, m0 + stage * C::STAGE);
-        }
-    };
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-        issue(s, s);
+    if (w >= C::NW) {
+        const int cw = w - C::NW;
+        const RingSource tok{(const char*)(p.tok + (int64_t)rt.row_start * p.KC) - kCopyBias, (uint32_t)p.KC, rt.rows, 8};
+        const RingSource ltok{(const char*)(p.ltok + (int64_t)rt.row_start * p.r) - kCopyBias, (uint32_t)p.r, rt.rows, p.r >> 3};
+        const RingSource out = COL ? RingSource{(const char*)(p.out + c0) - kCopyBias, (uint32_t)p.NC, BK, cols_valid >> 3}
+                                   : RingSource{(const char*)(p.out + (int64_t)c0 * p.KC) - kCopyBias, (uint32_t)p.KC, cols_valid, 8};
+        const RingSource lout = COL ? RingSource{(const char*)(p.lout + (int64_t)rt.g * p.r * p.NC + c0) - kCopyBias, (uint32_t)p.NC, p.r, cols_valid >> 3}
+                                    : RingSource{(const char*)(p.lout + ((int64_t)rt.g * p.NC + c0) * p.r) - kCopyBias, (uint32_t)p.r, cols_valid, p.r >> 3};
+        const int64_t out_adv = COL ? (int64_t)BK * p.NC * 2 : BK * 2;
+        const uint32_t lds = lds_addr_of(smem);
+        if constexpr (C::TW == 0)
+            RingCopies<C, COL, C::TM / 8 / C::OW, C::TN / 8 / C::OW>::run(cw, tok, out, out_adv, ltok, lout, nk, nkt, lds);
+        else if (cw < C::TW)
+            RingCopies<C, COL, C::TM / 8 / C::TW, 0>::run(cw, tok, out, out_adv, ltok, lout, nk, nkt, lds);
+        else
+            RingCopies<C, COL, 0, C::TN / 8 / C::OW>::run(cw - C::TW, tok, out, out_adv, ltok, lout, nk, nkt, lds);
+        return;
+    }
 
     // (5): keep flags of this lane's elements while the first slabs are on their way.  Block b = mi * NI + ni: bit
     // 2 * (b & 7) + pr of word b >> 3 for element 2 * pr, + 16 for element 2 * pr + 1.
@@ -279,74 +318,90 @@ __global__ void __launch_bounds__(C::THREADS) ring_gemm_kernel(RingArgsOf<TB> p)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    if (nkt >= NS) ring_wait<C::PASSES*(NS - 1), false>();
-    else ring_wait<0, false>();
     asm volatile("s_barrier" ::: "memory");
 
-    // Step kt computes slab kt.  The fragments of its second half are read while the first half's MFMAs run; then
-    // every read of the stage is behind this wave, the copies of slab kt + 1 have landed, and one barrier makes both
-    // true for the whole workgroup: the copies of slab kt + NS go into the stage just left.  (The last step reads
-    // fragments of a stage that may hold nothing; without a LoRA term they are not used.)
     int stage = 0;
-    RingFrags<C> f0, f1;
-    ring_read<C, COL>(f0, smem, 0, wm, wn);
-    auto step = [&](int kt, auto steady) {
-        const int next = stage + 1 == NS ? 0 : stage + 1;
-        auto hand_over = [&] {
-            if (steady() || kt + NS <= nkt) ring_wait<C::PASSES*(NS - 2), true>();
-            else ring_wait<0, true>();
-            asm volatile("s_barrier" ::: "memory");
-            if (!steady()) issue(kt + NS, stage);
+    RingFrags<C> fa[2];
+    ring_read<C, COL>(fa[0], smem, 0, wm, wn);
+    if constexpr (C::AHEAD) {
+        // Step kt computes slab kt from registers while it reads slab kt + 1.  At its barrier the copies of that slab have landed,
+        // and every wave holds slab kt: the copies of slab kt + NS go into the stage that it has left.  (The last step
+        // reads a stage that may hold nothing; without a LoRA term those fragments are not used.)
+        RingFrags<C> fb[2];
+        ring_read<C, COL>(fa[1], smem, 1, wm, wn);
+        auto step = [&](RingFrags<C> (&cur)[2], RingFrags<C> (&nxt)[2]) {
+            stage = stage + 1 == NS ? 0 : stage + 1;
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            ring_slab<C, COL, 0>(acc, cur, nxt, smem + stage * C::STAGE, wm, wn);
         };
-        ring_half<C, COL, false, false, 0>(acc, f0, f1, smem + stage * C::STAGE, 1, w, wm, wn, tok_src, out_src, base_lanes, 0u,
-                                           hand_over);
-        ring_half<C, COL, true, steady(), 0>(acc, f1, f0, smem + next * C::STAGE, 0, w, wm, wn, tok_src, out_src, base_lanes,
-                                             m0 + stage * C::STAGE, hand_over);
-        if (steady()) {
-            tok_src += BK * 2;
-            out_src += out_adv;
+        int kt = 0;
+        for (; kt + 1 < nk; kt += 2) {
+            step(fa, fb);
+            step(fb, fa);
         }
-        stage = next;
-    };
-    int kt = 0;
-    for (; kt + NS < nk; ++kt) step(kt, std::true_type{});
-    for (; kt < nk; ++kt) step(kt, std::false_type{});
+        if (kt < nk) {
+            step(fa, fb);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) fa[h] = fb[h];
+        }
+    } else {
+        // Step kt computes slab kt.  The fragments of its second half are read while the first half's MFMAs run; then every
+        // read of the stage is behind this wave, the copies of slab kt + 1 have landed, and one barrier makes both true for the
+        // whole workgroup: the copies of slab kt + NS go into the stage just left.
+        for (int kt = 0; kt < nk; ++kt) {
+            const int next = stage + 1 == NS ? 0 : stage + 1;
+            ring_half<C, COL, false, 0>(acc, fa[0], fa[1], smem + stage * C::STAGE, 1, wm, wn);
+            ring_half<C, COL, true, 0>(acc, fa[1], fa[0], smem + next * C::STAGE, 0, wm, wn);
+            stage = next;
+        }
+    }
+    RingFrags<C>& f0 = fa[0];
 
     // LoRA term: (2) on the same accumulators; (5) by itself, masked and added
     const int rank_chunks = has_lora ? p.tb.a[rt.g].rank >> 3 : 0;
     if (has_lora) {
-        f32x4 t[MI][NI];
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) t[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto term = [&](f32x4 (&to)[MI][NI]) {
+        // block rows of the tile from row `first` on into `to`; the fragments of sub-step 0 are in f0
+        auto term = [&](auto& to, auto first) {
+            constexpr int FIRST = first(), ROWS = sizeof(to) / sizeof(to[0]);
             ring_zero_past_rank<C>(f0, 0, rank_chunks);
-            ring_mfma<C, true>(to, f0);
+            ring_mfma<C, true, FIRST, ROWS>(to, f0);
             if (rank_chunks > 4) {
-                ring_read<C, COL>(f1, smem + stage * C::STAGE, 1, wm, wn);
-                ring_mfma<C, false>(to, f1);
+                ring_read<C, COL>(f0, smem + stage * C::STAGE, 1, wm, wn);
+                ring_mfma<C, false, FIRST, ROWS>(to, f0);
             }
-            ring_mfma_done<C>(to);
+            ring_mfma_done<ROWS, NI>(to);
         };
         if constexpr (!COL) {
-            term(acc);
+            term(acc, std::integral_constant<int, 0>{});
         } else {
-            term(t);
+            ring_mfma_done<MI, NI>(acc);
+            // half of the block rows at a time where there are four: t beside the accumulators is what the registers allow
+            constexpr int ROWS = MI >= 4 ? MI / 2 : MI;
+            auto part = [&](auto first) {
+                f32x4 t[ROWS][NI];
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
+                for (int mi = 0; mi < ROWS; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < NI; ++ni)
+                    for (int ni = 0; ni < NI; ++ni) t[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (first() > 0) ring_read<C, COL>(f0, smem + stage * C::STAGE, 0, wm, wn);
+                term(t, first);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int b = mi * NI + ni, bit = 2 * (b & 7) + (e >> 1) + (e & 1) * 16;
-                        const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)keep[b >> 3], bit, 1);
-                        const float te = t[mi][ni][e];            // (a copy: bit_cast of a vector element reads element 0)
-                        acc[mi][ni][e] += __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, te) & m);
-                    }
+                for (int mi = 0; mi < ROWS; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int b = (first() + mi) * NI + ni, bit = 2 * (b & 7) + (e >> 1) + (e & 1) * 16;
+                            const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)keep[b >> 3], bit, 1);
+                            const float te = t[mi][ni][e];        // (a copy: bit_cast of a vector element reads element 0)
+                            acc[first() + mi][ni][e] += __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, te) & m);
+                        }
+            };
+            part(std::integral_constant<int, 0>{});
+            if constexpr (ROWS < MI) part(std::integral_constant<int, ROWS>{});
         }
     } else {
-        ring_mfma_done<C>(acc);
+        ring_mfma_done<MI, NI>(acc);
     }
 
     // Way out: the bf16 tile goes through LDS (rows of TN * 2 bytes, eight-byte slots XOR-ed so that the 16 rows x 2
@@ -392,7 +447,7 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
             if (e != hipSuccess) return e;
             attr_set = true;
         }
-        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(C::THREADS), C::LDS, st, b);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(C::THREADS + 64 * C::CW), C::LDS, st, b);
         return hipGetLastError();
     });
 }
@@ -405,12 +460,12 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
 template <bool COL>
 static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
     switch (kind) {
-        case 0: return launch_ring_cfg<Ring<128, 256, 2, 4, 3>, COL>(a, st);
-        case 1: return launch_ring_cfg<Ring<128, 128, 2, 4, 4>, COL>(a, st);
-        case 2: return launch_ring_cfg<Ring<64, 128, 2, 4, 3>, COL>(a, st);
-        case 3: return launch_ring_cfg<Ring<64, 64, 2, 2, 4>, COL>(a, st);
-        case 4: return launch_ring_cfg<Ring<32, 64, 2, 2, 6>, COL>(a, st);
-        case 5: return launch_ring_cfg<Ring<128, 64, 4, 2, 6>, COL>(a, st);
+        case 0: return launch_ring_cfg<Ring<128, 256, 2, 4, 3, 0, 4>, COL>(a, st);
+        case 1: return launch_ring_cfg<Ring<128, 128, 2, 2, 4, 2, 2>, COL>(a, st);
+        case 2: return launch_ring_cfg<Ring<64, 128, 2, 4, 3, 1, 2>, COL>(a, st);
+        case 3: return launch_ring_cfg<Ring<64, 64, 2, 2, 5, 2, 2>, COL>(a, st);
+        case 4: return launch_ring_cfg<Ring<32, 64, 1, 2, 6, 1, 1>, COL>(a, st);
+        case 5: return launch_ring_cfg<Ring<128, 64, 2, 2, 6, 2, 1>, COL>(a, st);
     }
     return hipErrorInvalidValue;
 }
