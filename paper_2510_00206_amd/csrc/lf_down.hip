@@ -8,14 +8,13 @@
 // that the sweep of one workgroup over K, whose price is the number of vector memory instructions and of cache lines
 // they touch (an instruction over 16 rows x 64 bytes costs the compute unit about 60 cycles, one over 8 rows x 128 bytes
 // about 25), then the mask (12 vector instructions per column pair).  Hence X and A go global -> LDS in whole 128-byte
-// lines, several stages of 256 columns ahead; A is fetched once per workgroup and stage, not once per wave; the masks
-// of a stage are formed while its copies land, and not at all without dropout.
-// Measured against fragments loaded straight into registers (same rows and K, us): K = 14336: 64 rows r = 16 29 -> 23,
-// r = 64 65 -> 32; 5003 rows r = 16 57 -> 36, r = 64 128 -> 43; 8192 rows r = 64 83 -> 50.  K = 4096: 8192 rows r = 16
-// 18 -> 15, 4096 rows r = 64 24 -> 15.  Short contractions keep the registers (down_direct_kernel, rule in launch_down).  The
-// order of the sums is the same in both kernels and in every height, so S' has the same bits whichever is picked.
-#include <type_traits>
-
+// lines, several stages of 256 columns ahead, by waves that do nothing else; A is fetched once per workgroup and stage, not
+// once per wave; the masks of a stage are formed while its copies land, and not at all without dropout.
+// Measured, us: fragments loaded straight into registers / copies by the computing waves / as it is now: K = 14336: 5003 rows r = 16
+// 57 / 33.6 / 29.2, r = 64 128 / 39.5 / 35.0; K = 4096: 1024 rows r = 16 - / 7.9 / 7.2, r = 64 - / 11.2 / 8.7; 8192 rows r = 16 18 / 12.4 / 12.4,
+// r = 64 - / 16.2 / 14.9; 19 rows, K = 24960, r = 16 - / 33.4 / 29.7, r = 64 - / 50.3 / 38.3.  Short contractions keep the registers
+// (down_direct_kernel, rule in launch_down).  The order of the sums is the same in both kernels and in every height, so S' has
+// the same bits whichever is picked.
 #include "lf_device.h"
 #include "lf_gemm_parts.h"
 #include "lf_internal.h"
@@ -25,26 +24,63 @@ namespace lf {
 constexpr int DOWN_SLABS = 4;                       // 64-column slabs per stage
 constexpr int DOWN_PARTS = 2 * DOWN_SLABS;          // a wave owns one half (32 columns) of one slab of every stage
 
-// CB = r / 16 column blocks of S'; RB 16-row blocks per workgroup, WR of them on waves of their own (the others in the
-// same wave); ring of NS stages in LDS.
-template <int CB_, int RB_, int WR_, int NS_>
+// CB = r / 16 column blocks of S'; RB 16-row blocks per workgroup; ring of NS stages in LDS.  Eight waves compute, one for each
+// column part; further ones copy, N KB of a stage each: XW of them rows of X, AW rows of A.
+template <int CB_, int RB_, int NS_>
 struct Down {
-    static constexpr int CB = CB_, RB = RB_, WR = WR_, RW = RB / WR, NS = NS_;
-    static constexpr int NW = DOWN_PARTS * WR, THREADS = 64 * NW;
+    static constexpr int CB = CB_, RB = RB_, NS = NS_;
+    static constexpr int THREADS = 64 * DOWN_PARTS;                                        // that compute
     static constexpr int X_COPIES = DOWN_SLABS * RB * 2, A_COPIES = DOWN_SLABS * CB * 2;   // 1 KB wave copies per stage
-    static constexpr int P = (X_COPIES + A_COPIES) / NW;                                   // ... per wave
+    static constexpr int XN = RB == 2 && CB < 4 ? 8 : 4, AN = CB == 4 || RB == 2 ? 8 : 4;    // ... per wave
+    static constexpr int XW = X_COPIES / XN, AW = A_COPIES / AN;
     static constexpr int STAGE = (X_COPIES + A_COPIES) * 1024;
     static constexpr int LDS = NS * STAGE;
-    static_assert((X_COPIES + A_COPIES) % NW == 0 && P <= 8 && P * (NS - 1) < 64, "copies per wave; the wait counter has six bits");
-    static_assert(RB % WR == 0 && DOWN_PARTS * RB * CB * 1024 <= LDS, "the cross-wave sum goes through the ring");
+    static_assert(DOWN_PARTS + XW + AW <= 16 && AN * (NS - 1) < 64, "a workgroup; the wait counter has six bits");
+    static_assert(DOWN_PARTS * RB * CB * 1024 <= LDS, "the cross-wave sum goes through the ring");
 };
 
-// This wave's copies I .. of one stage; src[i] is the stage's first column in the matrix of copy i.
-template <class C, int I = 0>
-__device__ __forceinline__ void down_copy(const char* const (&src)[C::P], const uint32_t (&off)[C::P], uint32_t m0) {
-    if constexpr (I < C::P) {
-        copy16_to_lds<pass_imm(C::P, I), I == 0>(src[I], off[I], m0);
-        down_copy<C, I + 1>(src, off, m0);
+template <int N, int I = 0>
+__device__ __forceinline__ void down_copy(const char* src, const uint32_t (&off)[N], uint32_t m0) {
+    if constexpr (I < N) {
+        copy16_to_lds<pass_imm(N, I), I == 0>(src, off[I], m0);
+        down_copy<N, I + 1>(src, off, m0);
+    }
+}
+
+// A copying wave: copies N * w .. of every stage of one matrix, of which a slab has 8 * RP rows in RP copies; `last`: the last
+// valid row (those past it repeat it), lds: the matrix's part of stage 0.  The barriers are those of the computing waves: one per
+// stage, at which the stage has landed and the one before it is free.
+template <class C, int N, int RP>
+__device__ __forceinline__ void down_copier(int w, const lora_bf16* mat, int K, int last, int st, int nslabs, int nst, uint32_t lds) {
+    const int l = threadIdx.x & 63;
+    const char* base = (const char*)mat - kCopyBias;
+    const uint32_t m0 = lds + w * (N * 1024) + (N / 2) * 1024;
+    const int partial = nslabs % DOWN_SLABS;            // slabs of the last stage, if it is not full
+    uint32_t off[N], off_last[N];                       // (slabs past K: copies of the last one, never used)
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int q = w * N + i, slab = q / RP, row = q % RP * 8 + (l >> 3);
+        const uint32_t e = (uint32_t)min(row, last) * (uint32_t)K + (((l & 7) ^ row_slab_swz(row)) << 3);
+        off[i] = (e + slab * BK) * 2 + kCopyBias - pass_imm(N, i);
+        off_last[i] = (e + (partial ? min(slab, partial - 1) : slab) * BK) * 2 + kCopyBias - pass_imm(N, i);
+    }
+    auto issue = [&](int ring) {
+        const char* src = base + (int64_t)st * (DOWN_SLABS * BK * 2);
+        if (st == nst - 1) down_copy<N>(src, off_last, m0 + ring * C::STAGE);
+        else down_copy<N>(src, off, m0 + ring * C::STAGE);
+        st = st + 1 == nst ? 0 : st + 1;
+    };
+    constexpr int NS = C::NS;
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < nst) issue(s);
+    int ring = NS - 1;
+    for (int s = 0; s < nst; ++s) {
+        if (s + NS - 2 < nst) wait_slab_loads_but<N*(NS - 2)>();
+        else wait_slab_loads();
+        asm volatile("s_barrier" ::: "memory");
+        if (s + NS - 1 < nst) issue(ring);
+        ring = ring + 1 == NS ? 0 : ring + 1;
     }
 }
 
@@ -57,6 +93,7 @@ __device__ __forceinline__ void down_store(const DownArgsOf<TB>& p, const RowTil
         f32x4 v = red[idx];
 #pragma unroll
         for (int ww = 1; ww < DOWN_PARTS; ++ww) v += red[ww * (RB * CB * 64) + idx];
+        if (cb * 16 >= p.tb.a[rt.g].rank) v = f32x4{0.f, 0.f, 0.f, 0.f};
         const int row = rb * 16 + (lane & 15);
         if (row < rt.rows) {
             u32x2 out;
@@ -68,67 +105,38 @@ __device__ __forceinline__ void down_store(const DownArgsOf<TB>& p, const RowTil
 }
 
 template <class C, class TB>
-__global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgsOf<TB> p) {
-    constexpr int CB = C::CB, RB = C::RB, RW = C::RW, NS = C::NS, P = C::P;
+__global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel(DownArgsOf<TB> p) {
+    constexpr int CB = C::CB, RB = C::RB, NS = C::NS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     RowTile rt;
     if (!find_row_tile(p.tb, 16 * RB, blockIdx.x, rt)) return;
-    const int l = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = w % DOWN_PARTS, pos = part >> 1, sub = part & 1;
-    const int rb0 = w / DOWN_PARTS * RW;                // this wave's first row block
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = rt.g;
-    const uint32_t T = p.tb.a[g].T;
-    const KeepThreshold th = keep_threshold(T);
-    const int cbn = p.tb.a[g].rank >> 4;                  // 16-column blocks this adapter uses (<= CB)
     const int nslabs = p.K / BK, nst = (nslabs + DOWN_SLABS - 1) / DOWN_SLABS;
-
-    // This wave's copies: number q of a stage is X rows (8 per copy) of slab q / (2 RB), then A rows of a slab.
-    // Rows past the tile (or past the adapter's rank) repeat the last one.
-    uint32_t off[P];
-    const char* mat[P];
-    int slab[P];
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-        const int q = w * P + i, qa = q - C::X_COPIES;
-        const bool is_x = q < C::X_COPIES;
-        slab[i] = is_x ? q / (2 * RB) : qa / (2 * CB);
-        const int row = (is_x ? q % (2 * RB) : qa % (2 * CB)) * 8 + (l >> 3);
-        const int last = is_x ? rt.rows - 1 : p.tb.a[g].rank - 1;
-        mat[i] = (is_x ? (const char*)(p.X + (int64_t)rt.row_start * p.K) : (const char*)(p.A + (int64_t)g * p.r * p.K)) - kCopyBias;
-        off[i] = ((uint32_t)min(row, last) * (uint32_t)p.K + slab[i] * BK + (((l & 7) ^ row_slab_swz(row)) << 3)) * 2 +
-                 kCopyBias - pass_imm(P, i);
-    }
-    const uint32_t m0 = lds_addr_of(smem) + w * (P * 1024) + (P / 2) * 1024;
-    const int partial = nslabs % DOWN_SLABS;            // slabs of the last stage, if it is not full
-    auto issue = [&](int st, int ring) {
-        const char* src[P];
-#pragma unroll
-        for (int i = 0; i < P; ++i) src[i] = mat[i] + (int64_t)st * (DOWN_SLABS * BK * 2);
-        if (partial && st == nst - 1) {                 // slabs past K: copies of the last one (never used)
-#pragma unroll
-            for (int i = 0; i < P; ++i) src[i] -= max(slab[i] - (partial - 1), 0) * (BK * 2);
-        }
-        down_copy<C>(src, off, m0 + ring * C::STAGE);
-    };
-
     // Every workgroup starts its sweep over K at a different stage (a function of its 32-row group within the segment,
     // so that single- and multi-adapter calls, and both workgroup heights, sum in the same order): workgroups sweeping
     // in lockstep would all hit the same few L2 channels, the row pitch being a multiple of the channel interleave.
-    int st = (int)(((unsigned)(rt.local_row0 / 32) * 5u) % (unsigned)nst), st_copy = st;
-    auto advance = [&](int& t) { t = t + 1 == nst ? 0 : t + 1; };
-#pragma unroll
-    for (int s = 0; s < NS - 1; ++s)
-        if (s < nst) {
-            issue(st_copy, s);
-            advance(st_copy);
-        }
+    int st = (int)(((unsigned)(rt.local_row0 / 32) * 5u) % (unsigned)nst);
+    if (w >= DOWN_PARTS) {
+        const int cw = w - DOWN_PARTS;
+        const uint32_t lds = lds_addr_of(smem);
+        if (cw < C::XW)
+            down_copier<C, C::XN, 2 * RB>(cw, p.X + (int64_t)rt.row_start * p.K, p.K, rt.rows - 1, st, nslabs, nst, lds);
+        else
+            down_copier<C, C::AN, 2 * CB>(cw - C::XW, p.A + (int64_t)g * p.r * p.K, p.K, p.tb.a[g].rank - 1, st, nslabs, nst,
+                                          lds + C::X_COPIES * 1024);
+        return;
+    }
+    const int pos = w >> 1, sub = w & 1;                // this wave's slab and half of it
+    const uint32_t T = p.tb.a[g].T;
+    const KeepThreshold th = keep_threshold(T);
 
-    RowKey rk[RW];
-    f32x4 acc[RW][CB];
-    u32x4 keep[RW];
+    RowKey rk[RB];
+    f32x4 acc[RB][CB];
+    u32x4 keep[RB];
 #pragma unroll
-    for (int rb = 0; rb < RW; ++rb) {
-        rk[rb] = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.local_row0 + (rb0 + rb) * 16 + (l & 15)));
+    for (int rb = 0; rb < RB; ++rb) {
+        rk[rb] = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.local_row0 + rb * 16 + (l & 15)));
         keep[rb] = u32x4{~0u, ~0u, ~0u, ~0u};
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -137,62 +145,51 @@ __global__ void __launch_bounds__(C::THREADS) down_kernel(DownArgsOf<TB> p) {
     auto form_masks = [&](int t) {
         const uint32_t x0 = (uint32_t)((t * DOWN_SLABS + pos) * (BK / 2) + 16 * sub + 4 * (l >> 4)) * kGold;
 #pragma unroll
-        for (int rb = 0; rb < RW; ++rb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 keep[rb][i] = keep_pair_mask(hash_word_at(rk[rb], rk[rb].a + x0 + (uint32_t)i * kGold), th);
     };
     const int o = row_slab_off(l & 15, 4 * sub + (l >> 4));
-    const char* xs = smem + (pos * RB + rb0) * 2048 + o;
+    const char* xs = smem + pos * RB * 2048 + o;
     const char* as = smem + C::X_COPIES * 1024 + pos * (CB * 2048) + o;
 
     int ring = 0;
-    auto step = [&](int s, auto steady) {
+    for (int s = 0; s < nst; ++s) {
         if (T) form_masks(st);                          // while the stage's copies land
-        // the stage has landed for every wave, and every wave has left the stage that the next copies overwrite
-        if (steady() || s + NS - 2 < nst) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(P*(NS - 2)) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        asm volatile("s_barrier" ::: "memory");
-        u32x4 x[RW];
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        u32x4 x[RB];
         bf16x8 a[CB];
 #pragma unroll
-        for (int rb = 0; rb < RW; ++rb) x[rb] = *(const u32x4*)(xs + ring * C::STAGE + rb * 2048);
+        for (int rb = 0; rb < RB; ++rb) x[rb] = *(const u32x4*)(xs + ring * C::STAGE + rb * 2048);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) a[cb] = __builtin_bit_cast(bf16x8, *(const u32x4*)(as + ring * C::STAGE + cb * 2048));
         __builtin_amdgcn_sched_barrier(0);
-        if (steady()) {
-            issue(st_copy, ring == 0 ? NS - 1 : ring - 1);
-            advance(st_copy);
-        }
         if (st * DOWN_SLABS + pos < nslabs) {
 #pragma unroll
-            for (int rb = 0; rb < RW; ++rb) {
+            for (int rb = 0; rb < RB; ++rb) {
                 x[rb] &= keep[rb];
                 const bf16x8 xf = __builtin_bit_cast(bf16x8, x[rb]);
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    if (CB == 1 || cb < cbn)               // (blocks past the adapter's rank hold nothing that may be used)
-                        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[rb][cb]) : "v"(a[cb]), "v"(xf));
+                for (int cb = 0; cb < CB; ++cb)            // (the call's rank: columns past the adapter's are zeroed on the way out)
+                    asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[rb][cb]) : "v"(a[cb]), "v"(xf));
             }
         }
-        advance(st);
+        st = st + 1 == nst ? 0 : st + 1;
         ring = ring + 1 == NS ? 0 : ring + 1;
-    };
-    int s = 0;
-    for (; s + NS - 1 < nst; ++s) step(s, std::true_type{});
-    for (; s < nst; ++s) step(s, std::false_type{});
+    }
 
     asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
 #pragma unroll
-    for (int rb = 0; rb < RW; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+v"(acc[rb][cb]));
     __syncthreads();
     f32x4* red = (f32x4*)smem;                             // [DOWN_PARTS][RB][CB][64]
 #pragma unroll
-    for (int rb = 0; rb < RW; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) red[((part * RB + rb0 + rb) * CB + cb) * 64 + l] = acc[rb][cb];
+        for (int cb = 0; cb < CB; ++cb) red[((w * RB + rb) * CB + cb) * 64 + l] = acc[rb][cb];
     __syncthreads();
     down_store<CB, RB, C::THREADS>(p, rt, red);
 }
@@ -282,7 +279,7 @@ static hipError_t launch_down_cfg(const DownArgs& a, int tiles, hipStream_t st) 
             if (e != hipSuccess) return e;
             attr_set = true;
         }
-        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(C::THREADS), C::LDS, st, b);
+        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(C::THREADS + 64 * (C::XW + C::AW)), C::LDS, st, b);
         return hipGetLastError();
     });
 }
@@ -323,9 +320,9 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
     // r = 32: two of the 16-row workgroups fit on a compute unit, one of the 32-row ones (16 waves); in several rounds
     // that is worth more than the second reading of A up to K = 2048 (40000 rows: K = 1024 23 / 27 us, K = 4096 69 / 68 us).
     const bool small32 = forced ? forced == 128 : one_round || (many && a.K <= 2048);
-    if (a.r == 16) return small ? launch_down_cfg<Down<1, 1, 1, 5>>(a, tiles16, st) : launch_down_cfg<Down<1, 2, 1, 3>>(a, tiles32, st);
-    if (a.r == 32) return small32 ? launch_down_cfg<Down<2, 1, 1, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 2, 2, 4>>(a, tiles32, st);
-    if (a.r == 64) return small ? launch_down_cfg<Down<4, 1, 1, 4>>(a, tiles16, st) : launch_down_cfg<Down<4, 2, 2, 3>>(a, tiles32, st);
+    if (a.r == 16) return small ? launch_down_cfg<Down<1, 1, 5>>(a, tiles16, st) : launch_down_cfg<Down<1, 2, 3>>(a, tiles32, st);
+    if (a.r == 32) return small32 ? launch_down_cfg<Down<2, 1, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 2, 4>>(a, tiles32, st);
+    if (a.r == 64) return small ? launch_down_cfg<Down<4, 1, 4>>(a, tiles16, st) : launch_down_cfg<Down<4, 2, 3>>(a, tiles32, st);
     return hipErrorInvalidValue;
 }
 
