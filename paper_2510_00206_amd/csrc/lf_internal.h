@@ -217,8 +217,8 @@ inline int64_t max_stream_panels(int64_t M, int G) {
 }
 
 // `forced`: the row-tile knob as read by the entry point (0, 128 or 256).  The streaming launchers need
-// StreamArgs::panel_rows, the finalize launchers FinalizeArgs::panel_rows_db / _da, filled in by the caller (operation
-// (4) with DaPlan::direct needs no finalize launch).
+// StreamArgs::panel_rows, the finalize launchers FinalizeArgs::panel_rows_db / _da, filled in by the caller (strips that have
+// counters, or whole segments, need no finalize launch).
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st);
 hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st);
 hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st);
