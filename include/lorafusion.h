@@ -202,7 +202,7 @@ typedef enum {
     LORA_PROF_FWD_GEMM = 1,   /* operation (2): Y = X W + S' B                        */
     LORA_PROF_DS_DB = 2,      /* operation (3): dS and dB partials, or dS by itself   */
     LORA_PROF_FIN_DS_DB = 3,  /* fixed-order reduction of the dS / dB partials        */
-    LORA_PROF_DA = 4,         /* operation (4); dB too where (3) formed dS by itself   */
+    LORA_PROF_DA = 4,         /* operation (4), unless in the launch of (5); dB too where (3) formed dS by itself */
     LORA_PROF_FIN_DA = 5,     /* fixed-order reduction of the dA partials, if any     */
     LORA_PROF_DX_GEMM = 6,    /* operation (5): dX = dY W^T + mask*q*(dS A^T)         */
     LORA_PROF_KERNELS = 7

@@ -177,15 +177,16 @@ lora_status bwd_impl(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A,
         if (timed(LORA_PROF_DS_DB, st, [&] { return launch_stream_dsdb(s3, st); }) != hipSuccess) return LORA_ERR_HIP;
         if (timed(LORA_PROF_FIN_DS_DB, st, [&] { return launch_finalize_ds_db(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
     }
-    // (5) right after (3): it re-reads dY while that pass's copy still sits in the memory-side cache
-    if (dX) {
-        DxGemmArgs g5{dY, W, ws.dS, A, dX, (int)M, (int)K, (int)N, r, 0, 0, 0, tb};
-        if (timed(LORA_PROF_DX_GEMM, st, [&] { return launch_bwd_dx(g5, pl.forced, st); }) != hipSuccess) return LORA_ERR_HIP;
-    }
     StripArgs s4{{X, ws.dS, dA, ws.part_da, ws.counters, (int)K, pl.rows_da, 0, 0}, {}, 0, r, accumulate, tb};
     if (pl.split)
         s4.b = StripJob{dY, S, dB, ws.part_db, ws.counters + (pl.rows_da ? tb.G * (K / 64) : 0), (int)N, pl.rows_db, 0, 0};
-    if (timed(LORA_PROF_DA, st, [&] { return launch_strips(s4, st); }) != hipSuccess) return LORA_ERR_HIP;
+    // (5) right after (3): it re-reads dY while that pass's copy still sits in the memory-side cache
+    bool took_s4 = false;
+    if (dX) {
+        DxGemmArgs g5{dY, W, ws.dS, A, dX, (int)M, (int)K, (int)N, r, 0, 0, 0, tb};
+        if (timed(LORA_PROF_DX_GEMM, st, [&] { return launch_bwd_dx(g5, pl.forced, st, &s4, &took_s4); }) != hipSuccess) return LORA_ERR_HIP;
+    }
+    if (!took_s4 && timed(LORA_PROF_DA, st, [&] { return launch_strips(s4, st); }) != hipSuccess) return LORA_ERR_HIP;
     if (pl.rows_da && !ws.counters &&
         timed(LORA_PROF_FIN_DA, st, [&] { return launch_finalize_da(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
     return LORA_OK;

@@ -1084,6 +1084,13 @@ hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st) {
     return hipSuccess;
 }
 
+// (5) on tiles of 64 or 32 x 64 takes the strips of (4) (and dB) into its launch while all of them run at once, two workgroups to a
+// compute unit: a launch of few workgroups less, the strips in the shadow of the tiles.  Backward, us: 256 x 1024 x 1024, r = 16 15.2 -> 10.5;
+// 600 x 1024 x 1024 17.2 -> 11.1; 300 x 2048 x 2048 19.1 -> 13.7; 256 x 4096 x 4096 27.0 -> 23.2, r = 32 31.0 -> 26.7; 64 rows,
+// 14336 -> 4096 32.0 -> 28.4; 2500 rows, 320 -> 512 19.9 -> 14.9.  Not at r = 64, whose strips need more registers than two workgroups of
+// eight waves leave, nor on the larger tiles, of which one fills a compute unit's LDS.
+constexpr int kStripsBeside = 2 * kComputeUnits;
+
 static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t st) {
     a.tiles_n = (a.K + BN - 1) / BN;
     a.uniform_tiles = t.uniform;
@@ -1105,8 +1112,20 @@ static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t s
                   : launch_gemm(bwd_dx_kernel<4, false, 1>, attr_set[3], a, st);
 }
 
-hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st) {
+hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st, const StripArgs* strips, bool* took) {
     const GemmPlan t = plan_gemm(a.tb, a.M, a.N, a.K, a.r, forced);
+    if (strips && t.parts == 1 && t.part[0].kind >= 0 && ring_takes_strips(t.part[0].kind, a.r)) {
+        StripArgs s = *strips;
+        const hipError_t e = plan_strip_jobs(s);
+        if (e != hipSuccess) return e;
+        const GemmPart& part = t.part[0];
+        const int64_t tiles_n = (a.K + kRingTiles[part.kind][1] - 1) / kRingTiles[part.kind][1];
+        if (part.tiles_m * tiles_n + s.a.blocks + s.b.blocks <= kStripsBeside) {
+            *took = true;
+            return launch_ring_strips(part.kind, RingStripsArgs{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, (int)part.tiles_m, (int)tiles_n, part.row_lo,
+                                                                part.row_hi, s.a, s.b, s.b_first, s.accumulate, a.tb}, st);
+        }
+    }
     const RingArgs ring{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, 0, 0, 0, 0, a.tb};
     for (int i = 0; i < t.parts; ++i) {
         const hipError_t e = t.part[i].kind < 0 ? launch_dx_large(a, t, st) : launch_ring_part(t.part[i], true, ring, st);

@@ -16,9 +16,24 @@ struct RingArgsOf {
 };
 using RingArgs = RingArgsOf<AdapterTable>;
 
+// Operation (5) with (4), and dB if there is such a job, as further workgroups of the launch: the members of both.
+template <class TB>
+struct RingStripsArgsOf {
+    const lora_bf16* tok; const lora_bf16* out; const lora_bf16* ltok; const lora_bf16* lout; lora_bf16* res;
+    int M, KC, NC, r, tiles_m, tiles_n;
+    int row_lo, row_hi;
+    StripJob a, b;
+    int b_first, accumulate;
+    TB tb;
+};
+using RingStripsArgs = RingStripsArgsOf<AdapterTable>;
+
 constexpr int kRingKinds = 6;
 constexpr int kRingTiles[kRingKinds][2] = {{128, 256}, {128, 128}, {64, 128}, {64, 64}, {32, 64}, {128, 64}};   // rows x columns
 
 hipError_t launch_ring(int kind, bool col, const RingArgs& a, hipStream_t st);
+
+constexpr bool ring_takes_strips(int kind, int r) { return (kind == 3 || kind == 4) && (r == 16 || r == 32); }
+hipError_t launch_ring_strips(int kind, const RingStripsArgs& a, hipStream_t st);
 
 }  // namespace lf

@@ -25,6 +25,7 @@
 #include "lf_gemm_parts.h"
 #include "lf_gemm_ring.h"
 #include "lf_internal.h"
+#include "lf_strips.h"
 
 namespace lf {
 
@@ -106,13 +107,13 @@ struct RingCopies {
                                                const RingSource& lout, int nk, int nkt, uint32_t lds) {
         constexpr int NS = C::NS;
         uint32_t off[N];
-        auto slab = [&](int kt, int stage, auto form) {
+        auto slab = [&](int kt, int stage, auto form) {           // (first lane: an M0 value is scalar, whatever else the kernel holds)
             if (kt < nk) {
-                issue<form()>(w, tok, out, off, lds + stage * C::STAGE);
+                issue<form()>(w, tok, out, off, __builtin_amdgcn_readfirstlane(lds + stage * C::STAGE));
                 tok.biased += BK * 2;
                 out.biased += out_adv;
             } else if (kt < nkt) {
-                issue<true>(w, ltok, lout, off, lds + stage * C::STAGE);
+                issue<true>(w, ltok, lout, off, __builtin_amdgcn_readfirstlane(lds + stage * C::STAGE));
             }
         };
         slab(0, 0, std::true_type{});
@@ -251,10 +252,9 @@ __device__ __forceinline__ void ring_slab(f32x4 (&acc)[C::MI][C::NI], const Ring
     }
 }
 
-template <class C, bool COL, class TB>
-__global__ void __launch_bounds__(C::THREADS + 64 * C::CW) ring_gemm_kernel(RingArgsOf<TB> p) {
+template <class C, bool COL, class Args>
+__device__ __forceinline__ void ring_tile(const Args& p, char* smem) {
     constexpr int NS = C::NS, MI = C::MI, NI = C::NI;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     int tm, tn;
     tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
     RowTile rt;
@@ -435,6 +435,42 @@ __global__ void __launch_bounds__(C::THREADS + 64 * C::CW) ring_gemm_kernel(Ring
     }
 }
 
+template <class C, bool COL, class TB>
+__global__ void __launch_bounds__(C::THREADS + 64 * C::CW) ring_gemm_kernel(RingArgsOf<TB> p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    ring_tile<C, COL>(p, smem);
+}
+
+// (5) and the strips of (4) and dB, neither of which needs the other, in one launch of DA_THREADS a workgroup (rule and figures at
+// kStripsBeside); the waves that a tile has no work for end at once.  Bounded by the latency of one sweep over the contraction.
+template <class C, int CB, class TB>
+__global__ void __launch_bounds__(DA_THREADS, 4) ring_strips_kernel(RingStripsArgsOf<TB> p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int tiles = p.tiles_m * p.tiles_n;
+    if ((int)blockIdx.x >= tiles) {
+        strip_of<CB>(p, blockIdx.x - tiles, smem);
+        return;
+    }
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= C::NW + C::CW) return;
+    ring_tile<C, true>(p, smem);
+}
+
+template <class C, int CB>
+static hipError_t launch_ring_strips_t(const RingStripsArgs& a, hipStream_t st) {
+    static_assert(C::LDS >= strip_lds(CB) && C::THREADS + 64 * C::CW <= DA_THREADS, "a strip in a tile's LDS, a tile in a strip's threads");
+    return with_few(a, [&](const auto& b) {
+        constexpr auto kernel = ring_strips_kernel<C, CB, std::decay_t<decltype(b.tb)>>;
+        static bool attr_set = false;                  // one flag per instantiation
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(b.tiles_m * b.tiles_n + b.a.blocks + b.b.blocks)), dim3(DA_THREADS), C::LDS, st, b);
+        return hipGetLastError();
+    });
+}
+
 template <class C, bool COL>
 static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
@@ -457,16 +493,25 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
 // take 64 - 72 KB of LDS), one of the others.  Kind 5 is for launches of at most one workgroup per compute unit: the deeper
 // ring and the single pass over the weight pay when that comes from HBM (77 rows, 4096 -> 14336, weight not cached: 64 x 128
 // tiles 38 us, 128 x 64 tiles 32 us).
+using Ring64x64 = Ring<64, 64, 2, 2, 5, 2, 2>;
+using Ring32x64 = Ring<32, 64, 1, 2, 6, 1, 1>;
+
 template <bool COL>
 static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
     switch (kind) {
         case 0: return launch_ring_cfg<Ring<128, 256, 2, 4, 3, 0, 4>, COL>(a, st);
         case 1: return launch_ring_cfg<Ring<128, 128, 2, 2, 4, 2, 2>, COL>(a, st);
         case 2: return launch_ring_cfg<Ring<64, 128, 2, 4, 3, 1, 2>, COL>(a, st);
-        case 3: return launch_ring_cfg<Ring<64, 64, 2, 2, 5, 2, 2>, COL>(a, st);
-        case 4: return launch_ring_cfg<Ring<32, 64, 1, 2, 6, 1, 1>, COL>(a, st);
+        case 3: return launch_ring_cfg<Ring64x64, COL>(a, st);
+        case 4: return launch_ring_cfg<Ring32x64, COL>(a, st);
         case 5: return launch_ring_cfg<Ring<128, 64, 2, 2, 6, 2, 1>, COL>(a, st);
     }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_ring_strips(int kind, const RingStripsArgs& a, hipStream_t st) {
+    if (kind == 3) return a.r == 16 ? launch_ring_strips_t<Ring64x64, 1>(a, st) : launch_ring_strips_t<Ring64x64, 2>(a, st);
+    if (kind == 4) return a.r == 16 ? launch_ring_strips_t<Ring32x64, 1>(a, st) : launch_ring_strips_t<Ring32x64, 2>(a, st);
     return hipErrorInvalidValue;
 }
 
