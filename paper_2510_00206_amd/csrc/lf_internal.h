@@ -159,14 +159,36 @@ inline int stream_panel_rows(const AdapterTable& tb, int C, int forced) {
     return best;
 }
 
-// How the strips of operation (4), and of dB beside it, cut their rows.  A workgroup owns 64 columns of a panel and takes
-// about 1.3 us (dA: the mask) or 0.6 us (dB) per 256 rows, two of them on a compute unit as long as one after the other;
-// panels shorter than a segment leave an fp32 piece of r x 64 each, which the last workgroup of the strip adds: 2 us, and
-// 40 ns per panel and 1000 columns.  Height 0: whole segments, no pieces.  (dA, 8192 x 4096, r = 16: 2048-row panels 16 us, 512-row
-// panels 19 us, whole 43 us, as 64 workgroups; 5003 x 14336: whole 31 us, 512-row panels 34 us.)  The rule knows no rank, so
-// that adapters of any rank are summed alike.  The panels are never more than fill_panel_rows gives for the same
-// sizes, which is what the workspace provides for.
+// How operation (4) cuts its rows in a launch of its own.  A workgroup owns 64 columns of a panel and takes about 4 us + 1.3 us
+// per 256 rows, a few of them on every compute unit; panels shorter than a segment cost the sum over them (finalize launch:
+// 5 us) and an fp32 piece of r x K each.  Height 0: whole segments, no pieces.  (8192 x 4096, r = 16: 2048-row panels 16.7 us, 512-row
+// panels 18.6 us, whole 43 us, as 64 workgroups; 5003 x 14336: whole 31 us, 512-row panels 34 us.)  The rule counts whole rounds of
+// workgroups: one that prices their mean load instead makes taller panels, which chain more MFMAs on a sum (8192 x 26496, r = 16,
+// fp32 error against 64 bits: 1024-row panels 0.99e-7, whole segments 1.90e-7; 4096 x 20480 0.92e-7 / 1.34e-7) and run longer than
+// the rounds they save (6888 + 5702 rows x 4160, r = 16 29.7 -> 32.9 us).  It knows no rank, so that adapters of any rank are summed
+// alike.  The panels are never more than fill_panel_rows gives for the same sizes, which is what the workspace provides for.
+inline int plan_da(const AdapterTable& tb, int K, int forced) {
+    if (forced == 256) return fill_panel_rows(tb, K, forced);
+    const int64_t strips = K / 64;
+    const int longest = longest_panel(tb, 1 << 30);
+    auto cost = [&](int rows) {
+        const int64_t panels = rows ? count_panels(tb, rows) : tb.G;
+        const double rounds = (double)((panels * strips + kComputeUnits - 1) / kComputeUnits);
+        return 4.0 + rounds * 1.3 * (double)((longest_panel(tb, rows ? rows : 1 << 30) + 255) / 256) +
+               (rows ? 5.0 + 3.2e-5 * (double)(panels * K) : 0.0);
+    };
+    int best = 0, least = stream_panel_rows(tb, K, forced);
+    if (least < kRowTile) least = kRowTile;
+    for (int64_t h = least; h < longest; h <<= 1)
+        if (cost((int)h) < cost(best)) best = (int)h;
+    return best;
+}
+
+// ... and with the strips of dB beside it (split_ds_db): the two share the chip, two workgroups on a compute unit as long as
+// one after the other, at about 1.3 us (dA: the mask) or 0.6 us (dB) per 256 rows; the last workgroup of a strip adds its pieces: 2 us, and
+// 40 ns per panel and 1000 columns.
 constexpr int kLowestStripPanel = 512;               // (two rounds of a workgroup's eight 32-row blocks)
+constexpr double kDaBlock = 1.3, kDbBlock = 0.6;     // us per 256 rows
 struct StripLoad { double path, work; };           // us: the longest workgroup; all of them, per compute unit
 inline StripLoad strip_load(const AdapterTable& tb, int C, int rows, double us_per_block) {
     const int64_t panels = rows ? count_panels(tb, rows) : tb.G;
@@ -185,11 +207,6 @@ inline int plan_strips(const AdapterTable& tb, int C, double us_per_block, Strip
     for (int64_t h = least; h < longest && (h <= highest || best == 0); h <<= 1)
         if (cost((int)h) < cost(best) || (best == 0 && longest > highest)) best = (int)h;
     return best;
-}
-constexpr double kDaBlock = 1.3, kDbBlock = 0.6;   // us per 256 rows
-inline int plan_da(const AdapterTable& tb, int K, int forced) {
-    if (forced == 256) return fill_panel_rows(tb, K, forced);
-    return plan_strips(tb, K, kDaBlock, StripLoad{0, 0});
 }
 // dB: at most 1024 rows to a panel, that no wave chains more than a few MFMAs on one sum (fp32 error against 64 bits, 2999 x 4096,
 // r = 32: whole segments 1.21e-7, the one-pass form 1.09e-7).

@@ -87,3 +87,24 @@ def test_da_accumulates(rows):
         binding.lora_set_row_tile(0)
     assert torch.equal(got, base + dA)
     assert torch.equal(got[1], base[1]) and not dA[1].any()
+
+
+@pytest.mark.parametrize("M,K,bound", [(4096, 20480, 1.1e-7), (8192, 26496, 1.4e-7)])
+def test_da_rounding_error(M, K, bound):
+    """fp32 error of dA's sum over the rows.  B picks the first r columns of dY, so dS is dY[:, :r] exactly (s = 1, no dropout) and the
+    64-bit result has the same bf16 factors.  Bounds: between the error of the panels that plan_da states (0.92e-7, 0.99e-7) and
+    that of whole segments (1.34e-7, 1.90e-7), whose waves chain four and eight times the MFMAs on a sum."""
+    r, N = 16, 64
+    print(f"rounding error of dA {M} x {K}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    X = torch.randn((M, K), generator=gen, device="cuda").bfloat16()
+    dY = torch.randn((M, N), generator=gen, device="cuda").bfloat16()
+    W, A = torch.zeros((N, K), dtype=torch.bfloat16, device="cuda"), torch.zeros((r, K), dtype=torch.bfloat16, device="cuda")
+    B = torch.eye(N, r, device="cuda").bfloat16()
+    S = torch.zeros((M, r), dtype=torch.bfloat16, device="cuda")
+    dA = binding.lora_bwd(X, W, A, B, S, dY, 1.0, 0.0, 1, need_dx=False)[1]
+    want = torch.cat([dY[:, :r].double().t() @ X[:, k:k + 4096].double() for k in range(0, K, 4096)], dim=1)
+    err = float((dA.double() - want).norm() / want.norm())
+    print(f"{err:.3e}", flush=True)
+    assert err <= bound

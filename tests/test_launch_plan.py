@@ -89,6 +89,17 @@ def test_da_planes_stay_within_the_workspace():
     assert seen == {(0, True), (0, False), (128, True), (128, False), (256, False)}
 
 
+@pytest.mark.parametrize("lens,K,height", [((8192,), 26496, 1024), ((6144,), 26496, 2048), ((4096,), 20480, 1024), ((6200,), 8192, 1024),
+                                           ((6888, 5702), 4160, 1024), ((3712, 128, 1792), 8640, 512), ((6200,), 2048, 1024),
+                                           ((2048,), 960, 256), ((8192,), 4096, 2048), ((5003,), 14336, 0)], ids=str)
+def test_da_panel_heights(lens, K, height):
+    """Heights that the fp32 error and the times beside plan_da belong to: none taller, none of more rounds."""
+    binding.lora_set_row_tile(0)
+    off, rows = (C.c_int64 * (len(lens) + 1))(*_offsets(lens)), C.c_int32()
+    assert binding.load_library().lora_debug_da_panels(sum(lens), K, len(lens), off, C.byref(rows), C.byref(C.c_int64()), C.byref(C.c_int64())) == 0
+    assert rows.value == height
+
+
 def test_diagnostics_refuse_what_the_entry_points_refuse():
     off = (C.c_int64 * 2)(0, 64)
     f = lambda M, k, c, r, G, o: binding.load_library().lora_debug_gemm_tiles(
