@@ -137,12 +137,13 @@ size_t workspace_bytes_of(int64_t M, int64_t K, int64_t N, int32_t r, int32_t G)
     return carve(nullptr, M, K, N, r, tiles, tiles, stream_chunks(N)).bytes;
 }
 
-// What a call lays out in `bytes` of it: the planes that its launches write, and behind them the counters of the strips.
+// What a call lays out in `bytes` of it: the planes that its launches write, and behind them the counters of the strips where
+// those add their pieces themselves.
 Workspace lay_out(void* base, size_t bytes, int64_t M, int64_t K, int64_t N, int32_t r, const AdapterTable& tb, BwdPlan& pl) {
     Workspace w = carve(base, M, K, N, r, pl.rows_db ? count_panels(tb, pl.rows_db) : 0,
                         pl.rows_da ? count_panels(tb, pl.rows_da) : 0, pl.split ? 0 : stream_chunks(N));
     const int64_t n = tb.G * ((pl.rows_da ? K / 64 : 0) + (pl.split && pl.rows_db ? N / 64 : 0));
-    if (n && w.bytes + (size_t)n * 4 <= bytes) {
+    if (n && w.bytes + (size_t)n * 4 <= bytes && (pl.split || strips_add_pieces(tb, pl.rows_da, r))) {
         w.counters = (uint32_t*)((char*)base + w.bytes);
         w.n_counters = (int)n;
     } else if (pl.split) {

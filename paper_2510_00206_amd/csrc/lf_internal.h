@@ -184,6 +184,19 @@ inline int plan_da(const AdapterTable& tb, int K, int forced) {
     return best;
 }
 
+// Who adds the pieces of (4) in a launch of its own: the last workgroup of every strip, which saves the finalize launch (0.7 - 1.4 us of a
+// backward pass) but reads all its pieces alone, where that launch spreads them over the chip.  us that the finalize launch
+// takes longer, r = 16 and 32: 2 - 4 panels 0.7 - 1.1, 9 - 12 panels -0.1 - 1.1, 16 panels (4096 x 1024) -1.0, 32 panels (8192 x 512) -1.1; r = 64:
+// 2 panels 0.7, 4 panels -0.1, 9 panels -0.3, 16 panels -2.4, 32 panels -4.1.  The order of the sum is the same either way.
+inline bool strips_add_pieces(const AdapterTable& tb, int rows, int r) {
+    int most = 0;
+    for (int g = 0; rows && g < tb.G; ++g) {
+        const SegmentPanels sp = segment_panels(tb, rows, g);
+        if (sp.nreg + sp.has_long + sp.has_short > most) most = sp.nreg + sp.has_long + sp.has_short;
+    }
+    return most <= (r == 64 ? 3 : 12);
+}
+
 // ... and with the strips of dB beside it (split_ds_db): the two share the chip, two workgroups on a compute unit as long as
 // one after the other, at about 1.3 us (dA: the mask) or 0.6 us (dB) per 256 rows; the last workgroup of a strip adds its pieces: 2 us, and
 // 40 ns per panel and 1000 columns.

@@ -108,3 +108,35 @@ def test_da_rounding_error(M, K, bound):
     err = float((dA.double() - want).norm() / want.norm())
     print(f"{err:.3e}", flush=True)
     assert err <= bound
+
+
+# rows of the first segment, K: its panels, on both sides of the rule's 12 (r = 16 and 32) and 3 (r = 64)
+PIECES = {(3072, 4096): 3, (4352, 8192): 4, (6144, 1024): 12, (3328, 1024): 13, (4096, 512): 16}
+
+
+@pytest.mark.parametrize("rows,K", list(PIECES), ids=str)
+def test_pieces_added_either_way(rows, K):
+    """The sum over the panels by the last workgroup of a strip and by the finalize launch: an adapter of rank 16 has the same dA
+    whichever rank the call allocates, and with it whichever way the call takes; gradients are added to under accumulate."""
+    N, lens = 4160, (rows, 0, 40)                  # (N past the rule for dS by itself)
+    L = workloads.custom_layer(sum(lens), K, N, 64, 1.0, 0.1, seg_lens=lens, cfg=74)
+    print(f"pieces either way {L}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    new = lambda *shape: torch.randn(shape, generator=gen, device="cuda").mul_(0.05).bfloat16()
+    X, W, A, B, dY, S = new(L.M, K), new(N, K), new(3, 64, K), new(3, N, 64), new(L.M, N), new(L.M, 64)
+    s, p, o, out, launches = [L.s] * 3, [L.p] * 3, L.seg_offsets, [], []
+    for r in (16, 32, 64):
+        S[:, 16:] = 0
+        args = (X, W, A[:, :r].contiguous(), B[:, :, :r].contiguous(), S[:, :r].contiguous(), dY, o, s, p, L.seeds)
+        binding.profile_begin()
+        dA = binding.multi_lora_bwd(*args, need_dx=False, ranks=[16] * 3)[1]
+        launches.append(binding.profile_end()["finalize_da"][1])
+        base = torch.randn_like(dA)
+        got = base.clone()
+        binding.multi_lora_bwd(*args, need_dx=False, ranks=[16] * 3, dA=got, dB=torch.zeros(3, N, r, device="cuda"), accumulate=True)
+        torch.cuda.synchronize()
+        assert torch.equal(got, base + dA) and not dA[:, 16:].any() and not dA[1].any()
+        out.append(dA[:, :16])
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+    assert launches == [int(PIECES[rows, K] > most) for most in (12, 12, 3)]
