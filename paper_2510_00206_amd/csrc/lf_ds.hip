@@ -1,7 +1,8 @@
 // dS of operation (3) by itself (Section 5.1, FusedLoRA Design), for the launches whose pass over dY is short:
 //     dS[i,c] = s q sum_n dY[i,n] B[n,c]        (bf16, as operations (4) and (5) take it)
-// A workgroup owns 16 rows and sweeps all of N, so that dS leaves it finished: no partial sums and no second launch.  The
-// other half of the operation, dB, then runs beside operation (4) (lf_da.hip), whose strips read dY a second time.
+// A workgroup owns 16 rows (and of the rank's columns all, or a part: rule in launch_ds) and sweeps all of N, so that dS leaves
+// it finished: no partial sums and no second launch.  The other half of the operation, dB, then runs beside operation (4)
+// (lf_da.hip), whose strips read dY a second time.
 #include "lf_device.h"
 #include "lf_gemm_parts.h"
 #include "lf_internal.h"
@@ -10,13 +11,13 @@ namespace lf {
 
 constexpr int DS_ROWS = 16;
 
-// CB = r / 16; stages of SC columns of dY and as many rows of B, ring of NS stages in LDS.  A task is a quarter (128
+// CB * 16 of the call's RANK columns to a workgroup, PARTS workgroups to 16 rows; stages of SC columns of dY and as many rows of B, ring of NS stages in LDS.  A task is a quarter (128
 // columns) of a 512-column chunk by 16 columns of the rank, four MFMAs; there is a wave for every task of a stage.  CW more
 // waves do nothing but copy: a copy holds the wave that issues it up until the memory pipeline takes it, and forty of them a
 // stage, shared among the waves with the tasks, took longer than the tasks.
-template <int CB_, int SC_, int NS_, int CW_>
+template <int CB_, int SC_, int NS_, int CW_, int RANK_ = CB_ * 16>
 struct Ds {
-    static constexpr int CB = CB_, SC = SC_, NS = NS_, CW = CW_;
+    static constexpr int CB = CB_, SC = SC_, NS = NS_, CW = CW_, RANK = RANK_, PARTS = RANK / (CB * 16);
     static constexpr int QUARTERS = SC / 128, TASKS = QUARTERS * CB;
     static constexpr int Y_COPIES = SC * DS_ROWS * 2 / 1024, B_COPIES = SC * CB * 32 / 1024;   // 1 KB wave copies per stage
     static constexpr int P = (Y_COPIES + B_COPIES) / CW;                                        // ... per copying wave
@@ -41,19 +42,21 @@ __device__ __forceinline__ void ds_copy(const char* const (&src)[C::P], const ui
 // zero per quarter, ((q0 + q1) + q2) + q3 per chunk, then chunk by chunk; dS is the same bits either way.
 template <class C, class TB>
 __global__ void __launch_bounds__(C::THREADS) ds_kernel(DsArgsOf<TB> p) {
-    constexpr int CB = C::CB, SC = C::SC, NS = C::NS, P = C::P, R = CB * 16, RCH = CB * 2;
+    constexpr int CB = C::CB, SC = C::SC, NS = C::NS, P = C::P, R = C::RANK, RCH = CB * 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    for (int i = blockIdx.x * C::THREADS + threadIdx.x; i < p.n_zero; i += gridDim.x * C::THREADS) p.zero[i] = 0;
+    if (C::PARTS == 1 || blockIdx.y == 0)
+        for (int i = blockIdx.x * C::THREADS + threadIdx.x; i < p.n_zero; i += gridDim.x * C::THREADS) p.zero[i] = 0;
     RowTile rt;
     if (!find_row_tile(p.tb, DS_ROWS, blockIdx.x, rt)) return;
     f32x4* red = (f32x4*)(smem + NS * C::STAGE);
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = rt.g, cbn = p.tb.a[g].rank >> 4;        // 16-column blocks this adapter uses (<= CB)
+    const int c0 = C::PARTS == 1 ? 0 : blockIdx.y * (CB * 16);                   // this workgroup's first column of dS
+    const int g = rt.g, cbn = (p.tb.a[g].rank - c0) >> 4;  // 16-column blocks this adapter uses of them
     const int nst = (p.C + SC - 1) / SC;
     if (w >= C::TASKS) {                                  // a copying wave
         const int cw = w - C::TASKS;
         const char* dY = (const char*)(p.dY + (int64_t)rt.row_start * p.C) - kCopyBias;
-        const char* Bg = (const char*)(p.Bmat + (int64_t)g * p.C * R) - kCopyBias;
+        const char* Bg = (const char*)(p.Bmat + (int64_t)g * p.C * R + c0) - kCopyBias;
         const uint32_t m0 = lds_addr_of(smem) + cw * (P * 1024) + (P / 2) * 1024;
         // Its copies of a stage: dY first (rows past the tile repeat the last one), then B.  `cols`: the stage's columns;
         // copies past them repeat the last ones (never used).
@@ -160,15 +163,13 @@ __global__ void __launch_bounds__(C::THREADS) ds_kernel(DsArgsOf<TB> p) {
             u32x2 o;
             o.x = pack_bf16x2(total[0] * sq, total[1] * sq);
             o.y = pack_bf16x2(total[2] * sq, total[3] * sq);
-            *(u32x2*)(p.dS + (int64_t)(rt.row_start + (l & 15)) * R + cb * 16 + 4 * (l >> 4)) = o;
+            *(u32x2*)(p.dS + (int64_t)(rt.row_start + (l & 15)) * R + c0 + cb * 16 + 4 * (l >> 4)) = o;
         }
     }
 }
 
 template <class C>
-static hipError_t launch_ds_t(const DsArgs& a, hipStream_t st) {
-    int tiles = 0;
-    for (int g = 0; g < a.tb.G; ++g) tiles += (a.tb.row0[g + 1] - a.tb.row0[g] + DS_ROWS - 1) / DS_ROWS;
+static hipError_t launch_ds_t(const DsArgs& a, int tiles, hipStream_t st) {
     if (tiles == 0 && a.n_zero == 0) return hipSuccess;
     return with_few(a, [&](const auto& b) {
         constexpr auto kernel = ds_kernel<C, std::decay_t<decltype(b.tb)>>;
@@ -178,16 +179,25 @@ static hipError_t launch_ds_t(const DsArgs& a, hipStream_t st) {
             if (e != hipSuccess) return e;
             attr_set = true;
         }
-        hipLaunchKernelGGL(kernel, dim3(tiles ? tiles : 1), dim3(C::THREADS), C::LDS, st, b);
+        hipLaunchKernelGGL(kernel, dim3(tiles ? tiles : 1, C::PARTS), dim3(C::THREADS), C::LDS, st, b);
         return hipGetLastError();
     });
 }
 
 hipError_t launch_ds(const DsArgs& a, hipStream_t st) {
+    int tiles = 0;
+    for (int g = 0; g < a.tb.G; ++g) tiles += (a.tb.row0[g + 1] - a.tb.row0[g] + DS_ROWS - 1) / DS_ROWS;
+    // A workgroup is bound by its copies, four fifths of which are rows of B at r = 64 (0.6 us a stage of 256 columns): while
+    // all of them run at once, several share 16 rows, each with columns of its own.  With the strips after it, us, one workgroup / two /
+    // four: r = 64: 16 x 4096 x 4096 18.9 / 14.6 / 12.1 (one pass over dY 16.7), 1024 x 4096 x 4096 26.5 / 21.9 / 21.7, 2048 x 4096 x 4096
+    // 37.2 / 32.7 / - (35.1); r = 32: 16 x 4096 x 4096 12.9 / 10.7 (12.4), 2048 x 4096 x 4096 22.7 / 21.9.  Same bits.
     switch (a.r) {
-        case 16: return launch_ds_t<Ds<1, 512, 4, 8>>(a, st);
-        case 32: return launch_ds_t<Ds<2, 512, 3, 8>>(a, st);
-        case 64: return launch_ds_t<Ds<4, 256, 3, 8>>(a, st);
+        case 16: return launch_ds_t<Ds<1, 512, 4, 8>>(a, tiles, st);
+        case 32: return 2 * tiles <= kComputeUnits ? launch_ds_t<Ds<1, 512, 4, 8, 32>>(a, tiles, st) : launch_ds_t<Ds<2, 512, 3, 8>>(a, tiles, st);
+        case 64:
+            return 4 * tiles <= kComputeUnits   ? launch_ds_t<Ds<1, 512, 4, 8, 64>>(a, tiles, st)
+                   : 2 * tiles <= kComputeUnits ? launch_ds_t<Ds<2, 512, 3, 8, 64>>(a, tiles, st)
+                                                : launch_ds_t<Ds<4, 256, 3, 8>>(a, tiles, st);
     }
     return hipErrorInvalidValue;
 }

@@ -22,6 +22,13 @@ CASES = [
     (320, 576, 64, (1536, 1024)),                  # whole panels
     (64, 64, 32, (6143,)),
     (64, 64, 32, (6145,)),
+    # dS by four, two and one workgroups to 16 rows: 64 and 65, 128 and 129 groups of 16 rows
+    (64, 832, 64, (1024,)),
+    (64, 832, 64, (1000, 0, 17)),
+    (64, 576, 64, (2048,)),
+    (64, 576, 64, (2040, 9)),
+    (128, 576, 32, (2048,)),
+    (128, 576, 32, (2049,)),
 ]
 
 
@@ -66,3 +73,28 @@ def test_counters_ranks_and_accumulation(lens, ranks):
         assert not outs[0][1][g, ranks[g]:].any() and not outs[0][2][g, :, ranks[g]:].any()
         if o[g] == o[g + 1]:
             assert not outs[0][1][g].any() and not outs[0][2][g].any()
+
+
+@pytest.mark.parametrize("r,ranks", [(64, (16, 64, 32)), (32, (16, 32, 16))])
+def test_rank_parts_of_ds(r, ranks):
+    """Adapters below the call's rank where several workgroups share the columns of 16 rows: dX, dA and dB are those of the one-pass
+    form, and padding that holds non-finite values is not used."""
+    lens = (33, 100, 16)
+    L = workloads.custom_layer(sum(lens), 128, 1088, r, 1.0, 0.1, seg_lens=lens, cfg=94)
+    print(f"rank parts {L} {ranks}", flush=True)
+    X, W, A, B, dY = (t.cuda() for t in workloads.make_inputs(L))
+    for g, q in enumerate(ranks):
+        A[g, q:], B[g, :, q:] = float("nan"), float("inf")
+    s, p, o = [L.s] * L.G, [L.p] * L.G, L.seg_offsets
+    _, S = binding.multi_lora_fwd(X, W, A, B, o, s, p, L.seeds, ranks=ranks)
+    out = []
+    try:
+        for rows in (0, 256):
+            binding.lora_set_row_tile(rows)
+            out.append(binding.multi_lora_bwd(X, W, A, B, S, dY, o, s, p, L.seeds, ranks=ranks))
+    finally:
+        binding.lora_set_row_tile(0)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0]) and torch.isfinite(out[0][0].float()).all()
+    for a, b in zip(out[0][1:], out[1][1:]):           # (fp32 sums in another order, as above)
+        assert rel_err(a, f64(b)) <= 1e-5
