@@ -103,7 +103,7 @@ struct BwdPlan {
 BwdPlan plan_bwd(const AdapterTable& tb, int64_t M, int64_t K, int64_t N) {
     BwdPlan pl;
     pl.forced = forced_row_tile();
-    pl.split = split_ds_db((int)M, (int)N, (int)K, pl.forced);
+    pl.split = split_ds_db(tb, (int)M, (int)N, (int)K, pl.forced);
     pl.rows_da = pl.split ? plan_strips(tb, (int)K, kDaBlock, StripLoad{0, 0}) : plan_da(tb, (int)K, pl.forced);
     pl.rows_db = pl.split ? plan_db(tb, (int)N, (int)K, pl.rows_da) : stream_panel_rows(tb, (int)N, pl.forced);
     return pl;

@@ -228,12 +228,16 @@ inline int plan_db(const AdapterTable& tb, int N, int K, int rows_da) {
 }
 // Operation (3) as one pass over dY whose partial sums a second launch adds (lf_stream.hip), or as dS in one launch without
 // partial sums (lf_ds.hip) and dB as further strips beside (4), reading dY twice: the latter while the pass is bound by the
-// latency of its launches rather than by memory.  One workgroup sweeps all of N for dS, and the strips of (4) and dB
-// share the chip.  (3) and (4) together, us, one pass / split, K = 2048: r = 16: 64 x 256 10.4 / 7.1, 1024 x 1024 16.1 / 11.6,
-// 3000 x 4096 27.8 / 21.9, 6000 x 4096 35.8 / 34.5, 8192 x 4096 34.2 / 39.9, 64 x 8192 11.2 / 13.6; r = 64: 1024 x 4096
-// 33 / 26, 3000 x 4096 1.32 times, 64 x 6144 0.81 times; K = 8192, r = 64, 4096 x 2048: 0.93 times.
-inline bool split_ds_db(int M, int N, int K, int forced) {
-    return forced != 256 && N <= 4096 && M <= 6144 && (int64_t)M * K <= (24ll << 20);
+// latency of its launches rather than by memory, and dS's workgroups, one to 16 rows and a compute unit, run at once or sweep
+// short rows.  Backward without dX, times that the split is faster, r = 16 / 32 / 64, K = 1024: 1024 x 4096 1.26 / 1.49 / 1.54; 4096 x 3072
+// 1.13 / 1.21 / 0.98, 4096 x 4096 1.06 / 1.17 / 0.99; in two rounds: 5003 x 1024 1.42 / 1.39 / 1.28, 6144 x 1024 1.07 / 1.12 / 0.98,
+// 5003 x 2048 1.13 / 1.13 / 0.99, 6144 x 2048 1.04 / 1.04 / 0.89, 6144 x 4096 0.85 / 0.90 / 0.72.  K = 2048: 64 x 8192 0.82 (r = 16), 64 x 6144
+// 0.81 (r = 64).
+inline bool split_ds_db(const AdapterTable& tb, int M, int N, int K, int forced) {
+    if (forced == 256 || N > 4096 || M > 6144 || (int64_t)M * K > (24ll << 20)) return false;
+    int groups = 0;
+    for (int g = 0; g < tb.G; ++g) groups += (tb.row0[g + 1] - tb.row0[g] + 15) / 16;
+    return groups <= kComputeUnits || (int64_t)M * N <= (7ll << 20);
 }
 
 // Upper bound on the number of panels (planes of dA / dB partials) of any launch over M rows in G

@@ -98,3 +98,31 @@ def test_rank_parts_of_ds(r, ranks):
     assert torch.equal(out[0][0], out[1][0]) and torch.isfinite(out[0][0].float()).all()
     for a, b in zip(out[0][1:], out[1][1:]):           # (fp32 sums in another order, as above)
         assert rel_err(a, f64(b)) <= 1e-5
+
+
+# K, N, segments: whether dS goes by itself.  One round of its 16-row groups (256), or short sweeps (M N up to 7 Mi), up to 6144 rows
+ROUTES = [(64, 4096, (4096,), True), (64, 4096, (4097,), False), (64, 4096, (2049, 2040), False), (64, 1152, (6144,), True),
+          (64, 1216, (6144,), False), (64, 64, (6144,), True), (64, 64, (6145,), False), (64, 4160, (64,), False), (4096, 64, (6144,), True),
+          (4160, 64, (6144,), False)]
+
+
+@pytest.mark.parametrize("K,N,lens,alone", ROUTES, ids=str)
+def test_which_form(K, N, lens, alone):
+    L = workloads.custom_layer(sum(lens), K, N, 16, 1.5, 0.1, seg_lens=lens, cfg=95)
+    print(f"form of (3) {L}", flush=True)
+    X, W, A, B, dY = (t.cuda() for t in workloads.make_inputs(L))
+    S = torch.randn((L.M, L.r), device="cuda").bfloat16()
+    args = (X, W, A, B, S, dY, L.seg_offsets, [L.s] * L.G, [L.p] * L.G, L.seeds)
+    out, finalized = [], []
+    try:
+        for rows in (0, 256):
+            binding.lora_set_row_tile(rows)
+            binding.profile_begin()
+            out.append(binding.multi_lora_bwd(*args))
+            finalized.append(binding.profile_end()["finalize_ds_db"][1])
+    finally:
+        binding.lora_set_row_tile(0)
+    assert finalized == [int(not alone), 1]
+    assert torch.equal(out[0][0], out[1][0])
+    for a, b in zip(out[0][1:], out[1][1:]):           # (fp32 sums in another order, as above)
+        assert rel_err(a, f64(b)) <= 1e-5
