@@ -74,6 +74,39 @@ __device__ __forceinline__ bool find_row_tile(const TB& tb, int gran, int tile, 
     return false;
 }
 
+// The same, for a whole wave and from the full table: a lane for every adapter, a sum over the lanes.  Every wave of a workgroup walks the
+// table for itself, and the loop above is some ten scalar instructions an adapter on the one scalar unit of the compute
+// unit: with waves that only copy beside those that compute it cost 64 adapters more than their copying saves.
+template <class TB>
+__device__ __forceinline__ bool find_row_tile_by_lanes(const TB& tb, int gran, int tile, RowTile& rt, int row_lo = 0,
+                                                       int row_hi = 0x7FFFFFFF) {
+    if constexpr (sizeof(tb.a) / sizeof(tb.a[0]) <= kFewAdapters) {
+        return find_row_tile(tb, gran, tile, rt, row_lo, row_hi);
+    } else {
+        static_assert(sizeof(tb.a) / sizeof(tb.a[0]) <= 64, "a lane for every adapter");
+        const int l = threadIdx.x & 63, g0 = min(l, tb.G - 1);
+        const int first = tb.row0[g0], lo = max(first, row_lo), hi = min(tb.row0[g0 + 1], row_hi);
+        const int nt = l < tb.G ? max(hi - lo + gran - 1, 0) / gran : 0;
+        int sum = nt;                                        // of lanes 0 .. l: within rows of 16 lanes, then row 0 into 1 and 2 into 3, 1 into 2 and 3
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x111, 0xF, 0xF, false);
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x112, 0xF, 0xF, false);
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x114, 0xF, 0xF, false);
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x118, 0xF, 0xF, false);
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x142, 0xA, 0xF, false);
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x143, 0xC, 0xF, false);
+        const uint64_t past = __ballot(sum > tile);
+        if (past == 0) return false;
+        const int g = __builtin_ctzll(past);
+        auto of_g = [&](int v) { return __builtin_amdgcn_readlane(v, g); };
+        const int in_g = (tile - of_g(sum - nt)) * gran;
+        rt.g = g;
+        rt.row_start = of_g(lo) + in_g;
+        rt.rows = min(gran, of_g(hi) - rt.row_start);
+        rt.local_row0 = rt.row_start - of_g(first);
+        return true;
+    }
+}
+
 // Row panels of the streaming reductions (operations (3) and (4)).  A segment of length len holds
 // nf = len / gran full panels; a remainder is merged into the segment's last panel (a "long" panel of
 // fewer than 2*gran rows) or, when the segment is shorter than gran, forms one "short" panel.  Cutting

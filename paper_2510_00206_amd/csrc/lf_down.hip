@@ -109,7 +109,7 @@ __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel
     constexpr int CB = C::CB, RB = C::RB, NS = C::NS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     RowTile rt;
-    if (!find_row_tile(p.tb, 16 * RB, blockIdx.x, rt)) return;
+    if (!find_row_tile_by_lanes(p.tb, 16 * RB, blockIdx.x, rt)) return;
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = rt.g;
     const int nslabs = p.K / BK, nst = (nslabs + DOWN_SLABS - 1) / DOWN_SLABS;

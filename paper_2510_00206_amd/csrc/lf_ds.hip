@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(C::THREADS) ds_kernel(DsArgsOf<TB> p) {
     if (C::PARTS == 1 || blockIdx.y == 0)
         for (int i = blockIdx.x * C::THREADS + threadIdx.x; i < p.n_zero; i += gridDim.x * C::THREADS) p.zero[i] = 0;
     RowTile rt;
-    if (!find_row_tile(p.tb, DS_ROWS, blockIdx.x, rt)) return;
+    if (!find_row_tile_by_lanes(p.tb, DS_ROWS, blockIdx.x, rt)) return;
     f32x4* red = (f32x4*)(smem + NS * C::STAGE);
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c0 = C::PARTS == 1 ? 0 : blockIdx.y * (CB * 16);                   // this workgroup's first column of dS

@@ -258,7 +258,7 @@ __device__ __forceinline__ void ring_tile(const Args& p, char* smem) {
     int tm, tn;
     tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
     RowTile rt;
-    if (!find_row_tile(p.tb, C::TM, tm, rt, p.row_lo, p.row_hi)) return;
+    if (!find_row_tile_by_lanes(p.tb, C::TM, tm, rt, p.row_lo, p.row_hi)) return;
     const int c0 = tn * C::TN, cols_valid = min(C::TN, p.NC - c0);
     const int l = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w % C::WM, wn = w / C::WM;
