@@ -458,6 +458,7 @@ __global__ void __launch_bounds__(DA_THREADS, 4) ring_strips_kernel(RingStripsAr
 template <class C, int CB>
 static hipError_t launch_ring_strips_t(const RingStripsArgs& a, hipStream_t st) {
     static_assert(C::LDS >= strip_lds(CB) && C::THREADS + 64 * C::CW <= DA_THREADS, "a strip in a tile's LDS, a tile in a strip's threads");
+    static_assert(2 * C::LDS <= 160 * 1024, "two workgroups on a compute unit (kStripsBeside)");
     return with_few(a, [&](const auto& b) {
         constexpr auto kernel = ring_strips_kernel<C, CB, std::decay_t<decltype(b.tb)>>;
         static bool attr_set = false;                  // one flag per instantiation
@@ -490,11 +491,16 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
 
 
 // Which kernel of the family: see kRingTiles.  Two workgroups of kinds 2, 3 and 4 fit on a compute unit (their rings
-// take 64 - 72 KB of LDS), one of the others.  Kind 5 is for launches of at most one workgroup per compute unit: the deeper
+// take 64 - 80 KB of LDS), one of the others.  Kind 5 is for launches of at most one workgroup per compute unit: the deeper
 // ring and the single pass over the weight pay when that comes from HBM (77 rows, 4096 -> 14336, weight not cached: 64 x 128
 // tiles 38 us, 128 x 64 tiles 32 us).
-using Ring64x64 = Ring<64, 64, 2, 2, 5, 2, 2>;
+// Kind 4, us, two computing and two copying waves / four and three, (2): 26496 -> 960, 16 rows 59.4 / 54.4; 14336 -> 4096, 16 rows 33.6 / 31.2; 4096 ->
+// 4096 11.6 / 11.1; 1024 -> 1024 4.80 / 4.75.  Two and two / four and four, (5): contraction of 14336 to 4096 columns, 128 rows 41.8 / 40.6;
+// 8192 to 8192, 64 rows 28.1 / 27.2; 4096 to 4096, 128 rows 14.1 / 13.6; 1024 to 1024, 256 rows 4.70 / 4.78, 512 to 14336 3.79 / 3.94.
+// Kind 3, ring of five stages / four, (2): 4096 -> 4096, 160 rows 13.1 / 13.8; (5): 8192 to 8192, 100 rows 29.2 / 28.1, 128 rows 31.2 / 29.6.
+using Ring64x64 = Ring<64, 64, 2, 2, 5, 2, 2>;       // of the launches that take the strips
 using Ring32x64 = Ring<32, 64, 1, 2, 6, 1, 1>;
+constexpr int kLongContraction = 4096;
 
 template <bool COL>
 static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
@@ -502,8 +508,10 @@ static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
         case 0: return launch_ring_cfg<Ring<128, 256, 2, 4, 3, 0, 4>, COL>(a, st);
         case 1: return launch_ring_cfg<Ring<128, 128, 2, 2, 4, 2, 2>, COL>(a, st);
         case 2: return launch_ring_cfg<Ring<64, 128, 2, 4, 3, 1, 2>, COL>(a, st);
-        case 3: return launch_ring_cfg<Ring64x64, COL>(a, st);
-        case 4: return launch_ring_cfg<Ring32x64, COL>(a, st);
+        case 3: return launch_ring_cfg<Ring<64, 64, 2, 2, COL ? 4 : 5, 2, 2>, COL>(a, st);
+        case 4:
+            if (COL && a.KC < kLongContraction) return launch_ring_cfg<Ring32x64, COL>(a, st);
+            return launch_ring_cfg<Ring<32, 64, 2, 2, 6, COL ? 2 : 1, 2>, COL>(a, st);
         case 5: return launch_ring_cfg<Ring<128, 64, 2, 2, 6, 2, 1>, COL>(a, st);
     }
     return hipErrorInvalidValue;

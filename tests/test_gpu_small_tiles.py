@@ -108,3 +108,27 @@ def test_diverged_adapter_and_padding_stay_where_they_are(case, value):
             for name, a, b in zip(("Y", "S", "dX"), got, clean):
                 assert torch.equal(a[sl], b[sl]) and torch.isfinite(a[sl]).all(), (g, name)
             assert torch.equal(dA[g], clean[3][g]) and torch.equal(dB[g], clean[4][g]), g
+
+
+@pytest.mark.parametrize("N", [4032, 4096, 4160])
+@pytest.mark.parametrize("lens", [(1,), (33, 0, 31, 65)], ids=str)
+def test_wave_splits_of_32_row_tiles(N, lens):
+    """(5) over contractions on both sides of the one from which more waves share a 32 x 64 tile, with no strips in its launch (rank 64);
+    (2) the other way round; the frozen products."""
+    K = 320
+    print(f"wave splits {K} {N} {lens}", flush=True)
+    for k, n in ((K, N), (N, K)):
+        L = workloads.custom_layer(sum(lens), k, n, 64, 1.5, 0.25, seg_lens=lens, cfg=63)
+        inp = workloads.make_inputs(L)
+        X, W, dY = inp[0].cuda(), inp[1].cuda(), inp[4].cuda()
+        out = []
+        try:
+            for rows in (0, 256):
+                binding.lora_set_row_tile(rows)
+                out.append(dict(run_gpu(L, *inp), F=binding.frozen_fwd(X, W), D=binding.frozen_bwd(dY, W)))
+        finally:
+            binding.lora_set_row_tile(0)
+        assert binding.lora_debug_gemm_tiles(N, K, 64, L.seg_offsets) == [(32, 64, 0)]
+        for name in ("Y", "S", "dX", "F", "D"):
+            assert torch.equal(out[0][name], out[1][name]), (k, n, name)
+        compare({k: v for k, v in out[0].items() if k not in "FD"}, run_oracle(L, *inp), label=f"wave splits {k} {n} {lens}")
