@@ -151,11 +151,12 @@ lora_status lora_debug_mask(int64_t M, int64_t K, float p, uint64_t seed, uint8_
 
 /* Tuning knob and test hook (process-wide, not thread safe).  Several kernels exist in more than
  * one height: the GEMMs of operations (2) and (5) (Section 5.1) with 256 down to 32 token rows per output
- * tile, the down-projection of operation (1) with 32 or 16 token rows per workgroup, operation (3) with row
- * panels of 1024 down to 64 rows, and operation (4) with whole segments or row panels of 256 rows and more.
+ * tile, the down-projection of operation (1) with 32 or 16 token rows per workgroup, operation (3) as one pass with row
+ * panels of 1024 down to 64 rows or, in batches of up to 6144 rows, as dS by itself and dB beside (4), and operation
+ * (4) with whole segments or row panels of 256 rows (beside dB 512) and more.
  * By default every launch picks the height that fills the chip better (the small ones for short batches and
  * narrow projections; a GEMM may take two launches of different heights).  rows = 256 fixes the large height
- * of the GEMMs and of (1) and panels of at least 256 rows in (3) and (4) for all later calls, rows = 128
+ * of the GEMMs and of (1), one pass in (3) and panels of at least 256 rows in (3) and (4) for all later calls, rows = 128
  * GEMM tiles of 128 rows x 256 columns and the small height of (1), rows = 0 restores the automatic choice;
  * any other value returns LORA_ERR_PARAM.  Y, S_saved and dX are bit-identical under all three settings; dA
  * and dB are fp32 sums over the row panels and agree up to the order of those sums. */
@@ -169,18 +170,32 @@ lora_status lora_set_row_tile(int32_t rows);
  * is bit-identical under all three settings. */
 lora_status lora_set_slab_lookahead(int32_t slabs);
 
-/* Diagnostic (host only, nothing is enqueued): the row-panel height the streaming reduction of operation
- * (3) (Section 5.1) would choose for an activation of C columns over these segments under the current
- * lora_set_row_tile setting, the number of panels that gives (each leaves one fp32 plane of partial dB in the workspace), and the number of planes lora_bwd_workspace_bytes provides for.  seg_offsets: host,
- * G+1 entries rising from 0 to M. */
+/* Diagnostic (host only, nothing is enqueued): the row-panel height that operation (3) (Section 5.1) would choose as one pass
+ * over dY (the form of larger batches: lora_debug_bwd_plan) for an activation of C columns over these segments under the
+ * current lora_set_row_tile setting, the number of panels that gives (each leaves one fp32 plane of partial dB in the
+ * workspace), and the number of planes lora_bwd_workspace_bytes provides for.  seg_offsets: host, G+1 entries rising from 0 to M. */
 lora_status lora_debug_stream_panels(int64_t M, int64_t C, int32_t G, const int64_t* seg_offsets,
                                      int32_t* panel_rows, int64_t* panels, int64_t* panels_bound);
 
-/* Diagnostic (host only): how operation (4) would cut its rows for an input of K columns over these segments.  *panel_rows = 0:
- * one panel per segment, no partial sums; otherwise panels of that height, *panels fp32 partial sums in the
- * workspace.  panels_bound as in lora_debug_stream_panels. */
+/* Diagnostic (host only): how operation (4) would cut its rows in a launch of its own, after (3) as one pass over dY, for an
+ * input of K columns over these segments.  *panel_rows = 0: one panel per segment, no partial sums; otherwise panels of that
+ * height, *panels fp32 partial sums in the workspace.  panels_bound as in lora_debug_stream_panels. */
 lora_status lora_debug_da_panels(int64_t M, int64_t K, int32_t G, const int64_t* seg_offsets,
                                  int32_t* panel_rows, int64_t* panels, int64_t* panels_bound);
+
+/* Diagnostic (host only): what a backward call of these sizes would launch under the current lora_set_row_tile setting.
+ * scratch: bytes it may lay its partial sums out in, 0 for those of lora_bwd_workspace_bytes (lora_bwd_noalloc has
+ * LORA_NOALLOC_SCRATCH_BYTES).  need_dx = 0: no operation (5). */
+typedef struct {
+    int32_t ds_alone;         /* 1: operation (3) forms dS by itself and dB goes beside (4); 0: one pass over dY */
+    int32_t panel_rows_db;    /* row panels of dB and dA; 0: whole segments, no partial sums */
+    int32_t panel_rows_da;
+    int32_t added_in_strips;  /* 1: the last workgroup of a strip adds its partial sums; 0: a finalize launch does (if there are any) */
+    int32_t with_dx;          /* 1: (4), and dB beside it, run in the launch of (5) */
+    int64_t bytes;            /* of the scratch that the call writes */
+} lora_bwd_plan;
+lora_status lora_debug_bwd_plan(int64_t M, int64_t K, int64_t N, int32_t r, int32_t G, const int64_t* seg_offsets,
+                                int32_t need_dx, size_t scratch, lora_bwd_plan* plan);
 
 /* Diagnostic (host only): the output tiles that a GEMM over `contraction` elements to `columns` columns (operation (2):
  * K, N; operation (5): N, K) would run with under the current lora_set_row_tile setting; r = 0: no LoRA term.  *parts launches

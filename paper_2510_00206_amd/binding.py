@@ -19,10 +19,16 @@ LIB_PATH = os.path.join(_HERE, "liblorafusion_hip.so")
 EXPORTS = ("lora_fwd", "lora_bwd", "lora_bwd_noalloc", "multi_lora_fwd", "multi_lora_bwd", "multi_lora_fwd_ranked",
            "multi_lora_bwd_ranked", "lora_bwd_workspace_bytes",
            "lora_debug_mask", "lora_status_string", "lora_version", "lora_set_row_tile", "lora_set_slab_lookahead", "lora_debug_stream_panels",
-           "lora_debug_da_panels", "lora_debug_gemm_tiles",
+           "lora_debug_da_panels", "lora_debug_bwd_plan", "lora_debug_gemm_tiles",
            "lora_unfused_fwd", "lora_unfused_bwd", "lora_unfused_workspace_bytes")
 
 _lib = None
+
+
+class BwdPlan(C.Structure):
+    """What a backward call launches (lora_bwd_plan in the header)."""
+    _fields_ = [("ds_alone", C.c_int32), ("panel_rows_db", C.c_int32), ("panel_rows_da", C.c_int32), ("added_in_strips", C.c_int32),
+                ("with_dx", C.c_int32), ("bytes", C.c_int64)]
 
 
 def load_library() -> C.CDLL:
@@ -70,6 +76,8 @@ def load_library() -> C.CDLL:
     for f in ("lora_debug_stream_panels", "lora_debug_da_panels"):
         getattr(lib, f).argtypes = [I64, I64, I32, C.POINTER(I64), C.POINTER(I32), C.POINTER(I64), C.POINTER(I64)]
         getattr(lib, f).restype = C.c_int
+    lib.lora_debug_bwd_plan.argtypes = [I64, I64, I64, I32, I32, C.POINTER(I64), I32, SZ, C.POINTER(BwdPlan)]
+    lib.lora_debug_bwd_plan.restype = C.c_int
     lib.lora_profile_end.argtypes = [C.POINTER(F), C.POINTER(I32)]
     lib.lora_ceiling_mfma.argtypes = [P, P, I32, I32, I32, C.POINTER(C.c_double), P]
     lib.lora_ceiling_mfma.restype = C.c_int
@@ -218,6 +226,14 @@ def lora_debug_gemm_tiles(contraction, columns, r, seg_offsets):
     _check(load_library().lora_debug_gemm_tiles(seg_offsets[-1], contraction, columns, r, G, _arr(C.c_int64, seg_offsets),
                                                 C.byref(parts), rows, cols, first))
     return [(rows[i], cols[i], first[i]) for i in range(parts.value)]
+
+
+def lora_debug_bwd_plan(K, N, r, seg_offsets, need_dx=True, scratch=0) -> BwdPlan:
+    """What a backward over these segments would launch (host only); scratch: bytes for its partial sums, 0 = the workspace's."""
+    plan = BwdPlan()
+    _check(load_library().lora_debug_bwd_plan(seg_offsets[-1], K, N, r, len(seg_offsets) - 1, _arr(C.c_int64, seg_offsets), int(need_dx),
+                                              scratch, C.byref(plan)))
+    return plan
 
 
 def lora_set_row_tile(rows: int):

@@ -152,6 +152,15 @@ Workspace lay_out(void* base, size_t bytes, int64_t M, int64_t K, int64_t N, int
     return w;
 }
 
+// Operation (4), and dB beside it where (3) forms dS by itself.
+StripArgs strip_args(const lora_bf16* X, const lora_bf16* S, const lora_bf16* dY, int64_t K, int64_t N, int32_t r, const AdapterTable& tb,
+                     float* dA, float* dB, int accumulate, const Workspace& ws, const BwdPlan& pl) {
+    StripArgs s{{X, ws.dS, dA, ws.part_da, pl.rows_da ? ws.counters : nullptr, (int)K, pl.rows_da, 0, 0}, {}, 0, r, accumulate, tb};
+    if (pl.split)
+        s.b = StripJob{dY, S, dB, ws.part_db, pl.rows_db ? ws.counters + (pl.rows_da ? tb.G * (K / 64) : 0) : nullptr, (int)N, pl.rows_db, 0, 0};
+    return s;
+}
+
 lora_status fwd_impl(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A, const lora_bf16* B,
                      int64_t M, int64_t K, int64_t N, int32_t r, const AdapterTable& tb,
                      lora_bf16* Y, lora_bf16* S, hipStream_t st) {
@@ -178,9 +187,7 @@ lora_status bwd_impl(const lora_bf16* X, const lora_bf16* W, const lora_bf16* A,
         if (timed(LORA_PROF_DS_DB, st, [&] { return launch_stream_dsdb(s3, st); }) != hipSuccess) return LORA_ERR_HIP;
         if (timed(LORA_PROF_FIN_DS_DB, st, [&] { return launch_finalize_ds_db(fin, st); }) != hipSuccess) return LORA_ERR_HIP;
     }
-    StripArgs s4{{X, ws.dS, dA, ws.part_da, ws.counters, (int)K, pl.rows_da, 0, 0}, {}, 0, r, accumulate, tb};
-    if (pl.split)
-        s4.b = StripJob{dY, S, dB, ws.part_db, ws.counters + (pl.rows_da ? tb.G * (K / 64) : 0), (int)N, pl.rows_db, 0, 0};
+    const StripArgs s4 = strip_args(X, S, dY, K, N, r, tb, dA, dB, accumulate, ws, pl);
     // (5) right after (3): it re-reads dY while that pass's copy still sits in the memory-side cache
     bool took_s4 = false;
     if (dX) {
@@ -365,6 +372,25 @@ lora_status lora_debug_da_panels(int64_t M, int64_t K, int32_t G, const int64_t*
     *panel_rows = plan_da(tb, (int)K, forced_row_tile());
     *panels = *panel_rows ? count_panels(tb, *panel_rows) : 0;
     *panels_bound = max_stream_panels(M, G);
+    return LORA_OK;
+}
+
+lora_status lora_debug_bwd_plan(int64_t M, int64_t K, int64_t N, int32_t r, int32_t G, const int64_t* seg_offsets, int32_t need_dx,
+                                size_t scratch, lora_bwd_plan* plan) {
+    if (!seg_offsets || !plan) return LORA_ERR_NULL;
+    lora_status st = check_shape(M, K, N, r, G);
+    if (st != LORA_OK) return st;
+    AdapterTable tb;
+    st = segments_only(tb, M, K, G, seg_offsets);
+    if (st != LORA_OK) return st;
+    BwdPlan pl = plan_bwd(tb, M, K, N);
+    alignas(256) char base[256];                       // (addresses only: nothing is read or written through them)
+    const lora_bf16* any = (const lora_bf16*)base;
+    const Workspace ws = lay_out(base, scratch ? scratch : workspace_bytes_of(M, K, N, r, G), M, K, N, r, tb, pl);
+    *plan = lora_bwd_plan{pl.split, pl.rows_db, pl.rows_da, ws.counters != nullptr,
+                          need_dx && dx_takes_strips(tb, (int)M, (int)N, (int)K, r, pl.forced,
+                                                     strip_args(any, any, any, K, N, r, tb, (float*)base, (float*)base, 0, ws, pl)),
+                          (int64_t)(ws.bytes + (size_t)ws.n_counters * 4)};
     return LORA_OK;
 }
 

@@ -1091,6 +1091,18 @@ hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st) {
 // eight waves leave, nor on the larger tiles, of which one fills a compute unit's LDS.
 constexpr int kStripsBeside = 2 * kComputeUnits;
 
+static int ring_columns(const GemmPart& part, int K) { return (K + kRingTiles[part.kind][1] - 1) / kRingTiles[part.kind][1]; }
+
+static bool strips_fit(const GemmPlan& t, int K, int r, const StripArgs& s) {
+    const GemmPart& part = t.part[0];
+    return t.parts == 1 && part.kind >= 0 && ring_takes_strips(part.kind, r) &&
+           part.tiles_m * ring_columns(part, K) + s.a.blocks + s.b.blocks <= kStripsBeside;
+}
+
+bool dx_takes_strips(const AdapterTable& tb, int M, int N, int K, int r, int forced, StripArgs s) {
+    return plan_strip_jobs(s) == hipSuccess && strips_fit(plan_gemm(tb, M, N, K, r, forced), K, r, s);
+}
+
 static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t st) {
     a.tiles_n = (a.K + BN - 1) / BN;
     a.uniform_tiles = t.uniform;
@@ -1114,15 +1126,14 @@ static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t s
 
 hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st, const StripArgs* strips, bool* took) {
     const GemmPlan t = plan_gemm(a.tb, a.M, a.N, a.K, a.r, forced);
-    if (strips && t.parts == 1 && t.part[0].kind >= 0 && ring_takes_strips(t.part[0].kind, a.r)) {
+    if (strips) {
         StripArgs s = *strips;
         const hipError_t e = plan_strip_jobs(s);
         if (e != hipSuccess) return e;
-        const GemmPart& part = t.part[0];
-        const int64_t tiles_n = (a.K + kRingTiles[part.kind][1] - 1) / kRingTiles[part.kind][1];
-        if (part.tiles_m * tiles_n + s.a.blocks + s.b.blocks <= kStripsBeside) {
+        if (strips_fit(t, a.K, a.r, s)) {
+            const GemmPart& part = t.part[0];
             *took = true;
-            return launch_ring_strips(part.kind, RingStripsArgs{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, (int)part.tiles_m, (int)tiles_n, part.row_lo,
+            return launch_ring_strips(part.kind, RingStripsArgs{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, (int)part.tiles_m, ring_columns(part, a.K), part.row_lo,
                                                                 part.row_hi, s.a, s.b, s.b_first, s.accumulate, a.tb}, st);
         }
     }

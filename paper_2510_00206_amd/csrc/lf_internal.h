@@ -263,6 +263,7 @@ hipError_t launch_finalize_da(const FinalizeArgs& a, hipStream_t st);
 hipError_t plan_strip_jobs(StripArgs& a);           // the members that the launcher sets
 // `strips`: what the call will launch next; *took: it went into the GEMM's launch
 hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st, const StripArgs* strips = nullptr, bool* took = nullptr);
+bool dx_takes_strips(const AdapterTable& tb, int M, int N, int K, int r, int forced, StripArgs strips);   // ... whether it would
 
 // The output tiles of a GEMM's one or two launches (returns how many), as launch_fwd_gemm and launch_bwd_dx choose them.
 struct GemmTile { int rows, columns, first_row; };

@@ -1,6 +1,6 @@
 """Operations (1) and (4) at the edges of their tilings: rows around the 16- and 32-row blocks and the 256 rows that the
 waves of a workgroup walk together, contractions that end inside a 256-column stage, empty segments, ranks below the
-allocated one, no dropout, gradients written by the kernel itself and through partial planes, accumulation."""
+allocated one, no dropout, gradients written by the kernel itself, through pieces and through partial planes, accumulation."""
 import pytest
 import torch
 
@@ -67,15 +67,17 @@ def test_down_projection_same_bits_by_every_route(K, r, rows):
         assert rel_err(S[o[g]:o[g + 1]], s[g] * Sg) <= TOL
 
 
-@pytest.mark.parametrize("rows", [0, 256], ids=["whole", "planes"])
-def test_da_accumulates(rows):
-    """accumulate adds to what dA holds; an empty segment's gradient stays untouched."""
-    L = workloads.custom_layer(700, 192, 128, 16, 1.0, 0.1, seg_lens=(300, 0, 400), cfg=72)
+@pytest.mark.parametrize("rows,lens,added", [(0, (300, 0, 400), 0), (256, (300, 0, 400), 1), (256, (48, 5), 0)], ids=["whole", "counters", "planes"])
+def test_da_accumulates(rows, lens, added):
+    """accumulate adds to what dA holds; an empty segment's gradient stays untouched.  "planes": no room for counters, finalize launch."""
+    L = workloads.custom_layer(sum(lens), 192, 128, 16, 1.0, 0.1, seg_lens=lens, cfg=72)
     X, W, A, B, dY = (t.cuda() for t in workloads.make_inputs(L))
     s, p = [L.s] * L.G, [L.p] * L.G
     print(f"accumulate rows={rows}", flush=True)
     binding.lora_set_row_tile(rows)
     try:
+        plan = binding.lora_debug_bwd_plan(L.K, L.N, L.r, L.seg_offsets)
+        assert (plan.panel_rows_da, plan.added_in_strips) == (rows, added)
         _, S = binding.multi_lora_fwd(X, W, A, B, L.seg_offsets, s, p, L.seeds)
         args = (X, W, A, B, S, dY, L.seg_offsets, s, p, L.seeds)
         _, dA, _ = binding.multi_lora_bwd(*args)
@@ -86,7 +88,9 @@ def test_da_accumulates(rows):
     finally:
         binding.lora_set_row_tile(0)
     assert torch.equal(got, base + dA)
-    assert torch.equal(got[1], base[1]) and not dA[1].any()
+    for g in range(L.G):
+        if lens[g] == 0:
+            assert torch.equal(got[g], base[g]) and not dA[g].any()
 
 
 @pytest.mark.parametrize("M,K,bound", [(4096, 20480, 1.1e-7), (8192, 26496, 1.4e-7)])

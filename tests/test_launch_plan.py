@@ -100,6 +100,52 @@ def test_da_panel_heights(lens, K, height):
     assert rows.value == height
 
 
+def _noalloc_accepts(M, K, N, r):
+    """The documented limit of the allocation-free backward: dS, its partial sums and a plane per panel of the fill rule."""
+    def planes(C):
+        h = 1024
+        while h > 64 and _panels([M], h) * ((C + 511) // 512) < 224:
+            h //= 2
+        return _panels([M], h)
+    up = lambda v: (v + 255) // 256 * 256
+    return up(2 * M * r) + up(4 * M * r * ((N + 511) // 512)) + up(4 * planes(N) * r * N) + up(4 * planes(K) * r * K) <= binding.NOALLOC_SCRATCH_BYTES
+
+
+def test_backward_plan_stays_within_the_scratch():
+    """Partial sums and counters of any backward fit what the workspace query provides for; dB's strips, which nothing else adds,
+    always have their counters; the allocation-free call sums over the same panels as the one with a workspace."""
+    binding.lora_set_row_tile(0)
+    rnd = random.Random(11)
+    seen = set()
+    for it in range(4000):
+        G = 1 if it % 2 else rnd.choice((2, 5, 20, 64))
+        lens = [int(2 ** rnd.uniform(0, 13.5)) // (1 if G < 5 else G // 4) for _ in range(G)]
+        K, N = (64 * int(2 ** rnd.uniform(0, 9)) for _ in range(2))
+        r, off = rnd.choice((16, 32, 64)), _offsets(lens)
+        for rows in (0, 256):
+            binding.lora_set_row_tile(rows)
+            plan = binding.lora_debug_bwd_plan(K, N, r, off)
+            assert plan.bytes <= binding.workspace_bytes(sum(lens), K, N, r, G), (lens, K, N, r)
+            assert plan.added_in_strips or not (plan.ds_alone and (plan.panel_rows_db or plan.panel_rows_da)), (lens, K, N, r)
+            assert not (rows and plan.ds_alone)
+            seen.add((plan.ds_alone, plan.added_in_strips, plan.with_dx))
+            if G == 1 and rows == 0 and _noalloc_accepts(lens[0], K, N, r):
+                other = binding.lora_debug_bwd_plan(K, N, r, off, scratch=binding.NOALLOC_SCRATCH_BYTES)
+                assert other.bytes <= binding.NOALLOC_SCRATCH_BYTES
+                for f in ("ds_alone", "panel_rows_db", "panel_rows_da"):
+                    assert getattr(plan, f) == getattr(other, f), (f, lens, K, N, r)
+    binding.lora_set_row_tile(0)
+    assert seen >= {(1, 1, 0), (1, 0, 0), (1, 0, 1), (1, 1, 1), (0, 1, 0), (0, 0, 0), (0, 0, 1)}, seen
+
+
+def test_finalize_launch_where_the_counters_do_not_fit():
+    """Fewer than 64 rows with the large heights fixed leave no room behind the planes."""
+    binding.lora_set_row_tile(256)
+    plan = binding.lora_debug_bwd_plan(320, 64, 16, [0, 48, 53])
+    binding.lora_set_row_tile(0)
+    assert (plan.ds_alone, plan.panel_rows_da, plan.added_in_strips) == (0, 256, 0)
+
+
 def test_diagnostics_refuse_what_the_entry_points_refuse():
     off = (C.c_int64 * 2)(0, 64)
     f = lambda M, k, c, r, G, o: binding.load_library().lora_debug_gemm_tiles(
@@ -108,4 +154,7 @@ def test_diagnostics_refuse_what_the_entry_points_refuse():
             f(64, 64, 64, 8, 1, off), f(128, 64, 64, 16, 1, off), f(64, 64, 64, 16, 65, off)] == [0, 1, 2, 7, 7, 5, 7]
     g = lambda M, K, G, o: binding.load_library().lora_debug_da_panels(
         M, K, G, o, C.byref(C.c_int32()), C.byref(C.c_int64()), C.byref(C.c_int64()))
+    h = lambda M, K, N, r, G, o: binding.load_library().lora_debug_bwd_plan(M, K, N, r, G, o, 1, 0, C.byref(binding.BwdPlan()))
+    assert [h(64, 64, 64, 16, 1, off), h(64, 64, 64, 16, 1, None), h(64, 0, 64, 16, 1, off), h(64, 96, 64, 16, 1, off), h(64, 64, 64, 8, 1, off),
+            h(128, 64, 64, 16, 1, off), h(64, 64, 64, 16, 65, off)] == [0, 1, 2, 7, 7, 5, 7]
     assert [g(64, 64, 1, off), g(64, 64, 1, None), g(-1, 64, 1, off), g(128, 64, 1, off), g(64, 64, 65, off)] == [0, 1, 2, 5, 7]
