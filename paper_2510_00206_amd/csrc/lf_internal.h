@@ -221,10 +221,18 @@ inline int plan_strips(const AdapterTable& tb, int C, double us_per_block, Strip
         if (cost((int)h) < cost(best) || (best == 0 && longest > highest)) best = (int)h;
     return best;
 }
-// dB: at most 1024 rows to a panel, that no wave chains more than a few MFMAs on one sum (fp32 error against 64 bits, 2999 x 4096,
-// r = 32: whole segments 1.21e-7, the one-pass form 1.09e-7).
+// dB: panels of at most 1024 rows, 1792 with a remainder where that is the whole segment (a remainder joins the last panel), that no
+// wave chains more MFMAs on one sum than costs precision: fp32 error against 64 bits, 4096 columns, in panels of 512 rows and more / one panel /
+// the one-pass form: 1800 rows 0.75e-7 / 0.93e-7 / 0.94e-7, 2047 rows 0.77e-7 / 0.98e-7 / 0.96e-7; 2999 rows, 1024 + 1975 0.94e-7, whole 1.21e-7,
+// one pass 1.09e-7.  (2047 x 4096 x 4096 without dX, r = 16 19.0 -> 19.9 us, r = 64 27.4 -> 30.5; one pass 29.2, 44.5.)
 inline int plan_db(const AdapterTable& tb, int N, int K, int rows_da) {
-    return plan_strips(tb, N, kDbBlock, strip_load(tb, K, rows_da, kDaBlock), 1024);
+    const int h = plan_strips(tb, N, kDbBlock, strip_load(tb, K, rows_da, kDaBlock), 1024);
+    bool whole_too_long = false;
+    for (int g = 0; h == 1024 && g < tb.G; ++g) {
+        const int len = tb.row0[g + 1] - tb.row0[g];
+        whole_too_long |= len > 1792 && len < 2048;
+    }
+    return whole_too_long && fill_panel_rows(tb, N, 0) <= kLowestStripPanel ? kLowestStripPanel : h;
 }
 // Operation (3) as one pass over dY whose partial sums a second launch adds (lf_stream.hip), or as dS in one launch without
 // partial sums (lf_ds.hip) and dB as further strips beside (4), reading dY twice: the latter while the pass is bound by the

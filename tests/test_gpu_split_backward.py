@@ -126,3 +126,18 @@ def test_which_form(K, N, lens, alone):
     assert torch.equal(out[0][0], out[1][0])
     for a, b in zip(out[0][1:], out[1][1:]):           # (fp32 sums in another order, as above)
         assert rel_err(a, f64(b)) <= 1e-5
+
+
+@pytest.mark.parametrize("M", [1793, 2047])
+def test_db_rounding_error(M):
+    """fp32 error of dB's sum over the rows (dY and S' are its exact bf16 factors).  Bound: between that of the panels plan_db states
+    (0.75e-7 to 0.78e-7) and that of one panel over the segment (0.93e-7 to 0.98e-7)."""
+    K, N, r = 1024, 4096, 16
+    print(f"rounding error of dB {M} rows", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+    new = lambda *shape: torch.randn(shape, generator=gen, device="cuda").bfloat16()
+    X, dY, A, B, S, W = new(M, K), new(M, N), new(r, K), new(N, r), new(M, r), torch.zeros((N, K), dtype=torch.bfloat16, device="cuda")
+    dB = binding.lora_bwd(X, W, A, B, S, dY, 1.0, 0.0, 1, need_dx=False)[2]
+    want = dY.double().t() @ S.double()
+    assert float((dB.double() - want).norm() / want.norm()) <= 0.86e-7

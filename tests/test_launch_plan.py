@@ -138,6 +138,20 @@ def test_backward_plan_stays_within_the_scratch():
     assert seen >= {(1, 1, 0), (1, 0, 0), (1, 0, 1), (1, 1, 1), (0, 1, 0), (0, 0, 0), (0, 0, 1)}, seen
 
 
+def test_db_panels():
+    """No panel of dB that is a whole segment of more than 1792 rows, none of 2048 rows or more."""
+    binding.lora_set_row_tile(0)
+    rnd = random.Random(13)
+    for it in range(3000):
+        lens = [int(2 ** rnd.uniform(5, 12.5)) for _ in range(1 if it % 2 else rnd.randint(2, 4))]
+        K, N, off = 64 * rnd.randint(1, 80), 64 * rnd.randint(1, 64), _offsets(lens)
+        plan = binding.lora_debug_bwd_plan(K, N, 16, off)
+        if plan.ds_alone:
+            h = plan.panel_rows_db or 1 << 30
+            longest = [(n, h + n % h if n // h else n) if n % h else (n, h) for n in lens]
+            assert all(m < 2048 and (m < n or m <= 1792) for n, m in longest), (lens, K, N, plan.panel_rows_db)
+
+
 def test_finalize_launch_where_the_counters_do_not_fit():
     """Fewer than 64 rows with the large heights fixed leave no room behind the planes."""
     binding.lora_set_row_tile(256)
