@@ -351,20 +351,26 @@ def main():
     prof = binding.profile_end()
     kernels_us = {k: (ms / n * 1e3 if n else 0.0) for k, (ms, n) in prof.items()}
     launches = {k: n for k, (ms, n) in prof.items()}
-    # dominant kernel: the dX GEMM (operation 5); its algorithmic FLOPs per launch = 2MNK + 2MrK,
-    # averaged over the launches of one step (one per layer)
+    # dominant kernel: the slower GEMM; its algorithmic FLOPs per launch (dX: 2MNK + 2MrK, and those of operation 4 and
+    # of dB where they run in its launch), averaged over the launches of one step (one per layer)
+    layers = [st["L"] for st in state]
+    plans = [binding.lora_debug_bwd_plan(L.K, L.N, L.r, L.seg_offsets) for L in layers]
     dom = "dx_gemm" if kernels_us["dx_gemm"] >= kernels_us["fwd_gemm"] else "fwd_gemm"
     if dom == "dx_gemm":
-        dom_flops = sum(2 * st["L"].M * st["L"].N * st["L"].K + 2 * st["L"].M * st["L"].r * st["L"].K for st in state)
+        dom_flops = sum(2 * L.M * L.N * L.K + 2 * L.M * L.r * L.K + (2 * L.M * L.r * (L.K + (L.N if p.ds_alone else 0)) if p.with_dx else 0)
+                        for L, p in zip(layers, plans))
     else:
-        dom_flops = sum(2 * st["L"].M * st["L"].N * st["L"].K + 2 * st["L"].M * st["L"].r * st["L"].N for st in state)
-    dom_flops /= len(state)
+        dom_flops = sum(2 * L.M * L.N * L.K + 2 * L.M * L.r * L.N for L in layers)
+    dom_flops /= len(layers)
     achieved = dom_flops / (kernels_us[dom] * 1e-6) / 1e12
     traffic = read_traffic(args.workload)
-    # the bandwidth-bound kernels: algorithmic bytes (one read of X or dY per launch) over their launch time
-    stream_bytes = {"down": sum(2 * st["L"].M * st["L"].K for st in state) / len(state),
-                    "ds_db": sum(2 * st["L"].M * st["L"].N for st in state) / len(state),
-                    "da": sum(2 * st["L"].M * st["L"].K for st in state) / len(state)}
+    # the bandwidth-bound kernels: algorithmic bytes (one read of X or dY, and of both where dB runs beside operation 4) over their
+    # launch time; operation 4 has none where it runs in the dX GEMM's launch
+    def per_launch(nbytes):
+        return sum(nbytes) / len(nbytes) if nbytes else 0.0
+    stream_bytes = {"down": per_launch([2 * L.M * L.K for L in layers]),
+                    "ds_db": per_launch([2 * L.M * L.N for L in layers]),
+                    "da": per_launch([2 * L.M * (L.K + (L.N if p.ds_alone else 0)) for L, p in zip(layers, plans) if not p.with_dx])}
     stream_gbs = {k: round(b / (kernels_us[k] * 1e-6) / 1e9, 1) for k, b in stream_bytes.items() if kernels_us[k] > 0}
 
     out = {

@@ -7,8 +7,8 @@
 // walks the 32-row blocks w, w + 8, ... of the panel by itself: global -> registers two blocks ahead, mask, LDS of the
 // wave's own, transposing reads, 16x16x32 bf16 MFMAs.  No barrier until the waves' sums are added, pairwise.
 // A panel is a whole segment where that leaves the chip enough workgroups (the sum is then the gradient itself); otherwise the
-// panels leave fp32 pieces that the last workgroup of the strip adds in a fixed order (plan_strips).  Repeated runs
-// agree bit for bit.
+// panels (plan_da, with dB beside it plan_strips) leave fp32 pieces that the last workgroup of the strip adds in a fixed order or,
+// where there are many (strips_add_pieces), a finalize launch in the same one.  Repeated runs agree bit for bit.
 // What bounds it: the mask of dA (about 0.85 us of a compute unit per 256 rows x 64 columns; 13 vector instructions a
 // column pair), then memory.  (3) and (4) in two launches instead of four, us: 256 x 1024 x 1024, r = 16 12.2 -> 7.6; 1531 x 4096 ->
 // 1024 in three segments, r = 64 29 -> 16.4; 2999 x 4096 x 4096, r = 32 37 -> 29; 2048 x 4096 x 4096, r = 16 22 -> 18.6.

@@ -10,8 +10,8 @@
 // about 25), then the mask (12 vector instructions per column pair).  Hence X and A go global -> LDS in whole 128-byte
 // lines, several stages of 256 columns ahead, by waves that do nothing else; A is fetched once per workgroup and stage, not
 // once per wave; the masks of a stage are formed while its copies land, and not at all without dropout.
-// Measured, us: fragments loaded straight into registers / copies by the computing waves / as it is now: K = 14336: 5003 rows r = 16
-// 57 / 33.6 / 29.2, r = 64 128 / 39.5 / 35.0; K = 4096: 1024 rows r = 16 - / 7.9 / 7.2, r = 64 - / 11.2 / 8.7; 8192 rows r = 16 18 / 12.4 / 12.4,
+// Measured, us (cards differ by up to a tenth): fragments loaded straight into registers / copies by the computing waves / as it is
+// now: K = 14336: 5003 rows r = 16 57 / 33.6 / 29.2, r = 64 128 / 39.5 / 35.0; K = 4096: 1024 rows r = 16 - / 7.9 / 7.2, r = 64 - / 11.2 / 8.7; 8192 rows r = 16 18 / 12.4 / 12.4,
 // r = 64 - / 16.2 / 14.9; 19 rows, K = 24960, r = 16 - / 33.4 / 29.7, r = 64 - / 50.3 / 38.3.  Short contractions keep the registers
 // (down_direct_kernel, rule in launch_down).  The order of the sums is the same in both kernels and in every height, so S' has
 // the same bits whichever is picked.
@@ -301,15 +301,16 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
         tiles16 += (len + 15) / 16;
     }
     if (tiles32 == 0) return hipSuccess;
-    // A 16-row workgroup takes 0.6 - 0.75 of a 32-row one's time (its copies of A serve half as many rows), so it is the
-    // faster one exactly while all of them run at once: K = 14336, r = 64: 4096 rows 38 against 43 us, 5003 rows 65
-    // against 43 us; r = 16: 26 against 37 and 36 against 36 us.
+    // A 16-row workgroup takes 0.65 - 0.8 of a 32-row one's time (its copies of A serve half as many rows), so it is the
+    // faster one exactly while all of them run at once: K = 14336, r = 64: 4096 rows 29 against 36 us, 5003 rows 50
+    // against 37 us; r = 16: 21 against 30 and 30 against 31 us.
     const bool one_round = tiles16 <= kComputeUnits, many = tiles32 > kComputeUnits;
     const bool small = forced ? forced == 128 : one_round;
     // Short contractions: a ring of one or two stages has nothing to run ahead of, and its LDS leaves room for one or two
     // workgroups on a compute unit, which tells when they come in several rounds (us, direct / ring): K = 64, r = 64: 5000
-    // rows 3.8 / 5.2, 100000 rows 21 / 49; K = 256: r = 16 1000 rows 3.4 / 3.8, r = 64 16384 rows 7.0 / 9.9; K = 512, r = 64:
-    // 5000 rows 6.6 / 6.3, 40000 rows 19 / 23; K = 768: r = 32 40000 rows 18 / 20, r = 16 16384 rows 8.2 / 7.7.
+    // rows 3.8 / 4.7, 100000 rows 21 / 43; K = 256: r = 16 1000 rows 3.2 / 3.5, r = 64 16384 rows 6.9 / 9.4; K = 320, 1000 rows
+    // r = 16 3.4 / 3.9, r = 64 4.6 / 4.5; K = 512: r = 64 5000 rows 6.4 / 5.6, 40000 rows 19 / 24, r = 16 16384 rows 6.6 / 5.9 (the line is
+    // drawn for the larger ranks); K = 768: r = 32 40000 rows 18 / 20, r = 16 16384 rows 8.4 / 7.6.
     const int direct_up_to = !many ? 320 : a.r == 32 && tiles32 > 2 * kComputeUnits ? 768 : 512;
     if (a.K <= direct_up_to) {
         if (a.r == 16) return small ? launch_down_direct<1, 1>(a, tiles16, st) : launch_down_direct<1, 2>(a, tiles32, st);
@@ -317,8 +318,8 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
         if (a.r == 64) return small ? launch_down_direct<4, 1>(a, tiles16, st) : launch_down_direct<4, 2>(a, tiles32, st);
         return hipErrorInvalidValue;
     }
-    // r = 32: two of the 16-row workgroups fit on a compute unit, one of the 32-row ones (16 waves); in several rounds
-    // that is worth more than the second reading of A up to K = 2048 (40000 rows: K = 1024 23 / 27 us, K = 4096 69 / 68 us).
+    // r = 32: two of the 16-row workgroups fit on a compute unit, one of the 32-row ones (128 KB of LDS); in several rounds
+    // that is worth more than the second reading of A up to K = 2048 (40000 rows: K = 1024 22 / 25 us, K = 2048 33 / 40, K = 4096 69 / 65).
     const bool small32 = forced ? forced == 128 : one_round || (many && a.K <= 2048);
     if (a.r == 16) return small ? launch_down_cfg<Down<1, 1, 5>>(a, tiles16, st) : launch_down_cfg<Down<1, 2, 3>>(a, tiles32, st);
     if (a.r == 32) return small32 ? launch_down_cfg<Down<2, 1, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 2, 4>>(a, tiles32, st);

@@ -15,7 +15,8 @@
 // compiler's own moved every accumulator block in every step (M = 1024, 4096 x 4096: 40 -> 35 us).
 // Against copies issued by the computing waves between their MFMAs, us, (2) / (5): 1024 x 4096 x 4096 36.0 -> 33.4 / 36.1 -> 33.3; 1000 rows,
 // 14336 -> 4096 110 -> 104 / 109 -> 99; 512 x 4096 x 4096 23.6 -> 22.2 / 24.0 -> 22.9; 256 rows, 17024 -> 17856 247 -> 239 /
-// 236 -> 212; 128 rows, 26496 -> 960 54 -> 55 / 64 -> 54.5; 256 x 1024 x 1024 5.4 -> 4.8 / 5.8 -> 4.9.
+// 236 -> 212; 128 rows, 26496 -> 960 54 -> 54.6 / 64 -> 54.5; 256 x 1024 x 1024 5.4 -> 4.8 / 5.8 -> 4.8 (replayed back to back; in a
+// trace of whole steps 5.7 and, with the strips, 6.0).
 // Measured, one launch, against the 128-row tiles that served these sizes before: 256 x 1024 x 1024 16 -> 6.1 us
 // forward, 22 -> 6.7 us backward; 1024 x 4096 x 4096 56 -> 35 and 66 -> 39 us; 77 rows, 4096 -> 14336 51 -> 24 and
 // (backward) 174 -> 41 us; 64 rows, 15616 -> 320 176 -> 33 us.

@@ -197,9 +197,9 @@ inline bool strips_add_pieces(const AdapterTable& tb, int rows, int r) {
     return most <= (r == 64 ? 3 : 12);
 }
 
-// ... and with the strips of dB beside it (split_ds_db): the two share the chip, two workgroups on a compute unit as long as
-// one after the other, at about 1.3 us (dA: the mask) or 0.6 us (dB) per 256 rows; the last workgroup of a strip adds its pieces: 2 us, and
-// 40 ns per panel and 1000 columns.
+// ... and with the strips of dB beside it (split_ds_db): the two share the chip, two workgroups on a compute unit (at r = 64 one, which the
+// rule does not know) as long as one after the other, at about 1.3 us (dA: the mask) or 0.6 us (dB) per 256 rows; the last workgroup of a
+// strip adds its pieces: 2 us, and 40 ns per panel and 1000 columns.
 constexpr int kLowestStripPanel = 512;               // (two rounds of a workgroup's eight 32-row blocks)
 constexpr double kDaBlock = 1.3, kDbBlock = 0.6;     // us per 256 rows
 struct StripLoad { double path, work; };           // us: the longest workgroup; all of them, per compute unit
