@@ -20,6 +20,7 @@ namespace lf {
 
 template <int CB, class TB>                        // r / 16
 __global__ void __launch_bounds__(DA_THREADS, CB == 4 ? 2 : 4) strip_kernel(StripArgsOf<TB> p) {
+    fetch_args<StripArgsOf<TB>>();
     extern __shared__ __attribute__((aligned(16))) char smem[];
     strip_of<CB>(p, blockIdx.x, smem);
 }

@@ -48,6 +48,20 @@ using AdapterTable = AdapterTableOf<kMaxAdapters>;
 constexpr int kFewAdapters = 4;
 using FewAdapters = AdapterTableOf<kFewAdapters>;
 
+// First statement of a kernel whose arguments are of type Args: asks for every cache line of them at once.  A launch finds them in
+// memory, not in a cache, and the compiler loads a field where it is first needed: the number of adapters, behind that the walk over
+// the segments, behind that the adapter's entry.
+template <class Args>
+__device__ __forceinline__ void fetch_args() {
+    constexpr int LINES = ((int)sizeof(Args) + 63) / 64, N = LINES < 8 ? LINES : 3;     // (of a full table its first offsets)
+    const auto* w = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = w[i < N ? i * 16 : 0];
+    const uint32_t end = w[N == LINES ? sizeof(Args) / 4 - 1 : 0];
+    asm volatile("" :: "s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3]), "s"(v[4]), "s"(v[5]), "s"(v[6]), "s"(v[7]), "s"(end));
+}
+
 // A row tile: `rows` valid rows starting at global row `row_start`, owned by adapter g.
 struct RowTile {
     int g, row_start, rows, local_row0;   // local_row0 = row_start - row0[g] (mask row index base)

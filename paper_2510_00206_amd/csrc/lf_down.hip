@@ -106,6 +106,7 @@ __device__ __forceinline__ void down_store(const DownArgsOf<TB>& p, const RowTil
 
 template <class C, class TB>
 __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel(DownArgsOf<TB> p) {
+    fetch_args<DownArgsOf<TB>>();
     constexpr int CB = C::CB, RB = C::RB, NS = C::NS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     RowTile rt;
@@ -199,6 +200,7 @@ __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel
 // the faster way where a workgroup's sweep is short against its start and its end (see launch_down).
 template <int CB, int RB, class TB>
 __global__ void __launch_bounds__(64 * DOWN_PARTS) down_direct_kernel(DownArgsOf<TB> p) {
+    fetch_args<DownArgsOf<TB>>();
     __shared__ f32x4 red[DOWN_PARTS * RB * CB * 64];
     RowTile rt;
     if (!find_row_tile(p.tb, 16 * RB, blockIdx.x, rt)) return;

@@ -42,6 +42,7 @@ __device__ __forceinline__ void ds_copy(const char* const (&src)[C::P], const ui
 // zero per quarter, ((q0 + q1) + q2) + q3 per chunk, then chunk by chunk; dS is the same bits either way.
 template <class C, class TB>
 __global__ void __launch_bounds__(C::THREADS) ds_kernel(DsArgsOf<TB> p) {
+    fetch_args<DsArgsOf<TB>>();
     constexpr int CB = C::CB, SC = C::SC, NS = C::NS, P = C::P, R = C::RANK, RCH = CB * 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if (C::PARTS == 1 || blockIdx.y == 0)

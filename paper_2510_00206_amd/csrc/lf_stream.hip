@@ -53,6 +53,7 @@ __device__ __forceinline__ bf16x8 zero_past_rows(bf16x8 v, int rows) {
 
 template <class C, class TB>
 __global__ void __launch_bounds__(ST_THREADS, 2) stream_kernel(StreamArgsOf<TB> p) {
+    fetch_args<StreamArgsOf<TB>>();
     constexpr int CB = C::CB, NS = C::NS, R = CB * 16, RCH = CB * 2;     // rank, 16-byte chunks per S' row
     extern __shared__ __attribute__((aligned(16))) char smem[];
     f32x4* red = (f32x4*)(smem + NS * C::STAGE);
@@ -255,6 +256,7 @@ hipError_t launch_stream_dsdb(StreamArgs a, hipStream_t st) {
 // job 1: dS[i, c..c+3] = bf16(s_g * q_g * sum_chunks part_ds);  job 2: dB[g, n, c..c+3] (+)= sum over tiles of g
 template <class TB>
 __global__ void __launch_bounds__(256) finalize_ds_db_kernel(FinalizeArgsOf<TB> p, int blocks_ds) {
+    fetch_args<FinalizeArgsOf<TB>>();
     const int r4 = p.r >> 2;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < p.n_zero; i += gridDim.x * 256) p.zero[i] = 0;
     if ((int)blockIdx.x < blocks_ds) {
@@ -293,6 +295,7 @@ __global__ void __launch_bounds__(256) finalize_ds_db_kernel(FinalizeArgsOf<TB> 
 // dA[g, c, j..j+3] (+)= sum over the row tiles of segment g (q_g is already in dS)
 template <class TB>
 __global__ void __launch_bounds__(256) finalize_da_kernel(FinalizeArgsOf<TB> p) {
+    fetch_args<FinalizeArgsOf<TB>>();
     const int64_t per_g = (int64_t)p.r * (p.K >> 2);
     const int64_t idx = blockIdx.x * 256ll + threadIdx.x;
     if (idx >= per_g * p.tb.G) return;
