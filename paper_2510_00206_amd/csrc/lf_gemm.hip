@@ -105,6 +105,35 @@ struct Pipe {
     uint32_t rd;                                  // LDS byte offset of the stage being computed on: 0 or STAGE_BYTES
 };
 
+// A slab that comes from HBM is late even two slabs ahead: the memory pipeline then pushes back on the issue of the copies, each wave
+// stalls by itself and the hand-over waits for the last (two rounds of 8192 rows, 14336 -> 4096: 673 us, 601 with every slab in the
+// L2s).  So behind its copies of a step each wave asks for some lines of the slab after those, which then find them in their XCD's
+// L2.  An XCD holds about 8 x 4 neighbouring tiles: a tile asks for the quarter of its token rows and the eighth of its out lines
+// that its place among them says, the token rows 32 to a load (waves 0 and 1), the out lines 16 (waves 2 and 3); an eighth of the token
+// rows gains nothing, a half as much as a quarter.  The KB that a load brings lands where nobody reads.  Loads complete in order,
+// hence behind the copies: the next hand-over waits for all but this one, which so has until the one after.
+// Measured, us, without / with: (2) 8192 rows, 14336 -> 4096 673 / 618, 4096 rows, 28672 -> 8192 1324 / 1228, 3000 rows, 20480 -> 20480
+// 1954 / 1782; (5) 8192 rows, 14336 -> 4096 690 / 639, 4096 rows, 28672 -> 8192 1365 / 1275.  Two or three slabs further on: level or slower.
+constexpr int kTokLanes = 2, kOutLanes = 4;       // lanes to a line
+struct Warm {
+    const char* src; int64_t adv;                 // as in Pipe
+    int left;                                     // slabs that follow
+    uint32_t off, m0;                             // per lane: the line's offset from the slab's first element; the landing place
+    __device__ __forceinline__ void issue() {
+        copy16_to_lds<0, true>(src, off, m0);
+        if (left > 0) {
+            src += adv;
+            --left;
+        }
+    }
+};
+// This lane's line of a slab of 256, in a tile that is number `place` along the side that shares the slab.
+__device__ __forceinline__ int warm_line(bool tok, int place) {
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), per = tok ? kTokLanes : kOutLanes;
+    return ((place & (2 * per - 1)) * 2 + (w & 1)) * (64 / per) + l / per;
+}
+struct NoWarm { __device__ __forceinline__ void issue() {} };
+
 // This wave's M0 values (slab_m0) for the token and the out slab of LDS stage 0.
 struct CopyOrg { uint32_t tok, out; };
 template <int MB>
@@ -157,6 +186,7 @@ __device__ __forceinline__ TileCtx decode_tile(const AdapterTable& tb, int M, in
 // LDS of the GEMM kernels: the two slab stages, then 32 KB in which every wave has 8 KB of its own for the
 // way out (operation (5) also parks its keep flags there, 2 KB per wave, until then).
 constexpr int WAVE_EXTRA_BYTES = 8192;
+constexpr int FLAG_BYTES = 8 * NTHREADS * 4;                                  // operation (5): the parked keep flags, 2 KB per wave
 constexpr int GEMM_LDS_TOTAL = GEMM_LDS_BYTES + NWAVES * WAVE_EXTRA_BYTES;     // 160 KB: all of a compute unit's
 
 // ---- fragments and the MFMA --------------------------------------------------------------------------
@@ -287,9 +317,9 @@ struct StepLds {
     const char* nxt_tok; const char* nxt_out;     // ... and in the slabs being filled
 };
 
-template <bool COL_SLAB, int MB, int S, int MODE, class SH>
+template <bool COL_SLAB, int MB, int S, int MODE, class SH, class WM>
 __device__ __forceinline__ void slots(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, const StepLds& L, const FragLanes& fl,
-                                        const NextSlabs& nx, bool read_next, SH& sh, Pipe& pp) {
+                                        const NextSlabs& nx, bool read_next, SH& sh, Pipe& pp, WM& warm) {
     using SC = Sched<MB>;
     // the out blocks of a token-block row are walked forth on even rows and back on odd ones: at a row's turn the
     // MFMA keeps its out operand (consecutive MFMAs always share one operand; measured 0.3 - 0.6 % of a GEMM)
@@ -319,6 +349,7 @@ __device__ __forceinline__ void slots(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, con
     constexpr int j = SC::copy_at(sub, s, MODE);
     if constexpr (j >= 0) issue_copy<MB, j>(nx);
     shadow_slot<MB, sub, s, MODE>(sh);
+    if constexpr (sub == 1 && s == SC::SS - 4) warm.issue();       // behind the step's copies
     if constexpr (sub == 1 && s == 0) {
         // every copy of this step has been issued: the sources move on to the slab pair after
         pp.src_tok += pp.adv_tok;
@@ -328,29 +359,30 @@ __device__ __forceinline__ void slots(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, con
     if constexpr (sub == 1 && s == SC::ho(MODE)) {
         // two ahead: the copies that follow overwrite the stage this wave has just read its last fragments from,
         // so those reads are waited for, too, before the barrier lets the other waves' copies go
-        if constexpr (MODE == kCopyAhead2) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        if constexpr (!std::is_same_v<WM, NoWarm>) asm volatile("s_waitcnt vmcnt(1) lgkmcnt(0)" ::: "memory");    // (all but the last warming load)
+        else if constexpr (MODE == kCopyAhead2) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         else wait_slab_loads();
         __syncthreads();
     }
     static_assert(MB == 4 || MODE == kCopyAhead2, "see Sched");
-    if constexpr (S + 1 < 2 * SC::SS) slots<COL_SLAB, MB, S + 1, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
+    if constexpr (S + 1 < 2 * SC::SS) slots<COL_SLAB, MB, S + 1, MODE>(acc, f, L, fl, nx, read_next, sh, pp, warm);
 }
 
 // One 64-deep slab pair: two sub-steps of 16*MB MFMAs; the copies of the next slab pair ride on sub-step 0,
 // the hand-over (copies landed, workgroup barrier) sits in sub-step 1 and is followed by the first fragment
 // reads of the next slab (if read_next).  On entry f holds the fragments of sub-step 0 of the current slab.
-template <bool COL_SLAB, int MB, int MODE, class SH>
+template <bool COL_SLAB, int MB, int MODE, class SH, class WM>
 __device__ __forceinline__ void slab_step(f32x4 (&acc)[2 * MB][8], Frags<MB>& f, const char* lds_tok_org,
                                             const char* lds_out_org, CopyOrg lds_copy_org, const FragLanes& fl, Pipe& pp,
                                             const SlabLanes& lanes_tok, const SlabLanes& lanes_out, bool copy_next,
-                                            bool read_next, SH& sh) {
+                                            bool read_next, SH& sh, WM& warm) {
     const uint32_t nxt = STAGE_BYTES - pp.rd;
     const StepLds L{lds_tok_org + pp.rd, lds_out_org + pp.rd, lds_tok_org + nxt, lds_out_org + nxt};
     const uint32_t dst = MODE == kCopyAhead2 ? pp.rd : nxt;     // two ahead: into the stage being computed on, once it is free
     const NextSlabs nx{pp.src_tok, pp.src_out, lanes_tok, lanes_out, lds_copy_org.tok + dst, lds_copy_org.out + dst,
                        copy_next};
     __builtin_amdgcn_sched_barrier(0);
-    slots<COL_SLAB, MB, 0, MODE>(acc, f, L, fl, nx, read_next, sh, pp);
+    slots<COL_SLAB, MB, 0, MODE>(acc, f, L, fl, nx, read_next, sh, pp, warm);
     pp.rd = nxt;
 }
 
@@ -471,8 +503,8 @@ __device__ __forceinline__ void block_store(f32x4 (&acc)[2 * MB][8], int bp, con
 
 
 // ---- operation (2): Y = X W + S' B ---------------------------------------------------------------
-// LA: how many slabs ahead of the matrix work the copies run (1 or 2).
-template <int MB, int LA>
+// LA: how many slabs ahead of the matrix work the copies run (1 or 2); WARM: see Warm.
+template <int MB, int LA, bool WARM>
 __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
     constexpr int MODE = LA == 2 ? kCopyAhead2 : kCopyEarly1;
     constexpr int BM = 64 * MB, TB = 2 * MB;
@@ -492,6 +524,7 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
     const bool has_lora = p.r > 0;
     const int rr = has_lora ? p.r : 16;
     NoShadow none;
+    NoWarm cold;
     Pipe pp{nullptr, nullptr, BK * 2, BK * 2, 0u};
 
     // first slab pair of the first tile
@@ -530,8 +563,20 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
         if (nk > 0) read_frags<false, MB>(f, smem + pp.rd + tok_org, smem + pp.rd + out_org, fl);
         pp.src_tok = (const char*)(Xt + D * BK) - kCopyBias;
         pp.src_out = (const char*)(Wt + D * BK) - kCopyBias;
-        for (int kt = 0; kt + D < nk; ++kt)          // step kt brings slab kt + D
-            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sx, sw, true, true, none);
+        // step kt brings slab kt + D
+        if constexpr (WARM) {
+            const bool tok = w < 2;
+            const int first = min(2, nk - 1), line = warm_line(tok, tok ? n0 / BN : rt.row_start / BM);
+            Warm warm{(const char*)(tok ? Xt : Wt) + (int64_t)first * (BK * 2), BK * 2, nk - 1 - first,
+                      (uint32_t)min(line, (tok ? rt.rows : cols_valid) - 1) * (uint32_t)p.K * 2,
+                      (uint32_t)__builtin_amdgcn_readfirstlane(lds0 + GEMM_LDS_BYTES + w * WAVE_EXTRA_BYTES)};
+            if (D < nk) warm.issue();
+            for (int kt = 0; kt + D < nk; ++kt)
+                slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sx, sw, true, true, none, warm);
+        } else {
+            for (int kt = 0; kt + D < nk; ++kt)
+                slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sx, sw, true, true, none, cold);
+        }
         // the lane offsets of the LoRA slab pair are formed only now: through the main loop they would cost
         // sixteen registers that it does not have
         const SlabLanes ss = row_slab_lanes<2 * MB>(rr, rt.rows, rr >> 3), sb = row_slab_lanes(rr, cols_valid, rr >> 3);
@@ -541,10 +586,10 @@ __global__ void __launch_bounds__(NTHREADS) fwd_gemm_kernel(FwdGemmArgs p) {
         pp.src_tok = (const char*)Ssrc - kCopyBias;
         pp.src_out = (const char*)Bsrc - kCopyBias;
         if (D == 2 && nk > 1)
-            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, lora_piped, true, none);
+            slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, lora_piped, true, none, cold);
         if (nk > 0)
             slab_step<false, MB, MODE>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sb, D == 1 && lora_piped,
-                                        false, none);
+                                        false, none, cold);
         const uint32_t lo = pp.rd;                     // the stage that holds (or receives) the LoRA slab pair
 
         // The next tile of this workgroup: its first slab pair is asked for now, into the stage that the last
@@ -726,7 +771,7 @@ __device__ __forceinline__ SlabLanes col_slab_lanes(int64_t ld, int rows_valid, 
 // product first, while the keep flags of the tile are formed in the shadow of its MFMAs; the LoRA slab
 // pair [dS | A] rides in as one more slab during the last base slab, and the masked LoRA term is added
 // pair of block rows by pair on the way out.  p.N == 0 (LoRA term only) serves the unfused baseline.
-template <int MB, bool LORA, int LA>
+template <int MB, bool LORA, int LA, bool WARM>
 __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     constexpr int CM = LA == 2 ? kCopyAhead2 : kCopySpread1;
     constexpr bool PF = LA == 2;                      // copies two slabs ahead (LA as in fwd_gemm_kernel)
@@ -779,6 +824,7 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     // keep flags: state of the hash pieces, and what changes with the 16-row block row they work on
     KeepShadow ks;
     NoShadow none;
+    NoWarm cold;
     uint32_t keep_all = 0;
     uint32_t* flags = (uint32_t*)(smem + GEMM_LDS_BYTES) + threadIdx.x;     // [2 * MB][NTHREADS]
     const uint32_t cp0 = (uint32_t)(j0 + wn * 128 + 4 * (l >> 4)) >> 1;     // this lane's first column pair
@@ -824,15 +870,30 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
     Pipe pp{(const char*)(dYt + D * BK) - kCopyBias, (const char*)(Wt + (int64_t)D * BK * p.K) - kCopyBias, BK * 2,
             (int64_t)BK * p.K * 2, 0u};
     int kt = 0;
-    if constexpr (LORA) {
-        for (; kt < min(nk - D, FLAG_STEPS); ++kt) {
-            keep_step_begin(kt);
-            slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, ks);
-            keep_step_end(kt);
+    auto main_loop = [&](auto& warm) {
+        if constexpr (LORA) {
+            for (; kt < min(nk - D, FLAG_STEPS); ++kt) {
+                keep_step_begin(kt);
+                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, ks, warm);
+                keep_step_end(kt);
+            }
         }
+        for (; kt < nk - D; ++kt)
+            slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, none, warm);
+    };
+    if constexpr (WARM) {
+        const bool tok = w < 2;
+        const int first = min(2, nk - 1), line = warm_line(tok, tok ? tn : tm);
+        Warm warm{tok ? (const char*)(dYt + (int64_t)first * BK) : (const char*)(Wt + (int64_t)first * BK * p.K),
+                  tok ? BK * 2 : (int64_t)BK * p.K * 2, nk - 1 - first,
+                  tok ? (uint32_t)min(line, rt.rows - 1) * (uint32_t)p.N * 2
+                      : ((uint32_t)(line >> 2) * (uint32_t)p.K + (uint32_t)min((line & 3) * 64, cols_valid - 8)) * 2,
+                  (uint32_t)__builtin_amdgcn_readfirstlane(lds0 + GEMM_LDS_BYTES + FLAG_BYTES + w * 1024)};
+        if (D < nk) warm.issue();
+        main_loop(warm);
+    } else {
+        main_loop(cold);
     }
-    for (; kt < nk - D; ++kt)
-        slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, sd, sw, true, true, none);
     if (nk > 0) {
         // the last D base slabs: the LoRA slab pair [dS | A] rides in as one more slab (nothing if there is no
         // LoRA term); its lane offsets are formed only now, the main loop has no registers for them
@@ -847,10 +908,10 @@ __global__ void __launch_bounds__(NTHREADS) bwd_dx_kernel(DxGemmArgs p) {
                 // past the last of those steps the hash pieces still run, on a step number that is never flushed
                 const bool forming = kt < FLAG_STEPS;
                 if (forming) keep_step_begin(kt);
-                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, LORA && bring(), read_next(), ks);
+                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, LORA && bring(), read_next(), ks, cold);
                 if (forming) keep_step_end(kt);
             } else {
-                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, false, read_next(), none);
+                slab_step<true, MB, CM>(acc, f, smem + tok_org, smem + out_org, corg, fl, pp, ss, sa, false, read_next(), none, cold);
             }
             ++kt;
         };
@@ -1054,6 +1115,13 @@ void force_slab_lookahead(int slabs) { g_forced_lookahead.store(slabs, std::memo
 // streams from HBM in every launch.
 static bool weight_streams(int64_t K, int64_t N) { return K * N * 2 > (64ll << 20); }
 
+// Both operands together outgrow that cache: what one round of tiles has read is gone when the next comes back for it (Warm).  The line
+// is the cache's size: us, without / with, token rows and weight of 268 MB (8192 x 8192 x 8192) (2) 691 / 695, (5) 708 / 713; of 301 MB
+// (32768 x 4096 x 4096) 755 / 734, 749 / 749; of 331 MB (12000 x 8192 x 8192) 1182 / 1110, 1176 / 1127.
+static bool operands_stream(int64_t rows, int64_t contraction, int64_t columns) {
+    return (rows + columns) * contraction * 2 > (256ll << 20);
+}
+
 static hipError_t launch_ring_part(const GemmPart& t, bool col, RingArgs a, hipStream_t st) {
     a.tiles_m = (int)t.tiles_m;
     a.tiles_n = (a.NC + kRingTiles[t.kind][1] - 1) / kRingTiles[t.kind][1];
@@ -1066,14 +1134,18 @@ static hipError_t launch_fwd_large(FwdGemmArgs a, const GemmPlan& t, hipStream_t
     a.tiles_n = (a.N + BN - 1) / BN;
     a.uniform_tiles = t.uniform;
     a.tiles_m = (int)t.part[0].tiles_m;
-    static bool attr_set[3] = {false, false, false};
-    if (t.part[0].kind < -1) return launch_gemm(fwd_gemm_kernel<3, 2>, attr_set[2], a, st, GEMM_LDS_TOTAL, true);
+    static bool attr_set[5] = {};
+    const bool warm = operands_stream(t.part[0].row_hi, a.K, a.N);
+    if (t.part[0].kind < -1)
+        return warm ? launch_gemm(fwd_gemm_kernel<3, 2, true>, attr_set[3], a, st, GEMM_LDS_TOTAL, true)
+                    : launch_gemm(fwd_gemm_kernel<3, 2, false>, attr_set[2], a, st, GEMM_LDS_TOTAL, true);
     // copies two slabs ahead unless the contraction is short (measured: 2.5 % faster at K = N = 4096, 5 - 8 % with
     // weights of 117 and 470 MB; a contraction of 16 slabs, where every step waits for its copies anyway, 4 % slower)
     const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
     const bool ahead2 = knob ? knob == 2 : a.K >= 32 * BK;
-    return ahead2 ? launch_gemm(fwd_gemm_kernel<4, 2>, attr_set[0], a, st, GEMM_LDS_TOTAL, true)
-                  : launch_gemm(fwd_gemm_kernel<4, 1>, attr_set[1], a, st, GEMM_LDS_TOTAL, true);
+    if (ahead2 && warm) return launch_gemm(fwd_gemm_kernel<4, 2, true>, attr_set[4], a, st, GEMM_LDS_TOTAL, true);
+    return ahead2 ? launch_gemm(fwd_gemm_kernel<4, 2, false>, attr_set[0], a, st, GEMM_LDS_TOTAL, true)
+                  : launch_gemm(fwd_gemm_kernel<4, 1, false>, attr_set[1], a, st, GEMM_LDS_TOTAL, true);
 }
 
 hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st) {
@@ -1109,21 +1181,25 @@ static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t s
     a.tiles_n = (a.K + BN - 1) / BN;
     a.uniform_tiles = t.uniform;
     a.tiles_m = (int)t.part[0].tiles_m;
-    static bool attr_set[6] = {};
+    static bool attr_set[8] = {};
     // with a LoRA term: the slab stages plus the parked keep flags (one word per lane and 16-row block of the wave)
-    const int lds = GEMM_LDS_BYTES + 8 * NTHREADS * 4;
-    if (t.part[0].kind < -1)
-        return a.r > 0 ? launch_gemm(bwd_dx_kernel<3, true, 2>, attr_set[4], a, st, lds)
-                       : launch_gemm(bwd_dx_kernel<3, false, 2>, attr_set[5], a, st);
-    // copies two slabs ahead when the weight streams from HBM (measured: 3 - 7 % faster there, 0.5 - 1 % slower
+    const int lds = GEMM_LDS_BYTES + FLAG_BYTES;
+    const bool warm = a.r > 0 && operands_stream(t.part[0].row_hi, a.N, a.K);
+    if (t.part[0].kind < -1) {
+        if (warm) return launch_gemm(bwd_dx_kernel<3, true, 2, true>, attr_set[6], a, st, lds + NWAVES * 1024);
+        return a.r > 0 ? launch_gemm(bwd_dx_kernel<3, true, 2, false>, attr_set[4], a, st, lds)
+                       : launch_gemm(bwd_dx_kernel<3, false, 2, false>, attr_set[5], a, st);
+    }
+    // copies two slabs ahead when the weight, or both operands, stream from HBM (measured: 3 - 7 % faster there, 0.5 - 1 % slower
     // with a cache-resident weight, whose copies land in time anyway)
     const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
-    const bool ahead2 = knob ? knob == 2 : weight_streams(a.K, a.N);
+    const bool ahead2 = knob ? knob == 2 : weight_streams(a.K, a.N) || warm;
+    if (ahead2 && warm) return launch_gemm(bwd_dx_kernel<4, true, 2, true>, attr_set[7], a, st, lds + NWAVES * 1024);
     if (a.r > 0)
-        return ahead2 ? launch_gemm(bwd_dx_kernel<4, true, 2>, attr_set[0], a, st, lds)
-                      : launch_gemm(bwd_dx_kernel<4, true, 1>, attr_set[1], a, st, lds);
-    return ahead2 ? launch_gemm(bwd_dx_kernel<4, false, 2>, attr_set[2], a, st)
-                  : launch_gemm(bwd_dx_kernel<4, false, 1>, attr_set[3], a, st);
+        return ahead2 ? launch_gemm(bwd_dx_kernel<4, true, 2, false>, attr_set[0], a, st, lds)
+                      : launch_gemm(bwd_dx_kernel<4, true, 1, false>, attr_set[1], a, st, lds);
+    return ahead2 ? launch_gemm(bwd_dx_kernel<4, false, 2, false>, attr_set[2], a, st)
+                  : launch_gemm(bwd_dx_kernel<4, false, 1, false>, attr_set[3], a, st);
 }
 
 hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st, const StripArgs* strips, bool* took) {
