@@ -31,21 +31,24 @@
 namespace lf {
 
 // One kernel of the family.  TM x TN output tile, WM x WN computing waves of (TM / WM) x (TN / WN) each, ring of NS LDS stages,
-// one 64-deep slab pair per stage.  TW waves copy the token slabs and OW the out slabs; TW = 0: OW waves copy both (the better
+// one slab pair of 64 * D contraction elements per stage.  TW waves copy the token slabs and OW the out slabs; TW = 0: OW waves copy both (the better
 // way for the one tile whose out slab is the larger one: 256 rows, 17024 -> 17856, (5) 222 -> 212 us).
-template <int TM_, int TN_, int WM_, int WN_, int NS_, int TW_, int OW_>
+template <int TM_, int TN_, int WM_, int WN_, int NS_, int TW_, int OW_, int D_ = 1>
 struct Ring {
-    static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, NS = NS_, TW = TW_, OW = OW_, CW = TW + OW;
+    static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, NS = NS_, TW = TW_, OW = OW_, CW = TW + OW, D = D_;
     static constexpr int NW = WM * WN, THREADS = 64 * NW;             // waves and threads that compute
     static constexpr int MI = TM / WM / 16, NI = TN / WN / 16;        // 16x16 blocks per wave
-    static constexpr int STAGE = (TM + TN) * BK * 2;
+    static constexpr int DEPTH = D * BK, SUBS = 2 * D;                // contraction elements and sub-steps of 32 to a stage
+    static constexpr int ROWB = DEPTH * 2;                            // bytes of a row in a row-operand slab
+    static constexpr int STAGE = (TM + TN) * ROWB;
     static constexpr int LDS = NS * STAGE;
     static constexpr int REGS = 512 / ((NW + CW + 3) / 4);            // of a wave, with a SIMD's share of the workgroup on it
     // fragments of two slabs in registers: where they fit beside the accumulators and some forty others (128 x 64 tiles with the
     // shorter sub-steps of a 2 x 4 split, 512 x 4096 x 4096: 22.4 -> 23.8 us, so not below eight MFMAs)
-    static constexpr bool AHEAD = MI * NI >= 8 && MI * NI * 4 + (MI + NI) * 16 + 40 <= REGS;
-    static_assert(TM / 8 % (TW ? TW : OW) == 0 && TN / 8 % OW == 0, "the copies of a slab divide evenly over the waves");
+    static constexpr bool AHEAD = D == 2 || MI * NI >= 8 && MI * NI * 4 + (MI + NI) * 16 + 40 <= REGS;
+    static_assert(TM * D / 8 % (TW ? TW : OW) == 0 && TN * D / 8 % OW == 0, "the copies of a slab divide evenly over the waves");
     static_assert(NS >= 2, "ring depth");
+    static_assert(TM * TN / 8 % THREADS == 0 || TM * TN / 8 < THREADS, "whole passes on the way out, or one");
     static_assert(TM * TN * 2 <= LDS, "the way out goes through the ring");
 };
 
@@ -60,6 +63,11 @@ __device__ __forceinline__ int ring_col_swz(int row) {
 // ---- the copying waves -----------------------------------------------------------------------------
 // Where a slab comes from: rows (token: of the tile; out: output columns or, COL, contraction rows) `ld` elements apart, `rows`
 // of them valid; chunks: valid 16-byte chunks along the contraction (8, or r / 8 for the LoRA slab), COL: along the columns.
+// Position of 16-byte chunk `chunk` of row `row` in a row-operand slab: 64 elements to a row as in the large tiles, or 128, where the 16 rows of a
+// fragment read are 256 bytes apart and each needs a chunk position of its own.
+template <int D>
+__device__ __forceinline__ int ring_row_swz(int row) { return D == 1 ? row_slab_swz(row) : row & 15; }
+
 struct RingSource { const char* biased; uint32_t ld; int rows, chunks; };
 
 // Copies of a slab pair by one wave: NT of the token slab, then NO of the out slab (1 KB each); either may be none.  Those of
@@ -75,11 +83,11 @@ struct RingCopies {
         const int l = threadIdx.x & 63;
         uint32_t e;                                                   // < 2^30: at most 256 rows of 2^22 elements
         if constexpr (I < NT) {
-            const int row = 8 * (w * NT + I) + (l >> 3);
-            e = (uint32_t)min(row, tok.rows - 1) * tok.ld + min((l & 7) ^ row_slab_swz(row), tok.chunks - 1) * 8;
+            const int pos = (w * NT + I) * 64 + l, row = pos / (8 * C::D);
+            e = (uint32_t)min(row, tok.rows - 1) * tok.ld + min((pos % (8 * C::D)) ^ ring_row_swz<C::D>(row), tok.chunks - 1) * 8;
         } else if constexpr (!COL) {
-            const int row = 8 * (w * NO + I - NT) + (l >> 3);
-            e = (uint32_t)min(row, out.rows - 1) * out.ld + min((l & 7) ^ row_slab_swz(row), out.chunks - 1) * 8;
+            const int pos = (w * NO + I - NT) * 64 + l, row = pos / (8 * C::D);
+            e = (uint32_t)min(row, out.rows - 1) * out.ld + min((pos % (8 * C::D)) ^ ring_row_swz<C::D>(row), out.chunks - 1) * 8;
         } else {
             constexpr int CPR = C::TN / 8;                            // chunks per slab row
             const int pos = (w * NO + I - NT) * 64 + l, row = pos / CPR;
@@ -95,7 +103,7 @@ struct RingCopies {
         if constexpr (I < N) {
             if constexpr (FORM) off[I] = lane<I>(w, tok, out);
             if constexpr (I < NT) copy16_to_lds<pass_imm(NT, I), I == 0>(tok.biased, off[I], stage + (w * NT + NT / 2) * 1024);
-            else copy16_to_lds<pass_imm(NO, I - NT), I == NT>(out.biased, off[I], stage + C::TM * BK * 2 + (w * NO + NO / 2) * 1024);
+            else copy16_to_lds<pass_imm(NO, I - NT), I == NT>(out.biased, off[I], stage + C::TM * C::ROWB + (w * NO + NO / 2) * 1024);
             if constexpr (FORM) __builtin_amdgcn_sched_barrier(0);
             issue<FORM, I + 1>(w, tok, out, off, stage);
         }
@@ -105,14 +113,21 @@ struct RingCopies {
     // or nothing.  The barriers are those of the computing waves: one before the first slab, then one per slab, at which the
     // copies of slab kt + 1 have landed and the stage of slab kt is free.
     static __device__ __forceinline__ void run(int w, RingSource tok, RingSource out, int64_t out_adv, const RingSource& ltok,
-                                               const RingSource& lout, int nk, int nkt, uint32_t lds) {
+                                               const RingSource& lout, int slabs, bool has_lora, uint32_t lds) {
         constexpr int NS = C::NS;
+        const int nk = (slabs + C::D - 1) / C::D, nkt = nk + has_lora;
+        const int half_at = C::D == 2 && (slabs & 1) ? nk - 1 : nk;       // the stage of which half is past the contraction's end
         uint32_t off[N];
         auto slab = [&](int kt, int stage, auto form) {           // (first lane: an M0 value is scalar, whatever else the kernel holds)
-            if (kt < nk) {
+            if (kt < half_at) {
                 issue<form()>(w, tok, out, off, __builtin_amdgcn_readfirstlane(lds + stage * C::STAGE));
-                tok.biased += BK * 2;
+                tok.biased += C::ROWB;
                 out.biased += out_adv;
+            } else if (C::D == 2 && kt < nk) {
+                tok.chunks = 8;
+                if constexpr (COL) out.rows = BK;
+                else out.chunks = 8;
+                issue<true>(w, tok, out, off, __builtin_amdgcn_readfirstlane(lds + stage * C::STAGE));
             } else if (kt < nkt) {
                 issue<true>(w, ltok, lout, off, __builtin_amdgcn_readfirstlane(lds + stage * C::STAGE));
             }
@@ -141,13 +156,13 @@ template <class C> struct RingFrags { bf16x8 ft[C::MI], fo[C::NI]; };
 template <class C, bool COL, int J>
 __device__ __forceinline__ void ring_read_one(RingFrags<C>& f, const char* st, int sub, int wm, int wn) {
     const int l = threadIdx.x & 63;
-    const int off = row_slab_off(l & 15, 4 * sub + (l >> 4));
+    const int off = (l & 15) * C::ROWB + (((4 * sub + (l >> 4)) ^ ring_row_swz<C::D>(l & 15)) << 4);
     if constexpr (J == 0 || J > C::NI) {
         constexpr int mi = J == 0 ? 0 : J - C::NI;
-        f.ft[mi] = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + off + (wm * C::MI + mi) * 2048));
+        f.ft[mi] = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + off + (wm * C::MI + mi) * 16 * C::ROWB));
     } else {
         constexpr int ni = J - 1;
-        const char* so = st + C::TM * BK * 2;
+        const char* so = st + C::TM * C::ROWB;
         const int blk = wn * C::NI + ni;
         if constexpr (COL) {
             constexpr int PITCH = C::TN * 2;
@@ -156,7 +171,7 @@ __device__ __forceinline__ void ring_read_one(RingFrags<C>& f, const char* st, i
             const int a = (o ^ (blk << 5)) + sub * 32 * PITCH;
             f.fo[ni] = join_tr(lds_read_tr(so, a), lds_read_tr(so, a + 4 * PITCH));
         } else {
-            f.fo[ni] = __builtin_bit_cast(bf16x8, *(const u32x4*)(so + off + blk * 2048));
+            f.fo[ni] = __builtin_bit_cast(bf16x8, *(const u32x4*)(so + off + blk * 16 * C::ROWB));
         }
     }
 }
@@ -234,22 +249,29 @@ __device__ __forceinline__ void ring_half(f32x4 (&acc)[C::MI][C::NI], const Ring
     }
 }
 
-// A slab with the fragments of two slabs in registers (AHEAD): the MFMAs of `cur`, and in their first half the reads of the next
-// slab's fragments, from `st`.
+// Reads FIRST .. END - 1 of a stage's fragments, sub-step by sub-step.
+template <class C, bool COL, int FIRST, int END>
+__device__ __forceinline__ void ring_read_stage(RingFrags<C> (&f)[C::SUBS], const char* st, int wm, int wn) {
+    if constexpr (FIRST < END) {
+        constexpr int READS = C::MI + C::NI, sub = FIRST / READS;
+        ring_read_one<C, COL, FIRST % READS>(f[sub], st, sub, wm, wn);
+        ring_read_stage<C, COL, FIRST + 1, END>(f, st, wm, wn);
+    }
+}
+
+// A stage with the fragments of two stages in registers (AHEAD): the MFMAs of `cur`, and in their first half the reads of the next
+// stage's fragments, from `st`.
 template <class C, bool COL, int I>
-__device__ __forceinline__ void ring_slab(f32x4 (&acc)[C::MI][C::NI], const RingFrags<C> (&cur)[2], RingFrags<C> (&nxt)[2],
-                                          const char* st, int wm, int wn) {
-    constexpr int SLOTS = C::MI * C::NI, READS = C::MI + C::NI;
-    if constexpr (I < 2 * SLOTS) {
+__device__ __forceinline__ void ring_stage(f32x4 (&acc)[C::MI][C::NI], const RingFrags<C> (&cur)[C::SUBS], RingFrags<C> (&nxt)[C::SUBS],
+                                           const char* st, int wm, int wn) {
+    constexpr int SLOTS = C::MI * C::NI, READS = C::SUBS * (C::MI + C::NI), SPAN = C::SUBS * SLOTS / 2;
+    if constexpr (I < C::SUBS * SLOTS) {
         constexpr int h = I / SLOTS, mi = I % SLOTS / C::NI, ni = I % C::NI;
-        constexpr int lo = I * 2 * READS / SLOTS, hi = (I + 1) * 2 * READS / SLOTS;
-        if constexpr (lo < 2 * READS) {
-            ring_read<C, COL, lo < READS ? lo : READS, hi < READS ? hi : READS>(nxt[0], st, 0, wm, wn);
-            ring_read<C, COL, lo < READS ? 0 : lo - READS, hi < READS ? 0 : hi - READS>(nxt[1], st, 1, wm, wn);
-        }
+        constexpr int lo = I * READS / SPAN, hi = (I + 1) * READS / SPAN;
+        ring_read_stage<C, COL, lo < READS ? lo : READS, hi < READS ? hi : READS>(nxt, st, wm, wn);
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(cur[h].fo[ni]), "v"(cur[h].ft[mi]));
         __builtin_amdgcn_sched_barrier(0);
-        ring_slab<C, COL, I + 1>(acc, cur, nxt, st, wm, wn);
+        ring_stage<C, COL, I + 1>(acc, cur, nxt, st, wm, wn);
     }
 }
 
@@ -264,24 +286,24 @@ __device__ __forceinline__ void ring_tile(const Args& p, char* smem) {
     const int l = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w % C::WM, wn = w / C::WM;
     const bool has_lora = p.r > 0;
-    const int nk = p.KC / BK, nkt = nk + (has_lora ? 1 : 0);
+    const int nk = p.KC / BK;
 
     if (w >= C::NW) {
         const int cw = w - C::NW;
-        const RingSource tok{(const char*)(p.tok + (int64_t)rt.row_start * p.KC) - kCopyBias, (uint32_t)p.KC, rt.rows, 8};
+        const RingSource tok{(const char*)(p.tok + (int64_t)rt.row_start * p.KC) - kCopyBias, (uint32_t)p.KC, rt.rows, 8 * C::D};
         const RingSource ltok{(const char*)(p.ltok + (int64_t)rt.row_start * p.r) - kCopyBias, (uint32_t)p.r, rt.rows, p.r >> 3};
-        const RingSource out = COL ? RingSource{(const char*)(p.out + c0) - kCopyBias, (uint32_t)p.NC, BK, cols_valid >> 3}
-                                   : RingSource{(const char*)(p.out + (int64_t)c0 * p.KC) - kCopyBias, (uint32_t)p.KC, cols_valid, 8};
+        const RingSource out = COL ? RingSource{(const char*)(p.out + c0) - kCopyBias, (uint32_t)p.NC, C::DEPTH, cols_valid >> 3}
+                                   : RingSource{(const char*)(p.out + (int64_t)c0 * p.KC) - kCopyBias, (uint32_t)p.KC, cols_valid, 8 * C::D};
         const RingSource lout = COL ? RingSource{(const char*)(p.lout + (int64_t)rt.g * p.r * p.NC + c0) - kCopyBias, (uint32_t)p.NC, p.r, cols_valid >> 3}
                                     : RingSource{(const char*)(p.lout + ((int64_t)rt.g * p.NC + c0) * p.r) - kCopyBias, (uint32_t)p.r, cols_valid, p.r >> 3};
-        const int64_t out_adv = COL ? (int64_t)BK * p.NC * 2 : BK * 2;
+        const int64_t out_adv = COL ? (int64_t)C::DEPTH * p.NC * 2 : C::ROWB;
         const uint32_t lds = lds_addr_of(smem);
         if constexpr (C::TW == 0)
-            RingCopies<C, COL, C::TM / 8 / C::OW, C::TN / 8 / C::OW>::run(cw, tok, out, out_adv, ltok, lout, nk, nkt, lds);
+            RingCopies<C, COL, C::TM * C::D / 8 / C::OW, C::TN * C::D / 8 / C::OW>::run(cw, tok, out, out_adv, ltok, lout, nk, has_lora, lds);
         else if (cw < C::TW)
-            RingCopies<C, COL, C::TM / 8 / C::TW, 0>::run(cw, tok, out, out_adv, ltok, lout, nk, nkt, lds);
+            RingCopies<C, COL, C::TM * C::D / 8 / C::TW, 0>::run(cw, tok, out, out_adv, ltok, lout, nk, has_lora, lds);
         else
-            RingCopies<C, COL, 0, C::TN / 8 / C::OW>::run(cw - C::TW, tok, out, out_adv, ltok, lout, nk, nkt, lds);
+            RingCopies<C, COL, 0, C::TN * C::D / 8 / C::OW>::run(cw - C::TW, tok, out, out_adv, ltok, lout, nk, has_lora, lds);
         return;
     }
 
@@ -322,33 +344,44 @@ __device__ __forceinline__ void ring_tile(const Args& p, char* smem) {
     asm volatile("s_barrier" ::: "memory");
 
     int stage = 0;
-    RingFrags<C> fa[2];
-    ring_read<C, COL>(fa[0], smem, 0, wm, wn);
+    RingFrags<C> fa[C::SUBS];
     if constexpr (C::AHEAD) {
         // Step kt computes slab kt from registers while it reads slab kt + 1.  At its barrier the copies of that slab have landed,
         // and every wave holds slab kt: the copies of slab kt + NS go into the stage that it has left.  (The last step
         // reads a stage that may hold nothing; without a LoRA term those fragments are not used.)
-        RingFrags<C> fb[2];
-        ring_read<C, COL>(fa[1], smem, 1, wm, wn);
-        auto step = [&](RingFrags<C> (&cur)[2], RingFrags<C> (&nxt)[2]) {
+        RingFrags<C> fb[C::SUBS];
+        ring_read_stage<C, COL, 0, C::SUBS * (MI + NI)>(fa, smem, wm, wn);
+        const int stages = (nk + C::D - 1) / C::D, half_at = C::D == 2 && (nk & 1) ? stages - 1 : stages;
+        auto step = [&](RingFrags<C> (&cur)[C::SUBS], RingFrags<C> (&nxt)[C::SUBS], int kt) {
+            // half a stage at the end: the other half of it is zero (a second path with fewer MFMAs would move accumulators)
+            if (C::D == 2 && kt == half_at) {
+#pragma unroll
+                for (int h = C::SUBS / 2; h < C::SUBS; ++h) {
+#pragma unroll
+                    for (int mi = 0; mi < MI; ++mi) cur[h].ft[mi] = bf16x8{};
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni) cur[h].fo[ni] = bf16x8{};
+                }
+            }
             stage = stage + 1 == NS ? 0 : stage + 1;
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            ring_slab<C, COL, 0>(acc, cur, nxt, smem + stage * C::STAGE, wm, wn);
+            ring_stage<C, COL, 0>(acc, cur, nxt, smem + stage * C::STAGE, wm, wn);
         };
         int kt = 0;
-        for (; kt + 1 < nk; kt += 2) {
-            step(fa, fb);
-            step(fb, fa);
+        for (; kt + 1 < stages; kt += 2) {
+            step(fa, fb, kt);
+            step(fb, fa, kt + 1);
         }
-        if (kt < nk) {
-            step(fa, fb);
+        if (kt < stages) {
+            step(fa, fb, kt);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) fa[h] = fb[h];
+            for (int h = 0; h < C::SUBS; ++h) fa[h] = fb[h];
         }
     } else {
         // Step kt computes slab kt.  The fragments of its second half are read while the first half's MFMAs run; then every
         // read of the stage is behind this wave, the copies of slab kt + 1 have landed, and one barrier makes both true for the
         // whole workgroup: the copies of slab kt + NS go into the stage just left.
+        ring_read<C, COL>(fa[0], smem, 0, wm, wn);
         for (int kt = 0; kt < nk; ++kt) {
             const int next = stage + 1 == NS ? 0 : stage + 1;
             ring_half<C, COL, false, 0>(acc, fa[0], fa[1], smem + stage * C::STAGE, 1, wm, wn);
@@ -429,8 +462,9 @@ __device__ __forceinline__ void ring_tile(const Args& p, char* smem) {
     lora_bf16* res = p.res + (int64_t)rt.row_start * p.NC + c0;
     constexpr int CPR = C::TN / 8;                                    // 16-byte chunks per tile row
 #pragma unroll
-    for (int i = 0; i < C::TM * CPR / C::THREADS; ++i) {
+    for (int i = 0; i < (C::TM * CPR + C::THREADS - 1) / C::THREADS; ++i) {
         const int pos = i * C::THREADS + (int)threadIdx.x, row = pos / CPR, ch = pos % CPR;
+        if (C::TM * CPR < C::THREADS && pos >= C::TM * CPR) break;
         const u32x4 v = *(const u32x4*)(smem + row * PITCH + ((ch ^ (swz(row) >> 1)) << 4));
         if (row < rt.rows && ch * 8 < cols_valid) __builtin_nontemporal_store(v, (u32x4*)(res + (int64_t)row * p.NC + ch * 8));
     }
@@ -497,12 +531,16 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
 // take 64 - 80 KB of LDS), one of the others.  Kind 5 is for launches of at most one workgroup per compute unit: the deeper
 // ring and the single pass over the weight pay when that comes from HBM (77 rows, 4096 -> 14336, weight not cached: 64 x 128
 // tiles 38 us, 128 x 64 tiles 32 us).
-// Kind 4, us, two computing and two copying waves / four and three, (2): 26496 -> 960, 16 rows 59.4 / 54.4; 14336 -> 4096, 16 rows 33.6 / 31.2; 4096 ->
-// 4096 11.6 / 11.1; 1024 -> 1024 4.80 / 4.75.  Two and two / four and four, (5): contraction of 14336 to 4096 columns, 128 rows 41.8 / 40.6;
-// 8192 to 8192, 64 rows 28.1 / 27.2; 4096 to 4096, 128 rows 14.1 / 13.6; 1024 to 1024, 256 rows 4.70 / 4.78, 512 to 14336 3.79 / 3.94.
 // Kind 3, ring of five stages / four, (2): 4096 -> 4096, 160 rows 13.1 / 13.8; (5): 8192 to 8192, 100 rows 29.2 / 28.1, 128 rows 31.2 / 29.6.
+// Kind 4: 128-deep stages, both stages' fragments in registers, and half a tile to a workgroup while every half has a compute unit: a sweep is
+// bound by the bytes that a slab brings to the compute unit (12 KB in 0.13 us, 8 KB in 0.08; longer rings gain nothing).  us, one slab to a stage /
+// two / halves, (2): 1024 -> 1024, 16 rows 4.73 / 4.59 / 3.77, 256 rows 4.88 / 4.74 / 3.88; 2048 -> 2048, 128 rows 6.74 / 6.27 / 5.00; 4096 ->
+// 4096, 16 rows 11.1 / 11.0 / 7.7, 64 rows 11.3 / 12.1 / 8.6; 26496 -> 960, 128 rows 53.9 / 55.6 / 36.5; (5): 1024 -> 1024, 256 rows 4.83 / 4.63 / 4.07;
+// 2048 -> 2048, 128 rows 6.68 / 6.06 / 5.67; 4096 -> 4096, 64 rows 13.8 / 13.4 / 12.9; 8192 -> 1024, 64 rows 17.9 / 15.2 / 11.3.  Whole tiles of
+// (2) over long contractions keep one slab and five stages (128 rows, 4096 -> 4096 11.5 / 12.3).
 using Ring64x64 = Ring<64, 64, 2, 2, 5, 2, 2>;       // of the launches that take the strips
-using Ring32x64 = Ring<32, 64, 1, 2, 6, 1, 1>;
+using Ring32x64 = Ring<32, 64, 2, 2, 3, 1, 2, 2>;
+using Ring32x32 = Ring<32, 32, 2, 2, 4, 2, 2, 2>;    // half of such a tile
 constexpr int kLongContraction = 4096;
 
 template <bool COL>
@@ -513,8 +551,13 @@ static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
         case 2: return launch_ring_cfg<Ring<64, 128, 2, 4, 3, 1, 2>, COL>(a, st);
         case 3: return launch_ring_cfg<Ring<64, 64, 2, 2, COL ? 4 : 5, 2, 2>, COL>(a, st);
         case 4:
-            if (COL && a.KC < kLongContraction) return launch_ring_cfg<Ring32x64, COL>(a, st);
-            return launch_ring_cfg<Ring<32, 64, 2, 2, 6, COL ? 2 : 1, 2>, COL>(a, st);
+            if (ring_halves(a.tiles_m, a.tiles_n)) {
+                RingArgs h = a;
+                h.tiles_n *= 2;
+                return launch_ring_cfg<Ring32x32, COL>(h, st);
+            }
+            if (!COL && a.KC >= kLongContraction) return launch_ring_cfg<Ring<32, 64, 2, 2, 5, 1, 2>, COL>(a, st);
+            return launch_ring_cfg<Ring32x64, COL>(a, st);
         case 5: return launch_ring_cfg<Ring<128, 64, 2, 2, 6, 2, 1>, COL>(a, st);
     }
     return hipErrorInvalidValue;
@@ -522,6 +565,14 @@ static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
 
 hipError_t launch_ring_strips(int kind, const RingStripsArgs& a, hipStream_t st) {
     if (kind == 3) return a.r == 16 ? launch_ring_strips_t<Ring64x64, 1>(a, st) : launch_ring_strips_t<Ring64x64, 2>(a, st);
+    // halves beside the strips: with a compute unit for each, or where the longer contraction makes up for sharing one (us, whole / half tiles, backward:
+    // 256 x 1024 x 1024 8.9 / 9.4, r = 32 8.8 / 10.5; 200 rows, 2048 -> 1024 10.9 / 10.8; 64 x 4096 x 4096, r = 32 20.7 / 20.4; 300 rows, 4096 -> 512 16.6 / 15.6)
+    const bool own = 2 * a.tiles_m * a.tiles_n + a.a.blocks + a.b.blocks <= kComputeUnits;
+    if (kind == 4 && ring_halves(a.tiles_m, a.tiles_n) && (own || a.KC >= 2048)) {
+        RingStripsArgs h = a;
+        h.tiles_n *= 2;
+        return a.r == 16 ? launch_ring_strips_t<Ring32x32, 1>(h, st) : launch_ring_strips_t<Ring32x32, 2>(h, st);
+    }
     if (kind == 4) return a.r == 16 ? launch_ring_strips_t<Ring32x64, 1>(a, st) : launch_ring_strips_t<Ring32x64, 2>(a, st);
     return hipErrorInvalidValue;
 }
