@@ -573,6 +573,11 @@ hipError_t launch_ring_strips(int kind, const RingStripsArgs& a, hipStream_t st)
         h.tiles_n *= 2;
         return a.r == 16 ? launch_ring_strips_t<Ring32x32, 1>(h, st) : launch_ring_strips_t<Ring32x32, 2>(h, st);
     }
+    // whole tiles that share compute units: four waves instead of seven (20 rows of three adapters, 10048 -> 4288, r = 32, 402 workgroups 25.4 us, 26.5
+    // with seven); by themselves the seven are faster (256 x 1024 x 1024 backward 10.2, 10.5 with four)
+    using Shared = Ring<32, 64, 1, 2, 6, 1, 1>;
+    if (kind == 4 && a.tiles_m * a.tiles_n + a.a.blocks + a.b.blocks > kComputeUnits)
+        return a.r == 16 ? launch_ring_strips_t<Shared, 1>(a, st) : launch_ring_strips_t<Shared, 2>(a, st);
     if (kind == 4) return a.r == 16 ? launch_ring_strips_t<Ring32x64, 1>(a, st) : launch_ring_strips_t<Ring32x64, 2>(a, st);
     return hipErrorInvalidValue;
 }
