@@ -472,7 +472,6 @@ __device__ __forceinline__ void ring_tile(const Args& p, char* smem) {
 
 template <class C, bool COL, class TB>
 __global__ void __launch_bounds__(C::THREADS + 64 * C::CW) ring_gemm_kernel(RingArgsOf<TB> p) {
-    fetch_args<RingArgsOf<TB>>();
     extern __shared__ __attribute__((aligned(16))) char smem[];
     ring_tile<C, COL>(p, smem);
 }
@@ -481,7 +480,6 @@ __global__ void __launch_bounds__(C::THREADS + 64 * C::CW) ring_gemm_kernel(Ring
 // kStripsBeside); the waves that a tile has no work for end at once.  Bounded by the latency of one sweep over the contraction.
 template <class C, int CB, class TB>
 __global__ void __launch_bounds__(DA_THREADS, 4) ring_strips_kernel(RingStripsArgsOf<TB> p) {
-    fetch_args<RingStripsArgsOf<TB>>();
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tiles = p.tiles_m * p.tiles_n;
     if ((int)blockIdx.x >= tiles) {
