@@ -24,18 +24,22 @@ namespace lf {
 constexpr int DOWN_SLABS = 4;                       // 64-column slabs per stage
 constexpr int DOWN_PARTS = 2 * DOWN_SLABS;          // a wave owns one half (32 columns) of one slab of every stage
 
-// CB = r / 16 column blocks of S'; RB 16-row blocks per workgroup; ring of NS stages in LDS.  Eight waves compute, one for each
-// column part; further ones copy, N KB of a stage each: XW of them rows of X, AW rows of A.
-template <int CB_, int RB_, int NS_>
+// CB 16-column blocks of S' to a workgroup, PARTS workgroups to the call's rank; ROWS rows; ring of NS stages in LDS.  A wave computes for
+// each column part or, with eight rows, for two of them: a lane then holds row l & 7 of part (l >> 3) & 1, and an MFMA for either
+// part's columns of A has that part's sums in its half of the lanes.  Further waves copy, N KB of a stage each: XW of them rows of X,
+// AW rows of A.
+template <int CB_, int ROWS_, int NS_, int PARTS_ = 1>
 struct Down {
-    static constexpr int CB = CB_, RB = RB_, NS = NS_;
-    static constexpr int THREADS = 64 * DOWN_PARTS;                                        // that compute
-    static constexpr int X_COPIES = DOWN_SLABS * RB * 2, A_COPIES = DOWN_SLABS * CB * 2;   // 1 KB wave copies per stage
+    static constexpr int CB = CB_, ROWS = ROWS_, NS = NS_, PARTS = PARTS_;
+    static constexpr bool PAIR = ROWS == 8;
+    static constexpr int RB = PAIR ? 1 : ROWS / 16;                                        // fragments of rows
+    static constexpr int WAVES = PAIR ? DOWN_PARTS / 2 : DOWN_PARTS, THREADS = 64 * WAVES; // that compute
+    static constexpr int X_COPIES = DOWN_SLABS * ROWS / 8, A_COPIES = DOWN_SLABS * CB * 2; // 1 KB wave copies per stage
     static constexpr int XN = RB == 2 && CB < 4 ? 8 : 4, AN = CB == 4 || RB == 2 ? 8 : 4;    // ... per wave
     static constexpr int XW = X_COPIES / XN, AW = A_COPIES / AN;
     static constexpr int STAGE = (X_COPIES + A_COPIES) * 1024;
     static constexpr int LDS = NS * STAGE;
-    static_assert(DOWN_PARTS + XW + AW <= 16 && AN * (NS - 1) < 64, "a workgroup; the wait counter has six bits");
+    static_assert(WAVES + XW + AW <= 16 && AN * (NS - 1) < 64, "a workgroup; the wait counter has six bits");
     static_assert(DOWN_PARTS * RB * CB * 1024 <= LDS, "the cross-wave sum goes through the ring");
 };
 
@@ -84,22 +88,24 @@ __device__ __forceinline__ void down_copier(int w, const lora_bf16* mat, int K, 
     }
 }
 
-// Fixed-order sum over the column parts ([DOWN_PARTS][RB][CB][64] in LDS), scaled by s*q and rounded once to bf16.
-template <int CB, int RB, int THREADS, class TB>
-__device__ __forceinline__ void down_store(const DownArgsOf<TB>& p, const RowTile& rt, const f32x4* red) {
+// Fixed-order sum over the column parts ([DOWN_PARTS][RB][CB][4 * RL] in LDS, RL rows to a block), scaled by s*q and rounded once to
+// bf16, into columns c0 .. of S'.
+template <int CB, int RB, int THREADS, int RL = 16, class TB>
+__device__ __forceinline__ void down_store(const DownArgsOf<TB>& p, const RowTile& rt, const f32x4* red, int c0 = 0) {
     const float sq = p.tb.a[rt.g].s * p.tb.a[rt.g].q;
-    for (int idx = threadIdx.x; idx < RB * CB * 64; idx += THREADS) {
-        const int lane = idx & 63, cb = (idx >> 6) % CB, rb = (idx >> 6) / CB;
+    constexpr int BLOCK = 4 * RL;
+    for (int idx = threadIdx.x; idx < RB * CB * BLOCK; idx += THREADS) {
+        const int lane = idx % BLOCK, cb = idx / BLOCK % CB, rb = idx / BLOCK / CB;
         f32x4 v = red[idx];
 #pragma unroll
-        for (int ww = 1; ww < DOWN_PARTS; ++ww) v += red[ww * (RB * CB * 64) + idx];
-        if (cb * 16 >= p.tb.a[rt.g].rank) v = f32x4{0.f, 0.f, 0.f, 0.f};
-        const int row = rb * 16 + (lane & 15);
+        for (int ww = 1; ww < DOWN_PARTS; ++ww) v += red[ww * (RB * CB * BLOCK) + idx];
+        if (c0 + cb * 16 >= p.tb.a[rt.g].rank) v = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int row = rb * 16 + lane % RL;
         if (row < rt.rows) {
             u32x2 out;
             out.x = pack_bf16x2(v[0] * sq, v[1] * sq);
             out.y = pack_bf16x2(v[2] * sq, v[3] * sq);
-            *(u32x2*)(p.S + (int64_t)(rt.row_start + row) * p.r + cb * 16 + 4 * (lane >> 4)) = out;
+            *(u32x2*)(p.S + (int64_t)(rt.row_start + row) * p.r + c0 + cb * 16 + 4 * (lane / RL)) = out;
         }
     }
 }
@@ -110,38 +116,42 @@ __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel
     constexpr int CB = C::CB, RB = C::RB, NS = C::NS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     RowTile rt;
-    if (!find_row_tile_by_lanes(p.tb, 16 * RB, blockIdx.x, rt)) return;
+    if (!find_row_tile_by_lanes(p.tb, C::ROWS, blockIdx.x, rt)) return;
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = rt.g;
+    const int g = rt.g, c0 = C::PARTS == 1 ? 0 : blockIdx.y * (CB * 16);          // this workgroup's first column of S'
     const int nslabs = p.K / BK, nst = (nslabs + DOWN_SLABS - 1) / DOWN_SLABS;
     // Every workgroup starts its sweep over K at a different stage (a function of its 32-row group within the segment,
     // so that single- and multi-adapter calls, and both workgroup heights, sum in the same order): workgroups sweeping
     // in lockstep would all hit the same few L2 channels, the row pitch being a multiple of the channel interleave.
     int st = (int)(((unsigned)(rt.local_row0 / 32) * 5u) % (unsigned)nst);
-    if (w >= DOWN_PARTS) {
-        const int cw = w - DOWN_PARTS;
+    if (w >= C::WAVES) {
+        const int cw = w - C::WAVES;
         const uint32_t lds = lds_addr_of(smem);
         if (cw < C::XW)
-            down_copier<C, C::XN, 2 * RB>(cw, p.X + (int64_t)rt.row_start * p.K, p.K, rt.rows - 1, st, nslabs, nst, lds);
+            down_copier<C, C::XN, C::ROWS / 8>(cw, p.X + (int64_t)rt.row_start * p.K, p.K, rt.rows - 1, st, nslabs, nst, lds);
         else
-            down_copier<C, C::AN, 2 * CB>(cw - C::XW, p.A + (int64_t)g * p.r * p.K, p.K, p.tb.a[g].rank - 1, st, nslabs, nst,
+            down_copier<C, C::AN, 2 * CB>(cw - C::XW, p.A + ((int64_t)g * p.r + c0) * p.K, p.K, max(p.tb.a[g].rank - c0, 1) - 1, st, nslabs, nst,
                                           lds + C::X_COPIES * 1024);
         return;
     }
-    const int pos = w >> 1, sub = w & 1;                // this wave's slab and half of it
+    const int pos = C::PAIR ? w : w >> 1, sub = C::PAIR ? (l >> 3) & 1 : w & 1;  // this wave's slab and half of it (PAIR: this lane's half)
+    const int lrow = C::PAIR ? l & 7 : l & 15;
     const uint32_t T = p.tb.a[g].T;
     const KeepThreshold th = keep_threshold(T);
 
     RowKey rk[RB];
-    f32x4 acc[RB][CB];
+    constexpr int H = C::PAIR ? 2 : 1;                  // halves that a wave forms
+    f32x4 acc[H * RB][CB];
     u32x4 keep[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        rk[rb] = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.local_row0 + rb * 16 + (l & 15)));
+        rk[rb] = row_key(p.tb.a[g].k0, p.tb.a[g].k1, (uint32_t)(rt.local_row0 + rb * 16 + lrow));
         keep[rb] = u32x4{~0u, ~0u, ~0u, ~0u};
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+#pragma unroll
+    for (int i = 0; i < H * RB; ++i)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[i][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     // keep masks of this lane's 8 columns in stage t
     auto form_masks = [&](int t) {
         const uint32_t x0 = (uint32_t)((t * DOWN_SLABS + pos) * (BK / 2) + 16 * sub + 4 * (l >> 4)) * kGold;
@@ -151,20 +161,24 @@ __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel
             for (int i = 0; i < 4; ++i)
                 keep[rb][i] = keep_pair_mask(hash_word_at(rk[rb], rk[rb].a + x0 + (uint32_t)i * kGold), th);
     };
-    const int o = row_slab_off(l & 15, 4 * sub + (l >> 4));
-    const char* xs = smem + pos * RB * 2048 + o;
-    const char* as = smem + C::X_COPIES * 1024 + pos * (CB * 2048) + o;
+    const char* xs = smem + pos * C::ROWS * 128 + row_slab_off(lrow, 4 * sub + (l >> 4));
+    const char* as[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+        as[h] = smem + C::X_COPIES * 1024 + pos * (CB * 2048) + row_slab_off(l & 15, 4 * (C::PAIR ? h : sub) + (l >> 4));
 
     int ring = 0;
     for (int s = 0; s < nst; ++s) {
         if (T) form_masks(st);                          // while the stage's copies land
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         u32x4 x[RB];
-        bf16x8 a[CB];
+        bf16x8 a[H][CB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) x[rb] = *(const u32x4*)(xs + ring * C::STAGE + rb * 2048);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) a[cb] = __builtin_bit_cast(bf16x8, *(const u32x4*)(as + ring * C::STAGE + cb * 2048));
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) a[h][cb] = __builtin_bit_cast(bf16x8, *(const u32x4*)(as[h] + ring * C::STAGE + cb * 2048));
         __builtin_amdgcn_sched_barrier(0);
         if (st * DOWN_SLABS + pos < nslabs) {
 #pragma unroll
@@ -172,8 +186,10 @@ __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel
                 x[rb] &= keep[rb];
                 const bf16x8 xf = __builtin_bit_cast(bf16x8, x[rb]);
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb)            // (the call's rank: columns past the adapter's are zeroed on the way out)
-                    asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[rb][cb]) : "v"(a[cb]), "v"(xf));
+                for (int h = 0; h < H; ++h)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)            // (the call's rank: columns past the adapter's are zeroed on the way out)
+                        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[h * RB + rb][cb]) : "v"(a[h][cb]), "v"(xf));
             }
         }
         st = st + 1 == nst ? 0 : st + 1;
@@ -182,17 +198,31 @@ __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel
 
     asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+    for (int i = 0; i < H * RB; ++i)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+v"(acc[rb][cb]));
+        for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+v"(acc[i][cb]));
     __syncthreads();
-    f32x4* red = (f32x4*)smem;                             // [DOWN_PARTS][RB][CB][64]
+    f32x4* red = (f32x4*)smem;                             // [DOWN_PARTS][RB][CB][64], PAIR: [DOWN_PARTS][CB][32]
+    if constexpr (C::PAIR) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+        for (int cb = 0; cb < CB; ++cb) {
+            f32x4 v = acc[0][cb];
+            const f32x4 other = acc[H - 1][cb];
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) red[((w * RB + rb) * CB + cb) * 64 + l] = acc[rb][cb];
+            for (int e = 0; e < 4; ++e) {
+                const float x = v[e], y = other[e];
+                v[e] = sub ? y : x;
+            }
+            red[((2 * w + sub) * CB + cb) * 32 + (l >> 4) * 8 + lrow] = v;
+        }
+    } else {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) red[((w * RB + rb) * CB + cb) * 64 + l] = acc[rb][cb];
+    }
     __syncthreads();
-    down_store<CB, RB, C::THREADS>(p, rt, red);
+    down_store<CB, RB, C::THREADS, C::PAIR ? 8 : 16>(p, rt, red, c0);
 }
 
 // The same sums without LDS: wave w loads the fragments of column part w of every stage straight into registers, D stages
@@ -281,7 +311,7 @@ static hipError_t launch_down_cfg(const DownArgs& a, int tiles, hipStream_t st) 
             if (e != hipSuccess) return e;
             attr_set = true;
         }
-        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(C::THREADS + 64 * (C::XW + C::AW)), C::LDS, st, b);
+        hipLaunchKernelGGL(kernel, dim3(tiles, C::PARTS), dim3(C::THREADS + 64 * (C::XW + C::AW)), C::LDS, st, b);
         return hipGetLastError();
     });
 }
@@ -296,11 +326,12 @@ static hipError_t launch_down_direct(const DownArgs& a, int tiles, hipStream_t s
 }
 
 hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
-    int tiles32 = 0, tiles16 = 0;
+    int tiles32 = 0, tiles16 = 0, tiles8 = 0;
     for (int g = 0; g < a.tb.G; ++g) {
         const int len = a.tb.row0[g + 1] - a.tb.row0[g];
         tiles32 += (len + 31) / 32;
         tiles16 += (len + 15) / 16;
+        tiles8 += (len + 7) / 8;
     }
     if (tiles32 == 0) return hipSuccess;
     // A 16-row workgroup takes 0.65 - 0.8 of a 32-row one's time (its copies of A serve half as many rows), so it is the
@@ -323,9 +354,27 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
     // r = 32: two of the 16-row workgroups fit on a compute unit, one of the 32-row ones (128 KB of LDS); in several rounds
     // that is worth more than the second reading of A up to K = 2048 (40000 rows: K = 1024 22 / 25 us, K = 2048 33 / 40, K = 4096 69 / 65).
     const bool small32 = forced ? forced == 128 : one_round || (many && a.K <= 2048);
-    if (a.r == 16) return small ? launch_down_cfg<Down<1, 1, 5>>(a, tiles16, st) : launch_down_cfg<Down<1, 2, 3>>(a, tiles32, st);
-    if (a.r == 32) return small32 ? launch_down_cfg<Down<2, 1, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 2, 4>>(a, tiles32, st);
-    if (a.r == 64) return small ? launch_down_cfg<Down<4, 1, 4>>(a, tiles16, st) : launch_down_cfg<Down<4, 2, 3>>(a, tiles32, st);
+    // A stage takes a workgroup the longer of its masks (16 rows 0.22 us: two waves of them to a SIMD) and its copies (X and A, 100 KB/us), so
+    // while all workgroups run at once it is given eight rows, and as few of the rank's columns as that leaves room for; 16 rows by half the
+    // columns at r = 64 (A is four fifths of its copies).  A forward over N = 256, operands from HBM, us, 16 rows by all columns / now: r = 16, K = 4096,
+    // 77 rows without dropout 16.6 / 13.6, 1024 rows 18.7 / 15.4, 2048 rows 23.9 / 23.0; K = 2048, 1000 rows 12.6 / 11.0; r = 32, K = 4096, 500 rows 19.0 /
+    // 15.2, 2000 rows 25.2 / 24.9; r = 64, 400 rows 20.3 / 15.7, 1531 rows 27.6 / 24.6.  Same bits.
+    auto fits = [&](int tiles, int parts) { return !forced && tiles * parts <= kComputeUnits; };
+    if (a.r == 16) {
+        if (fits(tiles8, 1)) return launch_down_cfg<Down<1, 8, 6>>(a, tiles8, st);
+        return small ? launch_down_cfg<Down<1, 16, 5>>(a, tiles16, st) : launch_down_cfg<Down<1, 32, 3>>(a, tiles32, st);
+    }
+    if (a.r == 32) {
+        if (fits(tiles8, 2)) return launch_down_cfg<Down<1, 8, 6, 2>>(a, tiles8, st);
+        if (fits(tiles8, 1)) return launch_down_cfg<Down<2, 8, 5>>(a, tiles8, st);
+        return small32 ? launch_down_cfg<Down<2, 16, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 32, 4>>(a, tiles32, st);
+    }
+    if (a.r == 64) {
+        if (fits(tiles8, 4)) return launch_down_cfg<Down<1, 8, 6, 4>>(a, tiles8, st);
+        if (fits(tiles8, 2)) return launch_down_cfg<Down<2, 8, 5, 2>>(a, tiles8, st);
+        if (fits(tiles16, 2)) return launch_down_cfg<Down<2, 16, 4, 2>>(a, tiles16, st);
+        return small ? launch_down_cfg<Down<4, 16, 4>>(a, tiles16, st) : launch_down_cfg<Down<4, 32, 3>>(a, tiles32, st);
+    }
     return hipErrorInvalidValue;
 }
 
