@@ -50,7 +50,9 @@ using FewAdapters = AdapterTableOf<kFewAdapters>;
 
 // First statement of a kernel whose arguments are of type Args: asks for every cache line of them at once.  A launch finds them in
 // memory, not in a cache, and the compiler loads a field where it is first needed: the number of adapters, behind that the walk over
-// the segments, behind that the adapter's entry.
+// the segments, behind that the adapter's entry, 0.35 us each.  Two accumulating backward passes over 2048 x 4096 x 4096 37.2 -> 36.6 us, a step of
+// 1531 packed rows 63.2 -> 62.6.  Not in the small-tile GEMMs, whose hundreds of workgroups would all wait for the last line (471 of them, a step of
+// 66.5 -> 67.9 us).
 template <class Args>
 __device__ __forceinline__ void fetch_args() {
     constexpr int LINES = ((int)sizeof(Args) + 63) / 64, N = LINES < 8 ? LINES : 3;     // (of a full table its first offsets)
