@@ -45,6 +45,7 @@ struct Ring {
     static constexpr int REGS = 512 / ((NW + CW + 3) / 4);            // of a wave, with a SIMD's share of the workgroup on it
     // fragments of two slabs in registers: where they fit beside the accumulators and some forty others (128 x 64 tiles with the
     // shorter sub-steps of a 2 x 4 split, 512 x 4096 x 4096: 22.4 -> 23.8 us, so not below eight MFMAs)
+    static constexpr bool STRAIGHT = D == 1 && TM == 32;              // see RingCopies::run
     static constexpr bool AHEAD = D == 2 || MI * NI >= 8 && MI * NI * 4 + (MI + NI) * 16 + 40 <= REGS;
     static_assert(TM * D / 8 % (TW ? TW : OW) == 0 && TN * D / 8 % OW == 0, "the copies of a slab divide evenly over the waves");
     static_assert(NS >= 2, "ring depth");
@@ -138,8 +139,23 @@ struct RingCopies {
         if (nkt >= NS) wait_slab_loads_but<N*(NS - 1)>();
         else wait_slab_loads();
         asm volatile("s_barrier" ::: "memory");
-        int stage = 0;
-        for (int kt = 0; kt < nk; ++kt) {
+        int stage = 0, kt = 0;
+        // While a whole base slab follows, without a branch: the loop below picks its wait and its sources anew in every step, some
+        // twenty instructions and four jumps between the barrier and the copies, which the slab of a lone 32 x 64 tile (0.13 us) waits for (and which a change
+        // elsewhere in the kernel moved by 2 - 5 % of it).  (2) alone, us, that loop / this, weight cached: 4096 -> 4096, 80 rows 11.9 / 10.6, 128
+        // rows 12.1 / 11.3; 8192 -> 4096, 128 rows 22.1 / 19.3; 4096 -> 2112, 128 rows 11.1 / 9.6; from HBM level (16.8 / 16.8, 29.0 / 28.9).  The other tiles keep
+        // that loop: copies that come at once are no better there and, with the weight from HBM, worse (256 rows, 17024 -> 17856
+        // 240 / 260; 1500 rows, 4096 -> 4096, backward 68 / 72).
+        if constexpr (C::STRAIGHT) {
+            for (; kt + NS < half_at; ++kt) {
+                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(N * (NS - 2)) : "memory");
+                issue<false>(w, tok, out, off, __builtin_amdgcn_readfirstlane(lds + stage * C::STAGE));
+                tok.biased += C::ROWB;
+                out.biased += out_adv;
+                stage = stage + 1 == NS ? 0 : stage + 1;
+            }
+        }
+        for (; kt < nk; ++kt) {
             if (kt + NS <= nkt) wait_slab_loads_but<N*(NS - 2)>();
             else wait_slab_loads();
             asm volatile("s_barrier" ::: "memory");
@@ -535,7 +551,8 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
 // two / halves, (2): 1024 -> 1024, 16 rows 4.73 / 4.59 / 3.77, 256 rows 4.88 / 4.74 / 3.88; 2048 -> 2048, 128 rows 6.74 / 6.27 / 5.00; 4096 ->
 // 4096, 16 rows 11.1 / 11.0 / 7.7, 64 rows 11.3 / 12.1 / 8.6; 26496 -> 960, 128 rows 53.9 / 55.6 / 36.5; (5): 1024 -> 1024, 256 rows 4.83 / 4.63 / 4.07;
 // 2048 -> 2048, 128 rows 6.68 / 6.06 / 5.67; 4096 -> 4096, 64 rows 13.8 / 13.4 / 12.9; 8192 -> 1024, 64 rows 17.9 / 15.2 / 11.3.  Whole tiles of
-// (2) over long contractions keep one slab and five stages (128 rows, 4096 -> 4096 11.5 / 12.3).
+// (2) over long contractions keep one slab to a stage (128 rows, 4096 -> 4096 11.5 / 12.3), in five stages (five / six: 4096 -> 4096, 80 rows 10.7 / 10.8,
+// 128 rows 11.2 / 11.4, from HBM 16.9 / 17.4; 8192 -> 2112, 128 rows 18.2 / 18.2, from HBM 28.0 / 28.5; 8192 -> 4096, 80 rows from HBM 28.0 / 27.7).
 using Ring64x64 = Ring<64, 64, 2, 2, 5, 2, 2>;       // of the launches that take the strips
 using Ring32x64 = Ring<32, 64, 2, 2, 3, 1, 2, 2>;
 using Ring32x32 = Ring<32, 32, 2, 2, 4, 2, 2, 2>;    // half of such a tile

@@ -5,7 +5,8 @@ assembly would give wrong results without an error.
   - along every path, an MFMA comes at least two wait states after a vector ALU write of one of its operands, and nothing touches
     its result within the next eight unless another MFMA has taken it as accumulator input, for which the matrix pipe waits by
     itself (the distances that the compiler keeps around the 16x16x32 MFMA; 16 for the 32x32x16 one);
-  - M0, which a copy to LDS takes over from the copy before it, is written by the copies alone."""
+  - M0, which a copy to LDS takes over from the copy before it, is written by the copies alone.
+And what a time depends on: the copying waves of whole 32 x 64 tiles reach the copies behind a barrier without a branch."""
 import os
 import re
 import shutil
@@ -150,6 +151,19 @@ def test_only_the_copies_write_m0(functions):
                 writes += 1
                 assert (mnemonic, code[i + 1][0], code[i + 2][0]) == ("s_mov_b32", "s_nop", "global_load_lds_dwordx4"), (name, i)
     assert writes > 100
+
+
+def test_copies_of_whole_narrow_tiles_follow_the_barrier(functions):
+    """A loop that holds the barrier and the copies, and nothing else but scalar arithmetic, for the token and for the out waves."""
+    kernels = [code for name, code in functions if re.search(r"ring_gemm_kernelINS_4RingILi32ELi64E(Li\d+E){5}Li1EEELb0E", name)]
+    assert len(kernels) == 2                                # both sizes of the adapter table
+    for code in kernels:
+        straight = 0
+        for i, (name, _, to) in enumerate(code):
+            body = [c[0] for c in code[to:i]] if to is not None and to < i else []
+            straight += "s_barrier" in body and "global_load_lds_dwordx4" in body[body.index("s_barrier"):] and \
+                all(n.startswith(("s_", "global_load_lds")) and not n.startswith(("s_branch", "s_cbranch")) for n in body)
+        assert straight == 2
 
 
 @pytest.mark.parametrize("body,expected", [
