@@ -571,7 +571,8 @@ static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
                 h.tiles_n *= 2;
                 return launch_ring_cfg<Ring32x32, COL>(h, st);
             }
-            if (!COL && a.KC >= kLongContraction) return launch_ring_cfg<Ring<32, 64, 2, 2, 5, 1, 2>, COL>(a, st);
+            if constexpr (!COL)
+                if (a.KC >= kLongContraction) return launch_ring_cfg<Ring<32, 64, 2, 2, 5, 1, 2>, COL>(a, st);
             return launch_ring_cfg<Ring32x64, COL>(a, st);
         case 5: return launch_ring_cfg<Ring<128, 64, 2, 2, 6, 2, 1>, COL>(a, st);
     }

@@ -166,6 +166,11 @@ def test_copies_of_whole_narrow_tiles_follow_the_barrier(functions):
         assert straight == 2
 
 
+def test_no_backward_kernel_of_one_slab_to_a_stage(functions):
+    """(5) by itself takes 32 x 64 tiles in 128-deep stages only: nothing could launch the others."""
+    assert not [name for name, _ in functions if re.search(r"ring_gemm_kernelINS_4RingILi32ELi64E(Li\d+E){5}Li1EEELb1E", name)]
+
+
 @pytest.mark.parametrize("body,expected", [
     ("\tv_mov_b32_e32 v4, v9 // 100:\n\tv_mfma_f32_16x16x32_bf16 v[0:3], v[4:7], v[8:11], v[0:3] // 104:\n\ts_nop 15 // 10C:\n", 1),
     ("\tv_mov_b32_e32 v4, v9 // 100:\n\ts_nop 1 // 102:\n\tv_mfma_f32_16x16x32_bf16 v[0:3], v[4:7], v[8:11], v[0:3] // 104:\n", 0),
