@@ -151,13 +151,13 @@ lora_status lora_debug_mask(int64_t M, int64_t K, float p, uint64_t seed, uint8_
 
 /* Tuning knob and test hook (process-wide, not thread safe).  Several kernels exist in more than
  * one height: the GEMMs of operations (2) and (5) (Section 5.1) with 256 down to 32 token rows per output
- * tile, the down-projection of operation (1) with 32 or 16 token rows per workgroup, operation (3) as one pass with row
+ * tile, the down-projection of operation (1) with 32, 16 or 8 token rows per workgroup, operation (3) as one pass with row
  * panels of 1024 down to 64 rows or, in batches of up to 6144 rows, as dS by itself and dB beside (4), and operation
  * (4) with whole segments or row panels of 256 rows (beside dB 512) and more.
  * By default every launch picks the height that fills the chip better (the small ones for short batches and
  * narrow projections; a GEMM may take two launches of different heights).  rows = 256 fixes the large height
  * of the GEMMs and of (1), one pass in (3) and panels of at least 256 rows in (3) and (4) for all later calls, rows = 128
- * GEMM tiles of 128 rows x 256 columns and the small height of (1), rows = 0 restores the automatic choice;
+ * GEMM tiles of 128 rows x 256 columns and 16 rows in (1), rows = 0 restores the automatic choice;
  * any other value returns LORA_ERR_PARAM.  Y, S_saved and dX are bit-identical under all three settings; dA
  * and dB are fp32 sums over the row panels and agree up to the order of those sums. */
 lora_status lora_set_row_tile(int32_t rows);
@@ -204,6 +204,26 @@ lora_status lora_debug_bwd_plan(int64_t M, int64_t K, int64_t N, int32_t r, int3
 lora_status lora_debug_gemm_tiles(int64_t M, int64_t contraction, int64_t columns, int32_t r, int32_t G,
                                   const int64_t* seg_offsets, int32_t* parts, int32_t* tile_rows, int32_t* tile_columns,
                                   int64_t* first_row);
+
+/* Diagnostic (host only): the kernels that operations (1), (2) and (5) of a forward and a backward call of these sizes would launch
+ * under the current settings of the two knobs; the backward with dX and the workspace of lora_bwd_workspace_bytes.
+ * fwd, dx: one or two launches each (M = 0: none); what is not launched is all zero. */
+typedef struct {
+    int32_t rows, columns;    /* output tile of a workgroup; 32 x 32 is half of a 32 x 64 tile of lora_debug_gemm_tiles */
+    int32_t depth, stages;    /* contraction elements to a stage in LDS, and the number of stages */
+    int32_t waves;            /* of a workgroup's tile, those that only copy among them */
+    int32_t asks_ahead;       /* 1: lines are asked for a slab ahead of their copies */
+    int64_t workgroups;       /* the strips of (4) and dB among them, where they run in the launch of (5) */
+} lora_gemm_launch;
+typedef struct {
+    int32_t down_rows;        /* operation (1): token rows of a workgroup */
+    int32_t down_parts;       /* ... and how many workgroups share the rank's columns */
+    int32_t down_ring;        /* ... 1: through a ring of stages in LDS; 0: straight into registers */
+    int64_t down_workgroups;
+    lora_gemm_launch fwd[2], dx[2];
+} lora_launches;
+lora_status lora_debug_launches(int64_t M, int64_t K, int64_t N, int32_t r, int32_t G, const int64_t* seg_offsets,
+                                lora_launches* out);
 
 /* Diagnostic per-kernel timing for benchmarks.  Between lora_profile_begin() and
  * lora_profile_end() every kernel the entry points above enqueue is bracketed by a pair of HIP

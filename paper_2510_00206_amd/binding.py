@@ -19,7 +19,7 @@ LIB_PATH = os.path.join(_HERE, "liblorafusion_hip.so")
 EXPORTS = ("lora_fwd", "lora_bwd", "lora_bwd_noalloc", "multi_lora_fwd", "multi_lora_bwd", "multi_lora_fwd_ranked",
            "multi_lora_bwd_ranked", "lora_bwd_workspace_bytes",
            "lora_debug_mask", "lora_status_string", "lora_version", "lora_set_row_tile", "lora_set_slab_lookahead", "lora_debug_stream_panels",
-           "lora_debug_da_panels", "lora_debug_bwd_plan", "lora_debug_gemm_tiles",
+           "lora_debug_da_panels", "lora_debug_bwd_plan", "lora_debug_gemm_tiles", "lora_debug_launches",
            "lora_unfused_fwd", "lora_unfused_bwd", "lora_unfused_workspace_bytes")
 
 _lib = None
@@ -29,6 +29,17 @@ class BwdPlan(C.Structure):
     """What a backward call launches (lora_bwd_plan in the header)."""
     _fields_ = [("ds_alone", C.c_int32), ("panel_rows_db", C.c_int32), ("panel_rows_da", C.c_int32), ("added_in_strips", C.c_int32),
                 ("with_dx", C.c_int32), ("bytes", C.c_int64)]
+
+
+class GemmLaunch(C.Structure):
+    """One kernel of operation (2) or (5) (lora_gemm_launch in the header)."""
+    _fields_ = [(f, C.c_int32) for f in ("rows", "columns", "depth", "stages", "waves", "asks_ahead")] + [("workgroups", C.c_int64)]
+
+
+class Launches(C.Structure):
+    """What operations (1), (2) and (5) launch (lora_launches in the header)."""
+    _fields_ = [(f, C.c_int32) for f in ("down_rows", "down_parts", "down_ring")] + \
+               [("down_workgroups", C.c_int64), ("fwd", GemmLaunch * 2), ("dx", GemmLaunch * 2)]
 
 
 def load_library() -> C.CDLL:
@@ -78,6 +89,8 @@ def load_library() -> C.CDLL:
         getattr(lib, f).restype = C.c_int
     lib.lora_debug_bwd_plan.argtypes = [I64, I64, I64, I32, I32, C.POINTER(I64), I32, SZ, C.POINTER(BwdPlan)]
     lib.lora_debug_bwd_plan.restype = C.c_int
+    lib.lora_debug_launches.argtypes = [I64, I64, I64, I32, I32, C.POINTER(I64), C.POINTER(Launches)]
+    lib.lora_debug_launches.restype = C.c_int
     lib.lora_profile_end.argtypes = [C.POINTER(F), C.POINTER(I32)]
     lib.lora_ceiling_mfma.argtypes = [P, P, I32, I32, I32, C.POINTER(C.c_double), P]
     lib.lora_ceiling_mfma.restype = C.c_int
@@ -234,6 +247,13 @@ def lora_debug_bwd_plan(K, N, r, seg_offsets, need_dx=True, scratch=0) -> BwdPla
     _check(load_library().lora_debug_bwd_plan(seg_offsets[-1], K, N, r, len(seg_offsets) - 1, _arr(C.c_int64, seg_offsets), int(need_dx),
                                               scratch, C.byref(plan)))
     return plan
+
+
+def lora_debug_launches(K, N, r, seg_offsets) -> Launches:
+    """The kernels of (1), (2) and (5) that a forward and a backward over these segments would launch (host only)."""
+    out = Launches()
+    _check(load_library().lora_debug_launches(seg_offsets[-1], K, N, r, len(seg_offsets) - 1, _arr(C.c_int64, seg_offsets), C.byref(out)))
+    return out
 
 
 def lora_set_row_tile(rows: int):

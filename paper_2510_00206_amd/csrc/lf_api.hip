@@ -413,6 +413,38 @@ lora_status lora_debug_gemm_tiles(int64_t M, int64_t contraction, int64_t column
     return LORA_OK;
 }
 
+static lora_gemm_launch as_abi(const GemmLaunch& g) {
+    return lora_gemm_launch{g.rows, g.columns, g.depth, g.stages, g.waves, g.asks_ahead, g.workgroups};
+}
+
+lora_status lora_debug_launches(int64_t M, int64_t K, int64_t N, int32_t r, int32_t G, const int64_t* seg_offsets,
+                                lora_launches* out) {
+    if (!seg_offsets || !out) return LORA_ERR_NULL;
+    lora_status st = check_shape(M, K, N, r, G);
+    if (st != LORA_OK) return st;
+    AdapterTable tb;
+    st = segments_only(tb, M, K, G, seg_offsets);
+    if (st != LORA_OK) return st;
+    *out = lora_launches{};
+    if (M == 0) return LORA_OK;
+    BwdPlan pl = plan_bwd(tb, M, K, N);
+    alignas(256) char base[256];                       // (addresses only, as in lora_debug_bwd_plan)
+    lora_bf16* any = (lora_bf16*)base;
+    const Workspace ws = lay_out(base, workspace_bytes_of(M, K, N, r, G), M, K, N, r, tb, pl);
+    const StripArgs strips = strip_args(any, any, any, K, N, r, tb, (float*)base, (float*)base, 0, ws, pl);
+    const DownLaunch d = down_launch(DownArgs{any, any, any, (int)M, (int)K, r, tb}, pl.forced);
+    out->down_rows = d.rows;
+    out->down_parts = d.parts;
+    out->down_ring = d.ring;
+    out->down_workgroups = d.workgroups;
+    GemmLaunch g[2];
+    int n = fwd_gemm_launches(FwdGemmArgs{any, any, any, any, any, (int)M, (int)K, (int)N, r, 0, 0, 0, tb}, pl.forced, g);
+    for (int i = 0; i < n; ++i) out->fwd[i] = as_abi(g[i]);
+    n = bwd_dx_launches(DxGemmArgs{any, any, any, any, any, (int)M, (int)K, (int)N, r, 0, 0, 0, tb}, pl.forced, &strips, g);
+    for (int i = 0; i < n; ++i) out->dx[i] = as_abi(g[i]);
+    return LORA_OK;
+}
+
 const char* lora_status_string(lora_status st) {
     switch (st) {
         case LORA_OK: return "ok";

@@ -325,7 +325,11 @@ static hipError_t launch_down_direct(const DownArgs& a, int tiles, hipStream_t s
     });
 }
 
-hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
+template <int V> using IC = std::integral_constant<int, V>;
+
+// Calls ring(kernel, row tiles) or direct(r / 16, 16-row blocks, row tiles) with what the launch takes.
+template <class R, class D>
+static auto with_down(const DownArgs& a, int forced, R&& ring, D&& direct) {
     int tiles32 = 0, tiles16 = 0, tiles8 = 0;
     for (int g = 0; g < a.tb.G; ++g) {
         const int len = a.tb.row0[g + 1] - a.tb.row0[g];
@@ -333,7 +337,6 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
         tiles16 += (len + 15) / 16;
         tiles8 += (len + 7) / 8;
     }
-    if (tiles32 == 0) return hipSuccess;
     // A 16-row workgroup takes 0.65 - 0.8 of a 32-row one's time (its copies of A serve half as many rows), so it is the
     // faster one exactly while all of them run at once: K = 14336, r = 64: 4096 rows 29 against 36 us, 5003 rows 50
     // against 37 us; r = 16: 21 against 30 and 30 against 31 us.
@@ -346,10 +349,9 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
     // drawn for the larger ranks); K = 768: r = 32 40000 rows 18 / 20, r = 16 16384 rows 8.4 / 7.6.
     const int direct_up_to = !many ? 320 : a.r == 32 && tiles32 > 2 * kComputeUnits ? 768 : 512;
     if (a.K <= direct_up_to) {
-        if (a.r == 16) return small ? launch_down_direct<1, 1>(a, tiles16, st) : launch_down_direct<1, 2>(a, tiles32, st);
-        if (a.r == 32) return small ? launch_down_direct<2, 1>(a, tiles16, st) : launch_down_direct<2, 2>(a, tiles32, st);
-        if (a.r == 64) return small ? launch_down_direct<4, 1>(a, tiles16, st) : launch_down_direct<4, 2>(a, tiles32, st);
-        return hipErrorInvalidValue;
+        if (a.r == 16) return small ? direct(IC<1>{}, IC<1>{}, tiles16) : direct(IC<1>{}, IC<2>{}, tiles32);
+        if (a.r == 32) return small ? direct(IC<2>{}, IC<1>{}, tiles16) : direct(IC<2>{}, IC<2>{}, tiles32);
+        return small ? direct(IC<4>{}, IC<1>{}, tiles16) : direct(IC<4>{}, IC<2>{}, tiles32);
     }
     // r = 32: two of the 16-row workgroups fit on a compute unit, one of the 32-row ones (128 KB of LDS); in several rounds
     // that is worth more than the second reading of A up to K = 2048 (40000 rows: K = 1024 22 / 25 us, K = 2048 33 / 40, K = 4096 69 / 65).
@@ -361,21 +363,30 @@ hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
     // 15.2, 2000 rows 25.2 / 24.9; r = 64, 400 rows 20.3 / 15.7, 1531 rows 27.6 / 24.6.  Same bits.
     auto fits = [&](int tiles, int parts) { return !forced && tiles * parts <= kComputeUnits; };
     if (a.r == 16) {
-        if (fits(tiles8, 1)) return launch_down_cfg<Down<1, 8, 6>>(a, tiles8, st);
-        return small ? launch_down_cfg<Down<1, 16, 5>>(a, tiles16, st) : launch_down_cfg<Down<1, 32, 3>>(a, tiles32, st);
+        if (fits(tiles8, 1)) return ring(Down<1, 8, 6>{}, tiles8);
+        return small ? ring(Down<1, 16, 5>{}, tiles16) : ring(Down<1, 32, 3>{}, tiles32);
     }
     if (a.r == 32) {
-        if (fits(tiles8, 2)) return launch_down_cfg<Down<1, 8, 6, 2>>(a, tiles8, st);
-        if (fits(tiles8, 1)) return launch_down_cfg<Down<2, 8, 5>>(a, tiles8, st);
-        return small32 ? launch_down_cfg<Down<2, 16, 3>>(a, tiles16, st) : launch_down_cfg<Down<2, 32, 4>>(a, tiles32, st);
+        if (fits(tiles8, 2)) return ring(Down<1, 8, 6, 2>{}, tiles8);
+        if (fits(tiles8, 1)) return ring(Down<2, 8, 5>{}, tiles8);
+        return small32 ? ring(Down<2, 16, 3>{}, tiles16) : ring(Down<2, 32, 4>{}, tiles32);
     }
-    if (a.r == 64) {
-        if (fits(tiles8, 4)) return launch_down_cfg<Down<1, 8, 6, 4>>(a, tiles8, st);
-        if (fits(tiles8, 2)) return launch_down_cfg<Down<2, 8, 5, 2>>(a, tiles8, st);
-        if (fits(tiles16, 2)) return launch_down_cfg<Down<2, 16, 4, 2>>(a, tiles16, st);
-        return small ? launch_down_cfg<Down<4, 16, 4>>(a, tiles16, st) : launch_down_cfg<Down<4, 32, 3>>(a, tiles32, st);
-    }
-    return hipErrorInvalidValue;
+    if (fits(tiles8, 4)) return ring(Down<1, 8, 6, 4>{}, tiles8);
+    if (fits(tiles8, 2)) return ring(Down<2, 8, 5, 2>{}, tiles8);
+    if (fits(tiles16, 2)) return ring(Down<2, 16, 4, 2>{}, tiles16);
+    return small ? ring(Down<4, 16, 4>{}, tiles16) : ring(Down<4, 32, 3>{}, tiles32);
+}
+
+hipError_t launch_down(const DownArgs& a, int forced, hipStream_t st) {
+    if (a.tb.row0[a.tb.G] == 0) return hipSuccess;
+    if (a.r != 16 && a.r != 32 && a.r != 64) return hipErrorInvalidValue;
+    return with_down(a, forced, [&](auto c, int tiles) { return launch_down_cfg<decltype(c)>(a, tiles, st); },
+                     [&](auto cb, auto rb, int tiles) { return launch_down_direct<cb(), rb()>(a, tiles, st); });
+}
+
+DownLaunch down_launch(const DownArgs& a, int forced) {
+    return with_down(a, forced, [](auto c, int tiles) { using C = decltype(c); return DownLaunch{C::ROWS, C::PARTS, 1, (int64_t)tiles * C::PARTS}; },
+                     [](auto, auto rb, int tiles) { return DownLaunch{16 * rb(), 1, 0, tiles}; });
 }
 
 // keep[i,j] for one adapter, one thread per column pair

@@ -1122,44 +1122,55 @@ static bool operands_stream(int64_t rows, int64_t contraction, int64_t columns) 
     return (rows + columns) * contraction * 2 > (256ll << 20);
 }
 
-static hipError_t launch_ring_part(const GemmPart& t, bool col, RingArgs a, hipStream_t st) {
+// How a launch of large tiles runs: how many slabs ahead its copies are (LA), and whether lines are asked for before them (WARM).
+struct LargeForm { int rows, ahead; bool warm; };
+static LargeForm large_form(const GemmPart& t, bool col, int K, int N, int r) {
+    const bool streams = (!col || r > 0) && operands_stream(t.row_hi, col ? N : K, col ? K : N);
+    if (t.kind < -1) return LargeForm{192, 2, streams};
+    // (2): copies two slabs ahead unless the contraction is short (measured: 2.5 % faster at K = N = 4096, 5 - 8 % with
+    // weights of 117 and 470 MB; a contraction of 16 slabs, where every step waits for its copies anyway, 4 % slower).
+    // (5): when the weight, or both operands, stream from HBM (3 - 7 % faster there, 0.5 - 1 % slower with a cache-resident
+    // weight, whose copies land in time anyway).
+    const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
+    const bool ahead2 = knob ? knob == 2 : col ? weight_streams(K, N) || streams : K >= 32 * BK;
+    return LargeForm{256, ahead2 ? 2 : 1, ahead2 && streams};
+}
+
+static RingArgs ring_part(const GemmPart& t, RingArgs a) {
     a.tiles_m = (int)t.tiles_m;
     a.tiles_n = (a.NC + kRingTiles[t.kind][1] - 1) / kRingTiles[t.kind][1];
     a.row_lo = t.row_lo;
     a.row_hi = t.row_hi;
-    return launch_ring(t.kind, col, a, st);
+    return a;
 }
+static RingArgs ring_args(const FwdGemmArgs& a) { return RingArgs{a.X, a.W, a.S, a.B, a.Y, a.M, a.K, a.N, a.r, 0, 0, 0, 0, a.tb}; }
+static RingArgs ring_args(const DxGemmArgs& a) { return RingArgs{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, 0, 0, 0, 0, a.tb}; }
 
 static hipError_t launch_fwd_large(FwdGemmArgs a, const GemmPlan& t, hipStream_t st) {
     a.tiles_n = (a.N + BN - 1) / BN;
     a.uniform_tiles = t.uniform;
     a.tiles_m = (int)t.part[0].tiles_m;
     static bool attr_set[5] = {};
-    const bool warm = operands_stream(t.part[0].row_hi, a.K, a.N);
-    if (t.part[0].kind < -1)
-        return warm ? launch_gemm(fwd_gemm_kernel<3, 2, true>, attr_set[3], a, st, GEMM_LDS_TOTAL, true)
-                    : launch_gemm(fwd_gemm_kernel<3, 2, false>, attr_set[2], a, st, GEMM_LDS_TOTAL, true);
-    // copies two slabs ahead unless the contraction is short (measured: 2.5 % faster at K = N = 4096, 5 - 8 % with
-    // weights of 117 and 470 MB; a contraction of 16 slabs, where every step waits for its copies anyway, 4 % slower)
-    const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
-    const bool ahead2 = knob ? knob == 2 : a.K >= 32 * BK;
-    if (ahead2 && warm) return launch_gemm(fwd_gemm_kernel<4, 2, true>, attr_set[4], a, st, GEMM_LDS_TOTAL, true);
-    return ahead2 ? launch_gemm(fwd_gemm_kernel<4, 2, false>, attr_set[0], a, st, GEMM_LDS_TOTAL, true)
-                  : launch_gemm(fwd_gemm_kernel<4, 1, false>, attr_set[1], a, st, GEMM_LDS_TOTAL, true);
+    const LargeForm f = large_form(t.part[0], false, a.K, a.N, a.r);
+    if (f.rows == 192)
+        return f.warm ? launch_gemm(fwd_gemm_kernel<3, 2, true>, attr_set[3], a, st, GEMM_LDS_TOTAL, true)
+                      : launch_gemm(fwd_gemm_kernel<3, 2, false>, attr_set[2], a, st, GEMM_LDS_TOTAL, true);
+    if (f.warm) return launch_gemm(fwd_gemm_kernel<4, 2, true>, attr_set[4], a, st, GEMM_LDS_TOTAL, true);
+    return f.ahead == 2 ? launch_gemm(fwd_gemm_kernel<4, 2, false>, attr_set[0], a, st, GEMM_LDS_TOTAL, true)
+                        : launch_gemm(fwd_gemm_kernel<4, 1, false>, attr_set[1], a, st, GEMM_LDS_TOTAL, true);
 }
 
 hipError_t launch_fwd_gemm(const FwdGemmArgs& a, int forced, hipStream_t st) {
     const GemmPlan t = plan_gemm(a.tb, a.M, a.K, a.N, a.r, forced);
-    const RingArgs ring{a.X, a.W, a.S, a.B, a.Y, a.M, a.K, a.N, a.r, 0, 0, 0, 0, a.tb};
     for (int i = 0; i < t.parts; ++i) {
-        const hipError_t e = t.part[i].kind < 0 ? launch_fwd_large(a, t, st) : launch_ring_part(t.part[i], false, ring, st);
+        const hipError_t e = t.part[i].kind < 0 ? launch_fwd_large(a, t, st) : launch_ring(t.part[i].kind, false, ring_part(t.part[i], ring_args(a)), st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 // (5) on tiles of 64 or 32 x 64 takes the strips of (4) (and dB) into its launch while all of them run at once, two workgroups to a
-// compute unit: a launch of few workgroups less, the strips in the shadow of the tiles.  Backward, us: 256 x 1024 x 1024, r = 16 15.2 -> 10.5;
+// compute unit (32 x 64 counted whole, also where two workgroups will share one: with_ring_strips): a launch of few workgroups less, the strips in the shadow of the tiles.  Backward, us: 256 x 1024 x 1024, r = 16 15.2 -> 10.5;
 // 600 x 1024 x 1024 17.2 -> 11.1; 300 x 2048 x 2048 19.1 -> 13.7; 256 x 4096 x 4096 27.0 -> 23.2, r = 32 31.0 -> 26.7; 64 rows,
 // 14336 -> 4096 32.0 -> 28.4; 2500 rows, 320 -> 512 19.9 -> 14.9.  Not at r = 64, whose strips need more registers than two workgroups of
 // eight waves leave, nor on the larger tiles, of which one fills a compute unit's LDS.
@@ -1177,6 +1188,11 @@ bool dx_takes_strips(const AdapterTable& tb, int M, int N, int K, int r, int for
     return plan_strip_jobs(s) == hipSuccess && strips_fit(plan_gemm(tb, M, N, K, r, forced), K, r, s);
 }
 
+static RingStripsArgs ring_strips_args(const DxGemmArgs& a, const GemmPart& part, const StripArgs& s) {
+    return RingStripsArgs{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, (int)part.tiles_m, ring_columns(part, a.K), part.row_lo, part.row_hi,
+                          s.a, s.b, s.b_first, s.accumulate, a.tb};
+}
+
 static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t st) {
     a.tiles_n = (a.K + BN - 1) / BN;
     a.uniform_tiles = t.uniform;
@@ -1184,22 +1200,18 @@ static hipError_t launch_dx_large(DxGemmArgs a, const GemmPlan& t, hipStream_t s
     static bool attr_set[8] = {};
     // with a LoRA term: the slab stages plus the parked keep flags (one word per lane and 16-row block of the wave)
     const int lds = GEMM_LDS_BYTES + FLAG_BYTES;
-    const bool warm = a.r > 0 && operands_stream(t.part[0].row_hi, a.N, a.K);
-    if (t.part[0].kind < -1) {
-        if (warm) return launch_gemm(bwd_dx_kernel<3, true, 2, true>, attr_set[6], a, st, lds + NWAVES * 1024);
+    const LargeForm f = large_form(t.part[0], true, a.K, a.N, a.r);
+    if (f.rows == 192) {
+        if (f.warm) return launch_gemm(bwd_dx_kernel<3, true, 2, true>, attr_set[6], a, st, lds + NWAVES * 1024);
         return a.r > 0 ? launch_gemm(bwd_dx_kernel<3, true, 2, false>, attr_set[4], a, st, lds)
                        : launch_gemm(bwd_dx_kernel<3, false, 2, false>, attr_set[5], a, st);
     }
-    // copies two slabs ahead when the weight, or both operands, stream from HBM (measured: 3 - 7 % faster there, 0.5 - 1 % slower
-    // with a cache-resident weight, whose copies land in time anyway)
-    const int knob = g_forced_lookahead.load(std::memory_order_relaxed);
-    const bool ahead2 = knob ? knob == 2 : weight_streams(a.K, a.N) || warm;
-    if (ahead2 && warm) return launch_gemm(bwd_dx_kernel<4, true, 2, true>, attr_set[7], a, st, lds + NWAVES * 1024);
+    if (f.warm) return launch_gemm(bwd_dx_kernel<4, true, 2, true>, attr_set[7], a, st, lds + NWAVES * 1024);
     if (a.r > 0)
-        return ahead2 ? launch_gemm(bwd_dx_kernel<4, true, 2, false>, attr_set[0], a, st, lds)
-                      : launch_gemm(bwd_dx_kernel<4, true, 1, false>, attr_set[1], a, st, lds);
-    return ahead2 ? launch_gemm(bwd_dx_kernel<4, false, 2, false>, attr_set[2], a, st)
-                  : launch_gemm(bwd_dx_kernel<4, false, 1, false>, attr_set[3], a, st);
+        return f.ahead == 2 ? launch_gemm(bwd_dx_kernel<4, true, 2, false>, attr_set[0], a, st, lds)
+                            : launch_gemm(bwd_dx_kernel<4, true, 1, false>, attr_set[1], a, st, lds);
+    return f.ahead == 2 ? launch_gemm(bwd_dx_kernel<4, false, 2, false>, attr_set[2], a, st)
+                        : launch_gemm(bwd_dx_kernel<4, false, 1, false>, attr_set[3], a, st);
 }
 
 hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st, const StripArgs* strips, bool* took) {
@@ -1209,18 +1221,42 @@ hipError_t launch_bwd_dx(const DxGemmArgs& a, int forced, hipStream_t st, const 
         const hipError_t e = plan_strip_jobs(s);
         if (e != hipSuccess) return e;
         if (strips_fit(t, a.K, a.r, s)) {
-            const GemmPart& part = t.part[0];
             *took = true;
-            return launch_ring_strips(part.kind, RingStripsArgs{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, (int)part.tiles_m, ring_columns(part, a.K), part.row_lo,
-                                                                part.row_hi, s.a, s.b, s.b_first, s.accumulate, a.tb}, st);
+            return launch_ring_strips(t.part[0].kind, ring_strips_args(a, t.part[0], s), st);
         }
     }
-    const RingArgs ring{a.dY, a.W, a.dS, a.A, a.dX, a.M, a.N, a.K, a.r, 0, 0, 0, 0, a.tb};
     for (int i = 0; i < t.parts; ++i) {
-        const hipError_t e = t.part[i].kind < 0 ? launch_dx_large(a, t, st) : launch_ring_part(t.part[i], true, ring, st);
+        const hipError_t e = t.part[i].kind < 0 ? launch_dx_large(a, t, st) : launch_ring(t.part[i].kind, true, ring_part(t.part[i], ring_args(a)), st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// `persistent` as in launch_gemm
+static GemmLaunch large_launch(const GemmPart& t, bool col, int K, int N, int r, bool persistent) {
+    const LargeForm f = large_form(t, col, K, N, r);
+    const int64_t tiles = t.tiles_m * (((col ? K : N) + BN - 1) / BN);
+    return GemmLaunch{f.rows, BN, BK, 2, NWAVES, f.warm, persistent && tiles > kComputeUnits ? kComputeUnits : tiles};
+}
+
+int fwd_gemm_launches(const FwdGemmArgs& a, int forced, GemmLaunch (&out)[2]) {
+    const GemmPlan t = plan_gemm(a.tb, a.M, a.K, a.N, a.r, forced);
+    for (int i = 0; i < t.parts; ++i)
+        out[i] = t.part[i].kind < 0 ? large_launch(t.part[i], false, a.K, a.N, a.r, true) : ring_launch(t.part[i].kind, false, ring_part(t.part[i], ring_args(a)));
+    return t.parts;
+}
+
+int bwd_dx_launches(const DxGemmArgs& a, int forced, const StripArgs* strips, GemmLaunch (&out)[2]) {
+    const GemmPlan t = plan_gemm(a.tb, a.M, a.N, a.K, a.r, forced);
+    StripArgs s{};
+    if (strips) s = *strips;
+    if (strips && plan_strip_jobs(s) == hipSuccess && strips_fit(t, a.K, a.r, s)) {
+        out[0] = ring_strips_launch(t.part[0].kind, ring_strips_args(a, t.part[0], s));
+        return 1;
+    }
+    for (int i = 0; i < t.parts; ++i)
+        out[i] = t.part[i].kind < 0 ? large_launch(t.part[i], true, a.K, a.N, a.r, false) : ring_launch(t.part[i].kind, true, ring_part(t.part[i], ring_args(a)));
+    return t.parts;
 }
 
 }  // namespace lf

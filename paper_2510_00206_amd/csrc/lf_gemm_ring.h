@@ -31,12 +31,14 @@ using RingStripsArgs = RingStripsArgsOf<AdapterTable>;
 constexpr int kRingKinds = 6;
 constexpr int kRingTiles[kRingKinds][2] = {{128, 256}, {128, 128}, {64, 128}, {64, 64}, {32, 64}, {128, 64}};   // rows x columns
 
-// A 32 x 64 tile is shared by two workgroups, 32 columns each, while every one of them has a compute unit to itself.
+// A 32 x 64 tile is shared by two workgroups, 32 columns each, while there is a compute unit for every one of them (beside strips: with_ring_strips).
 constexpr bool ring_halves(int tiles_m, int tiles_n) { return 2 * (int64_t)tiles_m * tiles_n <= kComputeUnits; }
 
 hipError_t launch_ring(int kind, bool col, const RingArgs& a, hipStream_t st);
+GemmLaunch ring_launch(int kind, bool col, const RingArgs& a);                    // ... what it would launch
 
 constexpr bool ring_takes_strips(int kind, int r) { return (kind == 3 || kind == 4) && (r == 16 || r == 32); }
 hipError_t launch_ring_strips(int kind, const RingStripsArgs& a, hipStream_t st);
+GemmLaunch ring_strips_launch(int kind, const RingStripsArgs& a);
 
 }  // namespace lf

@@ -540,7 +540,6 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
     });
 }
 
-
 // Which kernel of the family: see kRingTiles.  Two workgroups of kinds 2, 3 and 4 fit on a compute unit (their rings
 // take 64 - 80 KB of LDS), one of the others.  Kind 5 is for launches of at most one workgroup per compute unit: the deeper
 // ring and the single pass over the weight pay when that comes from HBM (77 rows, 4096 -> 14336, weight not cached: 64 x 128
@@ -558,48 +557,77 @@ using Ring32x64 = Ring<32, 64, 2, 2, 3, 1, 2, 2>;
 using Ring32x32 = Ring<32, 32, 2, 2, 4, 2, 2, 2>;    // half of such a tile
 constexpr int kLongContraction = 4096;
 
-template <bool COL>
-static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
+// Calls f(kernel, arguments) with what a launch of tiles of `kind` takes.
+template <bool COL, class F>
+static auto with_ring(int kind, const RingArgs& a, F&& f) {
     switch (kind) {
-        case 0: return launch_ring_cfg<Ring<128, 256, 2, 4, 3, 0, 4>, COL>(a, st);
-        case 1: return launch_ring_cfg<Ring<128, 128, 2, 2, 4, 2, 2>, COL>(a, st);
-        case 2: return launch_ring_cfg<Ring<64, 128, 2, 4, 3, 1, 2>, COL>(a, st);
-        case 3: return launch_ring_cfg<Ring<64, 64, 2, 2, COL ? 4 : 5, 2, 2>, COL>(a, st);
+        case 0: return f(Ring<128, 256, 2, 4, 3, 0, 4>{}, a);
+        case 1: return f(Ring<128, 128, 2, 2, 4, 2, 2>{}, a);
+        case 2: return f(Ring<64, 128, 2, 4, 3, 1, 2>{}, a);
+        case 3: return f(Ring<64, 64, 2, 2, COL ? 4 : 5, 2, 2>{}, a);
         case 4:
             if (ring_halves(a.tiles_m, a.tiles_n)) {
                 RingArgs h = a;
                 h.tiles_n *= 2;
-                return launch_ring_cfg<Ring32x32, COL>(h, st);
+                return f(Ring32x32{}, h);
             }
             if constexpr (!COL)
-                if (a.KC >= kLongContraction) return launch_ring_cfg<Ring<32, 64, 2, 2, 5, 1, 2>, COL>(a, st);
-            return launch_ring_cfg<Ring32x64, COL>(a, st);
-        case 5: return launch_ring_cfg<Ring<128, 64, 2, 2, 6, 2, 1>, COL>(a, st);
+                if (a.KC >= kLongContraction) return f(Ring<32, 64, 2, 2, 5, 1, 2>{}, a);
+            return f(Ring32x64{}, a);
+        default: return f(Ring<128, 64, 2, 2, 6, 2, 1>{}, a);
     }
-    return hipErrorInvalidValue;
 }
 
-hipError_t launch_ring_strips(int kind, const RingStripsArgs& a, hipStream_t st) {
-    if (kind == 3) return a.r == 16 ? launch_ring_strips_t<Ring64x64, 1>(a, st) : launch_ring_strips_t<Ring64x64, 2>(a, st);
+// ... with the strips beside them: f(kernel, r / 16, arguments).
+template <class F>
+static auto with_ring_strips(int kind, const RingStripsArgs& a, F&& f) {
+    auto of_rank = [&](auto c, const RingStripsArgs& b) {
+        return b.r == 16 ? f(c, std::integral_constant<int, 1>{}, b) : f(c, std::integral_constant<int, 2>{}, b);
+    };
+    if (kind == 3) return of_rank(Ring64x64{}, a);
     // halves beside the strips: with a compute unit for each, or where the longer contraction makes up for sharing one (us, whole / half tiles, backward:
-    // 256 x 1024 x 1024 8.9 / 9.4, r = 32 8.8 / 10.5; 200 rows, 2048 -> 1024 10.9 / 10.8; 64 x 4096 x 4096, r = 32 20.7 / 20.4; 300 rows, 4096 -> 512 16.6 / 15.6)
+    // 256 x 1024 x 1024 8.9 / 9.4, r = 32 8.8 / 10.5; 200 rows, 2048 -> 1024 10.9 / 10.8; 64 x 4096 x 4096, r = 32 20.7 / 20.4; 300 rows, 4096 -> 512 16.6 / 15.6).
+    // kStripsBeside bounds the whole tiles and the strips: with halves there are up to 640 workgroups, the last strips of which start when
+    // the first halves have ended, and which still are the faster way (560 workgroups, five adapters of 20 rows, 4096 -> 1024 17.7 / 15.0, r = 32 18.5 /
+    // 15.7; 640, four of 8 rows, 4096 -> 2048 18.3 / 16.4, r = 32 18.4 / 16.8).
     const bool own = 2 * a.tiles_m * a.tiles_n + a.a.blocks + a.b.blocks <= kComputeUnits;
-    if (kind == 4 && ring_halves(a.tiles_m, a.tiles_n) && (own || a.KC >= 2048)) {
+    if (ring_halves(a.tiles_m, a.tiles_n) && (own || a.KC >= 2048)) {
         RingStripsArgs h = a;
         h.tiles_n *= 2;
-        return a.r == 16 ? launch_ring_strips_t<Ring32x32, 1>(h, st) : launch_ring_strips_t<Ring32x32, 2>(h, st);
+        return of_rank(Ring32x32{}, h);
     }
     // whole tiles that share compute units: four waves instead of seven (20 rows of three adapters, 10048 -> 4288, r = 32, 402 workgroups 25.4 us, 26.5
     // with seven); by themselves the seven are faster (256 x 1024 x 1024 backward 10.2, 10.5 with four)
     using Shared = Ring<32, 64, 1, 2, 6, 1, 1>;
-    if (kind == 4 && a.tiles_m * a.tiles_n + a.a.blocks + a.b.blocks > kComputeUnits)
-        return a.r == 16 ? launch_ring_strips_t<Shared, 1>(a, st) : launch_ring_strips_t<Shared, 2>(a, st);
-    if (kind == 4) return a.r == 16 ? launch_ring_strips_t<Ring32x64, 1>(a, st) : launch_ring_strips_t<Ring32x64, 2>(a, st);
-    return hipErrorInvalidValue;
+    if (a.tiles_m * a.tiles_n + a.a.blocks + a.b.blocks > kComputeUnits) return of_rank(Shared{}, a);
+    return of_rank(Ring32x64{}, a);
+}
+
+template <bool COL>
+static hipError_t launch_ring_dir(int kind, const RingArgs& a, hipStream_t st) {
+    return with_ring<COL>(kind, a, [&](auto c, const RingArgs& b) { return launch_ring_cfg<decltype(c), COL>(b, st); });
 }
 
 hipError_t launch_ring(int kind, bool col, const RingArgs& a, hipStream_t st) {
     return col ? launch_ring_dir<true>(kind, a, st) : launch_ring_dir<false>(kind, a, st);
+}
+
+hipError_t launch_ring_strips(int kind, const RingStripsArgs& a, hipStream_t st) {
+    return with_ring_strips(kind, a, [&](auto c, auto cb, const RingStripsArgs& b) { return launch_ring_strips_t<decltype(c), cb()>(b, st); });
+}
+
+template <class C>
+static GemmLaunch describe(C, int64_t workgroups) { return GemmLaunch{C::TM, C::TN, C::DEPTH, C::NS, C::NW + C::CW, 0, workgroups}; }
+
+GemmLaunch ring_launch(int kind, bool col, const RingArgs& a) {
+    auto f = [](auto c, const RingArgs& b) { return describe(c, (int64_t)b.tiles_m * b.tiles_n); };
+    return col ? with_ring<true>(kind, a, f) : with_ring<false>(kind, a, f);
+}
+
+GemmLaunch ring_strips_launch(int kind, const RingStripsArgs& a) {
+    return with_ring_strips(kind, a, [](auto c, auto, const RingStripsArgs& b) {
+        return describe(c, (int64_t)b.tiles_m * b.tiles_n + b.a.blocks + b.b.blocks);
+    });
 }
 
 }  // namespace lf

@@ -277,6 +277,13 @@ bool dx_takes_strips(const AdapterTable& tb, int M, int N, int K, int r, int for
 struct GemmTile { int rows, columns, first_row; };
 int gemm_tiles(const AdapterTable& tb, int M, int contraction, int columns, int r, int forced, GemmTile (&out)[2]);
 
+// The kernels that launch_down, launch_fwd_gemm and launch_bwd_dx would launch for the same arguments (the GEMMs: returns how many).
+struct DownLaunch { int rows, parts, ring; int64_t workgroups; };
+struct GemmLaunch { int rows, columns, depth, stages, waves, asks_ahead; int64_t workgroups; };
+DownLaunch down_launch(const DownArgs& a, int forced);
+int fwd_gemm_launches(const FwdGemmArgs& a, int forced, GemmLaunch (&out)[2]);
+int bwd_dx_launches(const DxGemmArgs& a, int forced, const StripArgs* strips, GemmLaunch (&out)[2]);
+
 hipError_t launch_debug_mask(int64_t M, int64_t K, uint32_t T, uint32_t k0, uint32_t k1, uint8_t* keep,
                              hipStream_t st);
 

@@ -12,6 +12,16 @@ def f64(t):
     return t.to(torch.float64).cpu().numpy()
 
 
+def launch_names(K, N, r, lens):
+    """What (1), (2) and (5) launch over these segments, as the library says: rows[/parts of the rank][ direct]; rows x columns x stage depth,
+    waves[, + where lines are asked for ahead], one for each launch; and the workgroups of (5)."""
+    off = [sum(lens[:g]) for g in range(len(lens) + 1)]
+    q = binding.lora_debug_launches(K, N, r, off)
+    gemm = lambda ls: " and ".join(f"{g.rows}x{g.columns}x{g.depth}:{g.waves}" + ("+" if g.asks_ahead else "") for g in ls if g.rows)
+    down = f"{q.down_rows}" + (f"/{q.down_parts}" if q.down_parts > 1 else "") + ("" if q.down_ring else " direct")
+    return down, gemm(q.fwd), gemm(q.dx), sum(g.workgroups for g in q.dx)
+
+
 def rel_err(got, ref):
     ref = np.asarray(ref, dtype=np.float64)
     got = got.detach().to(torch.float64).cpu().numpy() if isinstance(got, torch.Tensor) else np.asarray(got)

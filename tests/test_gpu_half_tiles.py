@@ -1,34 +1,39 @@
 """32 x 64 tiles shared by two workgroups, and 128-deep stages: contractions that end in half a stage or fill less than the ring, row and
-column remainders, both sides of the line from which a tile is not shared, with the strips of (4) in the launch and without; Y and dX bit for bit
+column remainders, both sides of the lines between the forms (asked of the library), with the strips of (4) in the launch and without; Y and dX bit for bit
 against the 256 x 256 tiles, and every output against the oracle."""
 import pytest
 import torch
 
-from gpu_util import compare, run_gpu, run_oracle
+from gpu_util import compare, launch_names, run_gpu, run_oracle
 from paper_2510_00206_amd import binding, workloads
 
 pytestmark = pytest.mark.gpu
 
-# K, N, r, segments
-CASES = [
-    (64, 128, 16, (1,)),                    # half a stage and a whole one
-    (192, 64, 64, (33,)),                   # three slabs and one; no strips in the launch
-    (576, 704, 32, (31, 0, 34, 1)),
-    (1024, 1024, 16, (256,)),               # 128 tiles: all shared, but not beside the strips
-    (1024, 1088, 16, (250,)),               # 136 tiles (2): none shared
-    (2048, 1984, 32, (127,)),               # 124 and 128 tiles; beside the strips, contraction just below 2048
-    (1984, 2048, 32, (127,)),               # ... and from there on
-    (4032, 4096, 16, (50,)),                # 128 tiles (2) of a contraction of 63 slabs
-    (4160, 4160, 16, (50,)),                # 130: whole tiles of (2) over a long contraction
-    (320, 64, 32, (40, 7, 64, 1, 33)),      # the full adapter table
-]
+HALVES, DEEP, ONE_SLAB, SHARED = "32x32x128:8", "32x64x128:7", "32x64x64:7", "32x64x64:4"
+
+# (K, N, r, segments): what (2) and (5) run as, workgroups of (5) with the strips beside it
+CASES = {
+    (64, 128, 16, (1,)): (HALVES, HALVES, 5),                           # half a stage and a whole one
+    (192, 64, 64, (33,)): (HALVES, HALVES, 12),                         # three slabs and one; no strips in the launch
+    (576, 704, 32, (31, 0, 34, 1)): (HALVES, HALVES, 152),
+    (1024, 1024, 16, (256,)): (HALVES, DEEP, 160),                      # 128 tiles: shared, but not beside the strips
+    (1024, 1088, 16, (250,)): (DEEP, DEEP, 161),                        # 136 tiles (2)
+    (2048, 1984, 32, (127,)): (HALVES, DEEP, 191),                      # 124 and 128 tiles; beside the strips, contraction just below 2048
+    (1984, 2048, 32, (127,)): (HALVES, HALVES, 311),                    # ... and from there on
+    (4032, 4096, 16, (50,)): (HALVES, HALVES, 379),                     # 128 tiles (2) of a contraction of 63 slabs
+    (4160, 4160, 16, (50,)): (ONE_SLAB, DEEP, 195),                     # 130: whole tiles of (2) over a long contraction
+    (4096, 4096, 16, (5, 91)): (ONE_SLAB, SHARED, 512),                 # ... and of (5) that share compute units with the strips
+    (320, 64, 32, (40, 7, 64, 1, 33)): (HALVES, HALVES, 110),           # the full adapter table
+    (2048, 4096, 32, (8, 8, 8, 8)): (DEEP, HALVES, 640),                # as many halves and strips as there can be
+    (1024, 4096, 16, (20, 20, 20, 20, 20)): ("64x128x64:11", HALVES, 560),   # ... with the full adapter table
+}
 
 
 @pytest.mark.parametrize("K,N,r,lens", CASES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_half_tiles(K, N, r, lens):
     L = workloads.custom_layer(sum(lens), K, N, r, 1.5, 0.1, seg_lens=lens, cfg=71)
     print(f"half tiles {L}", flush=True)
-    assert binding.lora_debug_gemm_tiles(K, N, r, L.seg_offsets)[0][:2] == (32, 64)
+    assert launch_names(K, N, r, lens)[1:] == CASES[K, N, r, lens]
     inp = workloads.make_inputs(L)
     got = run_gpu(L, *inp)
     binding.lora_set_row_tile(256)

@@ -6,6 +6,8 @@ import random
 
 import pytest
 
+import test_gpu_half_tiles
+from gpu_util import launch_names
 from paper_2510_00206_amd import binding
 from test_gpu_small_tiles import PLANS, POISON_PLANS
 
@@ -54,6 +56,28 @@ def test_row_tile_setting_fixes_the_tiles():
         binding.lora_set_row_tile(rows)
         assert all(_name(binding.lora_debug_gemm_tiles(K, N, r, _offsets(lens))) == f"{rows}x256" for K, N, r, lens in PLANS)
     binding.lora_set_row_tile(0)
+
+
+def test_cases_take_the_kernels_they_stand_for():
+    binding.lora_set_row_tile(0)
+    for case, want in test_gpu_half_tiles.CASES.items():
+        assert launch_names(*case)[1:] == want, case
+
+
+def test_workgroups_beside_the_strips():
+    """Whole tiles and strips: at most two workgroups to a compute unit; where halves of tiles take their place, up to half as many tiles more."""
+    binding.lora_set_row_tile(0)
+    rnd = random.Random(17)
+    most = {}
+    for it in range(4000):
+        G = 1 if it % 2 else rnd.choice((2, 4, 5, 16))
+        lens = [rnd.randint(1, 260 // G + 1) for _ in range(G)]
+        K, N, r = 64 * rnd.randint(1, 72), 64 * rnd.randint(1, 72), rnd.choice((16, 32))
+        if binding.lora_debug_bwd_plan(K, N, r, _offsets(lens)).with_dx:
+            _, _, dx, n = launch_names(K, N, r, lens)
+            most[dx] = max(most.get(dx, 0), n)
+    assert set(most) == {"32x32x128:8", "32x64x128:7", "32x64x64:4", "64x64x64:8"}
+    assert most["32x64x128:7"] <= 256 < most["32x64x64:4"] <= 512 < most["32x32x128:8"] <= 640 and most["64x64x64:8"] <= 512, most
 
 
 def _panels(lens, height):
@@ -169,6 +193,11 @@ def test_diagnostics_refuse_what_the_entry_points_refuse():
     g = lambda M, K, G, o: binding.load_library().lora_debug_da_panels(
         M, K, G, o, C.byref(C.c_int32()), C.byref(C.c_int64()), C.byref(C.c_int64()))
     h = lambda M, K, N, r, G, o: binding.load_library().lora_debug_bwd_plan(M, K, N, r, G, o, 1, 0, C.byref(binding.BwdPlan()))
+    q = lambda M, K, N, r, G, o: binding.load_library().lora_debug_launches(M, K, N, r, G, o, C.byref(binding.Launches()))
+    assert [q(64, 64, 64, 16, 1, off), q(64, 64, 64, 16, 1, None), q(64, 0, 64, 16, 1, off), q(64, 96, 64, 16, 1, off), q(64, 64, 64, 8, 1, off),
+            q(128, 64, 64, 16, 1, off), q(64, 64, 64, 16, 65, off)] == [0, 1, 2, 7, 7, 5, 7]
+    none = binding.lora_debug_launches(64, 64, 16, [0, 0])
+    assert bytes(none) == bytes(len(bytes(none)))
     assert [h(64, 64, 64, 16, 1, off), h(64, 64, 64, 16, 1, None), h(64, 0, 64, 16, 1, off), h(64, 96, 64, 16, 1, off), h(64, 64, 64, 8, 1, off),
             h(128, 64, 64, 16, 1, off), h(64, 64, 64, 16, 65, off)] == [0, 1, 2, 7, 7, 5, 7]
     assert [g(64, 64, 1, off), g(64, 64, 1, None), g(-1, 64, 1, off), g(128, 64, 1, off), g(64, 64, 65, off)] == [0, 1, 2, 5, 7]
