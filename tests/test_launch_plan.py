@@ -6,7 +6,9 @@ import random
 
 import pytest
 
+import test_gpu_down_parts
 import test_gpu_half_tiles
+import test_gpu_streamed_operands
 from gpu_util import launch_names
 from paper_2510_00206_amd import binding
 from test_gpu_small_tiles import PLANS, POISON_PLANS
@@ -60,8 +62,33 @@ def test_row_tile_setting_fixes_the_tiles():
 
 def test_cases_take_the_kernels_they_stand_for():
     binding.lora_set_row_tile(0)
+    for (K, r, lens), down in test_gpu_down_parts.CASES.items():
+        assert launch_names(K, 64, r, lens)[0] == down, (K, r, lens)
     for case, want in test_gpu_half_tiles.CASES.items():
         assert launch_names(*case)[1:] == want, case
+    for case, want in test_gpu_streamed_operands.CASES.items():
+        assert launch_names(*case)[1:3] == want, case
+
+
+def test_row_tile_setting_fixes_the_kernels():
+    """The heights that the bit-for-bit tests compare against are other kernels than those they test."""
+    cases = [(K, 64, r, lens) for K, r, lens in test_gpu_down_parts.CASES] + [*test_gpu_half_tiles.CASES, *test_gpu_streamed_operands.CASES]
+    for setting, rows, tile in ((256, 32, "256x256x64:4"), (128, 16, "128x256x64:12")):
+        binding.lora_set_row_tile(setting)
+        for K, N, r, lens in cases:
+            down, fwd, dx, _ = launch_names(K, N, r, lens)
+            assert down.split()[0] == str(rows) and fwd.rstrip("+") == dx.rstrip("+") == tile
+            assert setting == 256 or "+" not in fwd + dx
+    binding.lora_set_row_tile(0)
+
+
+def test_slab_lookahead_setting_and_lines_asked_for_ahead():
+    """256-row tiles ask for lines only where their copies run two slabs ahead; 192-row tiles always do run so."""
+    for slabs, tall, low in ((1, "256x256x64:4", "192x256x64:4+"), (2, "256x256x64:4+", "192x256x64:4+")):
+        binding.lora_set_slab_lookahead(slabs)
+        assert launch_names(8192, 16384, 64, (1088, 1984, 1024))[1:3] == (tall, tall)
+        assert launch_names(28672, 4096, 16, (2999,))[1] == low
+    binding.lora_set_slab_lookahead(0)
 
 
 def test_workgroups_beside_the_strips():
