@@ -45,7 +45,7 @@ struct Ring {
     static constexpr int REGS = 512 / ((NW + CW + 3) / 4);            // of a wave, with a SIMD's share of the workgroup on it
     // fragments of two slabs in registers: where they fit beside the accumulators and some forty others (128 x 64 tiles with the
     // shorter sub-steps of a 2 x 4 split, 512 x 4096 x 4096: 22.4 -> 23.8 us, so not below eight MFMAs)
-    static constexpr bool STRAIGHT = D == 1 && TM == 32;              // see RingCopies::run
+    static constexpr bool NARROW = D == 1 && TM == 32;                // whole 32 x 64 tiles of one slab to a stage
     static constexpr bool AHEAD = D == 2 || MI * NI >= 8 && MI * NI * 4 + (MI + NI) * 16 + 40 <= REGS;
     static_assert(TM * D / 8 % (TW ? TW : OW) == 0 && TN * D / 8 % OW == 0, "the copies of a slab divide evenly over the waves");
     static_assert(NS >= 2, "ring depth");
@@ -114,7 +114,7 @@ struct RingCopies {
     // or nothing.  The barriers are those of the computing waves: one before the first slab, then one per slab, at which the
     // copies of slab kt + 1 have landed and the stage of slab kt is free.
     static __device__ __forceinline__ void run(int w, RingSource tok, RingSource out, int64_t out_adv, const RingSource& ltok,
-                                               const RingSource& lout, int slabs, bool has_lora, uint32_t lds) {
+                                               const RingSource& lout, int slabs, bool has_lora, bool at_once, uint32_t lds) {
         constexpr int NS = C::NS;
         const int nk = (slabs + C::D - 1) / C::D, nkt = nk + has_lora;
         const int half_at = C::D == 2 && (slabs & 1) ? nk - 1 : nk;       // the stage of which half is past the contraction's end
@@ -140,14 +140,16 @@ struct RingCopies {
         else wait_slab_loads();
         asm volatile("s_barrier" ::: "memory");
         int stage = 0, kt = 0;
-        // While a whole base slab follows, without a branch: the loop below picks its wait and its sources anew in every step, some
-        // twenty instructions and four jumps between the barrier and the copies, which the slab of a lone 32 x 64 tile (0.13 us) waits for (and which a change
-        // elsewhere in the kernel moved by 2 - 5 % of it).  (2) alone, us, that loop / this, weight cached: 4096 -> 4096, 80 rows 11.9 / 10.6, 128
-        // rows 12.1 / 11.3; 8192 -> 4096, 128 rows 22.1 / 19.3; 4096 -> 2112, 128 rows 11.1 / 9.6; from HBM level (16.8 / 16.8, 29.0 / 28.9).  The other tiles keep
-        // that loop: copies that come at once are no better there and, with the weight from HBM, worse (256 rows, 17024 -> 17856
-        // 240 / 260; 1500 rows, 4096 -> 4096, backward 68 / 72).
-        if constexpr (C::STRAIGHT) {
-            for (; kt + NS < half_at; ++kt) {
+        // (2) on whole 32 x 64 tiles, while a whole base slab follows, without a branch: the loop below picks its wait and its sources anew in
+        // every step, some twenty instructions and four jumps between the barrier and the copies, which the slab of such a tile (0.13 us) waits
+        // for.  us, that loop / this, weight cached: 4096 -> 4096, 80 rows 11.9 / 10.7, 128 rows 12.1 / 11.3; 8192 -> 4096, 128 rows 22.1 / 19.3; four
+        // adapters of 3 - 10 rows, 16384 -> 4096 54.1 / 47.9; from HBM 17.2 / 16.9, 29.0 / 28.9, 67.9 / 66.1.  Not where the weight outgrows the memory-side
+        // cache, whose copies come late anyway and are the worse for coming all at once (eight adapters of 1 - 16 rows, 8896 -> 20480 217 / 223; 16384 ->
+        // 9984 104.7 / 105.7; with 242 MB, 11008 -> 11008, three of 9 rows 78.1 / 74.5, from HBM 96.4 / 94.1), nor in (5) (eight adapters of 1 - 18 rows, 9856 to 2368
+        // columns 81.9 / 84.4) and on the other tiles (256 rows, 17024 -> 17856 240 / 260; 1500 rows, 4096 -> 4096, backward 68 / 72).
+        if constexpr (C::NARROW && !COL) {
+            const int whole = at_once ? half_at - NS : 0;
+            for (; kt < whole; ++kt) {
                 asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(N * (NS - 2)) : "memory");
                 issue<false>(w, tok, out, off, __builtin_amdgcn_readfirstlane(lds + stage * C::STAGE));
                 tok.biased += C::ROWB;
@@ -314,12 +316,13 @@ __device__ __forceinline__ void ring_tile(const Args& p, char* smem) {
                                     : RingSource{(const char*)(p.lout + ((int64_t)rt.g * p.NC + c0) * p.r) - kCopyBias, (uint32_t)p.r, cols_valid, p.r >> 3};
         const int64_t out_adv = COL ? (int64_t)C::DEPTH * p.NC * 2 : C::ROWB;
         const uint32_t lds = lds_addr_of(smem);
+        const bool at_once = (int64_t)p.KC * p.NC * 2 <= (256ll << 20);     // (the weight fits the memory-side cache)
         if constexpr (C::TW == 0)
-            RingCopies<C, COL, C::TM * C::D / 8 / C::OW, C::TN * C::D / 8 / C::OW>::run(cw, tok, out, out_adv, ltok, lout, nk, has_lora, lds);
+            RingCopies<C, COL, C::TM * C::D / 8 / C::OW, C::TN * C::D / 8 / C::OW>::run(cw, tok, out, out_adv, ltok, lout, nk, has_lora, at_once, lds);
         else if (cw < C::TW)
-            RingCopies<C, COL, C::TM * C::D / 8 / C::TW, 0>::run(cw, tok, out, out_adv, ltok, lout, nk, has_lora, lds);
+            RingCopies<C, COL, C::TM * C::D / 8 / C::TW, 0>::run(cw, tok, out, out_adv, ltok, lout, nk, has_lora, at_once, lds);
         else
-            RingCopies<C, COL, 0, C::TN * C::D / 8 / C::OW>::run(cw - C::TW, tok, out, out_adv, ltok, lout, nk, has_lora, lds);
+            RingCopies<C, COL, 0, C::TN * C::D / 8 / C::OW>::run(cw - C::TW, tok, out, out_adv, ltok, lout, nk, has_lora, at_once, lds);
         return;
     }
 

@@ -153,17 +153,23 @@ def test_only_the_copies_write_m0(functions):
     assert writes > 100
 
 
+def _straight_loops(code):
+    """Loops that hold a barrier and copies behind it, and nothing else but scalar arithmetic."""
+    n = 0
+    for i, (_, _, to) in enumerate(code):
+        body = [c[0] for c in code[to:i]] if to is not None and to < i else []
+        n += "s_barrier" in body and "global_load_lds_dwordx4" in body[body.index("s_barrier"):] and \
+            all(c.startswith(("s_", "global_load_lds")) and not c.startswith(("s_branch", "s_cbranch")) for c in body)
+    return n
+
+
 def test_copies_of_whole_narrow_tiles_follow_the_barrier(functions):
-    """A loop that holds the barrier and the copies, and nothing else but scalar arithmetic, for the token and for the out waves."""
-    kernels = [code for name, code in functions if re.search(r"ring_gemm_kernelINS_4RingILi32ELi64E(Li\d+E){5}Li1EEELb0E", name)]
-    assert len(kernels) == 2                                # both sizes of the adapter table
-    for code in kernels:
-        straight = 0
-        for i, (name, _, to) in enumerate(code):
-            body = [c[0] for c in code[to:i]] if to is not None and to < i else []
-            straight += "s_barrier" in body and "global_load_lds_dwordx4" in body[body.index("s_barrier"):] and \
-                all(n.startswith(("s_", "global_load_lds")) and not n.startswith(("s_branch", "s_cbranch")) for n in body)
-        assert straight == 2
+    """In (2) those of the token and of the out waves; in (5), where that is no faster, neither."""
+    tile = r"_kernelINS_4RingILi32ELi64E(Li\d+E){5}Li1EE"
+    forward = [code for name, code in functions if re.search(rf"ring_gemm{tile}ELb0E", name)]
+    backward = [code for name, code in functions if re.search(rf"ring_gemm{tile}ELb1E|ring_strips{tile}", name)]
+    assert len(forward) == 2 and len(backward) >= 4          # both sizes of the adapter table; with strips both ranks
+    assert {_straight_loops(code) for code in forward} == {2} and {_straight_loops(code) for code in backward} == {0}
 
 
 def test_no_backward_kernel_of_one_slab_to_a_stage(functions):
