@@ -553,8 +553,8 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
 // two / halves, (2): 1024 -> 1024, 16 rows 4.73 / 4.59 / 3.77, 256 rows 4.88 / 4.74 / 3.88; 2048 -> 2048, 128 rows 6.74 / 6.27 / 5.00; 4096 ->
 // 4096, 16 rows 11.1 / 11.0 / 7.7, 64 rows 11.3 / 12.1 / 8.6; 26496 -> 960, 128 rows 53.9 / 55.6 / 36.5; (5): 1024 -> 1024, 256 rows 4.83 / 4.63 / 4.07;
 // 2048 -> 2048, 128 rows 6.68 / 6.06 / 5.67; 4096 -> 4096, 64 rows 13.8 / 13.4 / 12.9; 8192 -> 1024, 64 rows 17.9 / 15.2 / 11.3.  Whole tiles of
-// (2) over long contractions keep one slab to a stage (128 rows, 4096 -> 4096 11.5 / 12.3), in five stages (five / six: 4096 -> 4096, 80 rows 10.7 / 10.8,
-// 128 rows 11.2 / 11.4, from HBM 16.9 / 17.4; 8192 -> 2112, 128 rows 18.2 / 18.2, from HBM 28.0 / 28.5; 8192 -> 4096, 80 rows from HBM 28.0 / 27.7).
+// (2) over long contractions keep one slab to a stage (128 rows, 4096 -> 4096 11.5 / 12.3), in six stages (five / six: 4096 -> 4096, 100 rows 10.7 / 10.7, from HBM
+// 15.5 / 15.0, 128 rows from HBM 16.8 / 16.9; 8192 -> 4096, 100 rows 18.1 / 18.0, from HBM 26.4 / 25.5; eight adapters of 1 - 16 rows, 8896 -> 20480 218 / 214).
 using Ring64x64 = Ring<64, 64, 2, 2, 5, 2, 2>;       // of the launches that take the strips
 using Ring32x64 = Ring<32, 64, 2, 2, 3, 1, 2, 2>;
 using Ring32x32 = Ring<32, 32, 2, 2, 4, 2, 2, 2>;    // half of such a tile
@@ -575,7 +575,7 @@ static auto with_ring(int kind, const RingArgs& a, F&& f) {
                 return f(Ring32x32{}, h);
             }
             if constexpr (!COL)
-                if (a.KC >= kLongContraction) return f(Ring<32, 64, 2, 2, 5, 1, 2>{}, a);
+                if (a.KC >= kLongContraction) return f(Ring<32, 64, 2, 2, 6, 1, 2>{}, a);
             return f(Ring32x64{}, a);
         default: return f(Ring<128, 64, 2, 2, 6, 2, 1>{}, a);
     }

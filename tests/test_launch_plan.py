@@ -91,6 +91,14 @@ def test_slab_lookahead_setting_and_lines_asked_for_ahead():
     binding.lora_set_slab_lookahead(0)
 
 
+def test_stages_of_whole_narrow_tiles():
+    """One slab to a stage, six stages, over long contractions of (2)."""
+    binding.lora_set_row_tile(0)
+    for K, N, lens in ((4096, 4096, (100,)), (8192, 4096, (70, 30)), (8896, 20480, (1, 5, 7, 16, 3, 5, 2, 29))):
+        g = binding.lora_debug_launches(K, N, 16, _offsets(lens)).fwd[0]
+        assert (g.rows, g.columns, g.depth, g.stages) == (32, 64, 64, 6)
+
+
 def test_workgroups_beside_the_strips():
     """Whole tiles and strips: at most two workgroups to a compute unit; where halves of tiles take their place, up to half as many tiles more."""
     binding.lora_set_row_tile(0)
