@@ -548,17 +548,28 @@ static hipError_t launch_ring_cfg(const RingArgs& a, hipStream_t st) {
 // ring and the single pass over the weight pay when that comes from HBM (77 rows, 4096 -> 14336, weight not cached: 64 x 128
 // tiles 38 us, 128 x 64 tiles 32 us).
 // Kind 3, ring of five stages / four, (2): 4096 -> 4096, 160 rows 13.1 / 13.8; (5): 8192 to 8192, 100 rows 29.2 / 28.1, 128 rows 31.2 / 29.6.
-// Kind 4: 128-deep stages, both stages' fragments in registers, and half a tile to a workgroup while every half has a compute unit: a sweep is
-// bound by the bytes that a slab brings to the compute unit (12 KB in 0.13 us, 8 KB in 0.08; longer rings gain nothing).  us, one slab to a stage /
-// two / halves, (2): 1024 -> 1024, 16 rows 4.73 / 4.59 / 3.77, 256 rows 4.88 / 4.74 / 3.88; 2048 -> 2048, 128 rows 6.74 / 6.27 / 5.00; 4096 ->
-// 4096, 16 rows 11.1 / 11.0 / 7.7, 64 rows 11.3 / 12.1 / 8.6; 26496 -> 960, 128 rows 53.9 / 55.6 / 36.5; (5): 1024 -> 1024, 256 rows 4.83 / 4.63 / 4.07;
-// 2048 -> 2048, 128 rows 6.68 / 6.06 / 5.67; 4096 -> 4096, 64 rows 13.8 / 13.4 / 12.9; 8192 -> 1024, 64 rows 17.9 / 15.2 / 11.3.  Whole tiles of
-// (2) over long contractions keep one slab to a stage (128 rows, 4096 -> 4096 11.5 / 12.3), in six stages (five / six: 4096 -> 4096, 100 rows 10.7 / 10.7, from HBM
-// 15.5 / 15.0, 128 rows from HBM 16.8 / 16.9; 8192 -> 4096, 100 rows 18.1 / 18.0, from HBM 26.4 / 25.5; eight adapters of 1 - 16 rows, 8896 -> 20480 218 / 214).
+// Kind 4, half a tile to a workgroup while every half has a compute unit, in 128-deep stages with both stages' fragments in registers: a sweep is
+// bound by the bytes that a slab brings to the compute unit (12 KB in 0.13 us, 8 KB in 0.08; longer rings gain nothing).  us, whole tiles of one slab to a stage /
+// halves, (2): 1024 -> 1024, 16 rows 4.73 / 3.77, 256 rows 4.88 / 3.88; 2048 -> 2048, 128 rows 6.74 / 5.00; 4096 -> 4096, 16 rows 11.1 / 7.7, 64 rows
+// 11.3 / 8.6; 26496 -> 960, 128 rows 53.9 / 36.5; (5): 1024 -> 1024, 256 rows 4.83 / 4.07; 2048 -> 2048, 128 rows 6.68 / 5.67; 4096 -> 4096, 64 rows
+// 13.8 / 12.9; 8192 -> 1024, 64 rows 17.9 / 11.3; 4096 -> 2112, 64 rows 10.4 / 7.8; 2048 -> 960, 250 rows 6.8 / 6.4.
+// Whole tiles have one slab to a stage, six of them.  (2): five / six: 4096 -> 4096, 100 rows 10.7 / 10.7, from HBM 15.5 / 15.0, 128 rows from HBM 16.8 / 16.9; 8192 ->
+// 4096, 100 rows 18.1 / 18.0, from HBM 26.4 / 25.5; eight adapters of 1 - 16 rows, 8896 -> 20480 218 / 214; one slab to a stage / two: 448 -> 4160, 64 rows 3.85 /
+// 4.04; 1024 -> 4096, 100 rows from HBM 5.41 / 5.62; 3968 -> 5440, 64 rows 11.2 / 12.0; 4096 -> 4096, 128 rows 11.5 / 12.3; 3072 -> 2112, 128 rows from HBM 13.1 / 13.0.
+// (5): two computing and two copying waves, over long contractions four of each (14336 to 4096 columns, 128 rows 41.8 / 40.6; 8192 to 8192, 64 rows 28.1 /
+// 27.2; 1024 to 1024, 256 rows 4.70 / 4.78, 512 to 14336 3.79 / 3.94).
+// Only where a row of W is a multiple of 512 bytes, which puts the rows of a slab into few of the memory channels, do whole tiles of (5) take
+// stages of two slabs, from contractions of 1024 on and while all of them run at once.  One slab / two, weight cached and from HBM: to 4096 columns,
+// contraction of 1024, 128 rows 5.05 / 4.92, 5.97 / 5.91, of 2048 7.2 / 6.8, 13.0 / 12.1, of 4096, 96 rows 13.7 / 13.6, 21.9 / 21.0; to 8192, 4096, 64 rows
+// 15.4 / 14.1, 22.8 / 21.9; to 2560, 6144, 128 rows 21.0 / 20.2, 33.8 / 31.9; but to 4032, 4096, 96 rows 11.5 / 12.2, 17.5 / 17.8; to 2112, 8192, 128 rows 18.9 / 20.1,
+// 29.7 / 30.7; to 4160, 14336, 60 rows 31.1 / 33.7, 51.7 / 53.4; to 1088, 4096, 240 rows 10.8 / 11.0, 13.2 / 14.0; to 8064, 8192, 64 rows level; to 4096, 576, 110 rows
+// 4.20 / 4.27, 4.74 / 4.84; 2560 tiles to 20480, 8896, of eight adapters 291 / 296 (a whole backward; 384 tiles to 8192, 4096, of three 40.5 / 40.0).
 using Ring64x64 = Ring<64, 64, 2, 2, 5, 2, 2>;       // of the launches that take the strips
-using Ring32x64 = Ring<32, 64, 2, 2, 3, 1, 2, 2>;
+using Ring32x64 = Ring<32, 64, 2, 2, 3, 1, 2, 2>;    // two slabs to a stage
+using Narrow32x64 = Ring<32, 64, 1, 2, 6, 1, 1>;     // four waves
 using Ring32x32 = Ring<32, 32, 2, 2, 4, 2, 2, 2>;    // half of such a tile
 constexpr int kLongContraction = 4096;
+constexpr bool deep_stages(int KC, int NC, int64_t tiles) { return KC >= 1024 && NC % 256 == 0 && tiles <= 2 * kComputeUnits; }
 
 // Calls f(kernel, arguments) with what a launch of tiles of `kind` takes.
 template <bool COL, class F>
@@ -574,9 +585,12 @@ static auto with_ring(int kind, const RingArgs& a, F&& f) {
                 h.tiles_n *= 2;
                 return f(Ring32x32{}, h);
             }
-            if constexpr (!COL)
-                if (a.KC >= kLongContraction) return f(Ring<32, 64, 2, 2, 6, 1, 2>{}, a);
-            return f(Ring32x64{}, a);
+            if constexpr (COL) {
+                if (deep_stages(a.KC, a.NC, (int64_t)a.tiles_m * a.tiles_n)) return f(Ring32x64{}, a);
+                return a.KC < kLongContraction ? f(Narrow32x64{}, a) : f(Ring<32, 64, 2, 2, 6, 2, 2>{}, a);
+            } else {
+                return f(Ring<32, 64, 2, 2, 6, 1, 2>{}, a);
+            }
         default: return f(Ring<128, 64, 2, 2, 6, 2, 1>{}, a);
     }
 }
@@ -601,8 +615,7 @@ static auto with_ring_strips(int kind, const RingStripsArgs& a, F&& f) {
     }
     // whole tiles that share compute units: four waves instead of seven (20 rows of three adapters, 10048 -> 4288, r = 32, 402 workgroups 25.4 us, 26.5
     // with seven); by themselves the seven are faster (256 x 1024 x 1024 backward 10.2, 10.5 with four)
-    using Shared = Ring<32, 64, 1, 2, 6, 1, 1>;
-    if (a.tiles_m * a.tiles_n + a.a.blocks + a.b.blocks > kComputeUnits) return of_rank(Shared{}, a);
+    if (a.tiles_m * a.tiles_n + a.a.blocks + a.b.blocks > kComputeUnits) return of_rank(Narrow32x64{}, a);
     return of_rank(Ring32x64{}, a);
 }
 

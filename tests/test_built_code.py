@@ -172,9 +172,11 @@ def test_copies_of_whole_narrow_tiles_follow_the_barrier(functions):
     assert {_straight_loops(code) for code in forward} == {2} and {_straight_loops(code) for code in backward} == {0}
 
 
-def test_no_backward_kernel_of_one_slab_to_a_stage(functions):
-    """(5) by itself takes 32 x 64 tiles in 128-deep stages only: nothing could launch the others."""
-    assert not [name for name, _ in functions if re.search(r"ring_gemm_kernelINS_4RingILi32ELi64E(Li\d+E){5}Li1EEELb1E", name)]
+def test_kernels_of_whole_narrow_tiles(functions):
+    """Of 32 x 64 tiles by themselves only what a launch can choose is built: waves in rows and columns, stages, copying waves, slabs to a stage."""
+    found = {m.groups() for name, _ in functions if (m := re.search(r"ring_gemm_kernelINS_4RingILi32ELi64E((?:Li\d+E){6})EELb(\d)E", name))}
+    of = lambda *v: "".join(f"Li{x}E" for x in v)
+    assert found == {(of(2, 2, 6, 1, 2, 1), "0"), (of(1, 2, 6, 1, 1, 1), "1"), (of(2, 2, 6, 2, 2, 1), "1"), (of(2, 2, 3, 1, 2, 2), "1")}
 
 
 @pytest.mark.parametrize("body,expected", [

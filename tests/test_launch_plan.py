@@ -92,11 +92,23 @@ def test_slab_lookahead_setting_and_lines_asked_for_ahead():
 
 
 def test_stages_of_whole_narrow_tiles():
-    """One slab to a stage, six stages, over long contractions of (2)."""
+    """Two slabs to a stage: never in (2); in (5) by itself only where a row of W is a multiple of 512 bytes, the contraction has 16 slabs
+    and all workgroups run at once."""
     binding.lora_set_row_tile(0)
-    for K, N, lens in ((4096, 4096, (100,)), (8192, 4096, (70, 30)), (8896, 20480, (1, 5, 7, 16, 3, 5, 2, 29))):
-        g = binding.lora_debug_launches(K, N, 16, _offsets(lens)).fwd[0]
-        assert (g.rows, g.columns, g.depth, g.stages) == (32, 64, 64, 6)
+    rnd = random.Random(19)
+    seen = set()
+    for it in range(4000):
+        G = 1 if it % 2 else rnd.choice((2, 5, 12))
+        lens = [rnd.randint(1, 260 // G + 1) for _ in range(G)]
+        K, N = 64 * rnd.randint(1, 72), 64 * rnd.randint(1, 72)
+        q = binding.lora_debug_launches(K, N, 64, _offsets(lens))
+        for way, launches in (("fwd", q.fwd), ("dx", q.dx)):
+            for g in launches:
+                if (g.rows, g.columns) == (32, 64):
+                    deep = way == "dx" and N >= 1024 and K % 256 == 0 and g.workgroups <= 512
+                    assert (g.depth, g.stages) == ((128, 3) if deep else (64, 6)), (lens, K, N, way)
+                    seen.add((way, deep, g.waves))
+    assert seen == {("fwd", False, 7), ("dx", True, 7), ("dx", False, 4), ("dx", False, 8)}
 
 
 def test_workgroups_beside_the_strips():
