@@ -50,9 +50,11 @@ using FewAdapters = AdapterTableOf<kFewAdapters>;
 
 // First statement of a kernel whose arguments are of type Args: asks for every cache line of them at once.  A launch finds them in
 // memory, not in a cache, and the compiler loads a field where it is first needed: the number of adapters, behind that the walk over
-// the segments, behind that the adapter's entry, 0.35 us each.  Two accumulating backward passes over 2048 x 4096 x 4096 37.2 -> 36.6 us, a step of
-// 1531 packed rows 63.2 -> 62.6.  Not in the small-tile GEMMs, whose hundreds of workgroups would all wait for the last line (471 of them, a step of
-// 66.5 -> 67.9 us).
+// the segments, behind that the adapter's entry, 0.35 us each.  us, without / with: two accumulating backward passes over 2048 x 4096 x 4096 37.2 / 36.6, a step of
+// 1531 packed rows 63.2 / 62.6; backward without dX, of launches of many workgroups too, 256 x 1024 x 1024 7.89 / 7.84, ten adapters of 300 rows, 256 -> 512
+// 8.21 / 8.12, 8192 rows, 4096 -> 4096 38.0 / 37.6, -> 14336 75.2 / 74.5, 5003 rows, 14336 -> 4096 49.7 / 49.0; level for (1) straight into registers (16384 rows, K =
+// 256 7.8).  Not in the GEMMs of small tiles, whose entry code needs most of the lines at once and waits for the last (471 workgroups, a step of
+// 66.5 -> 67.9 us); those of few workgroups have not been told apart.
 template <class Args>
 __device__ __forceinline__ void fetch_args() {
     constexpr int LINES = ((int)sizeof(Args) + 63) / 64, N = LINES < 8 ? LINES : 3;     // (of a full table its first offsets)

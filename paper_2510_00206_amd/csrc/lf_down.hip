@@ -10,10 +10,12 @@
 // about 25), then the mask (12 vector instructions per column pair).  Hence X and A go global -> LDS in whole 128-byte
 // lines, several stages of 256 columns ahead, by waves that do nothing else; A is fetched once per workgroup and stage, not
 // once per wave; the masks of a stage are formed while its copies land, and not at all without dropout.
-// Measured, us (cards differ by up to a tenth): fragments loaded straight into registers / copies by the computing waves / as it is
-// now: K = 14336: 5003 rows r = 16 57 / 33.6 / 29.2, r = 64 128 / 39.5 / 35.0; K = 4096: 1024 rows r = 16 - / 7.9 / 7.2, r = 64 - / 11.2 / 8.7; 8192 rows r = 16 18 / 12.4 / 12.4,
-// r = 64 - / 16.2 / 14.9; 19 rows, K = 24960, r = 16 - / 33.4 / 29.7, r = 64 - / 50.3 / 38.3.  Short contractions keep the registers
-// (down_direct_kernel, rule in launch_down).  The order of the sums is the same in both kernels and in every height, so S' has
+// Measured, us (cards differ by up to a tenth): fragments loaded straight into registers / copies by the computing waves / by waves of their
+// own, 16 or 32 rows to a workgroup: K = 14336: 5003 rows r = 16 57 / 33.6 / 29.2, r = 64 128 / 39.5 / 35.0; K = 4096: 1024 rows r = 16 - / 7.9 / 7.2, r = 64 - /
+// 11.2 / 8.7; 8192 rows r = 16 18 / 12.4 / 12.4, r = 64 - / 16.2 / 14.9; 19 rows, K = 24960, r = 16 - / 33.4 / 29.7, r = 64 - / 50.3 / 38.3.  In a kernel trace, those / as it
+// is now, few rows in workgroups of eight and of a part of the rank: K = 4096, r = 16, 77 rows 7.5 / 6.8, 1024 rows 7.8 / 7.1, 2048 rows 8.2 / 7.6; r = 32, 500
+// rows 8.0 / 7.1; r = 64, 1024 rows 9.5 / 8.4, 1531 rows 9.9 / 9.2; 19 rows, K = 24960, r = 16 29.3 / 23.7, r = 64 40.6 / 24.0.  Short contractions keep the registers
+// (down_direct_kernel, rule in with_down).  The order of the sums is the same in both kernels and in every height, so S' has
 // the same bits whichever is picked.
 #include "lf_device.h"
 #include "lf_gemm_parts.h"
@@ -121,7 +123,7 @@ __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel
     const int g = rt.g, c0 = C::PARTS == 1 ? 0 : blockIdx.y * (CB * 16);          // this workgroup's first column of S'
     const int nslabs = p.K / BK, nst = (nslabs + DOWN_SLABS - 1) / DOWN_SLABS;
     // Every workgroup starts its sweep over K at a different stage (a function of its 32-row group within the segment,
-    // so that single- and multi-adapter calls, and both workgroup heights, sum in the same order): workgroups sweeping
+    // so that single- and multi-adapter calls, and workgroups of every height, sum in the same order): workgroups sweeping
     // in lockstep would all hit the same few L2 channels, the row pitch being a multiple of the channel interleave.
     int st = (int)(((unsigned)(rt.local_row0 / 32) * 5u) % (unsigned)nst);
     if (w >= C::WAVES) {
@@ -227,7 +229,7 @@ __global__ void __launch_bounds__(C::THREADS + 64 * (C::XW + C::AW)) down_kernel
 
 // The same sums without LDS: wave w loads the fragments of column part w of every stage straight into registers, D stages
 // ahead.  No stage to fill and 64 KB of LDS at most, so several workgroups share a compute unit and cover for each other:
-// the faster way where a workgroup's sweep is short against its start and its end (see launch_down).
+// the faster way where a workgroup's sweep is short against its start and its end (see with_down).
 template <int CB, int RB, class TB>
 __global__ void __launch_bounds__(64 * DOWN_PARTS) down_direct_kernel(DownArgsOf<TB> p) {
     fetch_args<DownArgsOf<TB>>();
@@ -360,7 +362,9 @@ static auto with_down(const DownArgs& a, int forced, R&& ring, D&& direct) {
     // while all workgroups run at once it is given eight rows, and as few of the rank's columns as that leaves room for; 16 rows by half the
     // columns at r = 64 (A is four fifths of its copies).  A forward over N = 256, operands from HBM, us, 16 rows by all columns / now: r = 16, K = 4096,
     // 77 rows without dropout 16.6 / 13.6, 1024 rows 18.7 / 15.4, 2048 rows 23.9 / 23.0; K = 2048, 1000 rows 12.6 / 11.0; r = 32, K = 4096, 500 rows 19.0 /
-    // 15.2, 2000 rows 25.2 / 24.9; r = 64, 400 rows 20.3 / 15.7, 1531 rows 27.6 / 24.6.  Same bits.
+    // 15.2, 2000 rows 25.2 / 24.9; r = 64, 400 rows 20.3 / 15.7, 1531 rows 27.6 / 24.6; N = 64, operands cached and
+    // from HBM: K = 384, r = 16, 1000 rows 6.6 / 6.4, 7.1 / 6.9, r = 64, 500 rows 7.3 / 6.6, 7.8 / 7.0; K = 1024, r = 16, 2048 rows 8.3 / 8.1, 8.7 / 8.8 (the least of 60
+    // sizes), r = 64, 2048 rows 9.2 / 8.9, 9.7 / 9.3; K = 14336, r = 64, 1000 rows 46.6 / 42.3, 64.7 / 49.2.  Same bits.
     auto fits = [&](int tiles, int parts) { return !forced && tiles * parts <= kComputeUnits; };
     if (a.r == 16) {
         if (fits(tiles8, 1)) return ring(Down<1, 8, 6>{}, tiles8);

@@ -1015,8 +1015,10 @@ int forced_row_tile() { return g_forced_row_tile.load(std::memory_order_relaxed)
 // What one launch costs, in microseconds: start and way out, plus the slabs of the contraction times the time a slab
 // takes the compute unit with the most tiles.  us[0] is that time for one tile on every compute unit, us[1] for two
 // of the small tiles sharing one (measured at K = N = 4096, 64 to 4096 rows, both directions alike, with the small tiles' copies
-// issued by their computing waves; now (2) takes 0.94 - 0.99 and (5) 0.87 - 0.98 of it, by kind; two of the large ones run one
-// after the other).  With few tiles the operands reach them faster: down to three
+// issued by their computing waves; two of the large ones run one after the other).  Now (2) takes 0.94 - 0.99 and (5) 0.87 - 0.98 of
+// it, by kind, and kind 4 less: whole tiles 0.9 in (2), shared ones, which the list does not know, 0.67 - 0.8 in (2) and 0.63 - 0.95 in
+// (5) (with_ring).  So it takes the larger tiles for some launches that shared ones would serve as well or better; the crossovers have not been
+// measured again.  With few tiles the operands reach them faster: down to three
 // quarters of it.
 // At 4096 x 4096, one adapter, r = 16, the table gives 32 x 64 tiles up to 128 rows, 64 x 64 up to 256, 128 x 64 up to 512,
 // 128 x 128 up to 1024 (then with a second launch for the rest of the rows), 128 x 256 from 1217, 192 x 256 from 2049 and

@@ -6,7 +6,7 @@
 // 32 from zero, then the LoRA term), so Y and dX are bit-identical whichever kernel a launch picks.
 //
 // What bounds them: the copies out of L2 (a compute unit takes in 120 GB/s when all of them copy, 147 by itself; 128 x 128 tiles,
-// one on every compute unit, use 80), and the meeting of the waves once a slab.  Hence: a ring of three to six slabs in LDS,
+// one on every compute unit, use 80), and the meeting of the waves once a slab.  Hence: a ring of three to eight slabs in LDS,
 // filled several slabs ahead by waves that do nothing else (a copy holds the wave that issues it up until the memory pipeline
 // takes it, and a wave that waits for copies to land is late for its MFMAs), one barrier per slab; the computing waves read
 // their fragments one sub-step ahead or, in the tiles whose waves have the registers and eight MFMAs or more a sub-step to
@@ -62,13 +62,13 @@ __device__ __forceinline__ int ring_col_swz(int row) {
 }
 
 // ---- the copying waves -----------------------------------------------------------------------------
-// Where a slab comes from: rows (token: of the tile; out: output columns or, COL, contraction rows) `ld` elements apart, `rows`
-// of them valid; chunks: valid 16-byte chunks along the contraction (8, or r / 8 for the LoRA slab), COL: along the columns.
 // Position of 16-byte chunk `chunk` of row `row` in a row-operand slab: 64 elements to a row as in the large tiles, or 128, where the 16 rows of a
 // fragment read are 256 bytes apart and each needs a chunk position of its own.
 template <int D>
 __device__ __forceinline__ int ring_row_swz(int row) { return D == 1 ? row_slab_swz(row) : row & 15; }
 
+// Where a slab comes from: rows (token: of the tile; out: output columns or, COL, contraction rows) `ld` elements apart, `rows`
+// of them valid; chunks: valid 16-byte chunks along the contraction (8 or 16, r / 8 for the LoRA slab), COL: along the columns.
 struct RingSource { const char* biased; uint32_t ld; int rows, chunks; };
 
 // Copies of a slab pair by one wave: NT of the token slab, then NO of the out slab (1 KB each); either may be none.  Those of
